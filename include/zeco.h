@@ -276,9 +276,9 @@ zeco_status zeco_gla_fwd_from_state(const zeco_gla_desc *desc, const void *q, co
                                     const void *v, const void *g, const float *S_init, void *o,
                                     void *stream);
 
-/* The whole forward in one call, for all P segments resident on this device.  The library may cut the
- * segments further (more, shorter segments keep every compute unit busy); the states of those pieces
- * live in the workspace.
+/* The whole forward in one call, for all P segments resident on this device.  The library cuts the P * L tokens
+ * into pieces of its own (as many as keep the compute units busy, whatever P and L are; a short run stays whole
+ * and takes a single launch); the states of those pieces live in the workspace.
  *   in   S0 [B,H,d_k,d_v] fp32 or NULL: state entering the first segment
  *   out  o;  S_last [B,H,d_k,d_v] fp32 or NULL: state after the last token
  *   out  S_save: NULL, or zeco_gla_saved_states_bytes(desc) bytes of device memory that receive the
@@ -343,7 +343,7 @@ zeco_status zeco_gla_bwd_from_state(const zeco_gla_desc *desc, const void *q, co
 
 /* The whole backward in one call: recomputes the forward segment states (phase 1 and its scan, from
  * S0), runs the state-gradient pass and its reverse scan (from dS_T), then the gradient passes.  Like
- * zeco_gla_fused_fwd it may cut the segments into shorter pieces.
+ * zeco_gla_fused_fwd it works on pieces of its own.
  *   in   S0, dS_T [B,H,d_k,d_v] fp32 or NULL (zero)
  *   in   S_saved: NULL, or what zeco_gla_fused_fwd left in S_save for the same descriptor and inputs
  *        (S0 is then not read: it is already part of the saved states)

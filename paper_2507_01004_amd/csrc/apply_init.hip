@@ -201,6 +201,13 @@ __global__ __launch_bounds__(256) void apply_init_bf16_kernel(ApplyParams p) {
         pad = 64 * n_chunks - (int)len;
         if (c0 >= n_chunks) return;
     }
+    if (p.cut.n) {   // (the grid is sized for the longest piece)
+        long long len;
+        piece_range(p.cut, seg, p.P, tok0, len, T);
+        n_chunks = (int)((len + 63) >> 6);
+        pad = (int)(64ll * n_chunks - len);
+        if (c0 >= n_chunks) return;
+    }
     const int nblk = min(p.tokens_per_wg / 64, n_chunks - c0);
     const uint16_t *qp = (const uint16_t *)p.q + b * p.sb + tok0 * p.st + h * p.sh;
     uint16_t *op = (uint16_t *)p.o + b * p.vb + tok0 * p.vt + h * p.vh;
@@ -298,9 +305,17 @@ __global__ __launch_bounds__(256) void apply_init_cd_bf16_kernel(ApplyParams p) 
     const int h = id % p.H;
     id /= p.H;
     const int b = id % p.B, seg = p.p0 + p.seg_step * (id / p.B);
-    const long long tok0 = (long long)seg * p.L;                 // the segment's first token
+    long long tok0 = (long long)seg * p.L;                       // the segment's first token
+    int n_chunks = p.n_chunks, pad = p.pad;
     const int c0 = tb * (p.tokens_per_wg / 64);                  // this workgroup's first block (= chunk)
-    const int nblk = min(p.tokens_per_wg / 64, p.n_chunks - c0);
+    if (p.cut.n) {   // (the grid is sized for the longest piece)
+        long long len, T;
+        piece_range(p.cut, seg, p.P, tok0, len, T);
+        n_chunks = (int)((len + 63) >> 6);
+        pad = (int)(64ll * n_chunks - len);
+        if (c0 >= n_chunks) return;
+    }
+    const int nblk = min(p.tokens_per_wg / 64, n_chunks - c0);
     const long long kb = b * p.sb + tok0 * p.st + h * p.sh;
     const uint16_t *qp = (const uint16_t *)p.q + kb + (long long)(tg * TPT) * p.st + 4 * cq;
     const unsigned char *gp = (const unsigned char *)p.g + (kb + (long long)(tg * TPT) * p.st + 4 * cq) * GB;
@@ -324,13 +339,13 @@ __global__ __launch_bounds__(256) void apply_init_cd_bf16_kernel(ApplyParams p) 
     auto load_raw = [&](int blk) {
 #pragma unroll
         for (int u = 0; u < TPT; ++u) {
-            const long long tt = apply_block_start(p.pad, c0 + blk) + u;
+            const long long tt = apply_block_start(pad, c0 + blk) + u;
             qn[u] = apply_ld<NT>(reinterpret_cast<const u32x2 *>(qp + tt * p.st));
             gn[u] = apply_ld<NT>(reinterpret_cast<const typename GV::raw_t *>(gp + tt * p.st * GB));
         }
     };
     load_raw(0);
-    apply_load_o<DV, NT>(op + apply_block_start(p.pad, c0) * p.vt, p.vt, onx);
+    apply_load_o<DV, NT>(op + apply_block_start(pad, c0) * p.vt, p.vt, onx);
     for (int blk = 0; blk < nblk; ++blk) {
         const f32x4 pre = pre_n;
         u32x2 qc[TPT];
@@ -349,7 +364,7 @@ __global__ __launch_bounds__(256) void apply_init_cd_bf16_kernel(ApplyParams p) 
         *reinterpret_cast<f32x4 *>(tot + tg * DK + 4 * cq) = run;
         if (blk + 1 < nblk) {   // (uniform) the next block's rows; nothing is fetched twice
             load_raw(blk + 1);
-            apply_load_o<DV, NT>(op + apply_block_start(p.pad, c0 + blk + 1) * p.vt, p.vt, onx);
+            apply_load_o<DV, NT>(op + apply_block_start(pad, c0 + blk + 1) * p.vt, p.vt, onx);
             pre_n = *reinterpret_cast<const f32x4 *>(Gk + (long long)(blk + 1) * gks);
         }
         __syncthreads();   // group sums visible; every thread is done with the staging tile of the last block
@@ -369,7 +384,7 @@ __global__ __launch_bounds__(256) void apply_init_cd_bf16_kernel(ApplyParams p) 
                       pack_bf16(bf16_lo(qc[u][1]) * fast_exp(G[2]) * p.scale, bf16_hi(qc[u][1]) * fast_exp(G[3]) * p.scale)};
         }
         __syncthreads();   // Qh complete
-        apply_block<DK, DV>(sf, Qh, Cs, op + apply_block_start(p.pad, c0 + blk) * p.vt, p.vt, ocur, apply_block_rows(p.pad, c0 + blk));
+        apply_block<DK, DV>(sf, Qh, Cs, op + apply_block_start(pad, c0 + blk) * p.vt, p.vt, ocur, apply_block_rows(pad, c0 + blk));
     }
 }
 

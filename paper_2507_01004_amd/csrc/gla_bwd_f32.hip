@@ -92,6 +92,7 @@ __global__ __launch_bounds__(DK * 4) void gla_bwd_qk_f32_kernel(BwdQKParams p) {
         len = p.seg_start[seg + 1] - tok0;
         if (tok0 < 0 || len < 64 || len > p.L || tok0 > T - len) return;   // (in this order: no sum can overflow)
     }
+    if (p.cut.n) piece_range(p.cut, seg, p.P, tok0, len, T);
     const int N = (int)((len + C - 1) / C);
     const long long kbase = b * p.sb + tok0 * p.st + h * p.sh;
     const long long vbase = b * p.vb + tok0 * p.vt + h * p.vh;

@@ -166,6 +166,12 @@ __global__ __launch_bounds__(DK * 4) void gla_bwd_qk_kernel(BwdQKParams p) {
         N = (int)((len + 63) >> 6);
         pad = 64 * N - (int)len;
     }
+    if (p.cut.n) {
+        long long len;
+        piece_range(p.cut, seg, p.P, tok0, len, T);
+        N = (int)((len + 63) >> 6);
+        pad = (int)(64ll * N - len);
+    }
     const long long kbase = b * p.sb + tok0 * p.st + h * p.sh;
     const long long vbase = b * p.vb + tok0 * p.vt + h * p.vh;
     const unsigned char *xb = (const unsigned char *)p.x + vbase * 2;

@@ -95,8 +95,8 @@ __device__ __forceinline__ bf16x8 pack8(const f32x16 &a, int base) {
 //   kLocal   the local pass from the zero state: o, S_loc, G_cum, G_tot          (Sec. 3.1)
 //   kStates  only the final local state and total decay of each segment: S_loc, G_tot
 //            (Alg. 1's chunk-state loop; q is not read, nothing per token is written)
-//   kOutput  the output pass from given initial states S_init[p]: o only
-//            (Alg. 1's output pass, the incoming state folded into the running state)
+//   kOutput  the output pass from given initial states S_init[p] (none: zero): o, and the end states (S_loc,
+//            S_loc2) and those entering the pieces of a backward (S_emit) if asked for (Alg. 1's output pass, the incoming state folded into the running state)
 //   kLocalCD the local pass with the cumulative decay kept per chunk, as Alg. 1 stores it (the list of
 //            gamma~_[n]): o, S_loc, G_tot and G_chunk[n] = log gamma~_[n-1], the log decay from the segment's
 //            first token up to the start of chunk n; no per-token G_cum is written
@@ -155,7 +155,7 @@ __global__ __launch_bounds__(chunk_threads(DK, DV, GM, MODE)) void gla_chunk_bf1
     constexpr bool GH = GM == kGateHead;
     constexpr bool REV = MODE == kDState || MODE == kDV;          // chunks and tokens in reverse
     constexpr bool NOQ = MODE == kStates || MODE == kDState;      // only the state is computed
-    constexpr bool FROM_INIT = MODE == kOutput || MODE == kDV || MODE == kLocalInit;   // start from S_init, emit no state
+    constexpr bool FROM_INIT = MODE == kOutput || MODE == kDV || MODE == kLocalInit;   // start from S_init (no state emitted, but see kOutput)
     constexpr bool EMIT_G = MODE == kLocal || MODE == kLocalInit;  // per-token cumulative log decay
     constexpr float SGN = REV ? -1.f : 1.f;                       // sign of the decay exponents
     constexpr float kLog2e = 1.4426950408889634f;
@@ -205,6 +205,12 @@ __global__ __launch_bounds__(chunk_threads(DK, DV, GM, MODE)) void gla_chunk_bf1
             N = (int)((len + 63) >> 6);
             pad = 64 * N - (int)len;
         }
+    }
+    if (p.cut.n) {
+        long long len;
+        piece_range(p.cut, seg, p.P, tok0, len, T);
+        N = (int)((len + 63) >> 6);
+        pad = (int)(64ll * N - len);
     }
     const long long kbase = b * p.sb + tok0 * p.st + h * p.sh;
     const long long vbase = b * p.vb + tok0 * p.vt + h * p.vh + slice * DV;
@@ -444,7 +450,7 @@ __global__ __launch_bounds__(chunk_threads(DK, DV, GM, MODE)) void gla_chunk_bf1
                     f32x4 gp;
 #pragma unroll
                     for (int a = 0; a < 4; ++a) gp[a] = seg_hi[a] + seg_lo[a];
-                    *reinterpret_cast<f32x4 *>(p.G_chunk + ((((long long)b * p.P + seg) * N + m) * p.H + h) * DK + 4 * cq) = gp;
+                    *reinterpret_cast<f32x4 *>(p.G_chunk + ((((long long)b * p.P + seg) * p.n_chunks + m) * p.H + h) * DK + 4 * cq) = gp;
                 }
             }
 #pragma unroll
@@ -535,8 +541,13 @@ __global__ __launch_bounds__(chunk_threads(DK, DV, GM, MODE)) void gla_chunk_bf1
 #pragma unroll
         for (int it = 0; it < Cfg::NIT; ++it)
 #pragma unroll
-            for (int rr = 0; rr < 16; ++rr)
-                Sacc[it][rr] = FROM_INIT ? Si[(size_t)(it * 32 + M::row(rr, kg)) * (DV * NS)] : 0.f;
+            for (int rr = 0; rr < 16; ++rr) Sacc[it][rr] = 0.f;
+        if (FROM_INIT && (MODE != kOutput || p.S_init)) {   // (kOutput: no S_init = the zero state)
+#pragma unroll
+            for (int it = 0; it < Cfg::NIT; ++it)
+#pragma unroll
+                for (int rr = 0; rr < 16; ++rr) Sacc[it][rr] = Si[(size_t)(it * 32 + M::row(rr, kg)) * (DV * NS)];
+        }
 
         // rows of the state scaled by the chunk decay
         auto decay_state = [&](const float *gam_n) __attribute__((always_inline)) {
@@ -633,23 +644,36 @@ __global__ __launch_bounds__(chunk_threads(DK, DV, GM, MODE)) void gla_chunk_bf1
             }
         };
 
+        auto store_state = [&](float *S) __attribute__((always_inline)) {
+#pragma unroll
+            for (int it = 0; it < Cfg::NIT; ++it)
+#pragma unroll
+                for (int rr = 0; rr < 16; ++rr)
+                    S[(size_t)(it * 32 + M::row(rr, kg)) * (DV * NS)] = Sacc[it][rr];
+        };
+        // kOutput over a whole run: the states entering the pieces a backward will work on (uniform branches)
+        int emit_at = 0, emit_j = 0;
+        float *emit_to = p.S_emit + sbh * DK * (DV * NS) + slice * DV + w * 32 + lt;
+        const bool emit = MODE == kOutput && p.S_emit;
         __syncthreads();
         __syncthreads();
         for (int n = 0; n < N; ++n) {
             const unsigned char *cur = lds + (n & 1) * Cfg::kTileBytes;
+            if (MODE == kOutput && emit && n == emit_at) {
+                store_state(emit_to);
+                emit_to += (size_t)p.B * p.H * DK * (DV * NS);
+                // the first piece has the short chunk on top of its whole ones
+                emit_at += p.emit.base + (emit_j >= p.emit.n - p.emit.rem ? 1 : 0) + (emit_j == 0 && pad ? 1 : 0);
+                ++emit_j;
+            }
             if constexpr (!NOQ) mfma_a(cur, gam + (n & 1) * DK);
             __syncthreads();
             mfma_b(n, cur, gam + (n & 1) * DK);
             __syncthreads();
         }
 
-        if constexpr (!FROM_INIT) {
-#pragma unroll
-            for (int it = 0; it < Cfg::NIT; ++it)
-#pragma unroll
-                for (int rr = 0; rr < 16; ++rr)
-                    Sl[(size_t)(it * 32 + M::row(rr, kg)) * (DV * NS)] = Sacc[it][rr];
-        }
+        if (!FROM_INIT || (MODE == kOutput && p.S_loc)) store_state(Sl);
+        if (MODE == kOutput && p.S_loc2) store_state(p.S_loc2 + sbh * DK * (DV * NS) + slice * DV + w * 32 + lt);
     }
 }
 

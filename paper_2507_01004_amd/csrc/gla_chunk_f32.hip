@@ -17,7 +17,8 @@
 //
 // MODE (the phases of Alg. 1, as in the bf16 kernel): kF32Local the local pass from the zero state
 // (o, S_loc, G_cum, G_tot); kF32States only the final state and total decay of each segment (S_loc,
-// G_tot; q is not read); kF32Output the output pass from given initial states S_init (o only).
+// G_tot; q is not read); kF32Output the output pass from given initial states S_init (none: zero; o, and the end
+// states if S_loc is given).
 //
 // Two more modes run the same equations over the REVERSED sequence for the backward pass (App. A.4):
 //   kF32DState  dS <- (gamma^T 1) .* dS + (Q .* Lambda)^T dO from zero; S_loc receives the gradient the
@@ -102,6 +103,11 @@ __global__ __launch_bounds__(DV * 4) void gla_chunk_f32_kernel(ChunkParams p) {
         n_chunks = (int)((len + C - 1) / C);
         pad = C * n_chunks - (int)len;
     }
+    if (p.cut.n) {
+        piece_range(p.cut, seg, p.P, tok0, len, T);
+        n_chunks = (int)((len + C - 1) / C);
+        pad = (int)((long long)C * n_chunks - len);
+    }
     const float *q = (const float *)p.q + b * p.sb + tok0 * p.st + h * p.sh;
     const float *k = (const float *)p.k + b * p.sb + tok0 * p.st + h * p.sh;
     const float *g = (const float *)p.g + b * p.sb + tok0 * p.st + h * p.sh;
@@ -114,7 +120,7 @@ __global__ __launch_bounds__(DV * 4) void gla_chunk_f32_kernel(ChunkParams p) {
     f32x4 Sacc[DK / 16];
 #pragma unroll
     for (int it = 0; it < DK / 16; ++it) {
-        if constexpr (FROM_INIT) {
+        if (FROM_INIT && (MODE != kF32Output || p.S_init)) {   // (output pass: no S_init = the zero state)
             const float *Si = p.S_init + sbh * DK * DV;
 #pragma unroll
             for (int r = 0; r < 4; ++r) Sacc[it][r] = Si[(16 * it + 4 * kg + r) * DV + 16 * w + l16];
@@ -249,13 +255,13 @@ __global__ __launch_bounds__(DV * 4) void gla_chunk_f32_kernel(ChunkParams p) {
         __syncthreads();
     }
 
-    if constexpr (!FROM_INIT) {
+    if (!FROM_INIT || (MODE == kF32Output && p.S_loc)) {
         float *Sl = p.S_loc + sbh * DK * DV;
 #pragma unroll
         for (int it = 0; it < DK / 16; ++it)
 #pragma unroll
             for (int r = 0; r < 4; ++r) Sl[(16 * it + 4 * kg + r) * DV + 16 * w + l16] = Sacc[it][r];
-        if (tg == 0 && (!REV || p.G_tot)) p.G_tot[sbh * DK + gc] = (float)seg_prefix;
+        if (!FROM_INIT && tg == 0 && (!REV || p.G_tot)) p.G_tot[sbh * DK + gc] = (float)seg_prefix;
     }
 }
 

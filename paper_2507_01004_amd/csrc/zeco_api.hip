@@ -75,7 +75,7 @@ int chunk_gate(const zeco_gla_desc *d);
 // state pass, 4 dV pass), on the segments p describes (p.L tokens each, or the table p.seg_start).
 hipError_t launch_phase(zeco::ChunkParams &p, const zeco_gla_desc *d, int mode, hipStream_t s) {
     if (d->io_dtype == ZECO_F32) {
-        set_length_c(p, p.L, d->C);
+        if (!p.cut.n) set_length_c(p, p.L, d->C);
         return zeco::launch_chunk_f32(p, d->d_k, d->d_v, d->C, mode, s);
     }
     return zeco::launch_chunk_bf16(p, d->d_k, d->d_v, chunk_gate(d), mode, s);
@@ -166,6 +166,9 @@ hipError_t static_scratch(void **out) {
 }  // namespace
 
 extern "C" {
+
+constexpr long long kComputeUnits = 256;
+constexpr long long kLongestPiece = 512;   // chunks
 
 // Can the S equal pieces of a segment of L tokens be halved once more?  Pieces of whole chunks stay pieces of
 // whole chunks; a length that is no multiple of 64 is cut into equal pieces wherever it divides, each
@@ -362,18 +365,117 @@ zeco_status zeco_gla_fwd_from_state(const zeco_gla_desc *d, const void *q, const
     return from_hip(launch_phase(p, d, 2, static_cast<hipStream_t>(stream)));
 }
 
-// Pieces each segment is cut into by zeco_gla_fused_fwd: up to 256 streams, at least 256 tokens each.
-static int fused_pieces(const zeco_gla_desc *d) {
-    const long long streams = (long long)d->B * d->P * d->H;
-    // as many workgroups as fit the 256 compute units in one round, not more; the fp32 kernels' tiles shrink
-    // with the chunk length, and 64 / C of their workgroups share a compute unit
-    const long long slots = 256 * (d->io_dtype == ZECO_F32 ? 64 / d->C : 1);
-    int S = 1;
-    while (streams * S * 2 <= slots && halves_evenly(d->L, S) && d->L / (2 * S) >= 256) S *= 2;
-    return S;
+// The one-call forms treat the P segments as what they are together, one run of P * L tokens, and cut it into pieces
+// of whole 64-token chunks as even as possible (Cut): where the pieces end is nobody's business but the library's,
+// so neither the caller's segments nor a length without a small factor decide how many compute units work.  A piece
+// is a workgroup's serial chain of chunks.  More pieces shorten the chain; each costs its states (written by the
+// first phase, scanned, read by the second), and a chunk takes the longer the more workgroups share the memory
+// system (two phases, d = 128: 3.5 us alone, 5.6 us among 192 workgroups, 6.3 us among 256).  Estimated microseconds, fitted to sweeps of the piece count (16 heads, d = 128, forward): 16384
+// tokens, 8 / 16 / 32 pieces: 157 / 130 / 147 us; 2048 tokens 46 (4) / 36 (8) / 36 (16) / 52 (32) us; 12 heads,
+// 16384 tokens, 16 / 21 pieces: 116 / 123 us (the same traffic, more states); a training step over 131072 tokens,
+// 12 / 16 / 32 pieces: 3.72 / 3.29 / 3.50 ms; 160 (batch, head) pairs x 4096
+// tokens, 1 / 3 pieces: 227 / 325 us.
+struct CostModel {
+    double chunk1, chunk2, chunkb;     // a chunk's chain alone on the chip: single pass, two phases, gradient passes [us]
+    double bytes1, bytes2, bytesb;     // a chunk's traffic in them
+    double state;                      // bytes of a state
+    double slots;                      // workgroups in flight
+    double fixed1 = 8., fixed2 = 13., fixedb = 30.;
+    double step = 0.07;                // of a scan, per piece
+    double rate = 5.9e6;               // bytes per microsecond of the chip (a lone round of workgroups hides part of it)
+};
+static CostModel cost_model(const zeco_gla_desc *d) {
+    const double io = d->io_dtype == ZECO_F32 ? 4. : 2., k = io * d->d_k, v = io * d->d_v;
+    const double g = d->g_per_head ? 4. : (d->g_dtype == ZECO_BF16 ? 2. : 4.) * d->d_k;
+    CostModel m;
+    m.bytes1 = 64. * (2. * k + 2. * v + g);
+    m.bytes2 = m.bytes1 + 64. * (k + v + g);
+    m.bytesb = 64. * (9. * k + 8. * v + 3. * g + (d->g_per_head ? 12. : 12. * d->d_k));
+    m.state = 4. * d->d_k * d->d_v;
+    m.slots = kComputeUnits;
+    if (d->io_dtype == ZECO_F32) {
+        const double f = (d->d_k * d->d_v) / 16384. * (d->C == 64 ? 1. : d->C == 32 ? 1.6 : 2.4);
+        m.chunk1 = 4. + 12. * f; m.chunk2 = 6. + 20. * f; m.chunkb = 20. + 70. * f;
+        m.slots = kComputeUnits * 64. / d->C;
+    } else {
+        m.chunk1 = d->d_k == 128 ? 2.0 : 1.3;
+        m.chunk2 = d->d_k == 128 ? 3.5 : 2.2;
+        m.chunkb = d->d_k == 128 ? 13.5 : 9.;
+    }
+    return m;
+}
+static double cost_chain(const CostModel &m, double wgs, double longest, double chunk, double bytes) {
+    const double rounds = (double)(long long)((wgs + m.slots - 1.) / m.slots), share = wgs < m.slots ? wgs : m.slots;
+    return rounds * longest * (chunk + share * bytes / (2.6 * m.rate));
+}
+static double cost_forward(const CostModel &m, double BH, double n, double longest, bool correct) {
+    // Pieces the AUTO schedule corrects instead of reading k, v, g twice: their first 35 chunks or so, what the decays of
+    // a trained layer leave of a state, are then worked on again.
+    if (n == 1.) return m.fixed1 + cost_chain(m, BH, longest, BH > 128. ? 1.2 * m.chunk1 : m.chunk1, m.bytes1);
+    const double part = correct ? 0.6 + 0.5 * 35. / longest : 1.;
+    return m.fixed2 + part * cost_chain(m, n * BH, longest, m.chunk2, m.bytes2) + 6. * n * BH * m.state / m.rate + m.step * n;
+}
+static double cost_backward(const CostModel &m, double BH, double n, double longest) {
+    return m.fixedb + cost_chain(m, n * BH, longest, m.chunkb, m.bytesb) + 7. * n * BH * m.state / m.rate + 2. * m.step * n;
 }
 
-static int bwd_pieces(const zeco_gla_desc *d);
+// Does ZECO_SCHEDULE_AUTO take the correction for pieces of this many whole chunks (4096 tokens)?
+static bool corrects(const zeco_gla_desc *d, long long chunks) { return d->io_dtype == ZECO_BF16 && chunks >= 64; }
+
+// Pieces per (batch, head).  Forward and backward share them, because the states the forward saves for the backward
+// are the ones entering the pieces; the estimate weighs a backward a tenth (not every forward has one, and the optimum is flat).  One
+// piece, where the forward alone favours it: a single launch that reads everything once, and leaves the states of the
+// pieces the backward then cuts for itself as it passes them.
+static long long pieces_for(const zeco_gla_desc *d, bool backward) {
+    const long long BH = (long long)d->B * d->H, T = (long long)d->P * d->L, chunks = T / 64;
+    if (BH == 0) return 1;
+    // a chain stays short enough for the workgroups of a launch to even out over several rounds
+    const long long least = (chunks + kLongestPiece - 1) / kLongestPiece;
+    const CostModel m = cost_model(d);
+    long long best = 0;
+    double cost = 0., cost_f = 0.;
+    long long seen = 0;
+    auto consider = [&](long long n) {
+        if (n > chunks) n = chunks;
+        if (n < 2 || n < least || n == seen || n == best) return;
+        seen = n;
+        const bool even = T % (64 * n) == 0;
+        const double longest = (double)(chunks / n + (even ? 0 : 1));
+        const double f = cost_forward(m, (double)BH, (double)n, longest, corrects(d, chunks / n)), b = cost_backward(m, (double)BH, (double)n, longest);
+        // (equal pieces stay in step: 15 heads, 32768 tokens, 16 / 17 pieces 153 / 161 us)
+        const double c = (backward ? b : f + 0.1 * b) * (even ? 0.92 : 1.);
+        if (best == 0 || c < cost) { cost = c; cost_f = f; best = n; }
+    };
+    // a quarter of the slots filled, .., four times over; the segments as they are, halved, ..; two to four chunks each
+    for (int k : {1, 2, 3, 4, 6, 8, 12, 16}) consider(k * (long long)m.slots / (4 * BH));
+    for (long long n = d->P; n <= chunks && n * BH <= 4 * (long long)m.slots; n *= 2) consider(n);
+    for (int k = 2; k <= 4; ++k) consider((chunks + k - 1) / k);
+    consider(chunks / 64);   // just enough for the correction
+    consider(least);
+    if (least <= 1) {
+        const double one = backward ? cost_backward(m, (double)BH, 1., (double)chunks) : cost_forward(m, (double)BH, 1., (double)chunks, false);
+        if (best == 0 || one <= 0.9 * (backward ? cost : cost_f)) best = 1;   // (clearly: the estimate is not that good)
+    }
+    if (best * BH > (1ll << 24)) best = d->P;   // (the limit on workgroups that the descriptor keeps)
+    return best;
+}
+
+// The cut itself, and what the launches need to know of it.
+static zeco::Cut cut_of(long long tokens, long long n) {
+    zeco::Cut c;
+    c.n = (int)n; c.base = (int)(tokens / 64 / n); c.rem = (int)(tokens / 64 % n); c.len = tokens;
+    return c;
+}
+static int longest_chunks(const zeco::Cut &c) {
+    const int tail = (c.len & 63) ? 1 : 0;
+    return c.base + (c.rem == 0 ? tail : 1);   // (rem < n: the first piece, which has the tail, is one of base chunks)
+}
+static int longest_tokens(const zeco::Cut &c) {   // upper bound of the pieces' lengths
+    return c.rem ? 64 * (c.base + 1) : 64 * c.base + (int)(c.len & 63);
+}
+static void set_cut(zeco::ChunkParams &p, const zeco::Cut &c) {
+    p.cut = c; p.P = c.n; p.n_chunks = longest_chunks(c); p.pad = 0;
+}
 
 // Workspace of zeco_gla_fused_fwd, in floats: piece states S_loc [n], S_init [n], their G_tot [n], the
 // cumulative decay of the CORRECT schedule (per chunk and channel, or per token with per-head gates), and
@@ -381,24 +483,29 @@ static int bwd_pieces(const zeco_gla_desc *d);
 struct FwdLayout {
     size_t n, states, off_Sinit, off_Gtot, off_decay, off_tree, total;
 };
-static FwdLayout fwd_layout(const zeco_gla_desc *d, int S) {
+static FwdLayout fwd_layout(const zeco_gla_desc *d, const zeco::Cut &cut) {
     FwdLayout w;
     const size_t gd = d->g_per_head ? 1 : d->d_k;
-    w.n = (size_t)d->P * S * d->B * d->H;
+    w.n = (size_t)cut.n * d->B * d->H;
     w.states = w.n * d->d_k * d->d_v;
     w.off_Sinit = w.states;
     w.off_Gtot = 2 * w.states;
     w.off_decay = w.off_Gtot + ((w.n * gd + 3) & ~(size_t)3);
     const size_t decay = d->g_per_head ? (size_t)d->B * d->P * d->L * d->H
-                                       : (size_t)d->B * d->P * S * chunks_of(d->L / S) * d->H * d->d_k;
+                                       : (size_t)d->B * cut.n * longest_chunks(cut) * d->H * d->d_k;
     w.off_tree = w.off_decay + ((decay + 3) & ~(size_t)3);
-    w.total = w.off_tree + chain_scratch_floats(d->P * S, d->B * d->H, d->d_k, d->d_v, d->g_per_head);
+    w.total = w.off_tree + chain_scratch_floats(cut.n, d->B * d->H, d->d_k, d->d_v, d->g_per_head);
     return w;
+}
+static zeco::Cut fwd_cut(const zeco_gla_desc *d) { return cut_of((long long)d->P * d->L, pieces_for(d, false)); }
+static zeco::Cut bwd_cut(const zeco_gla_desc *d) {
+    const zeco::Cut c = fwd_cut(d);
+    return c.n > 1 ? c : cut_of(c.len, pieces_for(d, true));
 }
 
 size_t zeco_gla_fused_fwd_workspace(const zeco_gla_desc *desc) {
     if (check_desc(desc, true) != ZECO_OK) return 0;
-    return fwd_layout(desc, fused_pieces(desc)).total * sizeof(float);
+    return fwd_layout(desc, fwd_cut(desc)).total * sizeof(float);
 }
 
 zeco_status zeco_gla_fused_fwd(const zeco_gla_desc *d, const void *q, const void *k, const void *v,
@@ -417,10 +524,10 @@ zeco_status zeco_gla_fused_fwd(const zeco_gla_desc *d, const void *q, const void
     if (d->io_dtype != ZECO_BF16 && S_save) return ZECO_ERR_UNSUPPORTED;
     const bool can_correct = d->io_dtype == ZECO_BF16;
     if (schedule == ZECO_SCHEDULE_CORRECT && !can_correct) return ZECO_ERR_UNSUPPORTED;
-    if (workspace_bytes < zeco_gla_fused_fwd_workspace(d)) return ZECO_ERR_WORKSPACE;
+    const zeco::Cut cut = fwd_cut(d);
+    const FwdLayout w = fwd_layout(d, cut);
+    if (workspace_bytes < w.total * sizeof(float)) return ZECO_ERR_WORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const int S = fused_pieces(d);
-    const FwdLayout w = fwd_layout(d, S);
     float *Sloc = static_cast<float *>(workspace), *Sinit = Sloc + w.off_Sinit, *Gtot = Sloc + w.off_Gtot;
     float *Gchunk = Sloc + w.off_decay, *tree = Sloc + w.off_tree;
     // With S_save the scan writes the states entering the pieces, and the end state after them, straight into
@@ -430,13 +537,25 @@ zeco_status zeco_gla_fused_fwd(const zeco_gla_desc *d, const void *q, const void
 
     zeco::ChunkParams p;
     fill_chunk_params(p, d);
-    p.P = d->P * S; set_length(p, d->L / S);
-    const bool correct = schedule == ZECO_SCHEDULE_CORRECT || (schedule == ZECO_SCHEDULE_AUTO && can_correct && p.L >= 4096);
+    set_cut(p, cut);
+    hipError_t e;
+    if (cut.n == 1) {
+        // one piece per (batch, head): the state entering it is S0, so the output pass alone does it all and leaves the
+        // end state, and the states entering the backward's pieces, on its way (the first phase, its scan and a second
+        // read of k, v, g would be for nothing)
+        p.q = q; p.k = k; p.v = v; p.g = g; p.o = o;
+        p.S_init = S0; p.S_loc = S_last;
+        if (S_save) {
+            p.emit = bwd_cut(d);
+            p.S_emit = S_save; p.S_loc2 = S_save + (size_t)p.emit.n * d->B * d->H * d->d_k * d->d_v;
+        }
+        return from_hip(launch_phase(p, d, 2, s));
+    }
+    const bool correct = schedule == ZECO_SCHEDULE_CORRECT || (schedule == ZECO_SCHEDULE_AUTO && corrects(d, cut.base));
 
     // first pass: the pieces from the zero state - with their local outputs and the cumulative decay per chunk
     // (per token with per-head gates, whose G_cum is 4 bytes per token and head), or their end states only
     p.k = k; p.v = v; p.g = g; p.S_loc = Sloc; p.G_tot = Gtot;
-    hipError_t e;
     if (correct) {
         p.q = q; p.o = o;
         if (d->g_per_head) p.G_cum = Gchunk; else p.G_chunk = Gchunk;
@@ -458,7 +577,9 @@ zeco_status zeco_gla_fused_fwd(const zeco_gla_desc *d, const void *q, const void
 
     if (correct) {   // correction of the pieces' heads
         zeco::ApplyParams ap;
-        fill_apply_params(ap, d, p.P, p.L);
+        fill_apply_params(ap, d, p.P, longest_tokens(cut));
+        ap.cut = cut; ap.n_chunks = longest_chunks(cut); ap.pad = 0;
+        set_apply_share(ap, longest_tokens(cut), 1024, false);
         ap.q = q; ap.S_init = Sinit; ap.o = o;
         ap.p0 = S0 ? 0 : 1;
         if (d->g_per_head) {
@@ -476,8 +597,10 @@ zeco_status zeco_gla_fused_fwd(const zeco_gla_desc *d, const void *q, const void
 // The gradient passes over `P` pieces of `L` tokens.  dQ from the forward states; with `dS_loc` it also
 // emits every piece's state gradient from dS = 0 (and with `G_tot_out` its total log decay), which is
 // what the reverse scan chains into dS_in.
+// `cut` null: the segments as they are; otherwise P counts its pieces and L bounds their lengths.
 static void fill_bwd_params(zeco::BwdQKParams &b, const zeco_gla_desc *d, int P, int L, const void *g,
-                            float *dg, const float *S_init, const float *S_last) {
+                            float *dg, const float *S_init, const float *S_last, const zeco::Cut *cut) {
+    if (cut) b.cut = *cut;
     b.g = g; b.B = d->B; b.P = P; b.H = d->H; b.L = L; b.n_chunks = chunks_of(L); b.pad = 64 * b.n_chunks - L;
     b.sb = d->stride_b; b.st = d->stride_t; b.sh = d->stride_h;
     b.vb = d->vstride_b; b.vt = d->vstride_t; b.vh = d->vstride_h;
@@ -494,9 +617,10 @@ static size_t bwd_checkpoint_floats(const zeco_gla_desc *d, int P, int L) {
 static zeco_status bwd_dq_pass(const zeco_gla_desc *d, int P, int L, const void *q, const void *k,
                                const void *v, const void *g, const void *dO, const float *S_init,
                                const float *S_last, void *dq, float *dg, float *dS_loc, float *G_tot_out,
-                               float *S_ck, hipStream_t s, const int64_t *seg_start = nullptr, int64_t T = 0) {
+                               float *S_ck, hipStream_t s, const int64_t *seg_start = nullptr, int64_t T = 0,
+                               const zeco::Cut *cut = nullptr) {
     zeco::BwdQKParams b;
-    fill_bwd_params(b, d, P, L, g, dg, S_init, S_last);
+    fill_bwd_params(b, d, P, L, g, dg, S_init, S_last, cut);
     if (S_ck && bwd_checkpoints(L) > 0) { b.S_ck = S_ck; b.n_ck = bwd_checkpoints(L); b.short_last = 1; }
     b.seg_start = reinterpret_cast<const long long *>(seg_start); b.T = T;
     b.x = dO; b.y = v; b.z = k; b.z2 = q; b.out = dq; b.W_init = S_init; b.zscale = 1.f; b.oscale = d->scale;
@@ -507,6 +631,7 @@ static zeco_status bwd_dq_pass(const zeco_gla_desc *d, int P, int L, const void 
         zeco::ChunkParams c;
         fill_chunk_params(c, d);
         c.P = P; set_length_c(c, L, d->C);
+        if (cut) set_cut(c, *cut);
         c.seg_start = reinterpret_cast<const long long *>(seg_start); c.T = T;
         c.k = q; c.v = dO; c.g = g; c.S_loc = dS_loc; c.G_tot = G_tot_out; c.scale = 1.f; c.kscale = d->scale;
         return from_hip(zeco::launch_chunk_f32(c, d->d_k, d->d_v, d->C, 3, s));
@@ -521,17 +646,18 @@ static zeco_status bwd_dv_dk_passes(const zeco_gla_desc *d, int P, int L, const 
                                     const void *v, const void *g, const void *dO, const float *S_init,
                                     const float *S_last, const float *dS_in, void *dk, void *dv,
                                     float *dg, float *S_ck, hipStream_t s, const int64_t *seg_start = nullptr,
-                                    int64_t T = 0) {
+                                    int64_t T = 0, const zeco::Cut *cut = nullptr) {
     const int gb = gate_mode(d);
     zeco::ChunkParams c;
     fill_chunk_params(c, d);
     c.P = P; set_length(c, L);
+    if (cut) set_cut(c, *cut);
     c.seg_start = reinterpret_cast<const long long *>(seg_start); c.T = T;
     c.q = k; c.k = q; c.v = dO; c.g = g; c.o = dv; c.S_init = dS_in; c.scale = 1.f; c.kscale = d->scale;
     if (launch_phase(c, d, 4, s) != hipSuccess) return ZECO_ERR_HIP;
 
     zeco::BwdQKParams b;
-    fill_bwd_params(b, d, P, L, g, dg, S_init, S_last);
+    fill_bwd_params(b, d, P, L, g, dg, S_init, S_last, cut);
     b.seg_start = reinterpret_cast<const long long *>(seg_start); b.T = T;
     b.x = v; b.y = dO; b.z = q; b.z2 = k; b.out = dk; b.W_init = dS_in; b.zscale = d->scale; b.oscale = 1.f;
     if (S_ck && bwd_checkpoints(L) > 0) { b.S_ck = S_ck; b.n_ck = bwd_checkpoints(L); }
@@ -580,24 +706,21 @@ zeco_status zeco_gla_bwd_from_state(const zeco_gla_desc *d, const void *q, const
     return bwd_dv_dk_passes(d, d->P, d->L, q, k, v, g, dO, S_init, S_last, dS_in, dk, dv, dg, S_ck, s);
 }
 
-// Pieces each segment is cut into by zeco_gla_fused_bwd: the forward's (as many streams as fill the compute units
-// once, whole chunks or equal ragged pieces).  The gate gradient, a running sum of nearly cancelling terms whose
-// bf16 rounding noise grows with the square root of the run length, is re-anchored every 512 tokens inside a
-// piece from the forward-state checkpoints of the dQ pass, so the pieces need not be short for its sake: cut
-// down to 512 tokens each (as this call once did) the same passes spend 12-20 % more time on pipeline prologues,
-// on the states of 64 times as many pieces and on scans over them (c3 3.58 -> 3.12 ms, c4 28.2 -> 22.6 ms,
-// c5 113 -> 93.5 ms).
-static int bwd_pieces(const zeco_gla_desc *d) { return fused_pieces(d); }
+// zeco_gla_fused_bwd works on the forward's pieces (bwd_cut), whose entering states the forward can save for it.  The
+// gate gradient, a running sum of nearly cancelling terms whose bf16 rounding noise grows with the square root of
+// the run length, is re-anchored every 512 tokens inside a piece from the forward-state checkpoints of the dQ pass, so
+// the pieces need not be short for its sake: cut down to 512 tokens each the same passes spend 12-20 % more time on
+// pipeline prologues, on the states of many more pieces and on scans over them.
 
 // Workspace of zeco_gla_fused_bwd, in floats: forward piece states S_loc [n], S_init [n + one more
 // slot per (b,h) for the final state], their G_tot [n]; state gradients dS_loc [n], dS_in [n].
 struct BwdLayout {
     size_t n, state, off_Sloc, off_Sinit, off_Gtot, off_dSloc, off_dSin, off_tree, off_ck, total;
 };
-static BwdLayout bwd_layout(const zeco_gla_desc *d, int S) {
+static BwdLayout bwd_layout(const zeco_gla_desc *d, const zeco::Cut &cut) {
     BwdLayout w;
     const size_t bh = (size_t)d->B * d->H;
-    w.n = (size_t)d->P * S * bh;
+    w.n = (size_t)cut.n * bh;
     w.state = (size_t)d->d_k * d->d_v;
     w.off_Sloc = 0;
     w.off_Sinit = w.off_Sloc + w.n * w.state;
@@ -605,21 +728,19 @@ static BwdLayout bwd_layout(const zeco_gla_desc *d, int S) {
     w.off_dSloc = w.off_Gtot + w.n * d->d_k;
     w.off_dSin = w.off_dSloc + w.n * w.state;
     w.off_tree = w.off_dSin + w.n * w.state;   // scratch of the two piece scans where they run as trees
-    // checkpoints inside pieces that could not be cut down to 512 tokens (a chunk count without a fitting factor)
-    w.off_ck = w.off_tree + chain_scratch_floats(d->P * S, d->B * d->H, d->d_k, d->d_v, d->g_per_head);
-    w.total = w.off_ck + bwd_checkpoint_floats(d, d->P * S, d->L / S);
+    w.off_ck = w.off_tree + chain_scratch_floats(cut.n, d->B * d->H, d->d_k, d->d_v, d->g_per_head);
+    w.total = w.off_ck + bwd_checkpoint_floats(d, cut.n, longest_tokens(cut));   // checkpoints inside the pieces
     return w;
 }
 
 size_t zeco_gla_saved_states_bytes(const zeco_gla_desc *desc) {
     if (check_desc(desc, true) != ZECO_OK || desc->io_dtype != ZECO_BF16) return 0;
-    const BwdLayout w = bwd_layout(desc, bwd_pieces(desc));
-    return (w.n + (size_t)desc->B * desc->H) * w.state * sizeof(float);
+    return ((size_t)bwd_cut(desc).n + 1) * desc->B * desc->H * desc->d_k * desc->d_v * sizeof(float);
 }
 
 size_t zeco_gla_fused_bwd_workspace(const zeco_gla_desc *desc) {
     if (check_desc(desc, true) != ZECO_OK) return 0;
-    return bwd_layout(desc, bwd_pieces(desc)).total * sizeof(float);
+    return bwd_layout(desc, bwd_cut(desc)).total * sizeof(float);
 }
 
 zeco_status zeco_gla_fused_bwd(const zeco_gla_desc *d, const void *q, const void *k, const void *v,
@@ -635,20 +756,19 @@ zeco_status zeco_gla_fused_bwd(const zeco_gla_desc *d, const void *q, const void
         !aligned16(dg) || !aligned16(dS0) || !aligned16(workspace))
         return ZECO_ERR_INVALID_ARG;
     if (d->io_dtype != ZECO_BF16 && S_saved) return ZECO_ERR_UNSUPPORTED;   // (the fp32 forward saves no states)
-    if (workspace_bytes < zeco_gla_fused_bwd_workspace(d)) return ZECO_ERR_WORKSPACE;
+    const zeco::Cut cut = bwd_cut(d);
+    const BwdLayout w = bwd_layout(d, cut);
+    if (workspace_bytes < w.total * sizeof(float)) return ZECO_ERR_WORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const int S = bwd_pieces(d);
-    const BwdLayout w = bwd_layout(d, S);
     float *ws = static_cast<float *>(workspace);
     float *Sloc = ws + w.off_Sloc, *Sinit = ws + w.off_Sinit, *Gtot = ws + w.off_Gtot;
     float *dSloc = ws + w.off_dSloc, *dSin = ws + w.off_dSin;
     float *Slast = Sinit + w.n * w.state;
-    const int gb = gate_mode(d);
-    const int P = d->P * S, L = d->L / S;
+    const int P = cut.n, L = longest_tokens(cut);
 
     zeco::ChunkParams p;
     fill_chunk_params(p, d);
-    p.P = P; set_length(p, L);
+    set_cut(p, cut);
     zeco::ScanParams sp;
     sp.P = P; sp.groups = 1; sp.BH = d->B * d->H; sp.d_k = d->d_k; sp.d_v = d->d_v;
     sp.rows_per_block = d->d_k / 16; sp.gate_per_head = d->g_per_head;
@@ -669,12 +789,13 @@ zeco_status zeco_gla_fused_bwd(const zeco_gla_desc *d, const void *q, const void
     // the pieces' total decays when the forward state pass did not run), which the reverse scan chains
     // from the last piece to the first
     float *S_ck = bwd_checkpoints(L) > 0 ? ws + w.off_ck : nullptr;
-    zeco_status zs = bwd_dq_pass(d, P, L, q, k, v, g, dO, Sin, Sl, dq, dg, dSloc, S_saved ? Gtot : nullptr, S_ck, s);
+    zeco_status zs = bwd_dq_pass(d, P, L, q, k, v, g, dO, Sin, Sl, dq, dg, dSloc, S_saved ? Gtot : nullptr, S_ck, s,
+                                 nullptr, 0, &cut);
     if (zs != ZECO_OK) return zs;
     sp.S_loc = dSloc; sp.G_tot = Gtot; sp.S0 = dS_T; sp.S_init = dSin; sp.S_last = dS0; sp.reverse = 1;
     if ((e = launch_scan_chain(sp, ws + w.off_tree, s)) != hipSuccess) return ZECO_ERR_HIP;
 
-    return bwd_dv_dk_passes(d, P, L, q, k, v, g, dO, Sin, Sl, dSin, dk, dv, dg, S_ck, s);
+    return bwd_dv_dk_passes(d, P, L, q, k, v, g, dO, Sin, Sl, dSin, dk, dv, dg, S_ck, s, nullptr, 0, &cut);
 }
 
 zeco_status zeco_state_scan(int32_t P, int32_t BH, int32_t d_k, int32_t d_v, int32_t K_blocks,

@@ -14,6 +14,16 @@ enum GateMode { kGateF32 = 0, kGateBF16 = 1, kGateHead = 2 };
 // total log decay (twice the range of gates, one more multiplication of the state per chunk)
 constexpr int kGateWide = 4;
 
+// Cut of a run of `len` tokens into n pieces of whole 64-token chunks, as even as that allows: the last `rem` pieces
+// hold base + 1 chunks, the others base (base >= 1), and the first one the len % 64 tokens left over as well, so
+// that no piece is shorter than 64 tokens whatever the length, and all pieces begin where a forward pass over the
+// whole run, which makes its first chunk the short one, begins a chunk.  n = 0: no cut, the launch's segments are
+// used as they are.  With a cut the launch's "segments" are pieces: piece s is piece s % n of run s / n.
+struct Cut {
+    int n = 0, base = 0, rem = 0;
+    long long len = 0;
+};
+
 struct ChunkParams {
     const void *q, *k, *v, *g;
     void *o;
@@ -29,6 +39,11 @@ struct ChunkParams {
     // lengths, n_chunks and pad are unused.
     const long long *seg_start = nullptr;
     long long T = 0;
+    // Output pass over a run in one piece, optional: the states entering the pieces of `emit` (a cut of the same run),
+    // S_emit [emit.n, B, H, d_k, d_v], for a backward on those pieces; and the end state a second time, S_loc2
+    float *S_emit = nullptr, *S_loc2 = nullptr;
+    Cut emit;
+    Cut cut;                   // P counts pieces, n_chunks is the longest piece's (the stride of G_chunk), L and pad are unused
     float scale;
     float kscale;              // backward modes: multiplier carried by the operand in the k role
     long long sb, st, sh;      // q/k/g element strides
@@ -51,6 +66,7 @@ struct ApplyParams {
     int wgs_per_seg;           // workgroups per segment, ceil(64 n_chunks / tokens_per_wg)
     const long long *seg_start = nullptr;   // segments of unequal length (the kernels that read G_cum):
     long long T = 0;                        //   as in ChunkParams; n_chunks, pad, wgs_per_seg describe the bound L
+    Cut cut;                   // as in ChunkParams; wgs_per_seg describes the longest piece
     int gate_per_head = 0;     // 1: G_cum [B,T,H] (bf16 kernel only)
     int dense = 0;             // 1: stream every token, also where exp(G_cum) has vanished
     float scale;
@@ -83,6 +99,7 @@ struct BwdQKParams {
     int pad = 0;                 // 64 n_chunks - L: the first chunk processed holds 64 - pad tokens
     const long long *seg_start = nullptr;   // segments of unequal length, as in ChunkParams (L = bound on the
     long long T = 0;                        //   lengths, T = tokens per batch entry)
+    Cut cut;                     // as in ChunkParams
     float zscale, oscale;        // multipliers of the gated operand and of the output
     // dQ pass only, optional: also emit each segment's state gradient from dS = 0,
     // dS_loc [P,B,H,d_k,d_v] = qscale * sum_t (q_t .* exp(G_t))^T x_t, and its total log decay G_tot_out

@@ -1,0 +1,63 @@
+"""The one-call forward and backward cut the whole run of P * L tokens into pieces of whole chunks as even as possible:
+lengths where the cut can go wrong (one piece, pieces of one chunk, uneven pieces, a remainder in the last piece,
+segments whose ends fall inside pieces), against the oracle's unsegmented recurrence."""
+import zlib
+
+import numpy as np
+import pytest
+import torch
+
+from gpu_util import TOL, host, rel_err_bh
+from oracle import oracle
+from paper_2507_01004_amd import synth, zeco
+
+pytestmark = pytest.mark.gpu
+
+#        B, H, P, L, dk, dv, io, gate, C
+CASES = [
+    (1, 1, 1, 64, 64, 64, "bf16", "f32", 64),        # one chunk, one piece
+    (1, 8, 1, 500, 64, 128, "bf16", "f32", 64),      # one piece, ragged: the output pass alone
+    (2, 3, 1, 767, 128, 128, "bf16", "bf16", 64),    # few chunks
+    (1, 3, 5, 203, 128, 64, "bf16", "f32", 64),      # 15 whole chunks and 55 tokens; segments end inside pieces
+    (1, 1, 1, 4159, 64, 128, "bf16", "f32", 64),     # 64 whole chunks and 63 tokens
+    (3, 8, 1, 1985, 64, 64, "bf16", "bf16", 64),     # uneven pieces, one token over
+    (1, 7, 3, 1100, 128, 128, "bf16", "head", 64),
+    (1, 48, 1, 700, 64, 64, "bf16", "head", 64),     # more (batch, head) pairs, few pieces
+    (1, 3, 2, 1037, 64, 128, "f32", "f32", 64),
+    (1, 2, 3, 333, 128, 64, "f32", "f32", 16),
+    (2, 1, 1, 127, 64, 64, "f32", "f32", 32),
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "B%d_H%d_P%d_L%d_%dx%d_%s_%s_C%d" % c)
+def test_one_call_forward_and_backward_at_the_edges_of_the_cut(case):
+    B, H, P, L, dk, dv, io, gate, C = case
+    print("case", case, flush=True)
+    tol, T, head = TOL[io], P * L, gate == "head"
+    seed = zlib.crc32(repr(case).encode()) % 10000
+    inp = synth.make_inputs(B, T, H, dk, dv, seed=seed, io=io, g="f32" if head else gate, device="cuda", gate_div=64.0,
+                            per_head_gate=head)
+    q, k, v, g = (inp[n] for n in "qkvg")
+    gen = torch.Generator(device="cuda").manual_seed(seed + 1)
+    dO = torch.randn(v.shape, generator=gen, device="cuda").to(v.dtype)
+    S0 = torch.randn(B, H, dk, dv, device="cuda", generator=gen) * 0.3
+    dS_T = torch.randn(B, H, dk, dv, device="cuda", generator=gen) * 0.3
+    hg = np.repeat(host(g)[..., None], dk, axis=-1) if head else host(g)
+    args = (host(q), host(k), host(v), hg)
+    for s0 in (None, S0):
+        o_r, S_r = oracle.gla_recurrent(*args, 0.5, None if s0 is None else host(s0))
+        ref = oracle.gla_recurrent_bwd(*args, host(dO), 0.5, None if s0 is None else host(s0), host(dS_T))
+        ref_dg = ref[3].sum(axis=-1) if head else ref[3]
+        scheds = (zeco.SCHEDULE_TWO_PHASE, zeco.SCHEDULE_CORRECT) if io == "bf16" else (zeco.SCHEDULE_AUTO,)
+        for sched in scheds:
+            save = torch.empty(zeco.saved_states_bytes(q, v, g, P, C), dtype=torch.uint8, device="cuda") if io == "bf16" else None
+            o, S_last = zeco.gla_fused_fwd(q, k, v, g, P, scale=0.5, S0=s0, C=C, save=save, schedule=sched)
+            torch.cuda.synchronize()
+            assert rel_err_bh(host(o), o_r, (0, 2)) <= tol and rel_err_bh(host(S_last), S_r, (0, 1)) <= tol
+            for saved in {None, save}:
+                got = zeco.gla_fused_bwd(q, k, v, g, dO, P, scale=0.5, S0=None if saved is not None else s0, dS_T=dS_T, C=C, saved=saved)
+                torch.cuda.synchronize()
+                for nm, x, r in zip(("dq", "dk", "dv"), got[:3], ref[:3]):
+                    assert rel_err_bh(host(x), r, (0, 2)) <= tol, nm
+                assert rel_err_bh(host(got[3]), ref_dg, (0, 2)) <= tol, "dg"
+                assert rel_err_bh(host(got[4]), ref[4], (0, 1)) <= tol, "dS0"
