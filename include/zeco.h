@@ -239,14 +239,15 @@ zeco_status zeco_gla_bwd_from_state_varlen(const zeco_gla_desc *desc, const int6
                                            const float *dS_in, void *dq, void *dk, void *dv, float *dg,
                                            void *workspace, size_t workspace_bytes, void *stream);
 
-/* The whole forward and the whole backward over the same table, each in one call, on the segments as given
- * (they are not cut into shorter pieces: the longest segment sets a pass's duration): the three phases of
+/* The whole forward and the whole backward over the same table, each in one call: the three phases of
  * Alg. 1 - states from the zero state, their scan from S0, output pass - and, for the backward (App. A.4),
  * the forward states and their scan again, the dQ pass, which also leaves every segment's state gradient, the
  * reverse scan from dS_T, and the dV and dK passes; dg is re-anchored every 512 tokens as in
  * zeco_gla_bwd_from_state.  Arguments as in zeco_gla_fused_fwd / zeco_gla_fused_bwd (no saved states, no
  * schedule); workspace sizes from the *_workspace queries, sized for the bound desc->L.  Both take bf16 and
- * fp32 q/k/v. */
+ * fp32 q/k/v.  Where desc->L exceeds 2112 tokens the library cuts the tokens the table covers into pieces of its
+ * own, as in zeco_gla_fused_fwd (still without reading the table on the host); a table with a segment that breaks
+ * the rules is worked on segment by segment, as the separate calls do. */
 size_t zeco_gla_fused_fwd_varlen_workspace(const zeco_gla_desc *desc);
 zeco_status zeco_gla_fused_fwd_varlen(const zeco_gla_desc *desc, const int64_t *seg_start, int64_t T,
                                       const void *q, const void *k, const void *v, const void *g,

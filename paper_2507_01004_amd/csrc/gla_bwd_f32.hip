@@ -87,13 +87,19 @@ __global__ __launch_bounds__(DK * 4) void gla_bwd_qk_f32_kernel(BwdQKParams p) {
     if (p.seg_start) {
         // segments of unequal length: this one's bounds from the table; a segment that cannot be taken (under
         // 64 tokens, over the bound L, outside the tensor) is left alone
+        long long bound = p.L;
+        if (p.plan) {   // a table of pieces: unused slots have no work
+            if (seg >= p.seg_start[p.plan + 1]) return;
+            bound = p.seg_start[p.plan + 2];
+        }
         tok0 = p.seg_start[seg];
         T = p.T;
         len = p.seg_start[seg + 1] - tok0;
-        if (tok0 < 0 || len < 64 || len > p.L || tok0 > T - len) return;   // (in this order: no sum can overflow)
+        if (tok0 < 0 || len < 64 || len > bound || tok0 > T - len) return;   // (in this order: no sum can overflow)
     }
     if (p.cut.n) piece_range(p.cut, seg, p.P, tok0, len, T);
     const int N = (int)((len + C - 1) / C);
+    const int n_ck = p.plan ? (int)p.seg_start[p.plan + 3] : p.n_ck;
     const long long kbase = b * p.sb + tok0 * p.st + h * p.sh;
     const long long vbase = b * p.vb + tok0 * p.vt + h * p.vh;
     const float *x = (const float *)p.x + vbase, *y = (const float *)p.y + vbase;
@@ -118,7 +124,7 @@ __global__ __launch_bounds__(DK * 4) void gla_bwd_qk_f32_kernel(BwdQKParams p) {
     float carry = 0.f;
     if constexpr (REV) {
         const float *A = p.W_init + sbh * DK * DV;
-        const float *Bm = (seg + 1 < p.P) ? p.S_init + (sbh + (size_t)p.B * p.H) * DK * DV
+        const float *Bm = (seg + 1 < (p.plan ? (int)p.seg_start[p.plan + 1] : p.P)) ? p.S_init + (sbh + (size_t)p.B * p.H) * DK * DV
                                           : p.S_last + ((size_t)b * p.H + h) * DK * DV;
         const int i = tid >> 2, part = tid & 3;
         float acc = 0.f;
@@ -142,7 +148,7 @@ __global__ __launch_bounds__(DK * 4) void gla_bwd_qk_f32_kernel(BwdQKParams p) {
             // checkpoint: the forward state entering this chunk, for the dK pass to re-anchor dG with (the
             // accumulators as they are: the dK pass holds the gradient in the same layout)
             if (p.S_ck && c > 0 && c % Cfg::kAnchor == 0) {
-                float *ck = p.S_ck + (sbh * p.n_ck + (c / Cfg::kAnchor - 1)) * DK * DV + (size_t)tid * (Cfg::kNIT * 4);
+                float *ck = p.S_ck + (sbh * n_ck + (c / Cfg::kAnchor - 1)) * DK * DV + (size_t)tid * (Cfg::kNIT * 4);
 #pragma unroll
                 for (int it = 0; it < Cfg::kNIT; ++it) *reinterpret_cast<f32x4 *>(ck + it * 4) = Wacc[it];
             }
@@ -259,7 +265,7 @@ __global__ __launch_bounds__(DK * 4) void gla_bwd_qk_f32_kernel(BwdQKParams p) {
             // row_sum(dS .* S) of the state at this boundary and its gradient
             at_anchor = p.S_ck && c > 0 && c % Cfg::kAnchor == 0;
             if (at_anchor) {
-                const float *ck = p.S_ck + (sbh * p.n_ck + (c / Cfg::kAnchor - 1)) * DK * DV + (size_t)tid * (Cfg::kNIT * 4);
+                const float *ck = p.S_ck + (sbh * n_ck + (c / Cfg::kAnchor - 1)) * DK * DV + (size_t)tid * (Cfg::kNIT * 4);
                 float part = 0.f;
 #pragma unroll
                 for (int it = 0; it < Cfg::kNIT; ++it) {

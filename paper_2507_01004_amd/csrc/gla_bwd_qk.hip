@@ -159,10 +159,15 @@ __global__ __launch_bounds__(DK * 4) void gla_bwd_qk_kernel(BwdQKParams p) {
     if (p.seg_start) {
         // segments of unequal length: this one's bounds from the table; a segment that cannot be taken (under
         // 64 tokens, over the bound L, outside the tensor) is left alone: the whole workgroup leaves
+        long long bound = p.L;
+        if (p.plan) {   // a table of pieces: unused slots have no work
+            if (seg >= p.seg_start[p.plan + 1]) return;
+            bound = p.seg_start[p.plan + 2];
+        }
         tok0 = p.seg_start[seg];
         T = p.T;
         const long long len = p.seg_start[seg + 1] - tok0;
-        if (tok0 < 0 || len < 64 || len > p.L || tok0 > T - len) return;   // (in this order: no sum can overflow)
+        if (tok0 < 0 || len < 64 || len > bound || tok0 > T - len) return;   // (in this order: no sum can overflow)
         N = (int)((len + 63) >> 6);
         pad = 64 * N - (int)len;
     }
@@ -172,6 +177,7 @@ __global__ __launch_bounds__(DK * 4) void gla_bwd_qk_kernel(BwdQKParams p) {
         N = (int)((len + 63) >> 6);
         pad = (int)(64ll * N - len);
     }
+    const int n_ck = p.plan ? (int)p.seg_start[p.plan + 3] : p.n_ck;
     const long long kbase = b * p.sb + tok0 * p.st + h * p.sh;
     const long long vbase = b * p.vb + tok0 * p.vt + h * p.vh;
     const unsigned char *xb = (const unsigned char *)p.x + vbase * 2;
@@ -213,7 +219,7 @@ __global__ __launch_bounds__(DK * 4) void gla_bwd_qk_kernel(BwdQKParams p) {
     f32x4 carry = {0.f, 0.f, 0.f, 0.f};
     if constexpr (REV) {
         const float *A = p.W_init + sbh * DK * DV;
-        const float *Bm = (seg + 1 < p.P) ? p.S_init + (sbh + (size_t)p.B * p.H) * DK * DV
+        const float *Bm = (seg + 1 < (p.plan ? (int)p.seg_start[p.plan + 1] : p.P)) ? p.S_init + (sbh + (size_t)p.B * p.H) * DK * DV
                                           : p.S_last + ((size_t)b * p.H + h) * DK * DV;
         const int i = tid >> 2, part = tid & 3;
         float acc = 0.f;
@@ -350,7 +356,7 @@ __global__ __launch_bounds__(DK * 4) void gla_bwd_qk_kernel(BwdQKParams p) {
         if constexpr (!REV) {
             // checkpoint: the forward state entering this chunk, for the dK pass to re-anchor dG with
             if (p.S_ck && n > 0 && n % kAnchor == 0) {
-                float *ck = p.S_ck + (sbh * p.n_ck + (n / kAnchor - 1)) * DK * DV + (size_t)(w * 16 + l16) * DV + 4 * kg;
+                float *ck = p.S_ck + (sbh * n_ck + (n / kAnchor - 1)) * DK * DV + (size_t)(w * 16 + l16) * DV + 4 * kg;
 #pragma unroll
                 for (int it = 0; it < Cfg::NIT; ++it) *reinterpret_cast<f32x4 *>(ck + it * 16) = Sacc[it];
             }
@@ -614,7 +620,7 @@ __global__ __launch_bounds__(DK * 4) void gla_bwd_qk_kernel(BwdQKParams p) {
             // contribution of this chunk and everything after it to the earlier tokens, row_sum(dS .* S)
             const int c = chunk_of(n);
             if (p.S_ck && c > 0 && c % kAnchor == 0) {
-                const float *ck = p.S_ck + (sbh * p.n_ck + (c / kAnchor - 1)) * DK * DV + (size_t)(w * 16 + l16) * DV + 4 * kg;
+                const float *ck = p.S_ck + (sbh * n_ck + (c / kAnchor - 1)) * DK * DV + (size_t)(w * 16 + l16) * DV + 4 * kg;
                 float acc = 0.f;
 #pragma unroll
                 for (int it = 0; it < Cfg::NIT; ++it) {

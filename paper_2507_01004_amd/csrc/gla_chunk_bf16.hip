@@ -198,10 +198,15 @@ __global__ __launch_bounds__(chunk_threads(DK, DV, GM, MODE)) void gla_chunk_bf1
         if (p.seg_start) {
             // segments of unequal length: this one's bounds from the table.  A segment the kernel cannot take
             // (under 64 tokens, over the bound L, outside the tensor) is left alone: the whole workgroup leaves.
+            long long bound = p.L;
+            if (p.plan) {   // a table of pieces: unused slots have no work
+                if (seg >= p.seg_start[p.plan + 1]) return;
+                bound = p.seg_start[p.plan + 2];
+            }
             tok0 = p.seg_start[seg];
             T = p.T;
             const long long len = p.seg_start[seg + 1] - tok0;
-            if (tok0 < 0 || len < 64 || len > p.L || tok0 > T - len) return;   // (in this order: no sum can overflow)
+            if (tok0 < 0 || len < 64 || len > bound || tok0 > T - len) return;   // (in this order: no sum can overflow)
             N = (int)((len + 63) >> 6);
             pad = 64 * N - (int)len;
         }

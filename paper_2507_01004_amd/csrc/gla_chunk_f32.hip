@@ -96,10 +96,15 @@ __global__ __launch_bounds__(DV * 4) void gla_chunk_f32_kernel(ChunkParams p) {
     if (p.seg_start) {
         // segments of unequal length: this one's bounds from the table; a segment that cannot be taken (under
         // 64 tokens, over the bound L, outside the tensor) is left alone
+        long long bound = p.L;
+        if (p.plan) {   // a table of pieces: unused slots have no work
+            if (seg >= p.seg_start[p.plan + 1]) return;
+            bound = p.seg_start[p.plan + 2];
+        }
         tok0 = p.seg_start[seg];
         T = p.T;
         len = p.seg_start[seg + 1] - tok0;
-        if (tok0 < 0 || len < 64 || len > p.L || tok0 > T - len) return;   // (in this order: no sum can overflow)
+        if (tok0 < 0 || len < 64 || len > bound || tok0 > T - len) return;   // (in this order: no sum can overflow)
         n_chunks = (int)((len + C - 1) / C);
         pad = C * n_chunks - (int)len;
     }

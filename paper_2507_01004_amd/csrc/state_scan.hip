@@ -41,11 +41,11 @@ template <int V> __device__ __forceinline__ void scan_store(float *ptr, const Sc
 // thread are in flight at every moment, not only at the start of a batch: with BH * d_k * d_v / V threads
 // and a DRAM latency of 1-2 us that product is what decides how much of the HBM rate the kernel sees.
 // The steady-state loop is free of branches (a branch makes the compiler wait for all outstanding loads at
-// the join): STORE (S_init is written) and BYP (the by-products G_pre / G_sum are wanted) are template
-// flags, and the rounds whose refills would run past the chain's end are peeled off into a guarded tail.
+// the join): STORE (S_init is written), BYP (the by-products G_pre / G_sum are wanted) and PD (the chain's length is
+// on the device) are template flags, and the rounds whose refills would run past the chain's end are peeled off into a guarded tail.
 // Loads, the gate loads and the stores all count against the 63 memory operations a wave can have
 // outstanding, so D beyond 20 buys nothing.
-template <int V, int D, bool STORE, bool BYP>
+template <int V, int D, bool STORE, bool BYP, bool PD>
 __global__ __launch_bounds__(256) void state_scan_kernel(ScanParams p, int parts) {
     typedef ScanVec<V> vec_t;
     const int blocks_per_head = p.d_k / p.rows_per_block;
@@ -59,7 +59,7 @@ __global__ __launch_bounds__(256) void state_scan_kernel(ScanParams p, int parts
     const size_t gdim = p.gate_per_head ? 1 : p.d_k;        // log decays per (segment, head)
     const size_t g_stride = (size_t)p.BH * gdim;
     const size_t grp = blockIdx.y;                          // chain (group of P segments)
-    const int P = p.P;
+    const int P = PD ? (int)*p.P_used : p.P;
 
     const int e = part * 256 + threadIdx.x;
     if (e >= slab) return;
@@ -156,11 +156,12 @@ template <int V, int D> static hipError_t launch_scan_vd(const ScanParams &p, hi
     const dim3 grid((unsigned)blocks, p.groups), block(threads);
     const bool byp = p.G_pre || p.G_sum;
     if (p.S_init) {
-        if (byp) hipLaunchKernelGGL((state_scan_kernel<V, D, true, true>), grid, block, 0, s, p, parts);
-        else hipLaunchKernelGGL((state_scan_kernel<V, D, true, false>), grid, block, 0, s, p, parts);
+        if (byp) hipLaunchKernelGGL((state_scan_kernel<V, D, true, true, false>), grid, block, 0, s, p, parts);
+        else if (p.P_used) hipLaunchKernelGGL((state_scan_kernel<V, D, true, false, true>), grid, block, 0, s, p, parts);
+        else hipLaunchKernelGGL((state_scan_kernel<V, D, true, false, false>), grid, block, 0, s, p, parts);
     } else {
-        if (byp) hipLaunchKernelGGL((state_scan_kernel<V, D, false, true>), grid, block, 0, s, p, parts);
-        else hipLaunchKernelGGL((state_scan_kernel<V, D, false, false>), grid, block, 0, s, p, parts);
+        if (byp) hipLaunchKernelGGL((state_scan_kernel<V, D, false, true, false>), grid, block, 0, s, p, parts);
+        else hipLaunchKernelGGL((state_scan_kernel<V, D, false, false, false>), grid, block, 0, s, p, parts);
     }
     return hipGetLastError();
 }
@@ -174,6 +175,32 @@ hipError_t launch_scan(const ScanParams &p, hipStream_t s) {
     if (quads >= 65536) return launch_scan_vd<4, 8>(p, s);
     if (quads >= 32768) return launch_scan_vd<2, 16>(p, s);
     return launch_scan_vd<1, 16>(p, s);
+}
+
+__global__ __launch_bounds__(256) void plan_kernel(SegPlan p) {
+    bool fine = true;
+    for (int i = threadIdx.x; i < p.P; i += 256) {
+        const long long a = p.seg_start[i], len = p.seg_start[i + 1] - a;
+        fine = fine && !(a < 0 || len < 64 || len > p.L || a > p.T - len);   // the kernels' own rule
+    }
+    const bool even = __syncthreads_and(fine);
+    const long long a = p.seg_start[0], len = p.seg_start[p.P] - a, chunks = len / 64;
+    const long long n = even ? min((long long)p.n, chunks) : p.P;
+    const long long base = even ? chunks / n : 0, plain = even ? n - chunks % n : 0;   // pieces of base chunks, then of base + 1
+    for (int j = threadIdx.x; j <= p.slots; j += 256) {
+        const long long i = min((long long)j, n);
+        p.table[j] = !even ? p.seg_start[i] : i == 0 ? a : a + 64 * (i * base + max(i - plain, 0ll)) + (len & 63);
+    }
+    if (threadIdx.x == 0) {
+        p.table[p.slots + 1] = n;
+        p.table[p.slots + 2] = even ? len : p.L;
+        p.table[p.slots + 3] = even ? p.ck_even : p.ck_segments;
+    }
+}
+
+hipError_t launch_plan(const SegPlan &p, hipStream_t s) {
+    hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(256), 0, s, p);
+    return hipGetLastError();
 }
 
 // G_cum[b, t, h] += G_pre[piece of t, b, h] for per-head log decays (G_cum [B,T,H], G_pre [pieces,B,H], pieces

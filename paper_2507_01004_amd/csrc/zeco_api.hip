@@ -426,8 +426,8 @@ static bool corrects(const zeco_gla_desc *d, long long chunks) { return d->io_dt
 // are the ones entering the pieces; the estimate weighs a backward a tenth (not every forward has one, and the optimum is flat).  One
 // piece, where the forward alone favours it: a single launch that reads everything once, and leaves the states of the
 // pieces the backward then cuts for itself as it passes them.
-static long long pieces_for(const zeco_gla_desc *d, bool backward) {
-    const long long BH = (long long)d->B * d->H, T = (long long)d->P * d->L, chunks = T / 64;
+static long long pieces_for(const zeco_gla_desc *d, long long T, bool backward, bool may_be_one = true) {
+    const long long BH = (long long)d->B * d->H, chunks = T / 64;
     if (BH == 0) return 1;
     // a chain stays short enough for the workgroups of a launch to even out over several rounds
     const long long least = (chunks + kLongestPiece - 1) / kLongestPiece;
@@ -452,10 +452,11 @@ static long long pieces_for(const zeco_gla_desc *d, bool backward) {
     for (int k = 2; k <= 4; ++k) consider((chunks + k - 1) / k);
     consider(chunks / 64);   // just enough for the correction
     consider(least);
-    if (least <= 1) {
+    if (least <= 1 && may_be_one) {
         const double one = backward ? cost_backward(m, (double)BH, 1., (double)chunks) : cost_forward(m, (double)BH, 1., (double)chunks, false);
-        if (best == 0 || one <= 0.9 * (backward ? cost : cost_f)) best = 1;   // (clearly: the estimate is not that good)
+        if (best == 0 || one <= 0.93 * (backward ? cost : cost_f)) best = 1;   // (clearly: the estimate is not that good)
     }
+    if (best == 0) best = 1;
     if (best * BH > (1ll << 24)) best = d->P;   // (the limit on workgroups that the descriptor keeps)
     return best;
 }
@@ -497,10 +498,10 @@ static FwdLayout fwd_layout(const zeco_gla_desc *d, const zeco::Cut &cut) {
     w.total = w.off_tree + chain_scratch_floats(cut.n, d->B * d->H, d->d_k, d->d_v, d->g_per_head);
     return w;
 }
-static zeco::Cut fwd_cut(const zeco_gla_desc *d) { return cut_of((long long)d->P * d->L, pieces_for(d, false)); }
+static zeco::Cut fwd_cut(const zeco_gla_desc *d) { const long long T = (long long)d->P * d->L; return cut_of(T, pieces_for(d, T, false)); }
 static zeco::Cut bwd_cut(const zeco_gla_desc *d) {
     const zeco::Cut c = fwd_cut(d);
-    return c.n > 1 ? c : cut_of(c.len, pieces_for(d, true));
+    return c.n > 1 ? c : cut_of(c.len, pieces_for(d, c.len, true));
 }
 
 size_t zeco_gla_fused_fwd_workspace(const zeco_gla_desc *desc) {
@@ -618,11 +619,11 @@ static zeco_status bwd_dq_pass(const zeco_gla_desc *d, int P, int L, const void 
                                const void *v, const void *g, const void *dO, const float *S_init,
                                const float *S_last, void *dq, float *dg, float *dS_loc, float *G_tot_out,
                                float *S_ck, hipStream_t s, const int64_t *seg_start = nullptr, int64_t T = 0,
-                               const zeco::Cut *cut = nullptr) {
+                               const zeco::Cut *cut = nullptr, int plan = 0) {
     zeco::BwdQKParams b;
     fill_bwd_params(b, d, P, L, g, dg, S_init, S_last, cut);
     if (S_ck && bwd_checkpoints(L) > 0) { b.S_ck = S_ck; b.n_ck = bwd_checkpoints(L); b.short_last = 1; }
-    b.seg_start = reinterpret_cast<const long long *>(seg_start); b.T = T;
+    b.seg_start = reinterpret_cast<const long long *>(seg_start); b.T = T; b.plan = plan;
     b.x = dO; b.y = v; b.z = k; b.z2 = q; b.out = dq; b.W_init = S_init; b.zscale = 1.f; b.oscale = d->scale;
     if (d->io_dtype == ZECO_F32) {
         // the fp32 kernels: dQ, and the segments' state gradients from dS = 0 as a pass of their own
@@ -632,7 +633,7 @@ static zeco_status bwd_dq_pass(const zeco_gla_desc *d, int P, int L, const void 
         fill_chunk_params(c, d);
         c.P = P; set_length_c(c, L, d->C);
         if (cut) set_cut(c, *cut);
-        c.seg_start = reinterpret_cast<const long long *>(seg_start); c.T = T;
+        c.seg_start = reinterpret_cast<const long long *>(seg_start); c.T = T; c.plan = plan;
         c.k = q; c.v = dO; c.g = g; c.S_loc = dS_loc; c.G_tot = G_tot_out; c.scale = 1.f; c.kscale = d->scale;
         return from_hip(zeco::launch_chunk_f32(c, d->d_k, d->d_v, d->C, 3, s));
     }
@@ -646,19 +647,19 @@ static zeco_status bwd_dv_dk_passes(const zeco_gla_desc *d, int P, int L, const 
                                     const void *v, const void *g, const void *dO, const float *S_init,
                                     const float *S_last, const float *dS_in, void *dk, void *dv,
                                     float *dg, float *S_ck, hipStream_t s, const int64_t *seg_start = nullptr,
-                                    int64_t T = 0, const zeco::Cut *cut = nullptr) {
+                                    int64_t T = 0, const zeco::Cut *cut = nullptr, int plan = 0) {
     const int gb = gate_mode(d);
     zeco::ChunkParams c;
     fill_chunk_params(c, d);
     c.P = P; set_length(c, L);
     if (cut) set_cut(c, *cut);
-    c.seg_start = reinterpret_cast<const long long *>(seg_start); c.T = T;
+    c.seg_start = reinterpret_cast<const long long *>(seg_start); c.T = T; c.plan = plan;
     c.q = k; c.k = q; c.v = dO; c.g = g; c.o = dv; c.S_init = dS_in; c.scale = 1.f; c.kscale = d->scale;
     if (launch_phase(c, d, 4, s) != hipSuccess) return ZECO_ERR_HIP;
 
     zeco::BwdQKParams b;
     fill_bwd_params(b, d, P, L, g, dg, S_init, S_last, cut);
-    b.seg_start = reinterpret_cast<const long long *>(seg_start); b.T = T;
+    b.seg_start = reinterpret_cast<const long long *>(seg_start); b.T = T; b.plan = plan;
     b.x = v; b.y = dO; b.z = q; b.z2 = k; b.out = dk; b.W_init = dS_in; b.zscale = d->scale; b.oscale = 1.f;
     if (S_ck && bwd_checkpoints(L) > 0) { b.S_ck = S_ck; b.n_ck = bwd_checkpoints(L); }
     if (d->io_dtype == ZECO_F32) return from_hip(zeco::launch_bwd_qk_f32(b, d->d_k, d->d_v, d->C, true, s));
@@ -1028,21 +1029,38 @@ zeco_status zeco_gla_bwd_from_state_varlen(const zeco_gla_desc *d, const int64_t
 
 // The whole forward and the whole backward over the same table, each in one call: the phases of Alg. 1 (states,
 // scan, output pass) and of the backward (forward states and their scan, dQ pass with the segments' state
-// gradients, reverse scan, dV and dK passes) on the segments as given.
+// gradients, reverse scan, dV and dK passes).
+//
+// Segments of up to 33 chunks are worked on as given: their chains are short, and the call then repeats the separate
+// calls bit for bit.  Longer ones are cut: the segments together are one run of tokens, whose pieces need not end where
+// they do, so the run is cut as in zeco_gla_fused_fwd, on the device (launch_plan), where the table is.  Measured with
+// 8 segments of 1160 .. 9287 tokens and 16 heads, forward and backward: 3.15 ms as given (the longest segment's
+// chain), 0.86 ms in 16 pieces.
+constexpr int kWholeSegments = 33 * 64;
 struct VarlenLayout {   // workspace carve-up, in floats
-    size_t state, off_Sinit, off_Gtot, off_dSloc, off_dSin, off_ck, total;
+    int slots;          // pieces, or segments
+    size_t state, off_Sinit, off_Gtot, off_dSloc, off_dSin, off_ck, off_table, total;
 };
 static VarlenLayout varlen_layout(const zeco_gla_desc *d, bool backward) {
     VarlenLayout w;
-    const size_t n = (size_t)d->P * d->B * d->H, bh = (size_t)d->B * d->H;
+    const bool cut = d->L > kWholeSegments;
+    const long long T = (long long)d->P * d->L;         // no valid table covers more
+    const long long n = cut ? pieces_for(d, T, false, false) : 0;
+    w.slots = n > d->P ? (int)n : d->P;
+    const size_t slots = (size_t)w.slots * d->B * d->H, bh = (size_t)d->B * d->H;
     w.state = (size_t)d->d_k * d->d_v;
-    w.off_Sinit = n * w.state;                          // S_loc [n] first
-    w.off_Gtot = w.off_Sinit + (n + bh) * w.state;      // S_init [n] and one more slot: the final state
-    w.off_dSloc = w.off_Gtot + ((n * (d->g_per_head ? 1 : d->d_k) + 3) & ~(size_t)3);
-    if (!backward) { w.off_dSin = w.off_ck = w.total = w.off_dSloc; return w; }
-    w.off_dSin = w.off_dSloc + n * w.state;
-    w.off_ck = w.off_dSin + n * w.state;
-    w.total = w.off_ck + bwd_checkpoint_floats(d, d->P, d->L);
+    w.off_Sinit = slots * w.state;                      // S_loc [slots] first
+    w.off_Gtot = w.off_Sinit + (slots + bh) * w.state;  // S_init [slots] and one more: the final state
+    w.off_dSloc = w.off_Gtot + ((slots * (d->g_per_head ? 1 : d->d_k) + 3) & ~(size_t)3);
+    w.off_dSin = w.off_ck = w.off_table = w.off_dSloc;
+    if (backward) {
+        w.off_dSin = w.off_dSloc + slots * w.state;
+        w.off_ck = w.off_dSin + slots * w.state;
+        // checkpoints: of the segments, or of n pieces with (chunks / n + 1) / 8 each at most
+        const size_t per = cut ? (size_t)T / 512 + w.slots : (size_t)d->P * bwd_checkpoints(d->L);
+        w.off_table = w.off_ck + per * bh * w.state;
+    }
+    w.total = w.off_table + (cut ? 2 * ((size_t)w.slots + 4) : 0);
     return w;
 }
 
@@ -1055,6 +1073,29 @@ size_t zeco_gla_fused_bwd_varlen_workspace(const zeco_gla_desc *desc) {
     return varlen_layout(desc, true).total * sizeof(float);
 }
 
+// What the passes of a varlen call work on: the caller's table, or a table of pieces made from it (enqueued here).
+struct VarlenRun {
+    int P = 0, L = 0, plan = 0;
+    const int64_t *table = nullptr;
+    const long long *used = nullptr;
+};
+static hipError_t varlen_run(VarlenRun &r, const zeco_gla_desc *d, const VarlenLayout &w, float *ws, const int64_t *seg_start,
+                             int64_t T, hipStream_t s) {
+    r.P = d->P; r.L = d->L; r.table = seg_start;
+    if (d->L <= kWholeSegments) return hipSuccess;
+    const long long run = (long long)d->P * d->L < T ? (long long)d->P * d->L : T;
+    long long n = pieces_for(d, run, false, false);
+    if (n > w.slots) n = w.slots;
+    zeco::SegPlan p;
+    p.seg_start = reinterpret_cast<const long long *>(seg_start);
+    p.table = reinterpret_cast<long long *>(ws + w.off_table);
+    p.P = d->P; p.slots = w.slots; p.n = (int)n; p.L = d->L; p.T = T;
+    p.ck_even = bwd_checkpoints(longest_tokens(cut_of(run, n)));
+    p.ck_segments = bwd_checkpoints(d->L);
+    r.P = r.plan = w.slots; r.table = reinterpret_cast<const int64_t *>(p.table); r.used = p.table + w.slots + 1;
+    return zeco::launch_plan(p, s);
+}
+
 zeco_status zeco_gla_fused_fwd_varlen(const zeco_gla_desc *d, const int64_t *seg_start, int64_t T, const void *q,
                                       const void *k, const void *v, const void *g, const float *S0, void *o,
                                       float *S_last, void *workspace, size_t workspace_bytes, void *stream) {
@@ -1065,18 +1106,21 @@ zeco_status zeco_gla_fused_fwd_varlen(const zeco_gla_desc *d, const int64_t *seg
     if (!aligned16(q) || !aligned16(k) || !aligned16(v) || !aligned16(g) || !aligned16(o) || !aligned16(S0) ||
         !aligned16(S_last) || !aligned16(workspace))
         return ZECO_ERR_INVALID_ARG;
-    if (workspace_bytes < zeco_gla_fused_fwd_varlen_workspace(d)) return ZECO_ERR_WORKSPACE;
-    hipStream_t s = static_cast<hipStream_t>(stream);
     const VarlenLayout w = varlen_layout(d, false);
+    if (workspace_bytes < w.total * sizeof(float)) return ZECO_ERR_WORKSPACE;
+    hipStream_t s = static_cast<hipStream_t>(stream);
     float *Sloc = static_cast<float *>(workspace), *Sinit = Sloc + w.off_Sinit, *Gtot = Sloc + w.off_Gtot;
+    VarlenRun run;
+    if (varlen_run(run, d, w, Sloc, seg_start, T, s) != hipSuccess) return ZECO_ERR_HIP;
     zeco::ChunkParams p;
     fill_chunk_params(p, d);
-    p.seg_start = reinterpret_cast<const long long *>(seg_start); p.T = T;
+    p.P = run.P; p.plan = run.plan;
+    p.seg_start = reinterpret_cast<const long long *>(run.table); p.T = T;
     p.k = k; p.v = v; p.g = g; p.S_loc = Sloc; p.G_tot = Gtot;
     if (launch_phase(p, d, 1, s) != hipSuccess) return ZECO_ERR_HIP;
     zeco::ScanParams sp;
     sp.S_loc = Sloc; sp.G_tot = Gtot; sp.S0 = S0; sp.S_init = Sinit; sp.S_last = S_last;
-    sp.P = d->P; sp.groups = 1; sp.BH = d->B * d->H; sp.d_k = d->d_k; sp.d_v = d->d_v;
+    sp.P = run.P; sp.P_used = run.used; sp.groups = 1; sp.BH = d->B * d->H; sp.d_k = d->d_k; sp.d_v = d->d_v;
     sp.rows_per_block = d->d_k / 16; sp.gate_per_head = d->g_per_head;
     if (zeco::launch_scan(sp, s) != hipSuccess) return ZECO_ERR_HIP;
     p.q = q; p.o = o; p.S_init = Sinit; p.S_loc = nullptr; p.G_tot = nullptr;
@@ -1095,29 +1139,34 @@ zeco_status zeco_gla_fused_bwd_varlen(const zeco_gla_desc *d, const int64_t *seg
         !aligned16(dS_T) || !aligned16(dq) || !aligned16(dk) || !aligned16(dv) || !aligned16(dg) || !aligned16(dS0) ||
         !aligned16(workspace))
         return ZECO_ERR_INVALID_ARG;
-    if (workspace_bytes < zeco_gla_fused_bwd_varlen_workspace(d)) return ZECO_ERR_WORKSPACE;
-    hipStream_t s = static_cast<hipStream_t>(stream);
     const VarlenLayout w = varlen_layout(d, true);
-    const size_t n = (size_t)d->P * d->B * d->H;
+    if (workspace_bytes < w.total * sizeof(float)) return ZECO_ERR_WORKSPACE;
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    const size_t slots = (size_t)w.slots * d->B * d->H;
     float *ws = static_cast<float *>(workspace);
-    float *Sloc = ws, *Sinit = ws + w.off_Sinit, *Slast = Sinit + n * w.state, *Gtot = ws + w.off_Gtot;
+    float *Sloc = ws, *Sinit = ws + w.off_Sinit, *Slast = Sinit + slots * w.state, *Gtot = ws + w.off_Gtot;
     float *dSloc = ws + w.off_dSloc, *dSin = ws + w.off_dSin;
     float *S_ck = bwd_checkpoints(d->L) > 0 ? ws + w.off_ck : nullptr;
+    VarlenRun run;
+    if (varlen_run(run, d, w, ws, seg_start, T, s) != hipSuccess) return ZECO_ERR_HIP;
     zeco::ChunkParams p;
     fill_chunk_params(p, d);
-    p.seg_start = reinterpret_cast<const long long *>(seg_start); p.T = T;
+    p.P = run.P; p.plan = run.plan;
+    p.seg_start = reinterpret_cast<const long long *>(run.table); p.T = T;
     p.k = k; p.v = v; p.g = g; p.S_loc = Sloc; p.G_tot = Gtot;
     if (launch_phase(p, d, 1, s) != hipSuccess) return ZECO_ERR_HIP;
     zeco::ScanParams sp;
     sp.S_loc = Sloc; sp.G_tot = Gtot; sp.S0 = S0; sp.S_init = Sinit; sp.S_last = Slast;
-    sp.P = d->P; sp.groups = 1; sp.BH = d->B * d->H; sp.d_k = d->d_k; sp.d_v = d->d_v;
+    sp.P = run.P; sp.P_used = run.used; sp.groups = 1; sp.BH = d->B * d->H; sp.d_k = d->d_k; sp.d_v = d->d_v;
     sp.rows_per_block = d->d_k / 16; sp.gate_per_head = d->g_per_head;
     if (zeco::launch_scan(sp, s) != hipSuccess) return ZECO_ERR_HIP;
-    zeco_status zs = bwd_dq_pass(d, d->P, d->L, q, k, v, g, dO, Sinit, Slast, dq, dg, dSloc, nullptr, S_ck, s, seg_start, T);
+    zeco_status zs = bwd_dq_pass(d, run.P, run.L, q, k, v, g, dO, Sinit, Slast, dq, dg, dSloc, nullptr, S_ck, s, run.table, T,
+                                 nullptr, run.plan);
     if (zs != ZECO_OK) return zs;
     sp.S_loc = dSloc; sp.S0 = dS_T; sp.S_init = dSin; sp.S_last = dS0; sp.reverse = 1;
     if (zeco::launch_scan(sp, s) != hipSuccess) return ZECO_ERR_HIP;
-    return bwd_dv_dk_passes(d, d->P, d->L, q, k, v, g, dO, Sinit, Slast, dSin, dk, dv, dg, S_ck, s, seg_start, T);
+    return bwd_dv_dk_passes(d, run.P, run.L, q, k, v, g, dO, Sinit, Slast, dSin, dk, dv, dg, S_ck, s, run.table, T, nullptr,
+                            run.plan);
 }
 
 // ---- chunk-decay form of the local pass and the correction ---------------------------------------------

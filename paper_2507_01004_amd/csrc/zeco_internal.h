@@ -24,30 +24,46 @@ struct Cut {
     long long len = 0;
 };
 
+// Table of pieces in the segments' place, made on the device from the caller's table of segments (which the host
+// cannot read): table [slots + 4] int64 = piece offsets [slots + 1], pieces in use, upper bound of their lengths,
+// checkpoints per piece.  The launches have a workgroup per slot; those of unused slots leave.
+// When all P segments keep the rules they are one run of tokens and it is cut into n even pieces (as Cut does); with a
+// segment that breaks them the pieces are the segments, under the caller's bound, and the kernels skip that one.
+struct SegPlan {
+    const long long *seg_start;
+    long long *table;
+    int P, slots, n;
+    long long L, T;              // bound on the segments' lengths, tokens per batch entry
+    int ck_even, ck_segments;    // checkpoints per piece in the two cases
+};
+
+// (The kernels find their tokens from the fields up to `vh`; together in a few cache lines because a workgroup's first
+// loads from the argument block, which lies in host memory, are on the critical path of a short launch.)
 struct ChunkParams {
+    int B, P, H, L;
+    int n_chunks;              // ceil(L / 64)
+    int pad = 0;               // 64 n_chunks - L: the first chunk processed holds 64 - pad tokens
+    int plan = 0;              // slots of a table written by launch_plan (SegPlan); 0: seg_start is the caller's own table
+    float scale;
+    Cut cut;                   // P counts pieces, n_chunks is the longest piece's (the stride of G_chunk), L and pad are unused
+    // Segments of unequal length (modes 0 to 4 of the bf16 kernel, and the fp32 kernel): segment p covers tokens
+    // [seg_start[p], seg_start[p+1]) of the T tokens of every batch entry; L is then the upper bound of the
+    // lengths, n_chunks and pad are unused.
+    const long long *seg_start = nullptr;
+    long long T = 0;
+    long long sb, st, sh;      // q/k/g element strides
+    long long vb, vt, vh;      // v/o element strides
     const void *q, *k, *v, *g;
     void *o;
     float *S_loc, *G_cum, *G_tot;
     const float *S_init;       // [P,B,H,d_k,d_v] initial states (modes that start from a given state)
     const float *G_off = nullptr;   // [P,B,H,d_k] ([P,B,H] per-head) log decay preceding each segment (mode 5 only)
     float *G_chunk = nullptr;       // [B,P,n_chunks,H,d_k] log decay from the segment start to each chunk's start (mode 6 only)
-    int B, P, H, L;
-    int n_chunks;              // ceil(L / 64)
-    int pad = 0;               // 64 n_chunks - L: the first chunk processed holds 64 - pad tokens
-    // Segments of unequal length (modes 0 to 4 of the bf16 kernel, and the fp32 kernel): segment p covers tokens
-    // [seg_start[p], seg_start[p+1]) of the T tokens of every batch entry; L is then the upper bound of the
-    // lengths, n_chunks and pad are unused.
-    const long long *seg_start = nullptr;
-    long long T = 0;
     // Output pass over a run in one piece, optional: the states entering the pieces of `emit` (a cut of the same run),
     // S_emit [emit.n, B, H, d_k, d_v], for a backward on those pieces; and the end state a second time, S_loc2
     float *S_emit = nullptr, *S_loc2 = nullptr;
     Cut emit;
-    Cut cut;                   // P counts pieces, n_chunks is the longest piece's (the stride of G_chunk), L and pad are unused
-    float scale;
     float kscale;              // backward modes: multiplier carried by the operand in the k role
-    long long sb, st, sh;      // q/k/g element strides
-    long long vb, vt, vh;      // v/o element strides
 };
 
 struct ApplyParams {
@@ -79,6 +95,7 @@ struct ScanParams {
     const float *S_loc, *G_tot, *S0;
     float *S_init, *S_last;      // either may be null (not stored)
     int P, BH, d_k, d_v, rows_per_block, groups;
+    const long long *P_used = nullptr;   // optional, one chain only: its length, on the device (at most P)
     int reverse = 0;             // 1: chain runs from segment P-1 down to 0
     // optional, each on its own: G_pre [groups*P, BH, d_k] = sum of G_tot over the earlier segments of the
     // chain (forward chains only), G_sum [groups, BH, d_k] = sum over all of them ([.., BH] with one decay per head)
@@ -91,15 +108,18 @@ struct ScanParams {
 // pass leaves q .* dq there, the dK pass turns it into dG); S_init, S_last: forward states (dK pass).
 // With per-head gates g and dg are [B,T,H] and the channel sums are taken before anything is stored.
 struct BwdQKParams {
+    int B, P, H, L, n_chunks;    // n_chunks = ceil(L / 64)
+    int pad = 0;                 // 64 n_chunks - L: the first chunk processed holds 64 - pad tokens
+    int plan = 0;                // as in ChunkParams
+    int n_ck = 0;
+    Cut cut;                     // as in ChunkParams
+    const long long *seg_start = nullptr;   // segments of unequal length, as in ChunkParams (L = bound on the
+    long long T = 0;                        //   lengths, T = tokens per batch entry)
+    long long sb, st, sh, vb, vt, vh;
     const void *x, *y, *z, *z2, *g;
     void *out;
     float *dg;
     const float *W_init, *S_init, *S_last;
-    int B, P, H, L, n_chunks;    // n_chunks = ceil(L / 64)
-    int pad = 0;                 // 64 n_chunks - L: the first chunk processed holds 64 - pad tokens
-    const long long *seg_start = nullptr;   // segments of unequal length, as in ChunkParams (L = bound on the
-    long long T = 0;                        //   lengths, T = tokens per batch entry)
-    Cut cut;                     // as in ChunkParams
     float zscale, oscale;        // multipliers of the gated operand and of the output
     // dQ pass only, optional: also emit each segment's state gradient from dS = 0,
     // dS_loc [P,B,H,d_k,d_v] = qscale * sum_t (q_t .* exp(G_t))^T x_t, and its total log decay G_tot_out
@@ -108,9 +128,8 @@ struct BwdQKParams {
     // optional checkpoints that re-anchor dG: S_ck [B*P*H, n_ck, d_k, d_v], the forward state entering every
     // 8th chunk (chunks 8, 16, ..) of each segment; written by the dQ pass, read by the dK pass.  With it the dQ
     // pass must be launched with short_last = 1 (the short chunk of a ragged length at the segment's end).
+    int short_last = 0;
     float *S_ck = nullptr;
-    int n_ck = 0, short_last = 0;
-    long long sb, st, sh, vb, vt, vh;
 };
 
 // A kernel that uses more dynamic LDS than the default limit has the limit raised once per device (the
@@ -145,6 +164,7 @@ hipError_t launch_apply_bf16(const ApplyParams &p, int d_k, int d_v, hipStream_t
 // from (g, G_chunk) instead of G_cum; per-channel gates
 hipError_t launch_apply_cd_bf16(const ApplyParams &p, int d_k, int d_v, hipStream_t s);
 hipError_t launch_scan(const ScanParams &p, hipStream_t s);
+hipError_t launch_plan(const SegPlan &p, hipStream_t s);
 // reverse = false: dQ (x = dO, y = v, z = k, z2 = q, W_init = forward states); true: dK (x = v, y = dO,
 // z = q, z2 = k, W_init = state gradients; must run after the dQ pass, whose q .* dq it consumes)
 hipError_t launch_bwd_qk(const BwdQKParams &p, int d_k, int d_v, int gate_mode, bool reverse, hipStream_t s);

@@ -61,3 +61,82 @@ def test_one_call_forward_and_backward_at_the_edges_of_the_cut(case):
                     assert rel_err_bh(host(x), r, (0, 2)) <= tol, nm
                 assert rel_err_bh(host(got[3]), ref_dg, (0, 2)) <= tol, "dg"
                 assert rel_err_bh(host(got[4]), ref[4], (0, 1)) <= tol, "dS0"
+
+
+VARLEN = [
+    # lengths (one over 2112 tokens, so that the call cuts), tokens before the first segment, H, dk, dv, io, gate, C
+    ((2113, 64, 700, 65), 0, 2, 128, 128, "bf16", "f32", 64),
+    ((100, 3001, 64), 37, 3, 64, 128, "bf16", "head", 64),
+    ((64, 64, 2500), 64, 1, 128, 64, "bf16", "bf16", 64),
+    ((2200, 129), 5, 2, 64, 64, "f32", "f32", 32),
+    ((64,) * 30 + (2176,), 0, 16, 64, 64, "bf16", "f32", 64),     # more segments than pieces
+]
+
+
+@pytest.mark.parametrize("case", VARLEN, ids=lambda c: "%dsegs_%d_H%d_%dx%d_%s_%s" % (len(c[0]), c[1], *c[2:7]))
+def test_one_call_over_long_unequal_segments(case):
+    """The calls that cut on the device, against the oracle over the tokens the table covers; the others stay as they
+    are.  Then the same captured in a graph and replayed with other tables: one with the same lengths in another
+    order, one with a segment that is too short, whose rows stay as they are while the segments before it, which it
+    cannot touch, come out as without it."""
+    lengths, lead, H, dk, dv, io, gate, C = case
+    print("case", case, flush=True)
+    tol, head, T = TOL[io], gate == "head", lead + sum(lengths) + 11
+    seed = zlib.crc32(repr(case).encode()) % 10000
+    inp = synth.make_inputs(1, T, H, dk, dv, seed=seed, io=io, g="f32" if head else gate, device="cuda", gate_div=64.0,
+                            per_head_gate=head)
+    q, k, v, g = (inp[n] for n in "qkvg")
+    gen = torch.Generator(device="cuda").manual_seed(seed + 1)
+    dO = torch.randn(v.shape, generator=gen, device="cuda").to(v.dtype)
+    S0 = torch.randn(1, H, dk, dv, device="cuda", generator=gen) * 0.3
+    dS_T = torch.randn(1, H, dk, dv, device="cuda", generator=gen) * 0.3
+    a, e = lead, lead + sum(lengths)
+    hg = np.repeat(host(g)[..., None], dk, axis=-1) if head else host(g)
+    args = [np.ascontiguousarray(x[:, a:e]) for x in (host(q), host(k), host(v), hg)]
+    o_r, S_r = oracle.gla_recurrent(*args, 0.5, host(S0))
+    ref = oracle.gla_recurrent_bwd(*args, np.ascontiguousarray(host(dO)[:, a:e]), 0.5, host(S0), host(dS_T))
+    ref_dg = ref[3].sum(axis=-1) if head else ref[3]
+    mark = 77.0
+    seg = torch.tensor([lead] + [lead + int(x) for x in np.cumsum(lengths)], dtype=torch.int64, device="cuda")
+    o, S_last = torch.empty_like(v), torch.empty_like(S0)
+    grads = (torch.empty_like(q), torch.empty_like(k), torch.empty_like(v), torch.empty(g.shape, device="cuda"), torch.empty_like(S0))
+    bound = max(lengths)
+    desc = zeco._varlen_desc(q, v, zeco._dtype_code(g), head, seg, bound, 0.5, C)
+    L = zeco.lib()
+    ws_f, ws_b = (torch.zeros(int(n(zeco.ctypes.byref(desc))), dtype=torch.uint8, device="cuda")
+                  for n in (L.zeco_gla_fused_fwd_varlen_workspace, L.zeco_gla_fused_bwd_varlen_workspace))
+
+    def run():
+        zeco.gla_fused_fwd_varlen(q, k, v, g, seg, bound, scale=0.5, C=C, S0=S0, out=(o, S_last), workspace=ws_f)
+        zeco.gla_fused_bwd_varlen(q, k, v, g, dO, seg, bound, scale=0.5, C=C, S0=S0, dS_T=dS_T, out=grads, workspace=ws_b)
+
+    def check():
+        torch.cuda.synchronize()
+        assert rel_err_bh(host(o)[:, a:e], o_r, (0, 2)) <= tol and rel_err_bh(host(S_last), S_r, (0, 1)) <= tol
+        for nm, x, r in zip(("dq", "dk", "dv", "dg"), grads, ref[:3] + (ref_dg,)):
+            assert rel_err_bh(host(x)[:, a:e], r, (0, 2)) <= tol, nm
+        assert rel_err_bh(host(grads[4]), ref[4], (0, 1)) <= tol
+        for x in (o,) + grads[:4]:
+            assert torch.all(x[:, :a] == mark) and torch.all(x[:, e:] == mark)
+
+    for x in (o,) + grads[:4]:
+        x.fill_(mark)
+    run()
+    check()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        run()
+    for order in (lengths, lengths[::-1]):
+        seg.copy_(torch.tensor([lead] + [lead + int(x) for x in np.cumsum(order)], dtype=torch.int64))
+        for x in (o,) + grads[:4]:
+            x.fill_(mark)
+        graph.replay()
+        check()
+    good = o.clone()
+    seg[-2] = e - 40                      # the last segment breaks the rules, and perhaps the one before it (too long)
+    o.fill_(mark)
+    graph.replay()
+    torch.cuda.synchronize()
+    assert torch.all(o[:, e - 40:] == mark)
+    n = int(seg[-3]) if len(lengths) > 2 else a
+    assert (o[:, a:n].float() - good[:, a:n].float()).abs().max().item() <= tol * good.float().abs().max().item() if n > a else True
