@@ -441,14 +441,35 @@ __global__ __launch_bounds__(DV * 4) void apply_init_f32_kernel(ApplyParams p) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) Sreg[it][r] = S[(size_t)(16 * it + 4 * kg + r) * DV + 16 * w + l16];
 
+    // q, G_cum and o of a block are fetched 16 (o: 4) bytes a load, all of them in flight together, q and G_cum a block
+    // ahead (loaded one by one, a single block took 12 us).
+    constexpr int ITEMS = 64 * (DK / 4) / NT;
+    f32x4 rq[ITEMS], rG[ITEMS];
+    auto fetch = [&](int blk) __attribute__((always_inline)) {
+        const long long t0 = apply_block_start(pad, c0 + blk);
+#pragma unroll
+        for (int m = 0; m < ITEMS; ++m) {
+            const int e = tid + NT * m, t = e / (DK / 4), c = 4 * (e % (DK / 4));
+            rq[m] = *reinterpret_cast<const f32x4 *>(qp + (t0 + t) * p.st + c);
+            rG[m] = *reinterpret_cast<const f32x4 *>(Gc + (t0 + t) * gcs + c);
+        }
+    };
+    fetch(0);
     for (int blk = 0; blk < nblk; ++blk) {
         const long long t0 = apply_block_start(pad, c0 + blk);
         const int rows = apply_block_rows(pad, c0 + blk);
-        for (int e = tid; e < 64 * DK; e += NT) {
-            const int t = e / DK, c = e % DK;
-            const long long tt = t0 + t;
-            Qh[t * QS + c] = qp[tt * p.st + c] * fast_exp(Gc[tt * gcs + c]) * p.scale;
+        float old[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) old[i] = op[(t0 + 16 * (i / 4) + 4 * kg + i % 4) * p.vt + 16 * w + l16];
+#pragma unroll
+        for (int m = 0; m < ITEMS; ++m) {
+            const int e = tid + NT * m, t = e / (DK / 4), c = 4 * (e % (DK / 4));
+            f32x4 x;
+#pragma unroll
+            for (int a = 0; a < 4; ++a) x[a] = rq[m][a] * fast_exp(rG[m][a]) * p.scale;
+            *reinterpret_cast<f32x4 *>(Qh + t * QS + c) = x;
         }
+        if (blk + 1 < nblk) fetch(blk + 1);
         __syncthreads();
 #pragma unroll
         for (int mt = 0; mt < 4; ++mt) {
@@ -460,7 +481,7 @@ __global__ __launch_bounds__(DV * 4) void apply_init_f32_kernel(ApplyParams p) {
                     acc = mma_f32(Qh[(16 * mt + l16) * QS + 16 * it + 4 * kg + r], Sreg[it][r], acc);
 #pragma unroll
             for (int r = 0; r < 4; ++r)
-                if (16 * mt + 4 * kg + r < rows) op[(t0 + 16 * mt + 4 * kg + r) * p.vt + 16 * w + l16] += acc[r];
+                if (16 * mt + 4 * kg + r < rows) op[(t0 + 16 * mt + 4 * kg + r) * p.vt + 16 * w + l16] = old[4 * mt + r] + acc[r];
         }
         __syncthreads();
     }

@@ -34,43 +34,52 @@ template <int DK, int DV, int C> struct QKF32Cfg {
     static constexpr int kWaves = DK / 16;          // 16 output channels each
     static constexpr int kThreads = 64 * kWaves;
     static constexpr int kNIT = DV / 16;            // row tiles of W per wave
-    static constexpr int kTG = kThreads / DK;       // token groups in the gate pass (4)
-    static constexpr int kTPT = C / kTG;            // tokens per thread in the gate pass
+    // gate pass: 4 channels x kTPT consecutive tokens per thread, the token groups of a wave stitched by shuffles
+    static constexpr int kCQ = DK / 4;              // channel quads
+    static constexpr int kTG = kThreads / kCQ;      // token groups (16: the waves' count times the groups in a wave)
+    static constexpr int kTPT = C / kTG;
+    static constexpr int kGW = 64 / kCQ;            // token groups inside a wave
+    // copy of X and Y: 4 columns x kTPV tokens, kVStep apart
+    static constexpr int kVQ = DV / 4;
+    static constexpr int kVStep = kThreads / kVQ < C ? kThreads / kVQ : C;
+    static constexpr int kTPV = C / kVStep;
     static constexpr int kNT = C / 16;              // 16-token tiles per chunk
     static constexpr int kTiles = kNT * (kNT + 1) / 2;
     static constexpr int kAnchor = 512 / C;         // chunks between two checkpoints of the forward state
     static constexpr int kXS = DV + 4;              // row strides (floats)
+    static constexpr int kYS = DV + 8;              // (between what the scores' rows and the state update's columns want)
     static constexpr int kZS = DK + 16;
     static constexpr int kFS = DK + 4;
     static constexpr int kPS = C + 4;
     static constexpr int kOffX = 0;
     static constexpr int kOffY = kOffX + C * kXS;
-    static constexpr int kOffZ = kOffY + C * kXS;
+    static constexpr int kOffZ = kOffY + C * kYS;
     static constexpr int kOffF = kOffZ + C * kZS;
-    static constexpr int kOffP = kOffF + C * kFS;
-    static constexpr int kOffTot = kOffP + C * kPS;
-    static constexpr int kOffTot2 = kOffTot + kTG * DK;
-    static constexpr int kOffGam = kOffTot2 + kTG * DK;
+    static constexpr int kOffP = kOffF + C * kFS;   // scores; before and after them, in the same place, the waves' sums
+    static constexpr int kOffGam = kOffP + (C * kPS > kWaves * DK ? C * kPS : kWaves * DK);
     static constexpr int kOffCarry = kOffGam + DK;
     static constexpr int kOffAnchor = kOffCarry + DK;
     static constexpr int kFloats = kOffAnchor + DK;
     static constexpr size_t kBytes = sizeof(float) * kFloats;
-    static_assert(kTPT >= 1 && C % 16 == 0 && 512 % C == 0 && kBytes <= 163840, "chunk length");
+    static_assert(kTPT >= 1 && kTG == kWaves * kGW && C % 16 == 0 && 512 % C == 0 && kBytes <= 163840, "chunk length");
 };
 
 // REV = false: dQ (x = dO, y = v, z = k, z2 = q, W_init = forward states; the query scale multiplies the
 // output).  REV = true: dK and dG (x = v, y = dO, z = q, z2 = k, W_init = state gradients entering each
 // segment's final state; the query scale rides on Q .* Lambda, so that the running dS is the true gradient).
+// Waves per SIMD to leave registers for: at C = 16 the tiles of several workgroups (of four or eight waves) fit a compute
+// unit's LDS, and one's gate pass then runs beside another's products.  (At C = 32 eight waves would spill.)
+constexpr int f32_bwd_waves(int waves, int C) { return C == 64 ? 1 : C == 32 ? 2 : waves == 8 ? 4 : 3; }
 template <int DK, int DV, int C, bool REV>
-__global__ __launch_bounds__(DK * 4) void gla_bwd_qk_f32_kernel(BwdQKParams p) {
+__global__ __launch_bounds__(DK * 4, f32_bwd_waves(DK / 16, C)) void gla_bwd_qk_f32_kernel(BwdQKParams p) {
     typedef QKF32Cfg<DK, DV, C> Cfg;
     constexpr float SZ = REV ? 1.f : -1.f;   // exponent sign of the operand Z~; the factor F takes the other
     extern __shared__ __align__(16) float lds[];
     float *Xs = lds + Cfg::kOffX, *Ys = lds + Cfg::kOffY, *Zs = lds + Cfg::kOffZ;
     float *Fs = lds + Cfg::kOffF;      // the factor F [row][i]; then the finished gradient tile
     float *Ps = lds + Cfg::kOffP;      // masked X Y^T [row][row']
-    float *tot = lds + Cfg::kOffTot;   // [token group][channel] gate sums
-    float *tot2 = lds + Cfg::kOffTot2; // [token group][channel] sums of the dG terms
+    float *tot = lds + Cfg::kOffP;     // [wave][channel] gate sums
+    float *tot2 = lds + Cfg::kOffP;    // [wave][channel] sums of the dG terms
     float *gam = lds + Cfg::kOffGam;   // sqrt(gamma) [channel]
     float *carry0 = lds + Cfg::kOffCarry;
     float *anchor = lds + Cfg::kOffAnchor;
@@ -117,11 +126,14 @@ __global__ __launch_bounds__(DK * 4) void gla_bwd_qk_f32_kernel(BwdQKParams p) {
         for (int it = 0; it < Cfg::kNIT; ++it) Wacc[it] = *reinterpret_cast<const f32x4 *>(Wi + it * 16);
     }
 
-    const int gc = tid % DK, tg = tid / DK;      // gate pass: channel and token group
+    // gate pass: channel quad and token group; copy of X and Y: column quad and first token
+    const int cq = tid % Cfg::kCQ, tg = tid / Cfg::kCQ, gl = tg % Cfg::kGW;
+    const int vq = tid % Cfg::kVQ, tv = tid / Cfg::kVQ;
+    const bool copies = tv < Cfg::kVStep;        // (uniform per wave)
     auto row_of = [](int t) { return REV ? C - 1 - t : t; };
 
     // dG carried in from the later segments: c[i] = sum_j dS_end[i][j] S_end[i][j]  (4 threads per row)
-    float carry = 0.f;
+    f32x4 carry = {0.f, 0.f, 0.f, 0.f};
     if constexpr (REV) {
         const float *A = p.W_init + sbh * DK * DV;
         const float *Bm = (seg + 1 < (p.plan ? (int)p.seg_start[p.plan + 1] : p.P)) ? p.S_init + (sbh + (size_t)p.B * p.H) * DK * DV
@@ -137,11 +149,38 @@ __global__ __launch_bounds__(DK * 4) void gla_bwd_qk_f32_kernel(BwdQKParams p) {
         acc += __shfl_xor(acc, 2, 64);
         if (part == 0) carry0[i] = acc;
         __syncthreads();
-        carry = carry0[gc];
+        carry = *reinterpret_cast<const f32x4 *>(carry0 + 4 * cq);
     }
+
+    // The raw rows of the chunk worked on next: fetched a whole chunk ahead, 16 bytes a load and all of a chunk's loads
+    // in flight together (loaded one by one where they were used, they took two thirds of a chunk's time).  Rows past
+    // the segment's end, which only the last chunk can have, are not fetched.
+    f32x4 rx[Cfg::kTPV], ry[Cfg::kTPV], rz[Cfg::kTPT], rg[Cfg::kTPT];
+    auto fetch_xyg = [&](int c) __attribute__((always_inline)) {
+        const long long tc = (long long)c * C, last = len - 1;
+        if (copies) {
+#pragma unroll
+            for (int u = 0; u < Cfg::kTPV; ++u) {
+                const long long t = min(tc + tv + u * Cfg::kVStep, last) * p.vt + 4 * vq;
+                rx[u] = *reinterpret_cast<const f32x4 *>(x + t);
+                ry[u] = *reinterpret_cast<const f32x4 *>(y + t);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < Cfg::kTPT; ++u)
+            rg[u] = *reinterpret_cast<const f32x4 *>(g + min(tc + tg * Cfg::kTPT + u, last) * p.st + 4 * cq);
+    };
+    auto fetch_z = [&](int c) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < Cfg::kTPT; ++u)
+            rz[u] = *reinterpret_cast<const f32x4 *>(z + min((long long)c * C + tg * Cfg::kTPT + u, len - 1) * p.st + 4 * cq);
+    };
+    fetch_xyg(REV ? N - 1 : 0);
+    fetch_z(REV ? N - 1 : 0);
 
     for (int n = 0; n < N; ++n) {
         const int c = REV ? N - 1 - n : n;                       // chunk index in the segment
+        const int next = n + 1 < N ? (REV ? c - 1 : c + 1) : c;
         const long long tc = (long long)c * C;                   // its first token
         const int rows = (c == N - 1) ? (int)(len - tc) : C;     // its real tokens
         if constexpr (!REV) {
@@ -155,44 +194,78 @@ __global__ __launch_bounds__(DK * 4) void gla_bwd_qk_f32_kernel(BwdQKParams p) {
         }
 
         // ---- gate pass, part 1: inclusive cumulative sum of g over the chunk, per channel; X, Y -> LDS ----
-        float cs[Cfg::kTPT];
+        f32x4 cs[Cfg::kTPT], pre;
         {
-            float run = 0.f;
+            f32x4 run = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int u = 0; u < Cfg::kTPT; ++u) {
-                const int t = tg * Cfg::kTPT + u;
-                run += t < rows ? g[(tc + t) * p.st + gc] : 0.f;
+                if (tg * Cfg::kTPT + u < rows) run += rg[u];
                 cs[u] = run;
             }
-            tot[tg * DK + gc] = run;
+            f32x4 inc = run;                      // inclusive scan over the wave's token groups
+#pragma unroll
+            for (int s = 1; s < Cfg::kGW; s <<= 1) {
+#pragma unroll
+                for (int a = 0; a < 4; ++a) {
+                    const float up = __shfl_up(inc[a], s * Cfg::kCQ, 64);
+                    if (gl >= s) inc[a] += up;
+                }
+            }
+            pre = inc - run;
+            if (gl == Cfg::kGW - 1) *reinterpret_cast<f32x4 *>(tot + w * DK + 4 * cq) = inc;
         }
-        for (int e = tid; e < C * DV; e += Cfg::kThreads) {
-            const int t = e / DV, j = e % DV;
-            Xs[row_of(t) * Cfg::kXS + j] = t < rows ? x[(tc + t) * p.vt + j] : 0.f;
-            Ys[row_of(t) * Cfg::kXS + j] = t < rows ? y[(tc + t) * p.vt + j] : 0.f;
+        if (copies) {
+#pragma unroll
+            for (int u = 0; u < Cfg::kTPV; ++u) {
+                const int t = tv + u * Cfg::kVStep;
+                const f32x4 none = {0.f, 0.f, 0.f, 0.f};
+                *reinterpret_cast<f32x4 *>(Xs + row_of(t) * Cfg::kXS + 4 * vq) = t < rows ? rx[u] : none;
+                *reinterpret_cast<f32x4 *>(Ys + row_of(t) * Cfg::kYS + 4 * vq) = t < rows ? ry[u] : none;
+            }
         }
+        fetch_xyg(next);
         __syncthreads();
 
         // ---- gate pass, part 2: Z~ and the factor tile -> LDS ------------------------------------------
         {
-            float pre = 0.f, total = 0.f;
+            f32x4 total = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int u = 0; u < Cfg::kTG; ++u) {
-                const float v = tot[u * DK + gc];
-                if (u < tg) pre += v;
+            for (int u = 0; u < Cfg::kWaves; ++u) {
+                const f32x4 v = *reinterpret_cast<const f32x4 *>(tot + u * DK + 4 * cq);
+                if (u < w) pre += v;
                 total += v;
             }
-            const float mid = 0.5f * total;
+            const f32x4 mid = 0.5f * total;
 #pragma unroll
             for (int u = 0; u < Cfg::kTPT; ++u) {
                 const int t = tg * Cfg::kTPT + u;
-                const float cc = pre + cs[u] - mid;
-                const float zv = t < rows ? z[(tc + t) * p.st + gc] : 0.f;
-                Zs[row_of(t) * Cfg::kZS + gc] = zv * fast_exp(SZ * cc) * p.zscale;
-                Fs[row_of(t) * Cfg::kFS + gc] = fast_exp(-SZ * cc) * p.oscale;
+                const f32x4 zv = t < rows ? rz[u] : f32x4{0.f, 0.f, 0.f, 0.f};
+                f32x4 ze, fe;
+#pragma unroll
+                for (int a = 0; a < 4; ++a) {
+                    const float cc = pre[a] + cs[u][a] - mid[a];
+                    ze[a] = zv[a] * fast_exp(SZ * cc) * p.zscale;
+                    fe[a] = fast_exp(-SZ * cc) * p.oscale;
+                }
+                *reinterpret_cast<f32x4 *>(Zs + row_of(t) * Cfg::kZS + 4 * cq) = ze;
+                *reinterpret_cast<f32x4 *>(Fs + row_of(t) * Cfg::kFS + 4 * cq) = fe;
             }
-            if (tg == 0) gam[gc] = fast_exp(mid);
+            if (tg == 0) {
+                f32x4 em;
+#pragma unroll
+                for (int a = 0; a < 4; ++a) em[a] = fast_exp(mid[a]);
+                *reinterpret_cast<f32x4 *>(gam + 4 * cq) = em;
+            }
         }
+        // operands of this chunk's dG terms, needed after the products (clamped like the others)
+        f32x4 rz2[Cfg::kTPT], rqd[REV ? Cfg::kTPT : 1];
+#pragma unroll
+        for (int u = 0; u < Cfg::kTPT; ++u) {
+            const long long t = min(tc + tg * Cfg::kTPT + u, len - 1);
+            rz2[u] = *reinterpret_cast<const f32x4 *>(z2 + t * p.st + 4 * cq);
+            if constexpr (REV) rqd[u] = *reinterpret_cast<const f32x4 *>(dg + t * gcs + 4 * cq);
+        }
+        fetch_z(next);
         __syncthreads();
 
         // ---- W <- sqrt(gamma) .* W (columns); scores; X W ----------------------------------------------
@@ -206,10 +279,15 @@ __global__ __launch_bounds__(DK * 4) void gla_bwd_qk_f32_kernel(BwdQKParams p) {
             while (rem > tt) { rem -= tt + 1; ++tt; }
             const int ts = rem;
             f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-            const float *xa = Xs + (16 * tt + l16) * Cfg::kXS + kg;
-            const float *yb = Ys + (16 * ts + l16) * Cfg::kXS + kg;
-#pragma unroll 8
-            for (int ks = 0; ks < DV / 4; ++ks) acc = mma_f32(xa[4 * ks], yb[4 * ks], acc);
+            // (a step's four k-slots are the channels 16 it + 4 kg + r, so that a lane reads 16 bytes at a time)
+            const float *xa = Xs + (16 * tt + l16) * Cfg::kXS + 4 * kg;
+            const float *yb = Ys + (16 * ts + l16) * Cfg::kYS + 4 * kg;
+#pragma unroll
+            for (int it = 0; it < DV / 16; ++it) {
+                const f32x4 a = *reinterpret_cast<const f32x4 *>(xa + 16 * it), b = *reinterpret_cast<const f32x4 *>(yb + 16 * it);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc = mma_f32(a[r], b[r], acc);
+            }
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int rr = 16 * tt + 4 * kg + r, rc = 16 * ts + l16;
@@ -234,31 +312,31 @@ __global__ __launch_bounds__(DK * 4) void gla_bwd_qk_f32_kernel(BwdQKParams p) {
         __syncthreads();
 
         // ---- + (masked scores) Z~, times F: the finished tile replaces F ---------------------------------
+        // (unrolled over independent accumulators, here and in the update of W: a rolled loop waits for its two LDS
+        // reads in every step)
+#pragma unroll
+        for (int ks = 0; ks < C / 4; ++ks) {
+            const float bv = Zs[(4 * ks + kg) * Cfg::kZS + 16 * w + l16];
+#pragma unroll
+            for (int mt = ks / 4; mt < Cfg::kNT; ++mt)
+                Oacc[mt] = mma_f32(Ps[(16 * mt + l16) * Cfg::kPS + 4 * ks + kg], bv, Oacc[mt]);
+        }
 #pragma unroll
         for (int mt = 0; mt < Cfg::kNT; ++mt) {
-            for (int ks = 0; ks < 4 * (mt + 1); ++ks) {
-                const float a = Ps[(16 * mt + l16) * Cfg::kPS + 4 * ks + kg];
-                const float bv = Zs[(4 * ks + kg) * Cfg::kZS + 16 * w + l16];
-                Oacc[mt] = mma_f32(a, bv, Oacc[mt]);
-            }
 #pragma unroll
             for (int r = 0; r < 4; ++r) Fs[(16 * mt + 4 * kg + r) * Cfg::kFS + 16 * w + l16] *= Oacc[mt][r];
         }
 
         // ---- W <- sqrt(gamma) .* (W + Y^T Z~) ------------------------------------------------------------
 #pragma unroll
-        for (int it = 0; it < Cfg::kNIT; ++it) {
-            f32x4 acc = Wacc[it];
-#pragma unroll 4
-            for (int ks = 0; ks < C / 4; ++ks) {
-                const float a = Ys[(4 * ks + kg) * Cfg::kXS + 16 * it + l16];
-                const float bv = Zs[(4 * ks + kg) * Cfg::kZS + 16 * w + l16];
-                acc = mma_f32(a, bv, acc);
-            }
+        for (int ks = 0; ks < C / 4; ++ks) {
+            const float bv = Zs[(4 * ks + kg) * Cfg::kZS + 16 * w + l16];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) acc[r] *= gcol;
-            Wacc[it] = acc;
+            for (int it = 0; it < Cfg::kNIT; ++it)
+                Wacc[it] = mma_f32(Ys[(4 * ks + kg) * Cfg::kYS + 16 * it + l16], bv, Wacc[it]);
         }
+#pragma unroll
+        for (int it = 0; it < Cfg::kNIT; ++it) Wacc[it] *= gcol;
         bool at_anchor = false;
         if constexpr (REV) {
             // the pass has arrived at a checkpoint: what the tokens from here on contribute to dG is exactly
@@ -285,38 +363,47 @@ __global__ __launch_bounds__(DK * 4) void gla_bwd_qk_f32_kernel(BwdQKParams p) {
             for (int u = 0; u < Cfg::kTPT; ++u) {
                 const int t = tg * Cfg::kTPT + u;
                 if (t >= rows) continue;
-                const float val = Fs[row_of(t) * Cfg::kFS + gc];
-                out[(tc + t) * p.st + gc] = val;
-                dg[(tc + t) * gcs + gc] = z2[(tc + t) * p.st + gc] * val;   // Q .* dQ, for the dK pass
+                const f32x4 val = *reinterpret_cast<const f32x4 *>(Fs + row_of(t) * Cfg::kFS + 4 * cq);
+                *reinterpret_cast<f32x4 *>(out + (tc + t) * p.st + 4 * cq) = val;
+                *reinterpret_cast<f32x4 *>(dg + (tc + t) * gcs + 4 * cq) = rz2[u] * val;   // Q .* dQ, for the dK pass
             }
         } else {
-            float dterm[Cfg::kTPT];
-            float run = 0.f;
+            f32x4 dterm[Cfg::kTPT];
+            f32x4 run = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int u = Cfg::kTPT - 1; u >= 0; --u) {   // sums over this thread's tokens >= u
                 const int t = tg * Cfg::kTPT + u;
                 if (t < rows) {
-                    const float val = Fs[row_of(t) * Cfg::kFS + gc];
-                    out[(tc + t) * p.st + gc] = val;
-                    run += dg[(tc + t) * gcs + gc] - z2[(tc + t) * p.st + gc] * val;
+                    const f32x4 val = *reinterpret_cast<const f32x4 *>(Fs + row_of(t) * Cfg::kFS + 4 * cq);
+                    *reinterpret_cast<f32x4 *>(out + (tc + t) * p.st + 4 * cq) = val;
+                    run += rqd[u] - rz2[u] * val;
                 }
                 dterm[u] = run;
             }
-            tot2[tg * DK + gc] = run;
-            __syncthreads();
-            float later = carry, total = 0.f;
+            f32x4 inc = run;                      // inclusive suffix scan over the wave's token groups
 #pragma unroll
-            for (int u = 0; u < Cfg::kTG; ++u) {
-                const float v = tot2[u * DK + gc];
-                if (u > tg) later += v;
+            for (int s = 1; s < Cfg::kGW; s <<= 1) {
+#pragma unroll
+                for (int a = 0; a < 4; ++a) {
+                    const float dn = __shfl_down(inc[a], s * Cfg::kCQ, 64);
+                    if (gl + s < Cfg::kGW) inc[a] += dn;
+                }
+            }
+            if (gl == 0) *reinterpret_cast<f32x4 *>(tot2 + w * DK + 4 * cq) = inc;
+            __syncthreads();
+            f32x4 later = carry + (inc - run), total = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int u = 0; u < Cfg::kWaves; ++u) {
+                const f32x4 v = *reinterpret_cast<const f32x4 *>(tot2 + u * DK + 4 * cq);
+                if (u > w) later += v;
                 total += v;
             }
 #pragma unroll
             for (int u = 0; u < Cfg::kTPT; ++u) {
                 const int t = tg * Cfg::kTPT + u;
-                if (t < rows) dg[(tc + t) * gcs + gc] = dterm[u] + later;
+                if (t < rows) *reinterpret_cast<f32x4 *>(dg + (tc + t) * gcs + 4 * cq) = dterm[u] + later;
             }
-            carry = at_anchor ? anchor[gc] : carry + total;
+            carry = at_anchor ? *reinterpret_cast<const f32x4 *>(anchor + 4 * cq) : carry + total;
         }
         __syncthreads();
     }

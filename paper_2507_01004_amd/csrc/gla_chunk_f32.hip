@@ -45,8 +45,16 @@ enum F32Mode { kF32Local = 0, kF32States = 1, kF32Output = 2, kF32DState = 3, kF
 template <int DK, int DV, int C> struct F32Cfg {
     static constexpr int kWaves = DV / 16;
     static constexpr int kThreads = 64 * kWaves;
-    static constexpr int kTG = kThreads / DK;       // token groups in the gate pass
-    static constexpr int kTPT = C / kTG;            // tokens per thread in the gate pass
+    // gate pass: 4 channels x kTPT consecutive tokens per thread, the token groups of a wave stitched by shuffles
+    static constexpr int kCQ = DK / 4;                                     // channel quads
+    static constexpr int kTG = kThreads / kCQ < C ? kThreads / kCQ : C;    // token groups
+    static constexpr int kTPT = C / kTG;
+    static constexpr int kGW = 64 / kCQ;                                   // token groups inside a wave
+    static constexpr int kTW = kTG / kGW;                                  // waves that take part
+    // copy of V: 4 columns x kTPV tokens, kVStep apart
+    static constexpr int kVQ = DV / 4;
+    static constexpr int kVStep = kThreads / kVQ < C ? kThreads / kVQ : C;
+    static constexpr int kTPV = C / kVStep;
     static constexpr int kNT = C / 16;              // 16-token tiles per chunk
     static constexpr int kTiles = kNT * (kNT + 1) / 2;   // score tiles on and below the diagonal
     static constexpr int kQS = DK + 4;              // row strides (floats), chosen bank-conflict free
@@ -57,17 +65,19 @@ template <int DK, int DV, int C> struct F32Cfg {
     static constexpr int kOffK = kOffQ + C * kQS;
     static constexpr int kOffKT = kOffK + C * kQS;
     static constexpr int kOffV = kOffKT + C * kKT;
-    static constexpr int kOffP = kOffV + C * kVS;
-    static constexpr int kOffTot = kOffP + C * kPS;
-    static constexpr int kOffGam = kOffTot + kTG * DK;
+    static constexpr int kOffP = kOffV + C * kVS;   // scores; before them, in the same place, the waves' gate sums
+    static constexpr int kOffGam = kOffP + (C * kPS > kTW * DK ? C * kPS : kTW * DK);
     static constexpr int kOffMid = kOffGam + DK;
     static constexpr int kFloats = kOffMid + DK;
     static constexpr size_t kBytes = sizeof(float) * kFloats;
-    static_assert(kTPT >= 1 && C % 16 == 0, "chunk length");
+    static_assert(kTPT >= 1 && kTW >= 1 && C % 16 == 0 && kBytes <= 163840, "chunk length");
 };
 
+// Waves per SIMD to leave registers for: at C = 16 and 32 the tiles of two or more workgroups (of four or eight waves)
+// fit a compute unit's LDS, and one's gate pass then runs beside another's products.
+constexpr int f32_waves(int waves, int C) { return C == 64 ? 1 : waves == 8 ? 4 : C == 16 ? 3 : 2; }
 template <int DK, int DV, int C, int MODE>
-__global__ __launch_bounds__(DV * 4) void gla_chunk_f32_kernel(ChunkParams p) {
+__global__ __launch_bounds__(DV * 4, f32_waves(DV / 16, C)) void gla_chunk_f32_kernel(ChunkParams p) {
     typedef F32Cfg<DK, DV, C> Cfg;
     constexpr bool REV = MODE == kF32DState || MODE == kF32DV;       // the sequence reversed
     constexpr bool NOQ = MODE == kF32States || MODE == kF32DState;   // only the state is computed
@@ -79,7 +89,7 @@ __global__ __launch_bounds__(DV * 4) void gla_chunk_f32_kernel(ChunkParams p) {
     float *Kt = lds + Cfg::kOffKT;   // K .* Gamma               [s][i]
     float *Vs = lds + Cfg::kOffV;    // V                        [s][j]
     float *Ps = lds + Cfg::kOffP;    // masked scores            [t][s]
-    float *tot = lds + Cfg::kOffTot; // per token-group gate sums [tg][i]
+    float *tot = lds + Cfg::kOffP;   // gate sums of each wave's tokens [wave][i]
     float *gam = lds + Cfg::kOffGam; // chunk decay gamma         [i]
     float *emid = lds + Cfg::kOffMid; // sqrt(gamma)               [i]
 
@@ -124,73 +134,142 @@ __global__ __launch_bounds__(DV * 4) void gla_chunk_f32_kernel(ChunkParams p) {
 
     f32x4 Sacc[DK / 16];
 #pragma unroll
-    for (int it = 0; it < DK / 16; ++it) {
-        if (FROM_INIT && (MODE != kF32Output || p.S_init)) {   // (output pass: no S_init = the zero state)
-            const float *Si = p.S_init + sbh * DK * DV;
+    for (int it = 0; it < DK / 16; ++it) Sacc[it] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (FROM_INIT && (MODE != kF32Output || p.S_init)) {   // (output pass: no S_init = the zero state)
+        const float *Si = p.S_init + sbh * DK * DV;
+#pragma unroll
+        for (int it = 0; it < DK / 16; ++it)
 #pragma unroll
             for (int r = 0; r < 4; ++r) Sacc[it][r] = Si[(16 * it + 4 * kg + r) * DV + 16 * w + l16];
-        } else {
-            Sacc[it] = f32x4{0.f, 0.f, 0.f, 0.f};
-        }
     }
 
-    const int gc = tid % DK, tg = tid / DK;      // gate pass: channel and token group
+    // gate pass: channel quad and token group; copy of V: column quad and first token
+    const int cq = tid % Cfg::kCQ, tg = tid / Cfg::kCQ, gl = tg % Cfg::kGW;
+    const int vq = tid % Cfg::kVQ, tv = tid / Cfg::kVQ;
+    const bool gates = tg < Cfg::kTG, copies = tv < Cfg::kVStep;   // (uniform per wave)
     // position in the segment of the token that sits at place x of the order the chunks are walked in
     auto at = [&](long long x) { return REV ? len - 1 - x : x; };
-    double seg_prefix = 0.0;                     // log decay accumulated over previous chunks
+    auto start_of = [&](int n) { return n ? (long long)n * C - pad : 0ll; };
+    double seg_prefix[4] = {0., 0., 0., 0.};     // log decay accumulated over previous chunks
 
-    for (int n = 0; n < n_chunks; ++n) {
-        const long long t0 = n ? (long long)n * C - pad : 0;
-        const int rows = n ? C : C - pad;        // real tokens of this chunk
-        // ---- gate pass: inclusive cumulative sum of g over the chunk, per channel -------------
-        float cs[Cfg::kTPT];
-        {
-            float run = 0.f;
+    // The raw rows of the chunk worked on next: fetched a whole chunk ahead, 16 bytes a load and all of a chunk's loads
+    // in flight together.  (Loaded one by one where they were used, four bytes a lane, they took two thirds of a chunk's
+    // time: output pass, d = 128, C = 64, 32 us a chunk where the products need 9.)
+    f32x4 rq[Cfg::kTPT], rk[Cfg::kTPT], rg[Cfg::kTPT], rv[Cfg::kTPV];
+    auto fetch_gv = [&](int n) __attribute__((always_inline)) {
+        const long long t0 = start_of(n);
+        if (gates) {
+#pragma unroll
+            for (int u = 0; u < Cfg::kTPT; ++u)
+                rg[u] = *reinterpret_cast<const f32x4 *>(g + at(t0 + tg * Cfg::kTPT + u) * p.st + 4 * cq);
+        }
+        if (copies) {
+#pragma unroll
+            for (int u = 0; u < Cfg::kTPV; ++u)
+                rv[u] = *reinterpret_cast<const f32x4 *>(v + at(t0 + tv + u * Cfg::kVStep) * p.vt + 4 * vq);
+        }
+    };
+    auto fetch_qk = [&](int n) __attribute__((always_inline)) {
+        const long long t0 = start_of(n);
+        if (gates) {
 #pragma unroll
             for (int u = 0; u < Cfg::kTPT; ++u) {
-                const int t = tg * Cfg::kTPT + u;
+                const long long r = at(t0 + tg * Cfg::kTPT + u) * p.st + 4 * cq;
+                rk[u] = *reinterpret_cast<const f32x4 *>(k + r);
+                if constexpr (!NOQ) rq[u] = *reinterpret_cast<const f32x4 *>(q + r);
+            }
+        }
+    };
+    fetch_gv(0);
+    fetch_qk(0);
+
+    for (int n = 0; n < n_chunks; ++n) {
+        const long long t0 = start_of(n);
+        const int rows = n ? C : C - pad;        // real tokens of this chunk
+        const int next = n + 1 < n_chunks ? n + 1 : n;
+        // ---- gate pass: inclusive cumulative sum of g over the chunk, per channel -------------
+        f32x4 cs[Cfg::kTPT], pre = {0.f, 0.f, 0.f, 0.f};
+        if (gates) {
+            f32x4 run = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int u = 0; u < Cfg::kTPT; ++u) {
                 if constexpr (REV) cs[u] = run;   // without the token's own gate
-                run += t < rows ? g[at(t0 + t) * p.st + gc] : 0.f;
+                if (tg * Cfg::kTPT + u < rows) run += rg[u];
                 if constexpr (!REV) cs[u] = run;
             }
-            tot[tg * DK + gc] = run;
+            f32x4 inc = run;                      // inclusive scan over the wave's token groups
+#pragma unroll
+            for (int s = 1; s < Cfg::kGW; s <<= 1) {
+#pragma unroll
+                for (int a = 0; a < 4; ++a) {
+                    const float up = __shfl_up(inc[a], s * Cfg::kCQ, 64);
+                    if (gl >= s) inc[a] += up;
+                }
+            }
+            pre = inc - run;
+            if (gl == Cfg::kGW - 1) *reinterpret_cast<f32x4 *>(tot + w * DK + 4 * cq) = inc;
         }
-        for (int e = tid; e < C * DV; e += Cfg::kThreads) {
-            const int t = e / DV, j = e % DV;
-            Vs[t * Cfg::kVS + j] = t < rows ? v[at(t0 + t) * p.vt + j] : 0.f;
+        if (copies) {
+#pragma unroll
+            for (int u = 0; u < Cfg::kTPV; ++u) {
+                const int t = tv + u * Cfg::kVStep;
+                *reinterpret_cast<f32x4 *>(Vs + t * Cfg::kVS + 4 * vq) = t < rows ? rv[u] : f32x4{0.f, 0.f, 0.f, 0.f};
+            }
         }
+        fetch_gv(next);
         __syncthreads();
         // The factors of Qs and Ks are taken relative to half the chunk's total log decay (mid = total / 2): the
         // same products e^(c_t - c_s) with no exponent beyond |total| / 2; the inter-chunk product makes up for it
         // with e^mid on the state's rows.
-        float pre = 0.f, total = 0.f;
+        if (gates) {
+            f32x4 total = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int u = 0; u < Cfg::kTG; ++u) {
-            const float x = tot[u * DK + gc];
-            if (u < tg) pre += x;
-            total += x;
-        }
-        const float mid = 0.5f * total;
+            for (int u = 0; u < Cfg::kTW; ++u) {
+                const f32x4 x = *reinterpret_cast<const f32x4 *>(tot + u * DK + 4 * cq);
+                if (u < w) pre += x;
+                total += x;
+            }
+            const f32x4 mid = 0.5f * total;
 #pragma unroll
-        for (int u = 0; u < Cfg::kTPT; ++u) {
-            const int t = tg * Cfg::kTPT + u;
-            const float c = pre + cs[u];
-            float kv = t < rows ? k[at(t0 + t) * p.st + gc] : 0.f;
-            if constexpr (REV) kv *= p.kscale;
-            if constexpr (!NOQ) {
-                Qs[t * Cfg::kQS + gc] = q[at(t0 + t) * p.st + gc] * fast_exp(c - mid) * p.scale;
-                Ks[t * Cfg::kQS + gc] = kv * fast_exp(mid - c);
+            for (int u = 0; u < Cfg::kTPT; ++u) {
+                const int t = tg * Cfg::kTPT + u;
+                const f32x4 c = pre + cs[u];
+                f32x4 kv = t < rows ? rk[u] : f32x4{0.f, 0.f, 0.f, 0.f};
+                if constexpr (REV) kv *= p.kscale;
+                if constexpr (!NOQ) {
+                    f32x4 qx, kx;
+#pragma unroll
+                    for (int a = 0; a < 4; ++a) {
+                        qx[a] = rq[u][a] * fast_exp(c[a] - mid[a]) * p.scale;
+                        kx[a] = kv[a] * fast_exp(mid[a] - c[a]);
+                    }
+                    *reinterpret_cast<f32x4 *>(Qs + t * Cfg::kQS + 4 * cq) = qx;
+                    *reinterpret_cast<f32x4 *>(Ks + t * Cfg::kQS + 4 * cq) = kx;
+                }
+                f32x4 kt;
+#pragma unroll
+                for (int a = 0; a < 4; ++a) kt[a] = kv[a] * fast_exp(total[a] - c[a]);
+                *reinterpret_cast<f32x4 *>(Kt + t * Cfg::kKT + 4 * cq) = kt;
+                if constexpr (EMIT_G) {
+                    if (t < rows) {
+                        f32x4 gout;
+#pragma unroll
+                        for (int a = 0; a < 4; ++a) gout[a] = (float)(seg_prefix[a] + (double)c[a]);
+                        *reinterpret_cast<f32x4 *>(Gc + (t0 + t) * gcs + 4 * cq) = gout;
+                    }
+                }
             }
-            Kt[t * Cfg::kKT + gc] = kv * fast_exp(total - c);
-            if constexpr (EMIT_G) {
-                if (t < rows) Gc[(t0 + t) * gcs + gc] = (float)(seg_prefix + (double)c);
+            if (tg == 0) {
+                f32x4 eg, em;
+#pragma unroll
+                for (int a = 0; a < 4; ++a) { eg[a] = fast_exp(total[a]); em[a] = fast_exp(mid[a]); }
+                *reinterpret_cast<f32x4 *>(gam + 4 * cq) = eg;
+                *reinterpret_cast<f32x4 *>(emid + 4 * cq) = em;
             }
+#pragma unroll
+            for (int a = 0; a < 4; ++a) seg_prefix[a] += (double)total[a];
         }
-        if (tg == 0) {
-            gam[gc] = fast_exp(total);
-            emid[gc] = fast_exp(mid);
-        }
-        seg_prefix += (double)total;
+        fetch_qk(next);
         __syncthreads();
 
         f32x4 Oacc[Cfg::kNT];
@@ -201,10 +280,15 @@ __global__ __launch_bounds__(DV * 4) void gla_chunk_f32_kernel(ChunkParams p) {
                 while (rem > tt) { rem -= tt + 1; ++tt; }
                 const int ts = rem;
                 f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-                const float *qa = Qs + (16 * tt + l16) * Cfg::kQS + kg;
-                const float *kb = Ks + (16 * ts + l16) * Cfg::kQS + kg;
-#pragma unroll 8
-                for (int ks = 0; ks < DK / 4; ++ks) acc = mma_f32(qa[4 * ks], kb[4 * ks], acc);
+                // (a step's four k-slots are the channels 16 it + 4 kg + r, so that a lane reads 16 bytes at a time)
+                const float *qa = Qs + (16 * tt + l16) * Cfg::kQS + 4 * kg;
+                const float *kb = Ks + (16 * ts + l16) * Cfg::kQS + 4 * kg;
+#pragma unroll
+                for (int it = 0; it < DK / 16; ++it) {
+                    const f32x4 a = *reinterpret_cast<const f32x4 *>(qa + 16 * it), b = *reinterpret_cast<const f32x4 *>(kb + 16 * it);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) acc = mma_f32(a[r], b[r], acc);
+                }
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const int t = 16 * tt + 4 * kg + r, s = 16 * ts + l16;
@@ -230,13 +314,17 @@ __global__ __launch_bounds__(DV * 4) void gla_chunk_f32_kernel(ChunkParams p) {
             __syncthreads();
 
             // ---- intra-chunk output P V (causal: only s < 16 (mt + 1)) ------------------------------
+            // (unrolled over independent accumulators, here and in the state update: a rolled loop waits for its two
+            // LDS reads in every step)
+#pragma unroll
+            for (int ks = 0; ks < C / 4; ++ks) {
+                const float bv = Vs[(4 * ks + kg) * Cfg::kVS + 16 * w + l16];
+#pragma unroll
+                for (int mt = ks / 4; mt < Cfg::kNT; ++mt)
+                    Oacc[mt] = mma_f32(Ps[(16 * mt + l16) * Cfg::kPS + 4 * ks + kg], bv, Oacc[mt]);
+            }
 #pragma unroll
             for (int mt = 0; mt < Cfg::kNT; ++mt) {
-                for (int ks = 0; ks < 4 * (mt + 1); ++ks) {
-                    const float a = Ps[(16 * mt + l16) * Cfg::kPS + 4 * ks + kg];
-                    const float bv = Vs[(4 * ks + kg) * Cfg::kVS + 16 * w + l16];
-                    Oacc[mt] = mma_f32(a, bv, Oacc[mt]);
-                }
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
                     if (16 * mt + 4 * kg + r < rows) o[at(t0 + 16 * mt + 4 * kg + r) * p.vt + 16 * w + l16] = Oacc[mt][r];
@@ -245,17 +333,13 @@ __global__ __launch_bounds__(DV * 4) void gla_chunk_f32_kernel(ChunkParams p) {
 
         // ---- state update S <- gamma .* S + (K .* Gamma)^T V -------------------------------------
 #pragma unroll
-        for (int it = 0; it < DK / 16; ++it) {
-            f32x4 acc = Sacc[it];
+        for (int it = 0; it < DK / 16; ++it) Sacc[it] *= *reinterpret_cast<const f32x4 *>(gam + 16 * it + 4 * kg);
 #pragma unroll
-            for (int r = 0; r < 4; ++r) acc[r] *= gam[16 * it + 4 * kg + r];
-#pragma unroll 4
-            for (int ks = 0; ks < C / 4; ++ks) {
-                const float a = Kt[(4 * ks + kg) * Cfg::kKT + 16 * it + l16];
-                const float bv = Vs[(4 * ks + kg) * Cfg::kVS + 16 * w + l16];
-                acc = mma_f32(a, bv, acc);
-            }
-            Sacc[it] = acc;
+        for (int ks = 0; ks < C / 4; ++ks) {
+            const float bv = Vs[(4 * ks + kg) * Cfg::kVS + 16 * w + l16];
+#pragma unroll
+            for (int it = 0; it < DK / 16; ++it)
+                Sacc[it] = mma_f32(Kt[(4 * ks + kg) * Cfg::kKT + 16 * it + l16], bv, Sacc[it]);
         }
         __syncthreads();
     }
@@ -266,7 +350,9 @@ __global__ __launch_bounds__(DV * 4) void gla_chunk_f32_kernel(ChunkParams p) {
         for (int it = 0; it < DK / 16; ++it)
 #pragma unroll
             for (int r = 0; r < 4; ++r) Sl[(16 * it + 4 * kg + r) * DV + 16 * w + l16] = Sacc[it][r];
-        if (!FROM_INIT && tg == 0 && (!REV || p.G_tot)) p.G_tot[sbh * DK + gc] = (float)seg_prefix;
+        if (!FROM_INIT && tg == 0 && (!REV || p.G_tot))
+            *reinterpret_cast<f32x4 *>(p.G_tot + sbh * DK + 4 * cq) =
+                f32x4{(float)seg_prefix[0], (float)seg_prefix[1], (float)seg_prefix[2], (float)seg_prefix[3]};
     }
 }
 

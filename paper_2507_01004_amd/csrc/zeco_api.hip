@@ -394,9 +394,9 @@ static CostModel cost_model(const zeco_gla_desc *d) {
     m.state = 4. * d->d_k * d->d_v;
     m.slots = kComputeUnits;
     if (d->io_dtype == ZECO_F32) {
-        const double f = (d->d_k * d->d_v) / 16384. * (d->C == 64 ? 1. : d->C == 32 ? 1.6 : 2.4);
-        m.chunk1 = 4. + 12. * f; m.chunk2 = 6. + 20. * f; m.chunkb = 20. + 70. * f;
-        m.slots = kComputeUnits * 64. / d->C;
+        const double f = (d->d_k * d->d_v) / 16384.;
+        m.chunk1 = 4. + 13. * f; m.chunk2 = 6. + 20. * f; m.chunkb = 15. + 55. * f;
+        m.slots = kComputeUnits * (d->C == 64 ? 1. : 2.);
     } else {
         m.chunk1 = d->d_k == 128 ? 2.0 : 1.3;
         m.chunk2 = d->d_k == 128 ? 3.5 : 2.2;
@@ -412,7 +412,7 @@ static double cost_forward(const CostModel &m, double BH, double n, double longe
     // Pieces the AUTO schedule corrects instead of reading k, v, g twice: their first 35 chunks or so, what the decays of
     // a trained layer leave of a state, are then worked on again.
     if (n == 1.) return m.fixed1 + cost_chain(m, BH, longest, BH > 128. ? 1.2 * m.chunk1 : m.chunk1, m.bytes1);
-    const double part = correct ? 0.6 + 0.5 * 35. / longest : 1.;
+    const double part = correct ? 0.55 + 0.5 * 35. / longest : 1.;
     return m.fixed2 + part * cost_chain(m, n * BH, longest, m.chunk2, m.bytes2) + 6. * n * BH * m.state / m.rate + m.step * n;
 }
 static double cost_backward(const CostModel &m, double BH, double n, double longest) {

@@ -140,3 +140,27 @@ def test_one_call_over_long_unequal_segments(case):
     assert torch.all(o[:, e - 40:] == mark)
     n = int(seg[-3]) if len(lengths) > 2 else a
     assert (o[:, a:n].float() - good[:, a:n].float()).abs().max().item() <= tol * good.float().abs().max().item() if n > a else True
+
+
+@pytest.mark.parametrize("dk,dv", [(64, 64), (64, 128), (128, 64), (128, 128)])
+@pytest.mark.parametrize("C", [16, 32, 64])
+def test_fp32_passes_at_chunk_edges(C, dk, dv):
+    """The fp32 kernels' thread mappings (16-byte loads, token groups per wave) for every tile shape: three calls and the
+    two fp32 directions over segments one token short of, at and one token past a multiple of the chunk."""
+    B, H, P = 1, 2, 2
+    for L in (64 + C - 1, 128, 64 + C + 1):
+        print("case", C, dk, dv, L, flush=True)
+        inp = synth.make_inputs(B, P * L, H, dk, dv, seed=500 + L, io="f32", g="f32", device="cuda", gate_div=32.0)
+        q, k, v, g = (inp[n] for n in "qkvg")
+        gen = torch.Generator(device="cuda").manual_seed(L)
+        dO = torch.randn(v.shape, generator=gen, device="cuda")
+        S0 = torch.randn(B, H, dk, dv, device="cuda", generator=gen) * 0.3
+        args = [host(x) for x in (q, k, v, g)]
+        o_r, S_r = oracle.gla_recurrent(*args, 0.5, host(S0))
+        o, S_last, _ = zeco.segmented_fwd(q, k, v, g, P, scale=0.5, S0=S0, C=C)
+        ref = oracle.gla_recurrent_bwd(*args, host(dO), 0.5, host(S0))
+        got = zeco.gla_fused_bwd(q, k, v, g, dO, P, scale=0.5, S0=S0, C=C)
+        torch.cuda.synchronize()
+        assert rel_err_bh(host(o), o_r, (0, 2)) <= TOL["f32"] and rel_err_bh(host(S_last), S_r, (0, 1)) <= TOL["f32"]
+        for nm, x, r in zip(("dq", "dk", "dv", "dg"), got, ref):
+            assert rel_err_bh(host(x), r, (0, 2)) <= TOL["f32"], nm
