@@ -143,20 +143,31 @@ def version():
     return int(lib().zeco_version())
 
 
+_DTYPE_CODES = {torch.float32: ZECO_F32, torch.bfloat16: ZECO_BF16}
+
+
 def _dtype_code(t):
-    if t.dtype == torch.float32:
-        return ZECO_F32
-    if t.dtype == torch.bfloat16:
-        return ZECO_BF16
-    raise TypeError("unsupported dtype %s" % t.dtype)
+    code = _DTYPE_CODES.get(t.dtype)
+    if code is None:
+        raise TypeError("unsupported dtype %s" % t.dtype)
+    return code
+
+
+# What a call costs on the host is what the smallest calls cost (the three calls of four 64-token segments: 20 us of
+# kernels, 30 us of Python): pointers and the stream go to ctypes as plain integers, the stream comes from torch's
+# raw accessor instead of through a Stream object, and a tensor's strides are asked for once.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """The current stream of the current device, as an integer."""
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 _WIDE_GATES = False
@@ -179,24 +190,17 @@ def _desc(q, v, g_code, per_head, P, C, scale):
     dv = v.shape[-1]
     if T % P != 0:
         raise ValueError("T=%d is not a multiple of P=%d" % (T, P))
-    if q.stride(-1) != 1 or v.stride(-1) != 1:
+    qs, vs = q.stride(), v.stride()
+    if qs[-1] != 1 or vs[-1] != 1:
         raise ValueError("innermost dimension must be contiguous")
-    return GlaDesc(B, P, H, T // P, dk, dv, C, _dtype_code(q), g_code, float(scale),
-                   q.stride(0), q.stride(1), q.stride(2), v.stride(0), v.stride(1), v.stride(2),
+    return GlaDesc(B, P, H, T // P, dk, dv, C, _dtype_code(q), g_code, float(scale), qs[0], qs[1], qs[2], vs[0], vs[1], vs[2],
                    int(per_head), int(_WIDE_GATES))
 
 
 def make_desc(q, v, g, P, C=64, scale=1.0):
     """Descriptor of a call that reads the gate g: [B,T,H,d_k] laid out like q, or, with one log decay
     per (token, head), a contiguous [B,T,H] tensor."""
-    B, T, H, dk = q.shape
-    per_head = g.dim() == 3
-    if per_head:
-        if tuple(g.shape) != (B, T, H) or not g.is_contiguous():
-            raise ValueError("a per-head gate must be a contiguous [B,T,H] tensor")
-    elif g.shape != q.shape or g.stride() != q.stride():
-        raise ValueError("a per-channel gate must have the shape and strides of q")
-    return _desc(q, v, _dtype_code(g), per_head, P, C, scale)
+    return _desc(q, v, _dtype_code(g), _gate_per_head(q, g), P, C, scale)
 
 
 def _gate_dims(g, dk):
@@ -205,8 +209,9 @@ def _gate_dims(g, dk):
 
 
 def _check_same_layout(ref, *others):
+    shape, stride, device = ref.shape, ref.stride(), ref.device
     for t in others:
-        if t.shape != ref.shape or t.stride() != ref.stride() or t.device != ref.device:
+        if t.shape != shape or t.stride() != stride or t.device != device:
             raise ValueError("tensors sharing a descriptor must share shape, strides and device")
 
 
