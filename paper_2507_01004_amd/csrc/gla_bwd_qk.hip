@@ -108,9 +108,13 @@ __device__ __forceinline__ bf16x8 pack2x4(f32x4 a, f32x4 b) {
 // final state; the query scale rides on Q .* Lambda, so that the running dS is the true gradient).
 // EMIT (dQ pass only): also accumulate the segment's state gradient dS_loc and emit it (and, when asked,
 // the segment's total log decay).
-template <int DK, int DV, bool REV, int GM, bool EMIT>
+// NS > 1 (per-channel gates): NS sibling workgroups share a stream, each with DK of its NS * DK channels - columns of W,
+// of the outputs and of everything gated; X, Y and the scores, which contract over d_v, each of them has whole.
+template <int DK, int DV, int NS, bool REV, int GM, bool EMIT>
 __global__ __launch_bounds__(DK * 4) void gla_bwd_qk_kernel(BwdQKParams p) {
     static_assert(!(REV && EMIT), "the state gradient is a by-product of the forward-direction pass");
+    static_assert(NS == 1 || GM != kGateHead, "one decay per head sums over all channels");
+    constexpr int DKF = DK * NS;
     typedef QKCfg<DK, DV, EMIT> Cfg;
     typedef Mma<16> M;
     typedef GateVal<GM> GV;
@@ -150,8 +154,11 @@ __global__ __launch_bounds__(DK * 4) void gla_bwd_qk_kernel(BwdQKParams p) {
     auto is_short = [&](int c) { return c == (short_last ? N - 1 : 0); };   // chunk c is the short one (if any is)
 
     // workgroup -> stream, dealt so that consecutive streams land on different XCDs
-    const size_t sbh = blockIdx.x;                  // (seg * B + b) * H + h
-    int sidx = blockIdx.x;
+    // (siblings in consecutive slots of one XCD, whose L2 they share for X and Y)
+    const int slice = NS == 1 ? 0 : (int)(blockIdx.x >> 3) % NS;
+    int sidx = NS == 1 ? (int)blockIdx.x : (int)(blockIdx.x >> 3) / NS * 8 + (int)(blockIdx.x & 7);
+    if (NS > 1 && sidx >= p.B * p.P * p.H) return;
+    const size_t sbh = sidx;                        // (seg * B + b) * H + h
     const int h = sidx % p.H;
     sidx /= p.H;
     const int b = sidx % p.B, seg = sidx / p.B;
@@ -178,7 +185,7 @@ __global__ __launch_bounds__(DK * 4) void gla_bwd_qk_kernel(BwdQKParams p) {
         pad = (int)(64ll * N - len);
     }
     const int n_ck = p.plan ? (int)p.seg_start[p.plan + 3] : p.n_ck;
-    const long long kbase = b * p.sb + tok0 * p.st + h * p.sh;
+    const long long kbase = b * p.sb + tok0 * p.st + h * p.sh + slice * DK;
     const long long vbase = b * p.vb + tok0 * p.vt + h * p.vh;
     const unsigned char *xb = (const unsigned char *)p.x + vbase * 2;
     const unsigned char *yb = (const unsigned char *)p.y + vbase * 2;
@@ -189,8 +196,8 @@ __global__ __launch_bounds__(DK * 4) void gla_bwd_qk_kernel(BwdQKParams p) {
     const unsigned char *z2b = (const unsigned char *)p.z2 + kbase * 2;
     unsigned char *ob = (unsigned char *)p.out + kbase * 2;
     const long long st = p.st, vt = p.vt;
-    float *dgb = p.dg + hbase * (GH ? 1 : DK);   // [B,T,H,d_k] contiguous ([B,T,H] with per-head gates)
-    const long long gcs = (long long)p.H * (GH ? 1 : DK);
+    float *dgb = p.dg + hbase * (GH ? 1 : DKF) + slice * DK;   // [B,T,H,d_k] contiguous ([B,T,H] with per-head gates)
+    const long long gcs = (long long)p.H * (GH ? 1 : DKF);
 
     // gate-pass coordinates (z, g) and copy-pass coordinates (x, y)
     const int cq = lane % CQ, gl = lane / CQ, tq = w * GW + gl;
@@ -200,7 +207,7 @@ __global__ __launch_bounds__(DK * 4) void gla_bwd_qk_kernel(BwdQKParams p) {
     // W^T tile init: Sacc[it][rr] = W[row 16 it + 4 kg + rr][col 16 w + l16] = W_init[col][row]
     f32x4 Sacc[Cfg::NIT];
     {
-        const float *Wi = p.W_init + sbh * DK * DV + (size_t)(w * 16 + l16) * DV + 4 * kg;
+        const float *Wi = p.W_init + sbh * DKF * DV + (size_t)(slice * DK + w * 16 + l16) * DV + 4 * kg;
 #pragma unroll
         for (int it = 0; it < Cfg::NIT; ++it) Sacc[it] = *reinterpret_cast<const f32x4 *>(Wi + it * 16);
     }
@@ -218,9 +225,9 @@ __global__ __launch_bounds__(DK * 4) void gla_bwd_qk_kernel(BwdQKParams p) {
     // dG carried in from the later segments: c[i] = sum_j dS_end[i][j] S_end[i][j]  (4 threads per row)
     f32x4 carry = {0.f, 0.f, 0.f, 0.f};
     if constexpr (REV) {
-        const float *A = p.W_init + sbh * DK * DV;
-        const float *Bm = (seg + 1 < (p.plan ? (int)p.seg_start[p.plan + 1] : p.P)) ? p.S_init + (sbh + (size_t)p.B * p.H) * DK * DV
-                                          : p.S_last + ((size_t)b * p.H + h) * DK * DV;
+        const float *A = p.W_init + (sbh * DKF + slice * DK) * DV;
+        const float *Bm = (seg + 1 < (p.plan ? (int)p.seg_start[p.plan + 1] : p.P)) ? p.S_init + ((sbh + (size_t)p.B * p.H) * DKF + slice * DK) * DV
+                                          : p.S_last + (((size_t)b * p.H + h) * DKF + slice * DK) * DV;
         const int i = tid >> 2, part = tid & 3;
         float acc = 0.f;
         for (int j = part * 4; j < DV; j += 16) {
@@ -356,7 +363,7 @@ __global__ __launch_bounds__(DK * 4) void gla_bwd_qk_kernel(BwdQKParams p) {
         if constexpr (!REV) {
             // checkpoint: the forward state entering this chunk, for the dK pass to re-anchor dG with
             if (p.S_ck && n > 0 && n % kAnchor == 0) {
-                float *ck = p.S_ck + (sbh * n_ck + (n / kAnchor - 1)) * DK * DV + (size_t)(w * 16 + l16) * DV + 4 * kg;
+                float *ck = p.S_ck + (sbh * n_ck + (n / kAnchor - 1)) * DKF * DV + (size_t)(slice * DK + w * 16 + l16) * DV + 4 * kg;
 #pragma unroll
                 for (int it = 0; it < Cfg::NIT; ++it) *reinterpret_cast<f32x4 *>(ck + it * 16) = Sacc[it];
             }
@@ -620,7 +627,7 @@ __global__ __launch_bounds__(DK * 4) void gla_bwd_qk_kernel(BwdQKParams p) {
             // contribution of this chunk and everything after it to the earlier tokens, row_sum(dS .* S)
             const int c = chunk_of(n);
             if (p.S_ck && c > 0 && c % kAnchor == 0) {
-                const float *ck = p.S_ck + (sbh * n_ck + (c / kAnchor - 1)) * DK * DV + (size_t)(w * 16 + l16) * DV + 4 * kg;
+                const float *ck = p.S_ck + (sbh * n_ck + (c / kAnchor - 1)) * DKF * DV + (size_t)(slice * DK + w * 16 + l16) * DV + 4 * kg;
                 float acc = 0.f;
 #pragma unroll
                 for (int it = 0; it < Cfg::NIT; ++it) {
@@ -645,14 +652,14 @@ __global__ __launch_bounds__(DK * 4) void gla_bwd_qk_kernel(BwdQKParams p) {
         __syncthreads();
     }
     if constexpr (EMIT) {
-        float *Dl = p.dS_loc + sbh * DK * DV + (size_t)(w * 16 + l16) * DV + 4 * kg;
+        float *Dl = p.dS_loc + sbh * DKF * DV + (size_t)(slice * DK + w * 16 + l16) * DV + 4 * kg;
 #pragma unroll
         for (int it = 0; it < Cfg::NIT; ++it) *reinterpret_cast<f32x4 *>(Dl + it * 16) = Dacc[it];
         if (p.G_tot_out && tq == 0) {   // total log decay of the segment
             if constexpr (GH) {
                 if (cq == 0) p.G_tot_out[sbh] = gpre[0];
             } else {
-                *reinterpret_cast<f32x4 *>(p.G_tot_out + sbh * DK + 4 * cq) = gpre;
+                *reinterpret_cast<f32x4 *>(p.G_tot_out + sbh * DKF + slice * DK + 4 * cq) = gpre;
             }
         }
     }
@@ -665,30 +672,35 @@ __global__ __launch_bounds__(DK * 4) void gla_bwd_qk_kernel(BwdQKParams p) {
     }
 }
 
-template <int DK, int DV, bool REV, int GM, bool EMIT>
+template <int DK, int DV, int NS, bool REV, int GM, bool EMIT>
 static hipError_t launch_qk2(const BwdQKParams &p, hipStream_t s) {
     typedef QKCfg<DK, DV, EMIT> Cfg;
-    auto kern = gla_bwd_qk_kernel<DK, DV, REV, GM, EMIT>;
+    auto kern = gla_bwd_qk_kernel<DK, DV, NS, REV, GM, EMIT>;
     static LdsLimit limit;   // one per instantiation
     hipError_t e = limit.raise((const void *)kern, Cfg::kBytes);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3(p.B * p.P * p.H), dim3(Cfg::NT), Cfg::kBytes, s, p);
+    const int streams = p.B * p.P * p.H, grid = NS == 1 ? streams : (streams + 7) / 8 * 8 * NS;
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(Cfg::NT), Cfg::kBytes, s, p);
     return hipGetLastError();
 }
-template <int DK, int DV, bool REV, int GM>
+template <int DK, int DV, int NS, bool REV, int GM>
 static hipError_t launch_qk(const BwdQKParams &p, hipStream_t s) {
     if constexpr (!REV) {
-        if (p.dS_loc) return launch_qk2<DK, DV, false, GM, true>(p, s);
+        if (p.dS_loc) return launch_qk2<DK, DV, NS, false, GM, true>(p, s);
     }
-    return launch_qk2<DK, DV, REV, GM, false>(p, s);
+    return launch_qk2<DK, DV, NS, REV, GM, false>(p, s);
 }
 
 template <bool REV, int GM>
 static hipError_t dispatch_qk(const BwdQKParams &p, int d_k, int d_v, hipStream_t s) {
-    if (d_k == 64 && d_v == 64) return launch_qk<64, 64, REV, GM>(p, s);
-    if (d_k == 128 && d_v == 64) return launch_qk<128, 64, REV, GM>(p, s);
-    if (d_k == 64 && d_v == 128) return launch_qk<64, 128, REV, GM>(p, s);
-    if (d_k == 128 && d_v == 128) return launch_qk<128, 128, REV, GM>(p, s);
+    if constexpr (GM != kGateHead) {
+        if (d_k == 128 && p.B * p.P * p.H * 2 <= 256)
+            return d_v == 64 ? launch_qk<64, 64, 2, REV, GM>(p, s) : launch_qk<64, 128, 2, REV, GM>(p, s);
+    }
+    if (d_k == 64 && d_v == 64) return launch_qk<64, 64, 1, REV, GM>(p, s);
+    if (d_k == 128 && d_v == 64) return launch_qk<128, 64, 1, REV, GM>(p, s);
+    if (d_k == 64 && d_v == 128) return launch_qk<64, 128, 1, REV, GM>(p, s);
+    if (d_k == 128 && d_v == 128) return launch_qk<128, 128, 1, REV, GM>(p, s);
     return hipErrorInvalidValue;
 }
 
