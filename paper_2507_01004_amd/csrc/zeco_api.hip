@@ -170,23 +170,9 @@ extern "C" {
 constexpr long long kComputeUnits = 256;
 constexpr long long kLongestPiece = 512;   // chunks
 
-// Can the S equal pieces of a segment of L tokens be halved once more?  Pieces of whole chunks stay pieces of
-// whole chunks; a length that is no multiple of 64 is cut into equal pieces wherever it divides, each
-// piece then starting with a short chunk of its own.
-static bool halves_evenly(int L, int S) { return L % 64 == 0 ? L % (2 * S * 64) == 0 : L % (2 * S) == 0; }
-
-// Number of sub-segments each segment is split into inside zeco_gla_local_fwd (1 = none).  A stream is
-// a serial chain over chunks, so with few (batch, segment, head) streams most compute units would
-// idle; the local pass then applies the method to itself: sub-segment states from the zero state, a scan
-// of them inside each segment, and the output pass of every sub-segment from its scanned state.
-static int subsegments(const zeco_gla_desc *d) {
-    if (d->io_dtype != ZECO_BF16) return 1;
-    const long long streams = (long long)d->B * d->P * d->H;
-    if (streams > 64) return 1;
-    int S = 1;   // as many workgroups as fit the 256 compute units in one round, not more
-    while (streams * S * 2 <= 256 && halves_evenly(d->L, S) && d->L / (2 * S) >= 256) S *= 2;
-    return S;
-}
+static int subsegments(const zeco_gla_desc *d);
+static zeco::Cut cut_of(long long tokens, long long n);
+static void set_cut(zeco::ChunkParams &p, const zeco::Cut &c);
 
 // With one decay per head and between 65 and 128 streams the local pass runs every segment as two halves
 // from the zero state on whole workgroups (256 streams), then corrects the second halves' outputs with the
@@ -283,7 +269,8 @@ zeco_status zeco_gla_local_fwd(const zeco_gla_desc *d, const void *q, const void
     const SubLayout w = sub_layout(d, S);
     float *ws = static_cast<float *>(workspace);
     float *Ssub = ws + w.off_Ssub, *Sinit = ws + w.off_Sinit, *Gtot = ws + w.off_Gtot, *Gpre = ws + w.off_Gpre;
-    p.P = d->P * S; set_length(p, d->L / S);
+    set_cut(p, cut_of(d->L, S));
+    p.P = d->P * S;
     p.S_loc = Ssub; p.G_tot = Gtot;
     hipError_t e = zeco::launch_chunk_bf16(p, d->d_k, d->d_v, chunk_gate(d), 1, s);
     if (e != hipSuccess) return ZECO_ERR_HIP;
@@ -459,6 +446,31 @@ static long long pieces_for(const zeco_gla_desc *d, long long T, bool backward, 
     if (best == 0) best = 1;
     if (best * BH > (1ll << 24)) best = d->P;   // (the limit on workgroups that the descriptor keeps)
     return best;
+}
+
+// Number of sub-segments each segment is cut into inside zeco_gla_local_fwd (1 = none).  A stream is
+// a serial chain over chunks, so with few (batch, segment, head) streams most compute units would
+// idle; the local pass then applies the method to itself: sub-segment states from the zero state, a scan
+// of them inside each segment, and the output pass of every sub-segment from its scanned state.  Sub-segments of at
+// least 256 tokens, in one round of workgroups; how many, by the estimate of the one-call forms (the cut need not
+// come out even: 5 x 2 streams of 7133 tokens took one workgroup pair each before).
+static int subsegments(const zeco_gla_desc *d) {
+    if (d->io_dtype != ZECO_BF16) return 1;
+    const long long streams = (long long)d->B * d->P * d->H, chunks = d->L / 64;
+    if (streams > 64 || streams == 0) return 1;
+    const CostModel m = cost_model(d);
+    long long best = 1;
+    double cost = 0.;
+    auto consider = [&](long long S) {
+        if (S * 4 > chunks) S = chunks / 4;
+        if (S < 2 || S * streams > kComputeUnits) return;
+        const bool even = d->L % (64 * S) == 0;
+        const double c = cost_forward(m, (double)streams, (double)S, (double)(d->L / 64 / S + (even ? 0 : 1)), false) * (even ? 0.92 : 1.);
+        if (best == 1 || c < cost) { cost = c; best = S; }
+    };
+    for (int k = 2; k <= 4; ++k) consider(64 * k / streams);
+    for (long long S = 2; S * streams <= kComputeUnits; S *= 2) consider(S);
+    return (int)best;
 }
 
 // The cut itself, and what the launches need to know of it.

@@ -7,7 +7,7 @@ import numpy as np
 import pytest
 import torch
 
-from gpu_util import TOL, host, rel_err_bh
+from gpu_util import TOL, host, log_err, rel_err_bh
 from oracle import oracle
 from paper_2507_01004_amd import synth, zeco
 
@@ -164,3 +164,29 @@ def test_fp32_passes_at_chunk_edges(C, dk, dv):
         assert rel_err_bh(host(o), o_r, (0, 2)) <= TOL["f32"] and rel_err_bh(host(S_last), S_r, (0, 1)) <= TOL["f32"]
         for nm, x, r in zip(("dq", "dk", "dv", "dg"), got, ref):
             assert rel_err_bh(host(x), r, (0, 2)) <= TOL["f32"], nm
+
+
+@pytest.mark.parametrize("case", [(1, 3, 2, 1700, 128, 128, "f32"), (2, 1, 1, 2111, 64, 128, "bf16"), (1, 5, 3, 1089, 128, 64, "head"),
+                                  (1, 21, 1, 831, 64, 64, "f32"), (1, 1, 7, 512, 128, 128, "f32")], ids=lambda c: "B%d_H%d_P%d_L%d_%dx%d_%s" % c)
+def test_local_pass_of_few_streams_at_odd_lengths(case):
+    """The local pass cuts segments of few streams into sub-segments that need not be equal: every output of it, and the
+    three calls together, against the oracle."""
+    B, H, P, L, dk, dv, gate = case
+    print("case", case, flush=True)
+    head, tol = gate == "head", TOL["bf16"]
+    inp = synth.make_inputs(B, P * L, H, dk, dv, seed=L, io="bf16", g="f32" if head else gate, device="cuda", gate_div=64.0,
+                            per_head_gate=head)
+    q, k, v, g = (inp[n] for n in "qkvg")
+    S0 = torch.randn(B, H, dk, dv, device="cuda", generator=torch.Generator(device="cuda").manual_seed(L)) * 0.3
+    hg = np.repeat(host(g)[..., None], dk, axis=-1) if head else host(g)
+    args = (host(q), host(k), host(v), hg)
+    o_l, S_l, Gc_l, Gt_l = oracle.gla_local(*args, P, 0.5)
+    o, S_loc, G_cum, G_tot = zeco.gla_local_fwd(q, k, v, g, P, scale=0.5)
+    torch.cuda.synchronize()
+    assert rel_err_bh(host(o), o_l, (0, 2)) <= tol and rel_err_bh(host(S_loc), S_l, (1, 2)) <= tol
+    assert log_err(host(G_cum), Gc_l[..., 0] if head else Gc_l) <= 1e-5
+    assert log_err(host(G_tot), Gt_l[..., 0] if head else Gt_l) <= 1e-5
+    o, S_last, _ = zeco.segmented_fwd(q, k, v, g, P, scale=0.5, S0=S0)
+    o_r, S_r = oracle.gla_recurrent(*args, 0.5, host(S0))
+    torch.cuda.synchronize()
+    assert rel_err_bh(host(o), o_r, (0, 2)) <= tol and rel_err_bh(host(S_last), S_r, (0, 1)) <= tol
