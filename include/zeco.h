@@ -75,12 +75,14 @@ typedef struct {
 } zeco_gla_desc;
 
 /* Bytes of device workspace zeco_gla_local_fwd needs for this descriptor (may be 0).
- * Non-zero when the problem has few (batch, segment, head) streams (bf16, B*P*H <= 64; with one decay per
- * head up to 128, where every segment is run as two halves and the second half corrected): the local pass
+ * Non-zero when the problem has few (batch, segment, head) streams (B*P*H <= 64, segments of 512 tokens or more;
+ * with bf16 and one decay per head up to 128, where every segment is run as two halves and the second half
+ * corrected): the local pass
  * then splits every segment into sub-segments and runs Alg. 1's own schedule inside each segment (end
  * states of the sub-segments from the zero state, their scan, the output pass of every sub-segment from
  * its scanned state), and keeps the sub-segment states in the workspace (device memory, 16-byte aligned,
- * caller-owned, contents unspecified afterwards).
+ * caller-owned, contents unspecified afterwards).  With fp32, and with lengths that do not halve evenly, the call
+ * also takes a smaller workspace and then runs the segments whole.
  * Returns 0 for an invalid descriptor. */
 size_t zeco_gla_local_fwd_workspace(const zeco_gla_desc *desc);
 

@@ -18,7 +18,8 @@
 // MODE (the phases of Alg. 1, as in the bf16 kernel): kF32Local the local pass from the zero state
 // (o, S_loc, G_cum, G_tot); kF32States only the final state and total decay of each segment (S_loc,
 // G_tot; q is not read); kF32Output the output pass from given initial states S_init (none: zero; o, and the end
-// states if S_loc is given).
+// states if S_loc is given); kF32LocalInit the output pass over the pieces of cut segments, from given initial states,
+// that also emits G_cum counted from each segment's first token (G_off holds the pieces' totals).
 //
 // Two more modes run the same equations over the REVERSED sequence for the backward pass (App. A.4):
 //   kF32DState  dS <- (gamma^T 1) .* dS + (Q .* Lambda)^T dO from zero; S_loc receives the gradient the
@@ -40,7 +41,7 @@
 
 namespace zeco {
 
-enum F32Mode { kF32Local = 0, kF32States = 1, kF32Output = 2, kF32DState = 3, kF32DV = 4 };
+enum F32Mode { kF32Local = 0, kF32States = 1, kF32Output = 2, kF32DState = 3, kF32DV = 4, kF32LocalInit = 5 };
 
 template <int DK, int DV, int C> struct F32Cfg {
     static constexpr int kWaves = DV / 16;
@@ -81,8 +82,8 @@ __global__ __launch_bounds__(DV * 4, f32_waves(DV / 16, C)) void gla_chunk_f32_k
     typedef F32Cfg<DK, DV, C> Cfg;
     constexpr bool REV = MODE == kF32DState || MODE == kF32DV;       // the sequence reversed
     constexpr bool NOQ = MODE == kF32States || MODE == kF32DState;   // only the state is computed
-    constexpr bool FROM_INIT = MODE == kF32Output || MODE == kF32DV; // start from S_init, emit o only
-    constexpr bool EMIT_G = MODE == kF32Local;
+    constexpr bool FROM_INIT = MODE == kF32Output || MODE == kF32DV || MODE == kF32LocalInit; // start from S_init, emit no state
+    constexpr bool EMIT_G = MODE == kF32Local || MODE == kF32LocalInit;
     extern __shared__ __align__(16) float lds[];
     float *Qs = lds + Cfg::kOffQ;    // Q .* Lambda * scale      [t][i]
     float *Ks = lds + Cfg::kOffK;    // K / Lambda               [s][i]
@@ -151,6 +152,15 @@ __global__ __launch_bounds__(DV * 4, f32_waves(DV / 16, C)) void gla_chunk_f32_k
     auto at = [&](long long x) { return REV ? len - 1 - x : x; };
     auto start_of = [&](int n) { return n ? (long long)n * C - pad : 0ll; };
     double seg_prefix[4] = {0., 0., 0., 0.};     // log decay accumulated over previous chunks
+    if constexpr (MODE == kF32LocalInit) {       // .. and over the run's earlier pieces, from their totals
+        const float *G = p.G_off + (((size_t)(seg - seg % p.cut.n) * p.B + b) * p.H + h) * DK + 4 * cq;
+#pragma unroll 4
+        for (int j = 0; j < seg % p.cut.n; ++j) {
+            const f32x4 x = *reinterpret_cast<const f32x4 *>(G + (size_t)j * p.B * p.H * DK);
+#pragma unroll
+            for (int a = 0; a < 4; ++a) seg_prefix[a] += (double)x[a];
+        }
+    }
 
     // The raw rows of the chunk worked on next: fetched a whole chunk ahead, 16 bytes a load and all of a chunk's loads
     // in flight together.  (Loaded one by one where they were used, four bytes a lane, they took two thirds of a chunk's
@@ -371,6 +381,7 @@ template <int DK, int DV, int C> static hipError_t dispatch_f32_mode(const Chunk
     if (mode == kF32Output) return launch_f32<DK, DV, C, kF32Output>(p, s);
     if (mode == kF32DState) return launch_f32<DK, DV, C, kF32DState>(p, s);
     if (mode == kF32DV) return launch_f32<DK, DV, C, kF32DV>(p, s);
+    if (mode == kF32LocalInit) return launch_f32<DK, DV, C, kF32LocalInit>(p, s);
     return launch_f32<DK, DV, C, kF32Local>(p, s);
 }
 
@@ -381,8 +392,8 @@ template <int DK, int DV> static hipError_t dispatch_f32_chunk(const ChunkParams
     return hipErrorInvalidValue;
 }
 
-// mode: 0 local pass, 1 states only, 2 output pass from S_init, 3 backward state pass, 4 dV pass (the same
-// numbering as the bf16 kernel's);
+// mode: 0 local pass, 1 states only, 2 output pass from S_init, 3 backward state pass, 4 dV pass, 5 output pass of the
+// pieces of a cut that also writes G_cum (the same numbering as the bf16 kernel's);
 // p.n_chunks and p.pad count chunks of C tokens
 hipError_t launch_chunk_f32(const ChunkParams &p, int d_k, int d_v, int C, int mode, hipStream_t s) {
     if (d_k == 64 && d_v == 64) return dispatch_f32_chunk<64, 64>(p, C, mode, s);

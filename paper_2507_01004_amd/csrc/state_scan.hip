@@ -78,7 +78,7 @@ __global__ __launch_bounds__(256) void state_scan_kernel(ScanParams p, int parts
     const bool prefix = BYP && e % dvv == 0 && (!p.gate_per_head || row == 0);
     const size_t gcol = (size_t)bh * gdim + (p.gate_per_head ? 0 : row);
     float *gpre = (prefix && p.G_pre) ? p.G_pre + grp * P * g_stride + gcol : nullptr;
-    float gsum = 0.f;
+    double gsum = 0.;   // (only BYP adds to it; sums of log decays reach the thousands)
 
     // running pointers: of the next step to fetch, of the next step to consume (chain order, either direction)
     const long long first = p.reverse ? P - 1 : 0, dir = p.reverse ? -1 : 1;
@@ -101,10 +101,10 @@ __global__ __launch_bounds__(256) void state_scan_kernel(ScanParams p, int parts
         }
         if (BYP) {
             if (gp) {
-                *gp = gsum;
+                *gp = (float)gsum;
                 gp += gstep;
             }
-            gsum += a[u];
+            gsum += (double)a[u];
         }
         const float d = fast_exp(a[u]);
 #pragma unroll
@@ -143,7 +143,7 @@ __global__ __launch_bounds__(256) void state_scan_kernel(ScanParams p, int parts
         }
     }
     if (p.S_last) *reinterpret_cast<vec_t *>(p.S_last + grp * seg_stride + off) = s;
-    if (prefix && p.G_sum) p.G_sum[grp * g_stride + gcol] = gsum;
+    if (prefix && p.G_sum) p.G_sum[grp * g_stride + gcol] = (float)gsum;
 }
 
 template <int V, int D> static hipError_t launch_scan_vd(const ScanParams &p, hipStream_t s) {

@@ -222,9 +222,13 @@ zeco_status zeco_gla_local_fwd(const zeco_gla_desc *d, const void *q, const void
         !aligned16(S_loc) || !aligned16(G_cum) || !aligned16(G_tot))
         return ZECO_ERR_INVALID_ARG;
     const size_t need = zeco_gla_local_fwd_workspace(d);
-    if (workspace_bytes < need) return ZECO_ERR_WORKSPACE;
-    if (need && (!workspace || !aligned16(workspace))) return ZECO_ERR_INVALID_ARG;
-    const int S = subsegments(d);
+    int S = subsegments(d);
+    if (workspace_bytes < need) {
+        // fp32, and lengths that do not halve, can do without: one chain a stream
+        const bool must = halves_with_correction(d) || (d->io_dtype == ZECO_BF16 && d->L % (d->L % 64 ? 2 : 128) == 0);
+        if (must) return ZECO_ERR_WORKSPACE;
+        S = 1;
+    } else if (need && (!workspace || !aligned16(workspace))) return ZECO_ERR_INVALID_ARG;
     hipStream_t s = static_cast<hipStream_t>(stream);
 
     zeco::ChunkParams p;
@@ -235,7 +239,7 @@ zeco_status zeco_gla_local_fwd(const zeco_gla_desc *d, const void *q, const void
     p.scale = d->scale; p.kscale = 1.f;
     p.sb = d->stride_b; p.st = d->stride_t; p.sh = d->stride_h;
     p.vb = d->vstride_b; p.vt = d->vstride_t; p.vh = d->vstride_h;
-    if (d->io_dtype == ZECO_F32) return from_hip(launch_phase(p, d, 0, s));
+    if (S == 1 && d->io_dtype == ZECO_F32) return from_hip(launch_phase(p, d, 0, s));
     if (halves_with_correction(d)) {
         const SubLayout w = sub_layout(d, 2);
         float *ws = static_cast<float *>(workspace);
@@ -272,7 +276,7 @@ zeco_status zeco_gla_local_fwd(const zeco_gla_desc *d, const void *q, const void
     set_cut(p, cut_of(d->L, S));
     p.P = d->P * S;
     p.S_loc = Ssub; p.G_tot = Gtot;
-    hipError_t e = zeco::launch_chunk_bf16(p, d->d_k, d->d_v, chunk_gate(d), 1, s);
+    hipError_t e = launch_phase(p, d, 1, s);
     if (e != hipSuccess) return ZECO_ERR_HIP;
 
     zeco::ScanParams sp;   // one chain of S sub-segments per segment; its end state is the segment's S_loc
@@ -282,8 +286,9 @@ zeco_status zeco_gla_local_fwd(const zeco_gla_desc *d, const void *q, const void
     sp.G_pre = Gpre; sp.G_sum = G_tot;   // log decay preceding each sub-segment; the segment's total
     if ((e = zeco::launch_scan(sp, s)) != hipSuccess) return ZECO_ERR_HIP;
 
-    p.S_loc = nullptr; p.G_tot = nullptr; p.S_init = Sinit; p.G_off = Gpre;
-    return from_hip(zeco::launch_chunk_bf16(p, d->d_k, d->d_v, chunk_gate(d), 5, s));
+    p.S_loc = nullptr; p.G_tot = nullptr; p.S_init = Sinit;
+    p.G_off = d->io_dtype == ZECO_F32 ? Gtot : Gpre;   // (the fp32 kernel adds the pieces' totals up in 64 bits)
+    return from_hip(launch_phase(p, d, 5, s));
 }
 
 // ---- two-phase forward ------------------------------------------------------------------------------
@@ -369,7 +374,7 @@ struct CostModel {
     double slots;                      // workgroups in flight
     double fixed1 = 8., fixed2 = 13., fixedb = 30.;
     double step = 0.07;                // of a scan, per piece
-    double rate = 5.9e6;               // bytes per microsecond of the chip (a lone round of workgroups hides part of it)
+    double rate = 5.9e6;               // bytes per microsecond of the chip (beside a chain's own latency part of the traffic is hidden)
 };
 static CostModel cost_model(const zeco_gla_desc *d) {
     const double io = d->io_dtype == ZECO_F32 ? 4. : 2., k = io * d->d_k, v = io * d->d_v;
@@ -393,7 +398,8 @@ static CostModel cost_model(const zeco_gla_desc *d) {
 }
 static double cost_chain(const CostModel &m, double wgs, double longest, double chunk, double bytes) {
     const double rounds = (double)(long long)((wgs + m.slots - 1.) / m.slots), share = wgs < m.slots ? wgs : m.slots;
-    return rounds * longest * (chunk + share * bytes / (2.6 * m.rate));
+    const double traffic = share * bytes / m.rate, alone = chunk + traffic / 2.6;
+    return rounds * longest * (alone > traffic ? alone : traffic);
 }
 static double cost_forward(const CostModel &m, double BH, double n, double longest, bool correct) {
     // Pieces the AUTO schedule corrects instead of reading k, v, g twice: their first 35 chunks or so, what the decays of
@@ -455,10 +461,10 @@ static long long pieces_for(const zeco_gla_desc *d, long long T, bool backward, 
 // least 256 tokens, in one round of workgroups; how many, by the estimate of the one-call forms (the cut need not
 // come out even: 5 x 2 streams of 7133 tokens took one workgroup pair each before).
 static int subsegments(const zeco_gla_desc *d) {
-    if (d->io_dtype != ZECO_BF16) return 1;
     const long long streams = (long long)d->B * d->P * d->H, chunks = d->L / 64;
     if (streams > 64 || streams == 0) return 1;
-    const CostModel m = cost_model(d);
+    CostModel m = cost_model(d);
+    m.bytes2 += 64. * (d->g_per_head ? 4. : 4. * d->d_k);   // G_cum
     long long best = 1;
     double cost = 0.;
     auto consider = [&](long long S) {

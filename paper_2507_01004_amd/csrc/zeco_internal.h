@@ -57,7 +57,8 @@ struct ChunkParams {
     void *o;
     float *S_loc, *G_cum, *G_tot;
     const float *S_init;       // [P,B,H,d_k,d_v] initial states (modes that start from a given state)
-    const float *G_off = nullptr;   // [P,B,H,d_k] ([P,B,H] per-head) log decay preceding each segment (mode 5 only)
+    const float *G_off = nullptr;   // [P,B,H,d_k] ([P,B,H] per-head) log decay preceding each segment (mode 5 only; fp32
+                                    // kernel: total log decay of each piece)
     float *G_chunk = nullptr;       // [B,P,n_chunks,H,d_k] log decay from the segment start to each chunk's start (mode 6 only)
     // Output pass over a run in one piece, optional: the states entering the pieces of `emit` (a cut of the same run),
     // S_emit [emit.n, B, H, d_k, d_v], for a backward on those pieces; and the end state a second time, S_loc2
@@ -151,7 +152,7 @@ struct LdsLimit {
 
 // Each returns hipSuccess or the launch error.  d_k, d_v in {64,128}.
 // fp32 kernel: chunk length C in {16, 32, 64} (p.n_chunks, p.pad count chunks of C tokens); mode 0 local pass,
-// 1 states only, 2 output pass from S_init, 3 backward state pass, 4 dV pass (as in the bf16 kernel below)
+// 1 states only, 2 output pass from S_init, 3 backward state pass, 4 dV pass, 5 (as in the bf16 kernel below)
 hipError_t launch_chunk_f32(const ChunkParams &p, int d_k, int d_v, int C, int mode, hipStream_t s);
 // mode: 0 local pass (o, S_loc, G_cum, G_tot), 1 states only (S_loc, G_tot), 2 output pass from S_init (o),
 // 3 backward state pass (k := q, v := dO; S_loc := dS leaving the segment), 4 dV pass (q := k, k := q,

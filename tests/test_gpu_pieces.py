@@ -166,15 +166,16 @@ def test_fp32_passes_at_chunk_edges(C, dk, dv):
             assert rel_err_bh(host(x), r, (0, 2)) <= TOL["f32"], nm
 
 
-@pytest.mark.parametrize("case", [(1, 3, 2, 1700, 128, 128, "f32"), (2, 1, 1, 2111, 64, 128, "bf16"), (1, 5, 3, 1089, 128, 64, "head"),
-                                  (1, 21, 1, 831, 64, 64, "f32"), (1, 1, 7, 512, 128, 128, "f32")], ids=lambda c: "B%d_H%d_P%d_L%d_%dx%d_%s" % c)
+@pytest.mark.parametrize("case", [(1, 3, 2, 1700, 128, 128, "bf16", "f32"), (2, 1, 1, 2111, 64, 128, "bf16", "bf16"), (1, 5, 3, 1089, 128, 64, "bf16", "head"),
+                                  (1, 21, 1, 831, 64, 64, "bf16", "f32"), (1, 1, 7, 512, 128, 128, "bf16", "f32"), (1, 2, 3, 1111, 64, 128, "f32", "f32"),
+                                  (2, 1, 1, 640, 128, 64, "f32", "f32")], ids=lambda c: "B%d_H%d_P%d_L%d_%dx%d_%s_%s" % c)
 def test_local_pass_of_few_streams_at_odd_lengths(case):
     """The local pass cuts segments of few streams into sub-segments that need not be equal: every output of it, and the
     three calls together, against the oracle."""
-    B, H, P, L, dk, dv, gate = case
+    B, H, P, L, dk, dv, io, gate = case
     print("case", case, flush=True)
-    head, tol = gate == "head", TOL["bf16"]
-    inp = synth.make_inputs(B, P * L, H, dk, dv, seed=L, io="bf16", g="f32" if head else gate, device="cuda", gate_div=64.0,
+    head, tol = gate == "head", TOL[io]
+    inp = synth.make_inputs(B, P * L, H, dk, dv, seed=L, io=io, g="f32" if head else gate, device="cuda", gate_div=64.0,
                             per_head_gate=head)
     q, k, v, g = (inp[n] for n in "qkvg")
     S0 = torch.randn(B, H, dk, dv, device="cuda", generator=torch.Generator(device="cuda").manual_seed(L)) * 0.3
@@ -190,3 +191,7 @@ def test_local_pass_of_few_streams_at_odd_lengths(case):
     o_r, S_r = oracle.gla_recurrent(*args, 0.5, host(S0))
     torch.cuda.synchronize()
     assert rel_err_bh(host(o), o_r, (0, 2)) <= tol and rel_err_bh(host(S_last), S_r, (0, 1)) <= tol
+    if io == "f32":   # a smaller workspace: the segments whole
+        whole = zeco.gla_local_fwd(q, k, v, g, P, scale=0.5, workspace=torch.empty(16, dtype=torch.uint8, device="cuda"))
+        torch.cuda.synchronize()
+        assert rel_err_bh(host(whole[0]), o_l, (0, 2)) <= tol and log_err(host(whole[2]), Gc_l) <= 1e-5
