@@ -442,7 +442,7 @@ __global__ __launch_bounds__(DV * 4) void apply_init_f32_kernel(ApplyParams p) {
         for (int r = 0; r < 4; ++r) Sreg[it][r] = S[(size_t)(16 * it + 4 * kg + r) * DV + 16 * w + l16];
 
     // q, G_cum and o of a block are fetched 16 (o: 4) bytes a load, all of them in flight together, q and G_cum a block
-    // ahead (loaded one by one, a single block took 12 us).
+    // ahead (loaded one by one, a single block took 12 us, now 5).
     constexpr int ITEMS = 64 * (DK / 4) / NT;
     f32x4 rq[ITEMS], rG[ITEMS];
     auto fetch = [&](int blk) __attribute__((always_inline)) {

@@ -110,6 +110,8 @@ __device__ __forceinline__ bf16x8 pack2x4(f32x4 a, f32x4 b) {
 // the segment's total log decay).
 // NS > 1 (per-channel gates): NS sibling workgroups share a stream, each with DK of its NS * DK channels - columns of W,
 // of the outputs and of everything gated; X, Y and the scores, which contract over d_v, each of them has whole.
+// Taken with at most 128 streams, half as many as compute units: 64 streams of 8192 tokens, d = 128: dK 769 -> 627 us,
+// dQ 681 -> 581 us; from 129 streams on one workgroup a stream leaves no compute unit idle for a sibling.
 template <int DK, int DV, int NS, bool REV, int GM, bool EMIT>
 __global__ __launch_bounds__(DK * 4) void gla_bwd_qk_kernel(BwdQKParams p) {
     static_assert(!(REV && EMIT), "the state gradient is a by-product of the forward-direction pass");

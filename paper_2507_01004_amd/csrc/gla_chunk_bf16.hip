@@ -95,8 +95,10 @@ __device__ __forceinline__ bf16x8 pack8(const f32x16 &a, int base) {
 //   kLocal   the local pass from the zero state: o, S_loc, G_cum, G_tot          (Sec. 3.1)
 //   kStates  only the final local state and total decay of each segment: S_loc, G_tot
 //            (Alg. 1's chunk-state loop; q is not read, nothing per token is written)
-//   kOutput  the output pass from given initial states S_init[p] (none: zero): o, and the end states (S_loc,
-//            S_loc2) and those entering the pieces of a backward (S_emit) if asked for (Alg. 1's output pass, the incoming state folded into the running state)
+//   kOutput  the output pass from given initial states S_init[p] (none: zero): o, and the end states if
+//            S_loc is given (Alg. 1's output pass, the incoming state folded into the running state)
+//   kOutputEmit  the same over runs in one piece, for a training step: also the states entering the pieces a backward
+//            will work on (S_emit) and the end states a second time (S_loc2)
 //   kLocalCD the local pass with the cumulative decay kept per chunk, as Alg. 1 stores it (the list of
 //            gamma~_[n]): o, S_loc, G_tot and G_chunk[n] = log gamma~_[n-1], the log decay from the segment's
 //            first token up to the start of chunk n; no per-token G_cum is written
@@ -114,7 +116,7 @@ __device__ __forceinline__ bf16x8 pack8(const f32x16 &a, int base) {
 // kDV: q := k, k := q, v := dO, o := dV), flip the sign of the decay exponents, apply gamma before the
 // chunk's products instead of after, and store token t of a chunk at tile row 63 - t, so that the
 // causal structure of the tiles is the one of the forward pass.
-enum ChunkMode { kLocal = 0, kStates = 1, kOutput = 2, kDState = 3, kDV = 4, kLocalInit = 5, kLocalCD = 6 };
+enum ChunkMode { kLocal = 0, kStates = 1, kOutput = 2, kDState = 3, kDV = 4, kLocalInit = 5, kLocalCD = 6, kOutputEmit = 7 };
 
 // Gate waves per workgroup: 4, one per SIMD beside an MFMA wave; 8 in the local pass with per-channel
 // gates at d_k = 128, which moves the most bytes per chunk and gains 2-3 % from the second set of
@@ -155,7 +157,8 @@ __global__ __launch_bounds__(chunk_threads(DK, DV, GM, MODE)) void gla_chunk_bf1
     constexpr bool GH = GM == kGateHead;
     constexpr bool REV = MODE == kDState || MODE == kDV;          // chunks and tokens in reverse
     constexpr bool NOQ = MODE == kStates || MODE == kDState;      // only the state is computed
-    constexpr bool FROM_INIT = MODE == kOutput || MODE == kDV || MODE == kLocalInit;   // start from S_init (no state emitted, but see kOutput)
+    constexpr bool OUT = MODE == kOutput || MODE == kOutputEmit;
+    constexpr bool FROM_INIT = OUT || MODE == kDV || MODE == kLocalInit;   // start from S_init (no state emitted, but see kOutput)
     constexpr bool EMIT_G = MODE == kLocal || MODE == kLocalInit;  // per-token cumulative log decay
     constexpr float SGN = REV ? -1.f : 1.f;                       // sign of the decay exponents
     constexpr float kLog2e = 1.4426950408889634f;
@@ -446,7 +449,7 @@ __global__ __launch_bounds__(chunk_threads(DK, DV, GM, MODE)) void gla_chunk_bf1
             }
             // decay outputs: the local pass and the two state passes (the backward one emits G_tot when
             // asked, so that the reverse scan does not need the forward state pass)
-            if constexpr (MODE == kOutput || MODE == kDV) return;
+            if constexpr (OUT || MODE == kDV) return;
             if constexpr (MODE == kDState) {
                 if (!p.G_tot) return;
             }
@@ -547,7 +550,7 @@ __global__ __launch_bounds__(chunk_threads(DK, DV, GM, MODE)) void gla_chunk_bf1
         for (int it = 0; it < Cfg::NIT; ++it)
 #pragma unroll
             for (int rr = 0; rr < 16; ++rr) Sacc[it][rr] = 0.f;
-        if (FROM_INIT && (MODE != kOutput || p.S_init)) {   // (kOutput: no S_init = the zero state)
+        if (FROM_INIT && (!OUT || p.S_init)) {   // (output pass: no S_init = the zero state)
 #pragma unroll
             for (int it = 0; it < Cfg::NIT; ++it)
 #pragma unroll
@@ -656,15 +659,13 @@ __global__ __launch_bounds__(chunk_threads(DK, DV, GM, MODE)) void gla_chunk_bf1
                 for (int rr = 0; rr < 16; ++rr)
                     S[(size_t)(it * 32 + M::row(rr, kg)) * (DV * NS)] = Sacc[it][rr];
         };
-        // kOutput over a whole run: the states entering the pieces a backward will work on (uniform branches)
-        int emit_at = 0, emit_j = 0;
-        float *emit_to = p.S_emit + sbh * DK * (DV * NS) + slice * DV + w * 32 + lt;
-        const bool emit = MODE == kOutput && p.S_emit;
+        int emit_at = 0, emit_j = 0;   // kOutputEmit: chunk and index of the next piece
+        float *emit_to = MODE == kOutputEmit ? p.S_emit + sbh * DK * (DV * NS) + slice * DV + w * 32 + lt : nullptr;
         __syncthreads();
         __syncthreads();
         for (int n = 0; n < N; ++n) {
             const unsigned char *cur = lds + (n & 1) * Cfg::kTileBytes;
-            if (MODE == kOutput && emit && n == emit_at) {
+            if (MODE == kOutputEmit && n == emit_at) {
                 store_state(emit_to);
                 emit_to += (size_t)p.B * p.H * DK * (DV * NS);
                 // the first piece has the short chunk on top of its whole ones
@@ -677,8 +678,8 @@ __global__ __launch_bounds__(chunk_threads(DK, DV, GM, MODE)) void gla_chunk_bf1
             __syncthreads();
         }
 
-        if (!FROM_INIT || (MODE == kOutput && p.S_loc)) store_state(Sl);
-        if (MODE == kOutput && p.S_loc2) store_state(p.S_loc2 + sbh * DK * (DV * NS) + slice * DV + w * 32 + lt);
+        if (!FROM_INIT || (OUT && p.S_loc)) store_state(Sl);
+        if constexpr (MODE == kOutputEmit) store_state(p.S_loc2 + sbh * DK * (DV * NS) + slice * DV + w * 32 + lt);
     }
 }
 
@@ -735,6 +736,7 @@ hipError_t launch_chunk_bf16(const ChunkParams &p, int d_k, int d_v, int gate_mo
     if (mode == kDV) return dispatch_gate<kDV>(p, d_k, d_v, gate_mode, s);
     if (mode == kLocalInit) return dispatch_gate<kLocalInit>(p, d_k, d_v, gate_mode, s);
     if (mode == kLocalCD) return dispatch_gate<kLocalCD>(p, d_k, d_v, gate_mode, s);
+    if (mode == kOutputEmit) return dispatch_gate<kOutputEmit>(p, d_k, d_v, gate_mode, s);
     return dispatch_gate<kLocal>(p, d_k, d_v, gate_mode, s);
 }
 

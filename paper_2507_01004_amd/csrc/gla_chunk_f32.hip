@@ -163,8 +163,8 @@ __global__ __launch_bounds__(DV * 4, f32_waves(DV / 16, C)) void gla_chunk_f32_k
     }
 
     // The raw rows of the chunk worked on next: fetched a whole chunk ahead, 16 bytes a load and all of a chunk's loads
-    // in flight together.  (Loaded one by one where they were used, four bytes a lane, they took two thirds of a chunk's
-    // time: output pass, d = 128, C = 64, 32 us a chunk where the products need 9.)
+    // in flight together.  (Loaded one by one where they were used, four bytes a lane, they took half of a chunk's time:
+    // output pass, d = 128, C = 64, 32 us a chunk, now 17; its products alone are 9.)
     f32x4 rq[Cfg::kTPT], rk[Cfg::kTPT], rg[Cfg::kTPT], rv[Cfg::kTPV];
     auto fetch_gv = [&](int n) __attribute__((always_inline)) {
         const long long t0 = start_of(n);

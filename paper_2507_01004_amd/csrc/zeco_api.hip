@@ -374,6 +374,7 @@ struct CostModel {
     double slots;                      // workgroups in flight
     double fixed1 = 8., fixed2 = 13., fixedb = 30.;
     double step = 0.07;                // of a scan, per piece
+    bool bound = false;                // no chunk faster than its traffic at `rate`
     double rate = 5.9e6;               // bytes per microsecond of the chip (beside a chain's own latency part of the traffic is hidden)
 };
 static CostModel cost_model(const zeco_gla_desc *d) {
@@ -399,7 +400,7 @@ static CostModel cost_model(const zeco_gla_desc *d) {
 static double cost_chain(const CostModel &m, double wgs, double longest, double chunk, double bytes) {
     const double rounds = (double)(long long)((wgs + m.slots - 1.) / m.slots), share = wgs < m.slots ? wgs : m.slots;
     const double traffic = share * bytes / m.rate, alone = chunk + traffic / 2.6;
-    return rounds * longest * (alone > traffic ? alone : traffic);
+    return rounds * longest * (m.bound && traffic > alone ? traffic : alone);
 }
 static double cost_forward(const CostModel &m, double BH, double n, double longest, bool correct) {
     // Pieces the AUTO schedule corrects instead of reading k, v, g twice: their first 35 chunks or so, what the decays of
@@ -465,6 +466,7 @@ static int subsegments(const zeco_gla_desc *d) {
     if (streams > 64 || streams == 0) return 1;
     CostModel m = cost_model(d);
     m.bytes2 += 64. * (d->g_per_head ? 4. : 4. * d->d_k);   // G_cum
+    m.bound = true;   // (three calls, 6 heads, 2 x 32768 tokens, 16 / 21 sub-segments: 285 / 302 us)
     long long best = 1;
     double cost = 0.;
     auto consider = [&](long long S) {
@@ -568,7 +570,7 @@ zeco_status zeco_gla_fused_fwd(const zeco_gla_desc *d, const void *q, const void
             p.emit = bwd_cut(d);
             p.S_emit = S_save; p.S_loc2 = S_save + (size_t)p.emit.n * d->B * d->H * d->d_k * d->d_v;
         }
-        return from_hip(launch_phase(p, d, 2, s));
+        return from_hip(launch_phase(p, d, S_save ? 7 : 2, s));
     }
     const bool correct = schedule == ZECO_SCHEDULE_CORRECT || (schedule == ZECO_SCHEDULE_AUTO && corrects(d, cut.base));
 
@@ -1053,7 +1055,7 @@ zeco_status zeco_gla_bwd_from_state_varlen(const zeco_gla_desc *d, const int64_t
 // calls bit for bit.  Longer ones are cut: the segments together are one run of tokens, whose pieces need not end where
 // they do, so the run is cut as in zeco_gla_fused_fwd, on the device (launch_plan), where the table is.  Measured with
 // 8 segments of 1160 .. 9287 tokens and 16 heads, forward and backward: 3.15 ms as given (the longest segment's
-// chain), 0.86 ms in 16 pieces.
+// chain), 1.05 ms in 16 pieces.
 constexpr int kWholeSegments = 33 * 64;
 struct VarlenLayout {   // workspace carve-up, in floats
     int slots;          // pieces, or segments
