@@ -187,14 +187,13 @@ __global__ __launch_bounds__(256) void apply_init_bf16_kernel(ApplyParams p) {
     id /= p.H;
     const int b = id % p.B, seg = p.p0 + p.seg_step * (id / p.B);
     long long tok0 = (long long)seg * p.L;                       // the segment's first token
-    long long T = (long long)p.P * p.L;                          // tokens per batch entry
+    const long long T = p.T;                                     // tokens per batch entry
     int n_chunks = p.n_chunks, pad = p.pad;
     const int c0 = tb * (p.tokens_per_wg / 64);                  // this workgroup's first block
     if (p.seg_start) {
         // segments of unequal length: bounds from the table; the grid is sized for the longest segment allowed,
         // so workgroups past this segment's end leave, and so do those of a segment that cannot be taken
         tok0 = p.seg_start[seg];
-        T = p.T;
         const long long len = p.seg_start[seg + 1] - tok0;
         if (tok0 < 0 || len < 64 || len > p.L || tok0 > T - len) return;   // (in this order: no sum can overflow)
         n_chunks = (int)((len + 63) >> 6);
@@ -203,7 +202,7 @@ __global__ __launch_bounds__(256) void apply_init_bf16_kernel(ApplyParams p) {
     }
     if (p.cut.n) {   // (the grid is sized for the longest piece)
         long long len;
-        piece_range(p.cut, seg, p.P, tok0, len, T);
+        piece_range(p.cut, seg, p.P, tok0, len);
         n_chunks = (int)((len + 63) >> 6);
         pad = (int)(64ll * n_chunks - len);
         if (c0 >= n_chunks) return;
@@ -309,8 +308,8 @@ __global__ __launch_bounds__(256) void apply_init_cd_bf16_kernel(ApplyParams p) 
     int n_chunks = p.n_chunks, pad = p.pad;
     const int c0 = tb * (p.tokens_per_wg / 64);                  // this workgroup's first block (= chunk)
     if (p.cut.n) {   // (the grid is sized for the longest piece)
-        long long len, T;
-        piece_range(p.cut, seg, p.P, tok0, len, T);
+        long long len;
+        piece_range(p.cut, seg, p.P, tok0, len);
         n_chunks = (int)((len + 63) >> 6);
         pad = (int)(64ll * n_chunks - len);
         if (c0 >= n_chunks) return;
@@ -414,12 +413,11 @@ __global__ __launch_bounds__(DV * 4) void apply_init_f32_kernel(ApplyParams p) {
     id /= p.H;
     const int b = id % p.B, seg = p.p0 + p.seg_step * (id / p.B);
     long long tok0 = (long long)seg * p.L;                       // the segment's first token
-    long long T = (long long)p.P * p.L;                          // tokens per batch entry
+    const long long T = p.T;                                     // tokens per batch entry
     int n_chunks = p.n_chunks, pad = p.pad;
     const int c0 = tb * (p.tokens_per_wg / 64);                  // this workgroup's first block
     if (p.seg_start) {   // segments of unequal length, as in the bf16 kernel
         tok0 = p.seg_start[seg];
-        T = p.T;
         const long long len = p.seg_start[seg + 1] - tok0;
         if (tok0 < 0 || len < 64 || len > p.L || tok0 > T - len) return;   // (in this order: no sum can overflow)
         n_chunks = (int)((len + 63) >> 6);

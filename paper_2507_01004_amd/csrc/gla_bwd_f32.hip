@@ -92,7 +92,8 @@ __global__ __launch_bounds__(DK * 4, f32_bwd_waves(DK / 16, C)) void gla_bwd_qk_
     const int h = sidx % p.H;
     sidx /= p.H;
     const int b = sidx % p.B, seg = sidx / p.B;
-    long long tok0 = (long long)seg * p.L, T = (long long)p.P * p.L, len = p.L;
+    long long tok0 = (long long)seg * p.L, len = p.L;
+    const long long T = p.T;                 // tokens per batch entry
     if (p.seg_start) {
         // segments of unequal length: this one's bounds from the table; a segment that cannot be taken (under
         // 64 tokens, over the bound L, outside the tensor) is left alone
@@ -102,11 +103,10 @@ __global__ __launch_bounds__(DK * 4, f32_bwd_waves(DK / 16, C)) void gla_bwd_qk_
             bound = p.seg_start[p.plan + 2];
         }
         tok0 = p.seg_start[seg];
-        T = p.T;
         len = p.seg_start[seg + 1] - tok0;
         if (tok0 < 0 || len < 64 || len > bound || tok0 > T - len) return;   // (in this order: no sum can overflow)
     }
-    if (p.cut.n) piece_range(p.cut, seg, p.P, tok0, len, T);
+    if (p.cut.n) piece_range(p.cut, seg, p.P, tok0, len);
     const int N = (int)((len + C - 1) / C);
     const int n_ck = p.plan ? (int)p.seg_start[p.plan + 3] : p.n_ck;
     const long long kbase = b * p.sb + tok0 * p.st + h * p.sh;

@@ -164,7 +164,8 @@ __global__ __launch_bounds__(DK * 4) void gla_bwd_qk_kernel(BwdQKParams p) {
     const int h = sidx % p.H;
     sidx /= p.H;
     const int b = sidx % p.B, seg = sidx / p.B;
-    long long tok0 = (long long)seg * p.L, T = (long long)p.P * p.L;   // first token; tokens per batch entry
+    long long tok0 = (long long)seg * p.L;   // first token
+    const long long T = p.T;                 // tokens per batch entry
     if (p.seg_start) {
         // segments of unequal length: this one's bounds from the table; a segment that cannot be taken (under
         // 64 tokens, over the bound L, outside the tensor) is left alone: the whole workgroup leaves
@@ -174,7 +175,6 @@ __global__ __launch_bounds__(DK * 4) void gla_bwd_qk_kernel(BwdQKParams p) {
             bound = p.seg_start[p.plan + 2];
         }
         tok0 = p.seg_start[seg];
-        T = p.T;
         const long long len = p.seg_start[seg + 1] - tok0;
         if (tok0 < 0 || len < 64 || len > bound || tok0 > T - len) return;   // (in this order: no sum can overflow)
         N = (int)((len + 63) >> 6);
@@ -182,7 +182,7 @@ __global__ __launch_bounds__(DK * 4) void gla_bwd_qk_kernel(BwdQKParams p) {
     }
     if (p.cut.n) {
         long long len;
-        piece_range(p.cut, seg, p.P, tok0, len, T);
+        piece_range(p.cut, seg, p.P, tok0, len);
         N = (int)((len + 63) >> 6);
         pad = (int)(64ll * N - len);
     }

@@ -95,10 +95,9 @@ __device__ __forceinline__ bf16x8 pack8(const f32x16 &a, int base) {
 //   kLocal   the local pass from the zero state: o, S_loc, G_cum, G_tot          (Sec. 3.1)
 //   kStates  only the final local state and total decay of each segment: S_loc, G_tot
 //            (Alg. 1's chunk-state loop; q is not read, nothing per token is written)
-//   kOutput  the output pass from given initial states S_init[p] (none: zero): o, and the end states if
-//            S_loc is given (Alg. 1's output pass, the incoming state folded into the running state)
-//   kOutputEmit  the same over runs in one piece, for a training step: also the states entering the pieces a backward
-//            will work on (S_emit) and the end states a second time (S_loc2)
+//   kOutput  the output pass from given initial states S_init[p]: o only (Alg. 1's output pass, the incoming state folded into the running state)
+//   kOutputRun  the same over runs in one piece: no S_init is the zero state; the end states if S_loc is given and, for
+//            a training step, a second time (S_loc2) with the states entering the pieces of a backward (S_emit)
 //   kLocalCD the local pass with the cumulative decay kept per chunk, as Alg. 1 stores it (the list of
 //            gamma~_[n]): o, S_loc, G_tot and G_chunk[n] = log gamma~_[n-1], the log decay from the segment's
 //            first token up to the start of chunk n; no per-token G_cum is written
@@ -116,7 +115,7 @@ __device__ __forceinline__ bf16x8 pack8(const f32x16 &a, int base) {
 // kDV: q := k, k := q, v := dO, o := dV), flip the sign of the decay exponents, apply gamma before the
 // chunk's products instead of after, and store token t of a chunk at tile row 63 - t, so that the
 // causal structure of the tiles is the one of the forward pass.
-enum ChunkMode { kLocal = 0, kStates = 1, kOutput = 2, kDState = 3, kDV = 4, kLocalInit = 5, kLocalCD = 6, kOutputEmit = 7 };
+enum ChunkMode { kLocal = 0, kStates = 1, kOutput = 2, kDState = 3, kDV = 4, kLocalInit = 5, kLocalCD = 6, kOutputRun = 7 };
 
 // Gate waves per workgroup: 4, one per SIMD beside an MFMA wave; 8 in the local pass with per-channel
 // gates at d_k = 128, which moves the most bytes per chunk and gains 2-3 % from the second set of
@@ -157,7 +156,7 @@ __global__ __launch_bounds__(chunk_threads(DK, DV, GM, MODE)) void gla_chunk_bf1
     constexpr bool GH = GM == kGateHead;
     constexpr bool REV = MODE == kDState || MODE == kDV;          // chunks and tokens in reverse
     constexpr bool NOQ = MODE == kStates || MODE == kDState;      // only the state is computed
-    constexpr bool OUT = MODE == kOutput || MODE == kOutputEmit;
+    constexpr bool OUT = MODE == kOutput || MODE == kOutputRun;
     constexpr bool FROM_INIT = OUT || MODE == kDV || MODE == kLocalInit;   // start from S_init (no state emitted, but see kOutput)
     constexpr bool EMIT_G = MODE == kLocal || MODE == kLocalInit;  // per-token cumulative log decay
     constexpr float SGN = REV ? -1.f : 1.f;                       // sign of the decay exponents
@@ -196,7 +195,8 @@ __global__ __launch_bounds__(chunk_threads(DK, DV, GM, MODE)) void gla_chunk_bf1
     const int h = sidx % p.H;
     sidx /= p.H;
     const int b = sidx % p.B, seg = sidx / p.B;
-    long long tok0 = (long long)seg * p.L, T = (long long)p.P * p.L;   // first token; tokens per batch entry
+    long long tok0 = (long long)seg * p.L;   // first token
+    const long long T = p.T;                 // tokens per batch entry
     if constexpr (MODE != kLocalInit && MODE != kLocalCD) {
         if (p.seg_start) {
             // segments of unequal length: this one's bounds from the table.  A segment the kernel cannot take
@@ -207,7 +207,6 @@ __global__ __launch_bounds__(chunk_threads(DK, DV, GM, MODE)) void gla_chunk_bf1
                 bound = p.seg_start[p.plan + 2];
             }
             tok0 = p.seg_start[seg];
-            T = p.T;
             const long long len = p.seg_start[seg + 1] - tok0;
             if (tok0 < 0 || len < 64 || len > bound || tok0 > T - len) return;   // (in this order: no sum can overflow)
             N = (int)((len + 63) >> 6);
@@ -216,7 +215,7 @@ __global__ __launch_bounds__(chunk_threads(DK, DV, GM, MODE)) void gla_chunk_bf1
     }
     if (p.cut.n) {
         long long len;
-        piece_range(p.cut, seg, p.P, tok0, len, T);
+        piece_range(p.cut, seg, p.P, tok0, len);
         N = (int)((len + 63) >> 6);
         pad = (int)(64ll * N - len);
     }
@@ -550,7 +549,7 @@ __global__ __launch_bounds__(chunk_threads(DK, DV, GM, MODE)) void gla_chunk_bf1
         for (int it = 0; it < Cfg::NIT; ++it)
 #pragma unroll
             for (int rr = 0; rr < 16; ++rr) Sacc[it][rr] = 0.f;
-        if (FROM_INIT && (!OUT || p.S_init)) {   // (output pass: no S_init = the zero state)
+        if (FROM_INIT && (MODE != kOutputRun || p.S_init)) {
 #pragma unroll
             for (int it = 0; it < Cfg::NIT; ++it)
 #pragma unroll
@@ -659,13 +658,13 @@ __global__ __launch_bounds__(chunk_threads(DK, DV, GM, MODE)) void gla_chunk_bf1
                 for (int rr = 0; rr < 16; ++rr)
                     S[(size_t)(it * 32 + M::row(rr, kg)) * (DV * NS)] = Sacc[it][rr];
         };
-        int emit_at = 0, emit_j = 0;   // kOutputEmit: chunk and index of the next piece
-        float *emit_to = MODE == kOutputEmit ? p.S_emit + sbh * DK * (DV * NS) + slice * DV + w * 32 + lt : nullptr;
+        int emit_at = 0, emit_j = 0;   // kOutputRun: chunk and index of the next piece
+        float *emit_to = MODE == kOutputRun ? p.S_emit + sbh * DK * (DV * NS) + slice * DV + w * 32 + lt : nullptr;
         __syncthreads();
         __syncthreads();
         for (int n = 0; n < N; ++n) {
             const unsigned char *cur = lds + (n & 1) * Cfg::kTileBytes;
-            if (MODE == kOutputEmit && n == emit_at) {
+            if (MODE == kOutputRun && p.S_emit && n == emit_at) {
                 store_state(emit_to);
                 emit_to += (size_t)p.B * p.H * DK * (DV * NS);
                 // the first piece has the short chunk on top of its whole ones
@@ -678,8 +677,8 @@ __global__ __launch_bounds__(chunk_threads(DK, DV, GM, MODE)) void gla_chunk_bf1
             __syncthreads();
         }
 
-        if (!FROM_INIT || (OUT && p.S_loc)) store_state(Sl);
-        if constexpr (MODE == kOutputEmit) store_state(p.S_loc2 + sbh * DK * (DV * NS) + slice * DV + w * 32 + lt);
+        if (!FROM_INIT || (MODE == kOutputRun && p.S_loc)) store_state(Sl);
+        if (MODE == kOutputRun && p.S_loc2) store_state(p.S_loc2 + sbh * DK * (DV * NS) + slice * DV + w * 32 + lt);
     }
 }
 
@@ -736,7 +735,7 @@ hipError_t launch_chunk_bf16(const ChunkParams &p, int d_k, int d_v, int gate_mo
     if (mode == kDV) return dispatch_gate<kDV>(p, d_k, d_v, gate_mode, s);
     if (mode == kLocalInit) return dispatch_gate<kLocalInit>(p, d_k, d_v, gate_mode, s);
     if (mode == kLocalCD) return dispatch_gate<kLocalCD>(p, d_k, d_v, gate_mode, s);
-    if (mode == kOutputEmit) return dispatch_gate<kOutputEmit>(p, d_k, d_v, gate_mode, s);
+    if (mode == kOutputRun) return dispatch_gate<kOutputRun>(p, d_k, d_v, gate_mode, s);
     return dispatch_gate<kLocal>(p, d_k, d_v, gate_mode, s);
 }
 

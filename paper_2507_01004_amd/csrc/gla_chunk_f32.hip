@@ -101,7 +101,8 @@ __global__ __launch_bounds__(DV * 4, f32_waves(DV / 16, C)) void gla_chunk_f32_k
     const int h = sidx % p.H;
     sidx /= p.H;
     const int seg = sidx % p.P, b = sidx / p.P;
-    long long tok0 = (long long)seg * p.L, T = (long long)p.P * p.L;   // first token; tokens per batch entry
+    long long tok0 = (long long)seg * p.L;   // first token
+    const long long T = p.T;                 // tokens per batch entry
     int n_chunks = p.n_chunks, pad = p.pad;
     long long len = p.L;
     if (p.seg_start) {
@@ -113,14 +114,13 @@ __global__ __launch_bounds__(DV * 4, f32_waves(DV / 16, C)) void gla_chunk_f32_k
             bound = p.seg_start[p.plan + 2];
         }
         tok0 = p.seg_start[seg];
-        T = p.T;
         len = p.seg_start[seg + 1] - tok0;
         if (tok0 < 0 || len < 64 || len > bound || tok0 > T - len) return;   // (in this order: no sum can overflow)
         n_chunks = (int)((len + C - 1) / C);
         pad = C * n_chunks - (int)len;
     }
     if (p.cut.n) {
-        piece_range(p.cut, seg, p.P, tok0, len, T);
+        piece_range(p.cut, seg, p.P, tok0, len);
         n_chunks = (int)((len + C - 1) / C);
         pad = (int)((long long)C * n_chunks - len);
     }

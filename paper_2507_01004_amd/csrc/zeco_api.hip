@@ -234,7 +234,7 @@ zeco_status zeco_gla_local_fwd(const zeco_gla_desc *d, const void *q, const void
     zeco::ChunkParams p;
     p.q = q; p.k = k; p.v = v; p.g = g; p.o = o;
     p.S_loc = S_loc; p.G_cum = G_cum; p.G_tot = G_tot; p.S_init = nullptr;
-    p.B = d->B; p.P = d->P; p.H = d->H;
+    p.B = d->B; p.P = d->P; p.H = d->H; p.T = (long long)d->P * d->L;
     set_length(p, d->L);
     p.scale = d->scale; p.kscale = 1.f;
     p.sb = d->stride_b; p.st = d->stride_t; p.sh = d->stride_h;
@@ -295,7 +295,7 @@ zeco_status zeco_gla_local_fwd(const zeco_gla_desc *d, const void *q, const void
 static void fill_chunk_params(zeco::ChunkParams &p, const zeco_gla_desc *d) {
     p.q = p.k = p.v = p.g = nullptr; p.o = nullptr;
     p.S_loc = p.G_cum = p.G_tot = nullptr; p.S_init = nullptr;
-    p.B = d->B; p.P = d->P; p.H = d->H;
+    p.B = d->B; p.P = d->P; p.H = d->H; p.T = (long long)d->P * d->L;
     set_length(p, d->L);
     p.scale = d->scale; p.kscale = 1.f;
     p.sb = d->stride_b; p.st = d->stride_t; p.sh = d->stride_h;
@@ -319,7 +319,7 @@ static void set_apply_share(zeco::ApplyParams &p, int L, int cap, bool divide) {
 
 // Correction over P segments of L tokens each (the caller's, or the pieces of a fused call).
 static void fill_apply_params(zeco::ApplyParams &p, const zeco_gla_desc *d, int P, int L) {
-    p.B = d->B; p.P = P; p.H = d->H; p.L = L;
+    p.B = d->B; p.P = P; p.H = d->H; p.L = L; p.T = (long long)d->P * d->L;
     p.p0 = 0; p.gate_per_head = d->g_per_head; p.dense = 0;
     p.n_chunks = chunks_of(L); p.pad = 64 * p.n_chunks - L;
     set_apply_share(p, L, 1024, p.pad == 0);
@@ -570,7 +570,7 @@ zeco_status zeco_gla_fused_fwd(const zeco_gla_desc *d, const void *q, const void
             p.emit = bwd_cut(d);
             p.S_emit = S_save; p.S_loc2 = S_save + (size_t)p.emit.n * d->B * d->H * d->d_k * d->d_v;
         }
-        return from_hip(launch_phase(p, d, S_save ? 7 : 2, s));
+        return from_hip(launch_phase(p, d, d->io_dtype == ZECO_F32 ? 2 : 7, s));
     }
     const bool correct = schedule == ZECO_SCHEDULE_CORRECT || (schedule == ZECO_SCHEDULE_AUTO && corrects(d, cut.base));
 
@@ -622,6 +622,7 @@ zeco_status zeco_gla_fused_fwd(const zeco_gla_desc *d, const void *q, const void
 static void fill_bwd_params(zeco::BwdQKParams &b, const zeco_gla_desc *d, int P, int L, const void *g,
                             float *dg, const float *S_init, const float *S_last, const zeco::Cut *cut) {
     if (cut) b.cut = *cut;
+    b.T = (long long)d->P * d->L;
     b.g = g; b.B = d->B; b.P = P; b.H = d->H; b.L = L; b.n_chunks = chunks_of(L); b.pad = 64 * b.n_chunks - L;
     b.sb = d->stride_b; b.st = d->stride_t; b.sh = d->stride_h;
     b.vb = d->vstride_b; b.vt = d->vstride_t; b.vh = d->vstride_h;
@@ -643,7 +644,7 @@ static zeco_status bwd_dq_pass(const zeco_gla_desc *d, int P, int L, const void 
     zeco::BwdQKParams b;
     fill_bwd_params(b, d, P, L, g, dg, S_init, S_last, cut);
     if (S_ck && bwd_checkpoints(L) > 0) { b.S_ck = S_ck; b.n_ck = bwd_checkpoints(L); b.short_last = 1; }
-    b.seg_start = reinterpret_cast<const long long *>(seg_start); b.T = T; b.plan = plan;
+    if (seg_start) { b.seg_start = reinterpret_cast<const long long *>(seg_start); b.T = T; b.plan = plan; }
     b.x = dO; b.y = v; b.z = k; b.z2 = q; b.out = dq; b.W_init = S_init; b.zscale = 1.f; b.oscale = d->scale;
     if (d->io_dtype == ZECO_F32) {
         // the fp32 kernels: dQ, and the segments' state gradients from dS = 0 as a pass of their own
@@ -653,7 +654,7 @@ static zeco_status bwd_dq_pass(const zeco_gla_desc *d, int P, int L, const void 
         fill_chunk_params(c, d);
         c.P = P; set_length_c(c, L, d->C);
         if (cut) set_cut(c, *cut);
-        c.seg_start = reinterpret_cast<const long long *>(seg_start); c.T = T; c.plan = plan;
+        if (seg_start) { c.seg_start = reinterpret_cast<const long long *>(seg_start); c.T = T; c.plan = plan; }
         c.k = q; c.v = dO; c.g = g; c.S_loc = dS_loc; c.G_tot = G_tot_out; c.scale = 1.f; c.kscale = d->scale;
         return from_hip(zeco::launch_chunk_f32(c, d->d_k, d->d_v, d->C, 3, s));
     }
@@ -673,13 +674,13 @@ static zeco_status bwd_dv_dk_passes(const zeco_gla_desc *d, int P, int L, const 
     fill_chunk_params(c, d);
     c.P = P; set_length(c, L);
     if (cut) set_cut(c, *cut);
-    c.seg_start = reinterpret_cast<const long long *>(seg_start); c.T = T; c.plan = plan;
+    if (seg_start) { c.seg_start = reinterpret_cast<const long long *>(seg_start); c.T = T; c.plan = plan; }
     c.q = k; c.k = q; c.v = dO; c.g = g; c.o = dv; c.S_init = dS_in; c.scale = 1.f; c.kscale = d->scale;
     if (launch_phase(c, d, 4, s) != hipSuccess) return ZECO_ERR_HIP;
 
     zeco::BwdQKParams b;
     fill_bwd_params(b, d, P, L, g, dg, S_init, S_last, cut);
-    b.seg_start = reinterpret_cast<const long long *>(seg_start); b.T = T; b.plan = plan;
+    if (seg_start) { b.seg_start = reinterpret_cast<const long long *>(seg_start); b.T = T; b.plan = plan; }
     b.x = v; b.y = dO; b.z = q; b.z2 = k; b.out = dk; b.W_init = dS_in; b.zscale = d->scale; b.oscale = 1.f;
     if (S_ck && bwd_checkpoints(L) > 0) { b.S_ck = S_ck; b.n_ck = bwd_checkpoints(L); }
     if (d->io_dtype == ZECO_F32) return from_hip(zeco::launch_bwd_qk_f32(b, d->d_k, d->d_v, d->C, true, s));

@@ -18,13 +18,12 @@ typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
 constexpr int kChunk = 64;  // chunk length C; equals the wavefront width
 
-// First token and length of piece s of a cut; `T` receives the tokens per batch entry (P pieces in all).
-__device__ __forceinline__ void piece_range(const Cut &c, int s, int P, long long &tok0, long long &len, long long &T) {
+// First token and length of piece s of a cut (P pieces in all).
+__device__ __forceinline__ void piece_range(const Cut &c, int s, int P, long long &tok0, long long &len) {
     const int run = c.n == P ? 0 : s / c.n, j = s - run * c.n;
     const int extra = j - (c.n - c.rem);   // pieces of base + 1 chunks before this one, if any
     tok0 = run * c.len + 64ll * ((long long)j * c.base + max(extra, 0)) + (j ? c.len & 63 : 0);
     len = 64ll * (c.base + (extra >= 0 ? 1 : 0)) + (j ? 0 : c.len & 63);
-    T = c.n == P ? c.len : (P / c.n) * c.len;
 }
 
 // Two floats -> packed bf16 pair (round to nearest even), low half = a.

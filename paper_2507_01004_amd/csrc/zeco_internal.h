@@ -50,7 +50,7 @@ struct ChunkParams {
     // [seg_start[p], seg_start[p+1]) of the T tokens of every batch entry; L is then the upper bound of the
     // lengths, n_chunks and pad are unused.
     const long long *seg_start = nullptr;
-    long long T = 0;
+    long long T = 0;           // tokens per batch entry, in every launch
     long long sb, st, sh;      // q/k/g element strides
     long long vb, vt, vh;      // v/o element strides
     const void *q, *k, *v, *g;
@@ -60,7 +60,7 @@ struct ChunkParams {
     const float *G_off = nullptr;   // [P,B,H,d_k] ([P,B,H] per-head) log decay preceding each segment (mode 5 only; fp32
                                     // kernel: total log decay of each piece)
     float *G_chunk = nullptr;       // [B,P,n_chunks,H,d_k] log decay from the segment start to each chunk's start (mode 6 only)
-    // Output pass over a run in one piece for a training step (mode 7): the states entering the pieces of `emit` (a cut of the same run),
+    // Output pass over a run in one piece (mode 7), for a training step: the states entering the pieces of `emit` (a cut of the same run),
     // S_emit [emit.n, B, H, d_k, d_v], for a backward on those pieces; and the end state a second time, S_loc2
     float *S_emit = nullptr, *S_loc2 = nullptr;
     Cut emit;
@@ -158,8 +158,8 @@ hipError_t launch_chunk_f32(const ChunkParams &p, int d_k, int d_v, int C, int m
 // 3 backward state pass (k := q, v := dO; S_loc := dS leaving the segment), 4 dV pass (q := k, k := q,
 // v := dO, S_init := dS entering the segment's final state, o := dV), 5 output pass from S_init that also
 // writes G_cum counted from G_off (o, G_cum), 6 local pass with the cumulative decay
-// per chunk instead of per token (o, S_loc, G_chunk, G_tot; per-channel gates only), 7 mode 2 that also leaves the
-// states of a backward's pieces (S_emit, S_loc2)
+// per chunk instead of per token (o, S_loc, G_chunk, G_tot; per-channel gates only), 7 mode 2 over whole runs:
+// S_init may be null (zero), also the end states (S_loc) and, for a backward, S_emit and S_loc2, each if given
 hipError_t launch_chunk_bf16(const ChunkParams &p, int d_k, int d_v, int gate_mode, int mode, hipStream_t s);
 hipError_t launch_apply_f32(const ApplyParams &p, int d_k, int d_v, hipStream_t s);
 hipError_t launch_apply_bf16(const ApplyParams &p, int d_k, int d_v, hipStream_t s);
