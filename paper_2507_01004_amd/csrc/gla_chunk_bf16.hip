@@ -279,10 +279,12 @@ __global__ __launch_bounds__(chunk_threads(DK, DV, GM, MODE)) void gla_chunk_bf1
         f32x4 seg_hi = {0.f, 0.f, 0.f, 0.f}, seg_lo = {0.f, 0.f, 0.f, 0.f};
         if constexpr (MODE == kLocalInit) {
             if constexpr (GH) {
-                const float x = p.G_off[sbh];   // one log decay per head
+                const float x = p.G_off[sbh], y = p.G_off_lo[sbh];   // one log decay per head
                 seg_hi = f32x4{x, x, x, x};
+                seg_lo = f32x4{y, y, y, y};
             } else {
                 seg_hi = *reinterpret_cast<const f32x4 *>(p.G_off + sbh * DK + 4 * cq);
+                seg_lo = *reinterpret_cast<const f32x4 *>(p.G_off_lo + sbh * DK + 4 * cq);
             }
         }
         f32x4 cs[TPT];                          // in-thread inclusive cumsum of g (part 1 -> part 2)
@@ -477,6 +479,16 @@ __global__ __launch_bounds__(chunk_threads(DK, DV, GM, MODE)) void gla_chunk_bf1
                     if (cq == 0) p.G_tot[sbh] = gt[0];
                 } else {
                     *reinterpret_cast<f32x4 *>(p.G_tot + sbh * DK + 4 * cq) = gt;
+                }
+                if (MODE == kStates && p.G_tot_lo) {
+                    f32x4 lo;
+#pragma unroll
+                    for (int a = 0; a < 4; ++a) lo[a] = (seg_hi[a] - gt[a]) + seg_lo[a];
+                    if constexpr (GH) {
+                        if (cq == 0) p.G_tot_lo[sbh] = lo[0];
+                    } else {
+                        *reinterpret_cast<f32x4 *>(p.G_tot_lo + sbh * DK + 4 * cq) = lo;
+                    }
                 }
             }
         };

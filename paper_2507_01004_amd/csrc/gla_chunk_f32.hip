@@ -19,7 +19,7 @@
 // (o, S_loc, G_cum, G_tot); kF32States only the final state and total decay of each segment (S_loc,
 // G_tot; q is not read); kF32Output the output pass from given initial states S_init (none: zero; o, and the end
 // states if S_loc is given); kF32LocalInit the output pass over the pieces of cut segments, from given initial states,
-// that also emits G_cum counted from each segment's first token (G_off holds the pieces' totals).
+// that also emits G_cum counted from each segment's first token (G_off: the log decay preceding each piece).
 //
 // Two more modes run the same equations over the REVERSED sequence for the backward pass (App. A.4):
 //   kF32DState  dS <- (gamma^T 1) .* dS + (Q .* Lambda)^T dO from zero; S_loc receives the gradient the
@@ -152,14 +152,11 @@ __global__ __launch_bounds__(DV * 4, f32_waves(DV / 16, C)) void gla_chunk_f32_k
     auto at = [&](long long x) { return REV ? len - 1 - x : x; };
     auto start_of = [&](int n) { return n ? (long long)n * C - pad : 0ll; };
     double seg_prefix[4] = {0., 0., 0., 0.};     // log decay accumulated over previous chunks
-    if constexpr (MODE == kF32LocalInit) {       // .. and over the run's earlier pieces, from their totals
-        const float *G = p.G_off + (((size_t)(seg - seg % p.cut.n) * p.B + b) * p.H + h) * DK + 4 * cq;
-#pragma unroll 4
-        for (int j = 0; j < seg % p.cut.n; ++j) {
-            const f32x4 x = *reinterpret_cast<const f32x4 *>(G + (size_t)j * p.B * p.H * DK);
+    if constexpr (MODE == kF32LocalInit) {       // .. and over the segment's earlier pieces
+        const f32x4 hi = *reinterpret_cast<const f32x4 *>(p.G_off + sbh * DK + 4 * cq);
+        const f32x4 lo = *reinterpret_cast<const f32x4 *>(p.G_off_lo + sbh * DK + 4 * cq);
 #pragma unroll
-            for (int a = 0; a < 4; ++a) seg_prefix[a] += (double)x[a];
-        }
+        for (int a = 0; a < 4; ++a) seg_prefix[a] = (double)hi[a] + (double)lo[a];
     }
 
     // The raw rows of the chunk worked on next: fetched a whole chunk ahead, 16 bytes a load and all of a chunk's loads
@@ -360,9 +357,16 @@ __global__ __launch_bounds__(DV * 4, f32_waves(DV / 16, C)) void gla_chunk_f32_k
         for (int it = 0; it < DK / 16; ++it)
 #pragma unroll
             for (int r = 0; r < 4; ++r) Sl[(16 * it + 4 * kg + r) * DV + 16 * w + l16] = Sacc[it][r];
-        if (!FROM_INIT && tg == 0 && (!REV || p.G_tot))
-            *reinterpret_cast<f32x4 *>(p.G_tot + sbh * DK + 4 * cq) =
-                f32x4{(float)seg_prefix[0], (float)seg_prefix[1], (float)seg_prefix[2], (float)seg_prefix[3]};
+        if (!FROM_INIT && tg == 0 && (!REV || p.G_tot)) {
+            const f32x4 hi = {(float)seg_prefix[0], (float)seg_prefix[1], (float)seg_prefix[2], (float)seg_prefix[3]};
+            *reinterpret_cast<f32x4 *>(p.G_tot + sbh * DK + 4 * cq) = hi;
+            if (MODE == kF32States && p.G_tot_lo) {
+                f32x4 lo;
+#pragma unroll
+                for (int a = 0; a < 4; ++a) lo[a] = (float)(seg_prefix[a] - (double)hi[a]);
+                *reinterpret_cast<f32x4 *>(p.G_tot_lo + sbh * DK + 4 * cq) = lo;
+            }
+        }
     }
 }
 

@@ -41,11 +41,11 @@ template <int V> __device__ __forceinline__ void scan_store(float *ptr, const Sc
 // thread are in flight at every moment, not only at the start of a batch: with BH * d_k * d_v / V threads
 // and a DRAM latency of 1-2 us that product is what decides how much of the HBM rate the kernel sees.
 // The steady-state loop is free of branches (a branch makes the compiler wait for all outstanding loads at
-// the join): STORE (S_init is written), BYP (the by-products G_pre / G_sum are wanted) and PD (the chain's length is
+// the join): STORE (S_init is written), BYP (1: the by-products G_pre / G_sum are wanted, 2: with their low parts) and PD (the chain's length is
 // on the device) are template flags, and the rounds whose refills would run past the chain's end are peeled off into a guarded tail.
 // Loads, the gate loads and the stores all count against the 63 memory operations a wave can have
 // outstanding, so D beyond 20 buys nothing.
-template <int V, int D, bool STORE, bool BYP, bool PD>
+template <int V, int D, bool STORE, int BYP, bool PD>
 __global__ __launch_bounds__(256) void state_scan_kernel(ScanParams p, int parts) {
     typedef ScanVec<V> vec_t;
     const int blocks_per_head = p.d_k / p.rows_per_block;
@@ -78,6 +78,8 @@ __global__ __launch_bounds__(256) void state_scan_kernel(ScanParams p, int parts
     const bool prefix = BYP && e % dvv == 0 && (!p.gate_per_head || row == 0);
     const size_t gcol = (size_t)bh * gdim + (p.gate_per_head ? 0 : row);
     float *gpre = (prefix && p.G_pre) ? p.G_pre + grp * P * g_stride + gcol : nullptr;
+    const float *lo = BYP == 2 ? p.G_tot_lo + grp * P * g_stride + gcol : nullptr;
+    float *gpre_lo = BYP == 2 && prefix ? p.G_pre_lo + grp * P * g_stride + gcol : nullptr;
     double gsum = 0.;   // (only BYP adds to it; sums of log decays reach the thousands)
 
     // running pointers: of the next step to fetch, of the next step to consume (chain order, either direction)
@@ -87,10 +89,14 @@ __global__ __launch_bounds__(256) void state_scan_kernel(ScanParams p, int parts
     float *sp = STORE ? init + first * (long long)seg_stride : nullptr;
     float *gp = gpre ? gpre + first * (long long)g_stride : nullptr;
     vec_t x[D];
-    float a[D];
+    float a[D], al[BYP == 2 ? D : 1];   // (forward chains: `lo` and `gpre_lo` start at the first segment)
     auto fetch = [&](int u) {
         x[u] = scan_load<V>(lf);
         a[u] = *gf;
+        if constexpr (BYP == 2) {
+            al[u] = *lo;
+            lo += gstep;
+        }
         lf += sstep;
         gf += gstep;
     };
@@ -103,6 +109,13 @@ __global__ __launch_bounds__(256) void state_scan_kernel(ScanParams p, int parts
             if (gp) {
                 *gp = (float)gsum;
                 gp += gstep;
+            }
+            if constexpr (BYP == 2) {
+                if (gpre_lo) {
+                    *gpre_lo = (float)(gsum - (double)(float)gsum);
+                    gpre_lo += gstep;
+                }
+                gsum += (double)al[u];
             }
             gsum += (double)a[u];
         }
@@ -156,12 +169,13 @@ template <int V, int D> static hipError_t launch_scan_vd(const ScanParams &p, hi
     const dim3 grid((unsigned)blocks, p.groups), block(threads);
     const bool byp = p.G_pre || p.G_sum;
     if (p.S_init) {
-        if (byp) hipLaunchKernelGGL((state_scan_kernel<V, D, true, true, false>), grid, block, 0, s, p, parts);
-        else if (p.P_used) hipLaunchKernelGGL((state_scan_kernel<V, D, true, false, true>), grid, block, 0, s, p, parts);
-        else hipLaunchKernelGGL((state_scan_kernel<V, D, true, false, false>), grid, block, 0, s, p, parts);
+        if (p.G_tot_lo) hipLaunchKernelGGL((state_scan_kernel<V, D, true, 2, false>), grid, block, 0, s, p, parts);
+        else if (byp) hipLaunchKernelGGL((state_scan_kernel<V, D, true, 1, false>), grid, block, 0, s, p, parts);
+        else if (p.P_used) hipLaunchKernelGGL((state_scan_kernel<V, D, true, 0, true>), grid, block, 0, s, p, parts);
+        else hipLaunchKernelGGL((state_scan_kernel<V, D, true, 0, false>), grid, block, 0, s, p, parts);
     } else {
-        if (byp) hipLaunchKernelGGL((state_scan_kernel<V, D, false, true, false>), grid, block, 0, s, p, parts);
-        else hipLaunchKernelGGL((state_scan_kernel<V, D, false, false, false>), grid, block, 0, s, p, parts);
+        if (byp) hipLaunchKernelGGL((state_scan_kernel<V, D, false, 1, false>), grid, block, 0, s, p, parts);
+        else hipLaunchKernelGGL((state_scan_kernel<V, D, false, 0, false>), grid, block, 0, s, p, parts);
     }
     return hipGetLastError();
 }

@@ -195,3 +195,29 @@ def test_local_pass_of_few_streams_at_odd_lengths(case):
         whole = zeco.gla_local_fwd(q, k, v, g, P, scale=0.5, workspace=torch.empty(16, dtype=torch.uint8, device="cuda"))
         torch.cuda.synchronize()
         assert rel_err_bh(host(whole[0]), o_l, (0, 2)) <= tol and log_err(host(whole[2]), Gc_l) <= 1e-5
+
+
+@pytest.mark.parametrize("case", [(1, 2, 1, 20011, 64, 64, "bf16", "f32"), (1, 3, 2, 4097, 128, 128, "bf16", "bf16"), (1, 5, 1, 8191, 64, 128, "bf16", "head"),
+                                  (1, 2, 1, 20011, 64, 64, "f32", "f32"), (2, 1, 2, 4096, 128, 64, "f32", "f32")], ids=lambda c: "B%d_H%d_P%d_L%d_%dx%d_%s_%s" % c)
+def test_log_decays_of_a_cut_segment_are_those_of_one_chain(case):
+    """A segment's cumulative log decay keeps the bits fp32 cannot hold from chunk to chunk, so that every G_cum is one sum
+    rounded to fp32; cut into sub-segments it is the same sum.  The cut ends where the whole segment's chunks end, so the
+    two differ only where the extended sums fall on different sides of a rounding boundary, and by one unit: in fp32
+    calls the extended sums hold 48 bits (about one value in 2^20; allowed one in 1000).  In bf16 calls a chunk's total,
+    below 8, joins the pair rounded to its own last place, by up to 2^-22: a random sum of 2^-23 sqrt(N) after N chunks,
+    where fp32 values are 2^-17 apart at sums of a hundred (16 chunks, 1 : 16) and 2^-13 at sums of two thousand (313
+    chunks, 1 : 60): allowed one value in 60.  A prefix rounded to fp32 moves by a quarter of a unit on average."""
+    B, H, P, L, dk, dv, io, gate = case
+    print("case", case, flush=True)
+    inp = synth.make_inputs(B, P * L, H, dk, dv, seed=L, io=io, g="f32" if gate == "head" else gate, device="cuda", gate_div=8.0,
+                            per_head_gate=gate == "head")
+    q, k, v, g = (inp[n] for n in "qkvg")
+    assert zeco.local_fwd_workspace_bytes(q, v, g, P) > 0          # the call cuts
+    cut = zeco.gla_local_fwd(q, k, v, g, P)
+    whole = zeco.gla_local_fwd(q, k, v, g, P, workspace=torch.empty(16, dtype=torch.uint8, device="cuda"))
+    torch.cuda.synchronize()
+    for nm, a, b in (("G_cum", cut[2], whole[2]), ("G_tot", cut[3], whole[3])):
+        other = (a != b).double().mean().item()
+        print(nm, "differ", other, flush=True)
+        assert other <= max(1e-3 if io == "f32" else 1 / 60, 1.0 / a.numel()), nm
+        assert ((a - b).abs() <= b.abs() * 2.0 ** -22).all(), nm
