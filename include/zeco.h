@@ -296,8 +296,9 @@ zeco_status zeco_gla_fwd_from_state(const zeco_gla_desc *desc, const void *q, co
  *                              e-folding length is far below the piece length k, v, g are read once
  *                              instead of twice; with decays near 1 it moves about 10 % more than
  *                              two-phase (measured 15 - 20 % more time: ask for TWO_PHASE with such data).
- *     ZECO_SCHEDULE_AUTO       CORRECT when it is available and the pieces are at least 4096 tokens long,
- *                              else TWO_PHASE.
+ *     ZECO_SCHEDULE_AUTO       CORRECT when it is available and both the library's pieces and the segments as
+ *                              given (halved while that fills the compute units) are several of at least
+ *                              4096 tokens each, else TWO_PHASE.
  * workspace: zeco_gla_fused_fwd_workspace(desc) bytes of device memory, 16-byte aligned (enough for
  * either schedule). */
 enum { ZECO_SCHEDULE_AUTO = 0, ZECO_SCHEDULE_TWO_PHASE = 1, ZECO_SCHEDULE_CORRECT = 2 };

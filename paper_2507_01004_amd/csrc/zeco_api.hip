@@ -417,8 +417,20 @@ static double cost_backward(const CostModel &m, double BH, double n, double long
     return m.fixedb + cost_chain(m, n * BH, longest, m.chunkb, m.bytesb) + 7. * n * BH * m.state / m.rate + 2. * m.step * n;
 }
 
-// Does ZECO_SCHEDULE_AUTO take the correction for pieces of this many whole chunks (4096 tokens)?
-static bool corrects(const zeco_gla_desc *d, long long chunks) { return d->io_dtype == ZECO_BF16 && chunks >= 64; }
+// Does ZECO_SCHEDULE_AUTO take the correction?  It rounds o twice and its time depends on the decays (with decays near 1
+// it is 15 - 20 % slower than two phases), so the cut must not bring calls to it: the caller's segments, halved while they
+// halve evenly, stay within a round of workgroups and keep 256 tokens, have to be of 4096 tokens or more, and more than
+// one (8 heads, 64 segments x 2048 tokens with decays near 1: two phases 0.47 ms, corrected in 32 pieces 0.51 ms) ..
+static bool may_correct(const zeco_gla_desc *d) {
+    if (d->io_dtype != ZECO_BF16) return false;
+    const long long streams = (long long)d->B * d->P * d->H;
+    int S = 1;
+    auto halves_evenly = [&](int n) { return d->L % 64 == 0 ? d->L % (2 * n * 64) == 0 : d->L % (2 * n) == 0; };
+    while (streams * S * 2 <= kComputeUnits && halves_evenly(S) && d->L / (2 * S) >= 256) S *= 2;
+    return (long long)d->P * S > 1 && d->L / S >= 4096;
+}
+// .. and so the pieces of the cut (this many whole chunks).
+static bool corrects(bool may, long long chunks) { return may && chunks >= 64; }
 
 // Pieces per (batch, head).  Forward and backward share them, because the states the forward saves for the backward
 // are the ones entering the pieces; the estimate weighs a backward a tenth (not every forward has one, and the optimum is flat).  One
@@ -430,6 +442,7 @@ static long long pieces_for(const zeco_gla_desc *d, long long T, bool backward, 
     // a chain stays short enough for the workgroups of a launch to even out over several rounds
     const long long least = (chunks + kLongestPiece - 1) / kLongestPiece;
     const CostModel m = cost_model(d);
+    const bool may = may_correct(d);
     long long best = 0;
     double cost = 0., cost_f = 0.;
     long long seen = 0;
@@ -439,7 +452,7 @@ static long long pieces_for(const zeco_gla_desc *d, long long T, bool backward, 
         seen = n;
         const bool even = T % (64 * n) == 0;
         const double longest = (double)(chunks / n + (even ? 0 : 1));
-        const double f = cost_forward(m, (double)BH, (double)n, longest, corrects(d, chunks / n)), b = cost_backward(m, (double)BH, (double)n, longest);
+        const double f = cost_forward(m, (double)BH, (double)n, longest, corrects(may, chunks / n)), b = cost_backward(m, (double)BH, (double)n, longest);
         // (equal pieces stay in step: 15 heads, 32768 tokens, 16 / 17 pieces 153 / 161 us)
         const double c = (backward ? b : f + 0.1 * b) * (even ? 0.92 : 1.);
         if (best == 0 || c < cost) { cost = c; cost_f = f; best = n; }
@@ -448,7 +461,7 @@ static long long pieces_for(const zeco_gla_desc *d, long long T, bool backward, 
     for (int k : {1, 2, 3, 4, 6, 8, 12, 16}) consider(k * (long long)m.slots / (4 * BH));
     for (long long n = d->P; n <= chunks && n * BH <= 4 * (long long)m.slots; n *= 2) consider(n);
     for (int k = 2; k <= 4; ++k) consider((chunks + k - 1) / k);
-    consider(chunks / 64);   // just enough for the correction
+    if (may) consider(chunks / 64);   // just enough for the correction
     consider(least);
     if (least <= 1 && may_be_one) {
         const double one = backward ? cost_backward(m, (double)BH, 1., (double)chunks) : cost_forward(m, (double)BH, 1., (double)chunks, false);
@@ -576,7 +589,7 @@ zeco_status zeco_gla_fused_fwd(const zeco_gla_desc *d, const void *q, const void
         }
         return from_hip(launch_phase(p, d, d->io_dtype == ZECO_F32 ? 2 : 7, s));
     }
-    const bool correct = schedule == ZECO_SCHEDULE_CORRECT || (schedule == ZECO_SCHEDULE_AUTO && corrects(d, cut.base));
+    const bool correct = schedule == ZECO_SCHEDULE_CORRECT || (schedule == ZECO_SCHEDULE_AUTO && corrects(may_correct(d), cut.base));
 
     // first pass: the pieces from the zero state - with their local outputs and the cumulative decay per chunk
     // (per token with per-head gates, whose G_cum is 4 bytes per token and head), or their end states only

@@ -221,3 +221,17 @@ def test_log_decays_of_a_cut_segment_are_those_of_one_chain(case):
         print(nm, "differ", other, flush=True)
         assert other <= max(1e-3 if io == "f32" else 1 / 60, 1.0 / a.numel()), nm
         assert ((a - b).abs() <= b.abs() * 2.0 ** -22).all(), nm
+
+
+@pytest.mark.parametrize("B,H,P,L", [(1, 8, 64, 2048), (1, 16, 64, 1000), (1, 1, 1, 70001), (2, 8, 1, 100001)])
+def test_the_cut_brings_no_call_to_the_correction(B, H, P, L):
+    """AUTO corrects only where the caller's own segments are long: short segments, and a single run whose odd length does
+    not halve, stay with the two phases (o rounded once, a time that does not depend on the decays), however long the
+    pieces of the library's cut are."""
+    print("case", B, H, P, L, flush=True)
+    inp = synth.make_inputs(B, P * L, H, 64, 64, seed=L, io="bf16", g="bf16", device="cuda", gate_div=512.0)
+    q, k, v, g = (inp[n] for n in "qkvg")
+    auto, _ = zeco.gla_fused_fwd(q, k, v, g, P)
+    two, _ = zeco.gla_fused_fwd(q, k, v, g, P, schedule=zeco.SCHEDULE_TWO_PHASE)
+    torch.cuda.synchronize()
+    assert torch.equal(auto, two)
