@@ -81,8 +81,9 @@ typedef struct {
  * then splits every segment into sub-segments and runs Alg. 1's own schedule inside each segment (end
  * states of the sub-segments from the zero state, their scan, the output pass of every sub-segment from
  * its scanned state), and keeps the sub-segment states in the workspace (device memory, 16-byte aligned,
- * caller-owned, contents unspecified afterwards).  With fp32, and with lengths that do not halve evenly, the call
- * also takes a smaller workspace and then runs the segments whole.
+ * caller-owned, contents unspecified afterwards).  The call can do without in fp32, and in bf16 with lengths
+ * that do not halve evenly (no multiple of 128, if one of 64; odd, if not): without a workspace, or with one that is
+ * smaller or not aligned, it then runs the segments whole, one chain a stream.  In the other cases it refuses that.
  * Returns 0 for an invalid descriptor. */
 size_t zeco_gla_local_fwd_workspace(const zeco_gla_desc *desc);
 

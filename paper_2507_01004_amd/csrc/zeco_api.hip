@@ -225,12 +225,12 @@ zeco_status zeco_gla_local_fwd(const zeco_gla_desc *d, const void *q, const void
         return ZECO_ERR_INVALID_ARG;
     const size_t need = zeco_gla_local_fwd_workspace(d);
     int S = subsegments(d);
-    if (workspace_bytes < need) {
+    if (workspace_bytes < need || (need && (!workspace || !aligned16(workspace)))) {
         // fp32, and lengths that do not halve, can do without: one chain a stream
         const bool must = halves_with_correction(d) || (d->io_dtype == ZECO_BF16 && d->L % (d->L % 64 ? 2 : 128) == 0);
-        if (must) return ZECO_ERR_WORKSPACE;
+        if (must) return workspace_bytes < need ? ZECO_ERR_WORKSPACE : ZECO_ERR_INVALID_ARG;
         S = 1;
-    } else if (need && (!workspace || !aligned16(workspace))) return ZECO_ERR_INVALID_ARG;
+    }
     hipStream_t s = static_cast<hipStream_t>(stream);
 
     zeco::ChunkParams p;

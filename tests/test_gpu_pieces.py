@@ -235,3 +235,20 @@ def test_the_cut_brings_no_call_to_the_correction(B, H, P, L):
     two, _ = zeco.gla_fused_fwd(q, k, v, g, P, schedule=zeco.SCHEDULE_TWO_PHASE)
     torch.cuda.synchronize()
     assert torch.equal(auto, two)
+
+
+@pytest.mark.parametrize("io,L", [("f32", 1024), ("f32", 1111), ("bf16", 1111), ("bf16", 576)])
+def test_local_pass_runs_whole_with_a_workspace_it_cannot_use(io, L):
+    """Where the local pass can do without a workspace it takes whatever it is given: nothing, too few bytes, or enough of
+    them at an address it cannot use - and then runs every segment as one chain."""
+    print("case", io, L, flush=True)
+    inp = synth.make_inputs(1, 2 * L, 2, 64, 64, seed=L, io=io, g="f32", device="cuda", gate_div=64.0)
+    q, k, v, g = (inp[n] for n in "qkvg")
+    n = zeco.local_fwd_workspace_bytes(q, v, g, 2)
+    assert n > 0
+    whole = zeco.gla_local_fwd(q, k, v, g, 2, workspace=torch.empty(0, dtype=torch.uint8, device="cuda"))
+    for ws in (torch.empty(n - 1, dtype=torch.uint8, device="cuda"), torch.empty(n + 8, dtype=torch.uint8, device="cuda")[8:]):
+        got = zeco.gla_local_fwd(q, k, v, g, 2, workspace=ws)
+        torch.cuda.synchronize()
+        for a, b in zip(got, whole):
+            assert torch.equal(a, b)
