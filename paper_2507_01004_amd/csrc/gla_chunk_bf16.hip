@@ -279,12 +279,13 @@ __global__ __launch_bounds__(chunk_threads(DK, DV, GM, MODE)) void gla_chunk_bf1
         f32x4 seg_hi = {0.f, 0.f, 0.f, 0.f}, seg_lo = {0.f, 0.f, 0.f, 0.f};
         if constexpr (MODE == kLocalInit) {
             if constexpr (GH) {
-                const float x = p.G_off[sbh], y = p.G_off_lo[sbh];   // one log decay per head
+                const float x = p.G_off[2 * sbh], y = p.G_off[2 * sbh + 1];   // one log decay per head
                 seg_hi = f32x4{x, x, x, x};
                 seg_lo = f32x4{y, y, y, y};
             } else {
-                seg_hi = *reinterpret_cast<const f32x4 *>(p.G_off + sbh * DK + 4 * cq);
-                seg_lo = *reinterpret_cast<const f32x4 *>(p.G_off_lo + sbh * DK + 4 * cq);
+                const f32x4 *G = reinterpret_cast<const f32x4 *>(p.G_off + 2 * (sbh * DK + 4 * cq));
+                seg_hi = f32x4{G[0][0], G[0][2], G[1][0], G[1][2]};
+                seg_lo = f32x4{G[0][1], G[0][3], G[1][1], G[1][3]};
             }
         }
         f32x4 cs[TPT];                          // in-thread inclusive cumsum of g (part 1 -> part 2)
@@ -475,20 +476,21 @@ __global__ __launch_bounds__(chunk_threads(DK, DV, GM, MODE)) void gla_chunk_bf1
                 f32x4 gt;
 #pragma unroll
                 for (int a = 0; a < 4; ++a) gt[a] = seg_hi[a] + seg_lo[a];
-                if constexpr (GH) {
-                    if (cq == 0) p.G_tot[sbh] = gt[0];
-                } else {
-                    *reinterpret_cast<f32x4 *>(p.G_tot + sbh * DK + 4 * cq) = gt;
-                }
-                if (MODE == kStates && p.G_tot_lo) {
+                if (MODE == kStates && p.pairs) {
                     f32x4 lo;
 #pragma unroll
                     for (int a = 0; a < 4; ++a) lo[a] = (seg_hi[a] - gt[a]) + seg_lo[a];
                     if constexpr (GH) {
-                        if (cq == 0) p.G_tot_lo[sbh] = lo[0];
+                        if (cq == 0) p.G_tot[2 * sbh] = gt[0], p.G_tot[2 * sbh + 1] = lo[0];
                     } else {
-                        *reinterpret_cast<f32x4 *>(p.G_tot_lo + sbh * DK + 4 * cq) = lo;
+                        f32x4 *G = reinterpret_cast<f32x4 *>(p.G_tot + 2 * (sbh * DK + 4 * cq));
+                        G[0] = f32x4{gt[0], lo[0], gt[1], lo[1]};
+                        G[1] = f32x4{gt[2], lo[2], gt[3], lo[3]};
                     }
+                } else if constexpr (GH) {
+                    if (cq == 0) p.G_tot[sbh] = gt[0];
+                } else {
+                    *reinterpret_cast<f32x4 *>(p.G_tot + sbh * DK + 4 * cq) = gt;
                 }
             }
         };

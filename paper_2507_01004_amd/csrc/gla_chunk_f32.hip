@@ -153,10 +153,9 @@ __global__ __launch_bounds__(DV * 4, f32_waves(DV / 16, C)) void gla_chunk_f32_k
     auto start_of = [&](int n) { return n ? (long long)n * C - pad : 0ll; };
     double seg_prefix[4] = {0., 0., 0., 0.};     // log decay accumulated over previous chunks
     if constexpr (MODE == kF32LocalInit) {       // .. and over the segment's earlier pieces
-        const f32x4 hi = *reinterpret_cast<const f32x4 *>(p.G_off + sbh * DK + 4 * cq);
-        const f32x4 lo = *reinterpret_cast<const f32x4 *>(p.G_off_lo + sbh * DK + 4 * cq);
+        const f32x4 *G = reinterpret_cast<const f32x4 *>(p.G_off + 2 * (sbh * DK + 4 * cq));
 #pragma unroll
-        for (int a = 0; a < 4; ++a) seg_prefix[a] = (double)hi[a] + (double)lo[a];
+        for (int a = 0; a < 4; ++a) seg_prefix[a] = (double)G[a / 2][2 * (a & 1)] + (double)G[a / 2][2 * (a & 1) + 1];
     }
 
     // The raw rows of the chunk worked on next: fetched a whole chunk ahead, 16 bytes a load and all of a chunk's loads
@@ -359,12 +358,15 @@ __global__ __launch_bounds__(DV * 4, f32_waves(DV / 16, C)) void gla_chunk_f32_k
             for (int r = 0; r < 4; ++r) Sl[(16 * it + 4 * kg + r) * DV + 16 * w + l16] = Sacc[it][r];
         if (!FROM_INIT && tg == 0 && (!REV || p.G_tot)) {
             const f32x4 hi = {(float)seg_prefix[0], (float)seg_prefix[1], (float)seg_prefix[2], (float)seg_prefix[3]};
-            *reinterpret_cast<f32x4 *>(p.G_tot + sbh * DK + 4 * cq) = hi;
-            if (MODE == kF32States && p.G_tot_lo) {
+            if (MODE == kF32States && p.pairs) {
                 f32x4 lo;
 #pragma unroll
                 for (int a = 0; a < 4; ++a) lo[a] = (float)(seg_prefix[a] - (double)hi[a]);
-                *reinterpret_cast<f32x4 *>(p.G_tot_lo + sbh * DK + 4 * cq) = lo;
+                f32x4 *G = reinterpret_cast<f32x4 *>(p.G_tot + 2 * (sbh * DK + 4 * cq));
+                G[0] = f32x4{hi[0], lo[0], hi[1], lo[1]};
+                G[1] = f32x4{hi[2], lo[2], hi[3], lo[3]};
+            } else {
+                *reinterpret_cast<f32x4 *>(p.G_tot + sbh * DK + 4 * cq) = hi;
             }
         }
     }

@@ -41,7 +41,7 @@ template <int V> __device__ __forceinline__ void scan_store(float *ptr, const Sc
 // thread are in flight at every moment, not only at the start of a batch: with BH * d_k * d_v / V threads
 // and a DRAM latency of 1-2 us that product is what decides how much of the HBM rate the kernel sees.
 // The steady-state loop is free of branches (a branch makes the compiler wait for all outstanding loads at
-// the join): STORE (S_init is written), BYP (1: the by-products G_pre / G_sum are wanted, 2: with their low parts) and PD (the chain's length is
+// the join): STORE (S_init is written), BYP (1: the by-products G_pre / G_sum are wanted, 2: with G_tot and G_pre as pairs) and PD (the chain's length is
 // on the device) are template flags, and the rounds whose refills would run past the chain's end are peeled off into a guarded tail.
 // Loads, the gate loads and the stores all count against the 63 memory operations a wave can have
 // outstanding, so D beyond 20 buys nothing.
@@ -66,7 +66,8 @@ __global__ __launch_bounds__(256) void state_scan_kernel(ScanParams p, int parts
     const int row = row0 + e / dvv;
     const size_t off = (size_t)bh * state + (size_t)row * p.d_v + (size_t)(e % dvv) * V;
     const float *loc = p.S_loc + grp * P * seg_stride + off;
-    const float *gt = p.G_tot + grp * P * g_stride + (size_t)bh * gdim + (p.gate_per_head ? 0 : row);
+    constexpr int GW = BYP == 2 ? 2 : 1;                    // floats of a log decay
+    const float *gt = p.G_tot + GW * (grp * P * g_stride + (size_t)bh * gdim + (p.gate_per_head ? 0 : row));
     float *init = STORE ? p.S_init + grp * P * seg_stride + off : nullptr;
     vec_t s;
 #pragma unroll
@@ -77,25 +78,25 @@ __global__ __launch_bounds__(256) void state_scan_kernel(ScanParams p, int parts
     // when the head has one decay)
     const bool prefix = BYP && e % dvv == 0 && (!p.gate_per_head || row == 0);
     const size_t gcol = (size_t)bh * gdim + (p.gate_per_head ? 0 : row);
-    float *gpre = (prefix && p.G_pre) ? p.G_pre + grp * P * g_stride + gcol : nullptr;
-    const float *lo = BYP == 2 ? p.G_tot_lo + grp * P * g_stride + gcol : nullptr;
-    float *gpre_lo = BYP == 2 && prefix ? p.G_pre_lo + grp * P * g_stride + gcol : nullptr;
+    float *gpre = (prefix && p.G_pre) ? p.G_pre + GW * (grp * P * g_stride + gcol) : nullptr;
     double gsum = 0.;   // (only BYP adds to it; sums of log decays reach the thousands)
 
     // running pointers: of the next step to fetch, of the next step to consume (chain order, either direction)
     const long long first = p.reverse ? P - 1 : 0, dir = p.reverse ? -1 : 1;
-    const long long sstep = dir * (long long)seg_stride, gstep = dir * (long long)g_stride;
-    const float *lf = loc + first * (long long)seg_stride, *gf = gt + first * (long long)g_stride;
+    const long long sstep = dir * (long long)seg_stride, gstep = dir * GW * (long long)g_stride;
+    const float *lf = loc + first * (long long)seg_stride, *gf = gt + first * GW * (long long)g_stride;
     float *sp = STORE ? init + first * (long long)seg_stride : nullptr;
-    float *gp = gpre ? gpre + first * (long long)g_stride : nullptr;
+    float *gp = gpre ? gpre + first * GW * (long long)g_stride : nullptr;
     vec_t x[D];
-    float a[D], al[BYP == 2 ? D : 1];   // (forward chains: `lo` and `gpre_lo` start at the first segment)
+    float a[D], lo[BYP == 2 ? D : 1];
     auto fetch = [&](int u) {
         x[u] = scan_load<V>(lf);
-        a[u] = *gf;
         if constexpr (BYP == 2) {
-            al[u] = *lo;
-            lo += gstep;
+            const ScanVec<2> pair = *reinterpret_cast<const ScanVec<2> *>(gf);
+            a[u] = pair.v[0];
+            lo[u] = pair.v[1];
+        } else {
+            a[u] = *gf;
         }
         lf += sstep;
         gf += gstep;
@@ -108,16 +109,11 @@ __global__ __launch_bounds__(256) void state_scan_kernel(ScanParams p, int parts
         if (BYP) {
             if (gp) {
                 *gp = (float)gsum;
+                if constexpr (BYP == 2) gp[1] = (float)(gsum - (double)(float)gsum);
                 gp += gstep;
             }
-            if constexpr (BYP == 2) {
-                if (gpre_lo) {
-                    *gpre_lo = (float)(gsum - (double)(float)gsum);
-                    gpre_lo += gstep;
-                }
-                gsum += (double)al[u];
-            }
             gsum += (double)a[u];
+            if constexpr (BYP == 2) gsum += (double)lo[u];
         }
         const float d = fast_exp(a[u]);
 #pragma unroll
@@ -169,7 +165,7 @@ template <int V, int D> static hipError_t launch_scan_vd(const ScanParams &p, hi
     const dim3 grid((unsigned)blocks, p.groups), block(threads);
     const bool byp = p.G_pre || p.G_sum;
     if (p.S_init) {
-        if (p.G_tot_lo) hipLaunchKernelGGL((state_scan_kernel<V, D, true, 2, false>), grid, block, 0, s, p, parts);
+        if (p.pairs) hipLaunchKernelGGL((state_scan_kernel<V, D, true, 2, false>), grid, block, 0, s, p, parts);
         else if (byp) hipLaunchKernelGGL((state_scan_kernel<V, D, true, 1, false>), grid, block, 0, s, p, parts);
         else if (p.P_used) hipLaunchKernelGGL((state_scan_kernel<V, D, true, 0, true>), grid, block, 0, s, p, parts);
         else hipLaunchKernelGGL((state_scan_kernel<V, D, true, 0, false>), grid, block, 0, s, p, parts);

@@ -187,20 +187,18 @@ static bool halves_with_correction(const zeco_gla_desc *d) {
 
 struct SubLayout {          // workspace carve-up, in floats
     size_t states, gates;   // elements of one state array / one gate array over all sub-segments
-    size_t off_Ssub, off_Sinit, off_Gtot, off_Gpre, off_Glo, off_Gprelo, total;   // (Glo, Gprelo: low parts of Gtot, Gpre)
+    size_t off_Ssub, off_Sinit, off_Gtot, off_Gpre, total;
 };
 static SubLayout sub_layout(const zeco_gla_desc *d, int S) {
     SubLayout w;
     const size_t n = (size_t)d->P * S * d->B * d->H;
     w.states = n * d->d_k * d->d_v;
-    w.gates = n * d->d_k;
+    w.gates = 2 * n * d->d_k;   // (pairs)
     w.off_Ssub = 0;
     w.off_Sinit = w.off_Ssub + w.states;
     w.off_Gtot = w.off_Sinit + w.states;
     w.off_Gpre = w.off_Gtot + w.gates;
-    w.off_Glo = w.off_Gpre + w.gates;
-    w.off_Gprelo = w.off_Glo + w.gates;
-    w.total = w.off_Gprelo + w.gates;
+    w.total = w.off_Gpre + w.gates;
     return w;
 }
 
@@ -275,10 +273,9 @@ zeco_status zeco_gla_local_fwd(const zeco_gla_desc *d, const void *q, const void
     const SubLayout w = sub_layout(d, S);
     float *ws = static_cast<float *>(workspace);
     float *Ssub = ws + w.off_Ssub, *Sinit = ws + w.off_Sinit, *Gtot = ws + w.off_Gtot, *Gpre = ws + w.off_Gpre;
-    float *Glo = ws + w.off_Glo, *Gprelo = ws + w.off_Gprelo;
     set_cut(p, cut_of(d->L, S));
     p.P = d->P * S;
-    p.S_loc = Ssub; p.G_tot = Gtot; p.G_tot_lo = Glo;
+    p.S_loc = Ssub; p.G_tot = Gtot; p.pairs = 1;
     hipError_t e = launch_phase(p, d, 1, s);
     if (e != hipSuccess) return ZECO_ERR_HIP;
 
@@ -287,11 +284,11 @@ zeco_status zeco_gla_local_fwd(const zeco_gla_desc *d, const void *q, const void
     sp.P = S; sp.groups = d->P; sp.BH = d->B * d->H; sp.d_k = d->d_k; sp.d_v = d->d_v;
     sp.rows_per_block = d->d_k / 16; sp.gate_per_head = d->g_per_head;
     sp.G_pre = Gpre; sp.G_sum = G_tot;   // log decay preceding each sub-segment; the segment's total
-    sp.G_tot_lo = Glo; sp.G_pre_lo = Gprelo;
+    sp.pairs = 1;
     if ((e = zeco::launch_scan(sp, s)) != hipSuccess) return ZECO_ERR_HIP;
 
     p.S_loc = nullptr; p.G_tot = nullptr; p.S_init = Sinit;
-    p.G_off = Gpre; p.G_off_lo = Gprelo;
+    p.G_off = Gpre;
     return from_hip(launch_phase(p, d, 5, s));
 }
 

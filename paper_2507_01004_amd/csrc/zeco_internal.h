@@ -37,8 +37,6 @@ struct SegPlan {
     int ck_even, ck_segments;    // checkpoints per piece in the two cases
 };
 
-// (The kernels find their tokens from the fields up to `vh`; together in a few cache lines because a workgroup's first
-// loads from the argument block, which lies in host memory, are on the critical path of a short launch.)
 struct ChunkParams {
     int B, P, H, L;
     int n_chunks;              // ceil(L / 64)
@@ -57,17 +55,16 @@ struct ChunkParams {
     void *o;
     float *S_loc, *G_cum, *G_tot;
     const float *S_init;       // [P,B,H,d_k,d_v] initial states (modes that start from a given state)
-    const float *G_off = nullptr;   // [P,B,H,d_k] ([P,B,H] per-head) log decay preceding each segment (mode 5 only)
+    const float *G_off = nullptr;   // [P,B,H,d_k] ([P,B,H] per-head) log decay preceding each segment, as pairs (mode 5 only)
     float *G_chunk = nullptr;       // [B,P,n_chunks,H,d_k] log decay from the segment start to each chunk's start (mode 6 only)
     // Output pass over a run in one piece (mode 7), for a training step: the states entering the pieces of `emit` (a cut of the same run),
     // S_emit [emit.n, B, H, d_k, d_v], for a backward on those pieces; and the end state a second time, S_loc2
     float *S_emit = nullptr, *S_loc2 = nullptr;
     Cut emit;
+    // 1: G_tot as pairs (mode 1) - every log decay with what fp32 leaves off it beside it, [.., 2], so that sums of log
+    // decays run on across the pieces of a segment as precisely as inside one
+    int pairs = 0;
     float kscale;              // backward modes: multiplier carried by the operand in the k role
-    // What fp32 leaves off G_tot (mode 1, if given) and off G_off (mode 5): sums of log decays run on across the pieces
-    // of a segment as precisely as inside one.
-    float *G_tot_lo = nullptr;
-    const float *G_off_lo = nullptr;
 };
 
 struct ApplyParams {
@@ -104,9 +101,7 @@ struct ScanParams {
     // optional, each on its own: G_pre [groups*P, BH, d_k] = sum of G_tot over the earlier segments of the
     // chain (forward chains only), G_sum [groups, BH, d_k] = sum over all of them ([.., BH] with one decay per head)
     float *G_pre = nullptr, *G_sum = nullptr;
-    // optional, with G_pre: what fp32 leaves off G_tot and off G_pre (added up in 64 bits)
-    const float *G_tot_lo = nullptr;
-    float *G_pre_lo = nullptr;
+    int pairs = 0;               // 1: G_tot and G_pre as pairs (see ChunkParams), added up in 64 bits
     int gate_per_head = 0;       // 1: G_tot [groups*P, BH], one log decay per head
 };
 
