@@ -198,7 +198,7 @@ __global__ __launch_bounds__(chunk_threads(DK, DV, GM, MODE)) void gla_chunk_bf1
     long long tok0 = (long long)seg * p.L;   // first token
     const long long T = p.T;                 // tokens per batch entry
     if constexpr (MODE != kLocalInit && MODE != kLocalCD) {
-        if (p.seg_start) {
+        if (__builtin_expect(p.seg_start != nullptr, 0)) {
             // segments of unequal length: this one's bounds from the table.  A segment the kernel cannot take
             // (under 64 tokens, over the bound L, outside the tensor) is left alone: the whole workgroup leaves.
             long long bound = p.L;
@@ -213,7 +213,7 @@ __global__ __launch_bounds__(chunk_threads(DK, DV, GM, MODE)) void gla_chunk_bf1
             pad = 64 * N - (int)len;
         }
     }
-    if (p.cut.n) {
+    if (__builtin_expect(p.cut.n != 0, 0)) {
         long long len;
         piece_range(p.cut, seg, p.P, tok0, len);
         N = (int)((len + 63) >> 6);
