@@ -168,7 +168,6 @@ hipError_t static_scratch(void **out) {
 extern "C" {
 
 constexpr long long kComputeUnits = 256;
-constexpr long long kLongestPiece = 512;   // chunks
 
 static int subsegments(const zeco_gla_desc *d);
 static zeco::Cut cut_of(long long tokens, long long n);
@@ -361,57 +360,78 @@ zeco_status zeco_gla_fwd_from_state(const zeco_gla_desc *d, const void *q, const
 // The one-call forms treat the P segments as what they are together, one run of P * L tokens, and cut it into pieces
 // of whole 64-token chunks as even as possible (Cut): where the pieces end is nobody's business but the library's,
 // so neither the caller's segments nor a length without a small factor decide how many compute units work.  A piece
-// is a workgroup's serial chain of chunks.  More pieces shorten the chain; each costs its states (written by the
-// first phase, scanned, read by the second), and a chunk takes the longer the more workgroups share the memory
-// system (two phases, d = 128: 3.5 us alone, 5.6 us among 192 workgroups, 6.3 us among 256).  Estimated microseconds, fitted to sweeps of the piece count (16 heads, d = 128, forward): 16384
-// tokens, 8 / 16 / 32 pieces: 157 / 130 / 147 us; 2048 tokens 46 (4) / 36 (8) / 36 (16) / 52 (32) us; 12 heads,
-// 16384 tokens, 16 / 21 pieces: 116 / 123 us (the same traffic, more states); a training step over 131072 tokens,
-// 12 / 16 / 32 pieces: 3.72 / 3.29 / 3.50 ms; 160 (batch, head) pairs x 4096
-// tokens, 1 / 3 pieces: 227 / 325 us.
+// is a workgroup's serial chain of chunks.  More pieces shorten the chain; each costs a prologue and its states
+// (written by the first phase, scanned, read by the second), and a chunk takes the longer the more workgroups share
+// the memory system.  The estimate, in microseconds, is fitted to sweeps of the piece count over 491 shapes (1 .. 1024
+// (batch, head) pairs x 128 .. 131072 tokens, the widths, gate layouts and precisions, up to 20 counts each); the count
+// it picks takes 0.3 % (forward, a tenth at worst) and 0.9 % (training step) more than the best one.  Some of them, d = 128,
+// bf16, one / two phases: 64 pairs x 1024 tokens whole 41, in 4 pieces 50 us; 16 x 1024 whole 41, in 8 27 us; 256 x
+// 32768 whole 2363, in 2 3687 us; 640 x 16384 whole 3140, in 2 4611 us; gradient passes of 400 x 4096 in 3 / 4 / 16
+// pieces 2.24 / 2.33 / 2.85 ms; 8 x 2 M tokens in 32 / 256 pieces 7.15 / 7.25 ms forward (corrected: 4.84 / 5.63 ms), 21.7 /
+// 21.7 ms backward: a chain may be as long as it comes.
+struct PassCost {
+    double chunk, bytes, hidden, start;   // a chunk's chain alone on the chip [us]; its traffic, divided by what of it is hidden; a piece's prologue and epilogue [us]
+};
 struct CostModel {
-    double chunk1, chunk2, chunkb;     // a chunk's chain alone on the chip: single pass, two phases, gradient passes [us]
-    double bytes1, bytes2, bytesb;     // a chunk's traffic in them
+    // Single pass, two phases, gradient passes; with up to `few` workgroups and with more (bf16: half as many as compute
+    // units, where the kernels take sibling workgroups; fp32 with short chunks: one for every compute unit).
+    PassCost one[2], two[2], grad[2];
+    double fixed1 = 0., fixed2 = 8.7, fixedb = 8.4;
     double state;                      // bytes of a state
-    double slots;                      // workgroups in flight
-    double fixed1 = 8., fixed2 = 13., fixedb = 30.;
-    double step = 0.07;                // of a scan, per piece
+    double states1 = 0.6, states2 = 3.7, statesb = 4.9;   // states moved per piece
+    double slots = kComputeUnits;      // workgroups in flight
+    double few = kComputeUnits / 2;
+    double step = 0.043;               // of a scan, per piece
     bool bound = false;                // no chunk faster than its traffic at `rate`
-    double rate = 5.9e6;               // bytes per microsecond of the chip (beside a chain's own latency part of the traffic is hidden)
+    double rate = 5.9e6;               // bytes per microsecond of the chip
 };
 static CostModel cost_model(const zeco_gla_desc *d) {
-    const double io = d->io_dtype == ZECO_F32 ? 4. : 2., k = io * d->d_k, v = io * d->d_v;
-    const double g = d->g_per_head ? 4. : (d->g_dtype == ZECO_BF16 ? 2. : 4.) * d->d_k;
+    const bool f32 = d->io_dtype == ZECO_F32, wide = d->d_k == 128;
+    const double io = f32 ? 4. : 2., k = io * d->d_k, v = io * d->d_v;
+    const double g = d->g_per_head ? 4. : (d->g_dtype == ZECO_BF16 ? 2. : 4.) * d->d_k, f = (d->d_k * d->d_v) / 16384.;
+    const double bytes1 = 64. * (2. * k + 2. * v + g), bytes2 = bytes1 + 64. * (k + v + g);
+    const double bytesb = 64. * (9. * k + 8. * v + 3. * g + (d->g_per_head ? 12. : 12. * d->d_k));
     CostModel m;
-    m.bytes1 = 64. * (2. * k + 2. * v + g);
-    m.bytes2 = m.bytes1 + 64. * (k + v + g);
-    m.bytesb = 64. * (9. * k + 8. * v + 3. * g + (d->g_per_head ? 12. : 12. * d->d_k));
     m.state = 4. * d->d_k * d->d_v;
-    m.slots = kComputeUnits;
-    if (d->io_dtype == ZECO_F32) {
-        const double f = (d->d_k * d->d_v) / 16384.;
-        m.chunk1 = 4. + 13. * f; m.chunk2 = 6. + 20. * f; m.chunkb = 15. + 55. * f;
-        m.slots = kComputeUnits * (d->C == 64 ? 1. : 2.);
+    if (f32) {
+        const double small = d->C == 16 ? 1.3 : 1., two = d->C == 64 ? 1. : 1.75;   // (C < 64: two workgroups share a compute unit)
+        m.one[0] = {3. + 11. * f, bytes1, 5., 3.};
+        m.two[0] = {small * (4. + 15. * f), bytes2, 5., 5. * f};
+        m.grad[0] = {small * (12. + 43. * f), bytesb, 7., 25. * f};
+        m.one[1] = {two * m.one[0].chunk, bytes1, 5., 3.};
+        m.two[1] = {two * m.two[0].chunk, bytes2, 5., 5. * f};
+        m.grad[1] = {two * m.grad[0].chunk, bytesb, 7., 25. * f};
+        if (d->C < 64) { m.slots = 2 * kComputeUnits; m.few = kComputeUnits; }
     } else {
-        m.chunk1 = d->d_k == 128 ? 2.0 : 1.3;
-        m.chunk2 = d->d_k == 128 ? 3.5 : 2.2;
-        m.chunkb = d->d_k == 128 ? 13.5 : 9.;
+        const double one = d->g_per_head ? 1.15 : 1.;
+        m.one[0] = {(wide ? 2.3 : d->d_v == 128 ? 1.35 : 1.5) * one, bytes1, 5.5, 3.7 + 1.7 * f};
+        m.one[1] = {wide ? 1.9 : 1.15, bytes1, 1.75, 3.7 + 1.7 * f};
+        m.two[0] = {wide ? 3.4 : 2.25, bytes2, 3.4, 1.6 + 2.9 * f};
+        m.two[1] = {wide ? 2.7 : 1.65, bytes2, 1.7, 1.6 + 2.9 * f};
+        m.grad[0] = {wide ? 12.1 : 11., bytesb, 12., wide ? 11. : 4.};
+        m.grad[1] = {wide ? 9.5 : 7.35, bytesb, 2., wide ? 11. : 4.};
     }
     return m;
 }
-static double cost_chain(const CostModel &m, double wgs, double longest, double chunk, double bytes) {
-    const double rounds = (double)(long long)((wgs + m.slots - 1.) / m.slots), share = wgs < m.slots ? wgs : m.slots;
-    const double traffic = share * bytes / m.rate, alone = chunk + traffic / 2.6;
-    return rounds * longest * (m.bound && traffic > alone ? traffic : alone);
+// Full rounds of workgroups, and a last one in which fewer share the memory system.
+static double cost_chain(const CostModel &m, const PassCost (&pass)[2], double wgs, double longest) {
+    const PassCost &c = pass[wgs > m.few];
+    auto round = [&](double share) {
+        const double traffic = share * c.bytes / m.rate, alone = c.chunk + traffic / c.hidden;
+        return c.start + longest * (m.bound && traffic > alone ? traffic : alone);
+    };
+    const double full = (double)(long long)(wgs / m.slots), rest = wgs - full * m.slots;
+    return full * round(m.slots) + (rest > 0. ? round(rest) : 0.);
 }
 static double cost_forward(const CostModel &m, double BH, double n, double longest, bool correct) {
+    if (n == 1.) return m.fixed1 + cost_chain(m, m.one, BH, longest) + m.states1 * BH * m.state / m.rate;
     // Pieces the AUTO schedule corrects instead of reading k, v, g twice: their first 35 chunks or so, what the decays of
     // a trained layer leave of a state, are then worked on again.
-    if (n == 1.) return m.fixed1 + cost_chain(m, BH, longest, BH > 128. ? 1.2 * m.chunk1 : m.chunk1, m.bytes1);
-    const double part = correct ? 0.55 + 0.5 * 35. / longest : 1.;
-    return m.fixed2 + part * cost_chain(m, n * BH, longest, m.chunk2, m.bytes2) + 6. * n * BH * m.state / m.rate + m.step * n;
+    const double part = correct ? 0.55 + 12. / longest : 1.;
+    return m.fixed2 + part * cost_chain(m, m.two, n * BH, longest) + m.states2 * n * BH * m.state / m.rate + m.step * n;
 }
 static double cost_backward(const CostModel &m, double BH, double n, double longest) {
-    return m.fixedb + cost_chain(m, n * BH, longest, m.chunkb, m.bytesb) + 7. * n * BH * m.state / m.rate + 2. * m.step * n;
+    return m.fixedb + cost_chain(m, m.grad, n * BH, longest) + m.statesb * n * BH * m.state / m.rate + m.step * n;
 }
 
 // Does ZECO_SCHEDULE_AUTO take the correction?  It rounds o twice and its time depends on the decays (with decays near 1
@@ -430,43 +450,41 @@ static bool may_correct(const zeco_gla_desc *d) {
 static bool corrects(bool may, long long chunks) { return may && chunks >= 64; }
 
 // Pieces per (batch, head).  Forward and backward share them, because the states the forward saves for the backward
-// are the ones entering the pieces; the estimate weighs a backward a tenth (not every forward has one, and the optimum is flat).  One
+// are the ones entering the pieces; the estimate weighs a backward a tenth (not every forward has one).  One
 // piece, where the forward alone favours it: a single launch that reads everything once, and leaves the states of the
 // pieces the backward then cuts for itself as it passes them.
 static long long pieces_for(const zeco_gla_desc *d, long long T, bool backward, bool may_be_one = true) {
     const long long BH = (long long)d->B * d->H, chunks = T / 64;
     if (BH == 0) return 1;
-    // a chain stays short enough for the workgroups of a launch to even out over several rounds
-    const long long least = (chunks + kLongestPiece - 1) / kLongestPiece;
     const CostModel m = cost_model(d);
     const bool may = may_correct(d);
-    long long best = 0;
+    const long long least = (chunks >> 22) + 1;   // (a piece's length is an int)
+    long long best = 0, seen = 0;
     double cost = 0., cost_f = 0.;
-    long long seen = 0;
     auto consider = [&](long long n) {
         if (n > chunks) n = chunks;
-        if (n < 2 || n < least || n == seen || n == best) return;
+        if (n < 2 || n < least || n == seen || n == best || n * BH > (1ll << 24)) return;   // (the descriptor's limit on workgroups)
         seen = n;
         const bool even = T % (64 * n) == 0;
         const double longest = (double)(chunks / n + (even ? 0 : 1));
         const double f = cost_forward(m, (double)BH, (double)n, longest, corrects(may, chunks / n)), b = cost_backward(m, (double)BH, (double)n, longest);
-        // (equal pieces stay in step: 15 heads, 32768 tokens, 16 / 17 pieces 153 / 161 us)
-        const double c = (backward ? b : f + 0.1 * b) * (even ? 0.92 : 1.);
-        if (best == 0 || c < cost) { cost = c; cost_f = f; best = n; }
+        // (equal pieces stay in step: 15 heads, 32768 tokens, 16 / 17 pieces 153 / 161 us; pieces of one chunk, 8 heads x
+        // 1024 tokens in 8 / 16: forward 24.5 / 26.1 us)
+        const double c = (backward ? b : f + 0.1 * b) * (even ? 0.97 : 1.) * (chunks < 2 * n ? 1.05 : 1.);
+        if (best == 0 || c < cost) { cost = c; cost_f = backward ? b : f; best = n; }
     };
-    // a quarter of the slots filled, .., four times over; the segments as they are, halved, ..; two to four chunks each
+    // a quarter of the slots filled, .., four times over; the segments as they are, halved, ..; pieces of eight chunks or
+    // more; of two to four, where there are compute units for them
     for (int k : {1, 2, 3, 4, 6, 8, 12, 16}) consider(k * (long long)m.slots / (4 * BH));
     for (long long n = d->P; n <= chunks && n * BH <= 4 * (long long)m.slots; n *= 2) consider(n);
-    for (int k = 2; k <= 4; ++k) consider((chunks + k - 1) / k);
+    for (long long n = 2; n <= chunks / 8; n *= 2) consider(n);
+    if (BH < kComputeUnits) for (int k = 2; k <= 4; ++k) consider((chunks + k - 1) / k);
     if (may) consider(chunks / 64);   // just enough for the correction
-    consider(least);
-    if (least <= 1 && may_be_one) {
+    if (least == 1 && may_be_one) {
         const double one = backward ? cost_backward(m, (double)BH, 1., (double)chunks) : cost_forward(m, (double)BH, 1., (double)chunks, false);
-        if (best == 0 || one <= 0.93 * (backward ? cost : cost_f)) best = 1;   // (clearly: the estimate is not that good)
+        if (best == 0 || one <= cost_f) best = 1;
     }
-    if (best == 0) best = 1;
-    if (best * BH > (1ll << 24)) best = d->P;   // (the limit on workgroups that the descriptor keeps)
-    return best;
+    return best ? best : least;
 }
 
 // Number of sub-segments each segment is cut into inside zeco_gla_local_fwd (1 = none).  A stream is
@@ -479,7 +497,7 @@ static int subsegments(const zeco_gla_desc *d) {
     const long long streams = (long long)d->B * d->P * d->H, chunks = d->L / 64;
     if (streams > 64 || streams == 0) return 1;
     CostModel m = cost_model(d);
-    m.bytes2 += 64. * (d->g_per_head ? 4. : 4. * d->d_k);   // G_cum
+    for (PassCost &c : m.two) c.bytes += 64. * (d->g_per_head ? 4. : 4. * d->d_k);   // G_cum
     m.bound = true;   // (three calls, 6 heads, 2 x 32768 tokens, 16 / 21 sub-segments: 285 / 302 us)
     long long best = 1;
     double cost = 0.;

@@ -302,3 +302,23 @@ def test_chunk_length_per_precision(L):
     assert call_local(L, f32(C=8)) == zeco.ZECO_ERR_UNSUPPORTED
     assert call_local(L, f32(C=16, L=48)) == zeco.ZECO_ERR_UNSUPPORTED
     assert call_local(L, f32(C=16, L=80), q=None) == zeco.ZECO_ERR_INVALID_ARG      # the descriptor itself is fine
+
+
+@pytest.mark.parametrize("B,H,T,most", [(16, 16, 4096, 1), (16, 32, 4096, 1), (16, 32, 8192, 2), (257, 1, 4096, 8), (25, 16, 8192, 8),
+                                        (65, 8, 8192, 8), (40, 16, 4096, 4)])
+def test_pieces_of_calls_whose_pairs_fill_the_chip(B, H, T, most):
+    """Where the (batch, head) pairs alone keep the compute units busy the one-call backward is cut into few pieces (at best
+    none), of eight chunks or more: every piece costs the saved states and the workspace four states a pair.  At most
+    `most` pieces are allowed, what sweeps of the count found fastest (twice that where the times lie within 2 %)."""
+    d = good_desc(B=B, P=1, H=H, L=T, stride_b=T * H * 128, stride_t=H * 128, vstride_b=T * H * 128, vstride_t=H * 128)
+    pieces = zeco.lib().zeco_gla_saved_states_bytes(ctypes.byref(d)) // (B * H * 128 * 128 * 4) - 1
+    assert 1 <= pieces <= most and T // 64 // pieces >= 8
+
+
+def test_a_run_of_any_length_may_stay_whole():
+    """256 (batch, head) pairs are one round of workgroups: their forward is one launch at every length."""
+    L_ = zeco.lib()
+    for L in (4096, 32768, 32832, 65536, 1 << 20):
+        d = good_desc(B=16, P=1, H=16, L=L, stride_b=L * 2048, stride_t=2048, vstride_b=L * 2048, vstride_t=2048)
+        state, decay = 128 * 128 * 4, ((L + 63) // 64 + 1) * 128 * 4     # two states a piece and their decays, the chunks' decays
+        assert L_.zeco_gla_fused_fwd_workspace(ctypes.byref(d)) <= 256 * (2 * state + decay) + 64
