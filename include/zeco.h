@@ -249,7 +249,9 @@ zeco_status zeco_gla_bwd_from_state_varlen(const zeco_gla_desc *desc, const int6
  * zeco_gla_bwd_from_state.  Arguments as in zeco_gla_fused_fwd / zeco_gla_fused_bwd (no saved states, no
  * schedule); workspace sizes from the *_workspace queries, sized for the bound desc->L.  Both take bf16 and
  * fp32 q/k/v.  Where desc->L exceeds 2112 tokens the library cuts the tokens the table covers into pieces of its
- * own, as in zeco_gla_fused_fwd (still without reading the table on the host); a table with a segment that breaks
+ * own, as in zeco_gla_fused_fwd (still without reading the table on the host; the workspace then holds states for
+ * as many pieces as P * L tokens would be cut into, or P if that is more: a bound far above the segments' lengths
+ * costs up to 4 workgroups' worth of states per compute unit, and in the backward a checkpoint per 512 tokens of it); a table with a segment that breaks
  * the rules is worked on segment by segment, as the separate calls do. */
 size_t zeco_gla_fused_fwd_varlen_workspace(const zeco_gla_desc *desc);
 zeco_status zeco_gla_fused_fwd_varlen(const zeco_gla_desc *desc, const int64_t *seg_start, int64_t T,

@@ -457,7 +457,7 @@ static long long pieces_for(const zeco_gla_desc *d, long long T, bool backward, 
     const long long BH = (long long)d->B * d->H, chunks = T / 64;
     if (BH == 0) return 1;
     const CostModel m = cost_model(d);
-    const bool may = may_correct(d);
+    const bool may = may_be_one && may_correct(d);   // (the calls over a table, which take two pieces at least, do not correct)
     const long long least = (chunks >> 22) + 1;   // (a piece's length is an int)
     long long best = 0, seen = 0;
     double cost = 0., cost_f = 0.;
@@ -1117,8 +1117,8 @@ static VarlenLayout varlen_layout(const zeco_gla_desc *d, bool backward) {
     if (backward) {
         w.off_dSin = w.off_dSloc + slots * w.state;
         w.off_ck = w.off_dSin + slots * w.state;
-        // checkpoints: of the segments, or of n pieces with (chunks / n + 1) / 8 each at most
-        const size_t per = cut ? (size_t)T / 512 + w.slots : (size_t)d->P * bwd_checkpoints(d->L);
+        // checkpoints: of the segments, or of n pieces, (whole chunks of a piece) / 8 each at most
+        const size_t per = cut ? (size_t)T / 512 : (size_t)d->P * bwd_checkpoints(d->L);
         w.off_table = w.off_ck + per * bh * w.state;
     }
     w.total = w.off_table + (cut ? 2 * ((size_t)w.slots + 4) : 0);

@@ -322,3 +322,14 @@ def test_a_run_of_any_length_may_stay_whole():
         d = good_desc(B=16, P=1, H=16, L=L, stride_b=L * 2048, stride_t=2048, vstride_b=L * 2048, vstride_t=2048)
         state, decay = 128 * 128 * 4, ((L + 63) // 64 + 1) * 128 * 4     # two states a piece and their decays, the chunks' decays
         assert L_.zeco_gla_fused_fwd_workspace(ctypes.byref(d)) <= 256 * (2 * state + decay) + 64
+
+
+@pytest.mark.parametrize("H,P,L", [(16, 64, 131072), (16, 8, 131072), (4, 64, 65536), (1, 4, 1 << 20), (16, 256, 4096), (8, 1024, 2200), (2, 3, 2113)])
+def test_workspace_over_a_table_is_bounded_by_the_segments_or_the_compute_units(H, P, L):
+    """States for the segments, or for the pieces that fill the compute units four times over, whatever the bound on the
+    lengths; a checkpoint per 512 tokens in the backward; beside them decays (1/128 of a state each) and the table."""
+    d = good_desc(P=P, H=H, L=L, stride_b=P * L * H * 128, stride_t=H * 128, vstride_b=P * L * H * 128, vstride_t=H * 128)
+    state, slots = 128 * 128 * 4, max(P, 1024 // H)
+    fwd = ((2 * slots + 1) * H + slots * H / 128) * state + 16 * (slots + 4) + 64
+    assert zeco.lib().zeco_gla_fused_fwd_varlen_workspace(ctypes.byref(d)) <= fwd
+    assert zeco.lib().zeco_gla_fused_bwd_varlen_workspace(ctypes.byref(d)) <= fwd + (2 * slots + P * L // 512) * H * state
