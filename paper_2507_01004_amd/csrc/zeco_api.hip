@@ -461,8 +461,7 @@ static long long pieces_for(const zeco_gla_desc *d, long long T, bool backward, 
     const long long least = (chunks >> 22) + 1;   // (a piece's length is an int)
     long long best = 0, seen = 0;
     double cost = 0., cost_f = 0.;
-    auto consider = [&](long long n) {
-        if (n > chunks) n = chunks;
+    auto count = [&](long long n) {
         if (n < 2 || n < least || n == seen || n == best || n * BH > (1ll << 24)) return;   // (the descriptor's limit on workgroups)
         seen = n;
         const bool even = T % (64 * n) == 0;
@@ -470,8 +469,17 @@ static long long pieces_for(const zeco_gla_desc *d, long long T, bool backward, 
         const double f = cost_forward(m, (double)BH, (double)n, longest, corrects(may, chunks / n)), b = cost_backward(m, (double)BH, (double)n, longest);
         // (equal pieces stay in step: 15 heads, 32768 tokens, 16 / 17 pieces 153 / 161 us; pieces of one chunk, 8 heads x
         // 1024 tokens in 8 / 16: forward 24.5 / 26.1 us)
-        const double c = (backward ? b : f + 0.1 * b) * (even ? 0.97 : 1.) * (chunks < 2 * n ? 1.05 : 1.);
+        const double c = (backward ? b : f + 0.1 * b) * (even ? 0.97 : 1.) * (longest < 2. ? 1.05 : 1.);
         if (best == 0 || c < cost) { cost = c; cost_f = backward ? b : f; best = n; }
+    };
+    // .. and the fewest pieces whose longest chain is no longer (24 pairs x 4001 tokens in 8 / 9 / 10 pieces, chains of 8 / 7 /
+    // 7 chunks: training step 160 / 148 / 151 us)
+    auto consider = [&](long long n) {
+        if (n > chunks) n = chunks;
+        if (n < 2) return;
+        count(n);
+        const long long longest = chunks / n + (T % (64 * n) == 0 ? 0 : 1);
+        count((chunks + longest - 1) / longest + (chunks % longest == 0 && T % 64 ? 1 : 0));
     };
     // a quarter of the slots filled, .., four times over; the segments as they are, halved, ..; pieces of eight chunks or
     // more; of two to four, where there are compute units for them
