@@ -68,10 +68,12 @@ template <int DK, int DV, int C> struct QKF32Cfg {
 // output).  REV = true: dK and dG (x = v, y = dO, z = q, z2 = k, W_init = state gradients entering each
 // segment's final state; the query scale rides on Q .* Lambda, so that the running dS is the true gradient).
 // Waves per SIMD to leave registers for: at C = 16 the tiles of several workgroups (of four or eight waves) fit a compute
-// unit's LDS, and one's gate pass then runs beside another's products.  (At C = 32 eight waves would spill.)
-constexpr int f32_bwd_waves(int waves, int C) { return C == 64 ? 1 : C == 32 ? 2 : waves == 8 ? 4 : 3; }
+// unit's LDS, and one's gate pass then runs beside another's products.  (At C = 32, and in the dK pass at d = 128, eight
+// waves would spill: dK pass at C = 16 with 27 registers spilled / with one workgroup, training step of 16 heads x 2048 tokens
+// 286 / 265 us, 16 heads x 8 x 2048 1.50 / 1.49 ms.)
+constexpr int f32_bwd_waves(int DK, int DV, int C, bool REV) { return C == 64 ? 1 : C == 32 || (DK == 128 && DV == 128 && REV) ? 2 : DK == 128 ? 4 : 3; }
 template <int DK, int DV, int C, bool REV>
-__global__ __launch_bounds__(DK * 4, f32_bwd_waves(DK / 16, C)) void gla_bwd_qk_f32_kernel(BwdQKParams p) {
+__global__ __launch_bounds__(DK * 4, f32_bwd_waves(DK, DV, C, REV)) void gla_bwd_qk_f32_kernel(BwdQKParams p) {
     typedef QKF32Cfg<DK, DV, C> Cfg;
     constexpr float SZ = REV ? 1.f : -1.f;   // exponent sign of the operand Z~; the factor F takes the other
     extern __shared__ __align__(16) float lds[];
@@ -129,7 +131,7 @@ __global__ __launch_bounds__(DK * 4, f32_bwd_waves(DK / 16, C)) void gla_bwd_qk_
     // gate pass: channel quad and token group; copy of X and Y: column quad and first token
     const int cq = tid % Cfg::kCQ, tg = tid / Cfg::kCQ, gl = tg % Cfg::kGW;
     const int vq = tid % Cfg::kVQ, tv = tid / Cfg::kVQ;
-    const bool copies = tv < Cfg::kVStep;        // (uniform per wave)
+    const bool copies = Cfg::kVStep * Cfg::kVQ == Cfg::kThreads || tv < Cfg::kVStep;   // (uniform per wave)
     auto row_of = [](int t) { return REV ? C - 1 - t : t; };
 
     // dG carried in from the later segments: c[i] = sum_j dS_end[i][j] S_end[i][j]  (4 threads per row)

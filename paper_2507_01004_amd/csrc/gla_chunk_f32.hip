@@ -75,10 +75,17 @@ template <int DK, int DV, int C> struct F32Cfg {
 };
 
 // Waves per SIMD to leave registers for: at C = 16 and 32 the tiles of two or more workgroups (of four or eight waves)
-// fit a compute unit's LDS, and one's gate pass then runs beside another's products.
-constexpr int f32_waves(int waves, int C) { return C == 64 ? 1 : waves == 8 ? 4 : C == 16 ? 3 : 2; }
+// fit a compute unit's LDS, and one's gate pass then runs beside another's products.  With d_v = 128 two of them leave 128
+// registers a lane.  The local pass at C = 32, d = 128 would spill 21 of them and is faster alone (16 heads, 64 x 1024 tokens:
+// 1.65 -> 1.45 ms), and the output pass that emits G_cum is launched on no more workgroups than there are compute units; what
+// the states and the output pass spill at C = 32 (2 and 6 registers) costs less than a second workgroup brings (8 x 2048
+// tokens, forward 357 against 373 us).
+constexpr int f32_waves(int DK, int DV, int C, int MODE) {
+    if (DV == 128 && C < 64 && (MODE == kF32LocalInit || (MODE == kF32Local && C == 32 && DK == 128))) return 2;
+    return C == 64 ? 1 : DV == 128 ? 4 : C == 16 ? 3 : 2;
+}
 template <int DK, int DV, int C, int MODE>
-__global__ __launch_bounds__(DV * 4, f32_waves(DV / 16, C)) void gla_chunk_f32_kernel(ChunkParams p) {
+__global__ __launch_bounds__(DV * 4, f32_waves(DK, DV, C, MODE)) void gla_chunk_f32_kernel(ChunkParams p) {
     typedef F32Cfg<DK, DV, C> Cfg;
     constexpr bool REV = MODE == kF32DState || MODE == kF32DV;       // the sequence reversed
     constexpr bool NOQ = MODE == kF32States || MODE == kF32DState;   // only the state is computed
@@ -147,17 +154,15 @@ __global__ __launch_bounds__(DV * 4, f32_waves(DV / 16, C)) void gla_chunk_f32_k
     // gate pass: channel quad and token group; copy of V: column quad and first token
     const int cq = tid % Cfg::kCQ, tg = tid / Cfg::kCQ, gl = tg % Cfg::kGW;
     const int vq = tid % Cfg::kVQ, tv = tid / Cfg::kVQ;
-    const bool gates = tg < Cfg::kTG, copies = tv < Cfg::kVStep;   // (uniform per wave)
+    // Uniform per wave; known where all threads take part, because a branch around loads makes the compiler wait for more of
+    // them than it uses (16 heads, 4 x 2048 tokens, three calls at C = 64 / 32 / 16: 322 / 318 / 373 -> 309 / 302 / 326 us).  Not in
+    // the local pass at C = 16, d = 128, which then spills 80 bytes a lane (16 heads, 32 x 1024 tokens: 765 -> 852 us).
+    const bool gates = (Cfg::kTG * Cfg::kCQ == Cfg::kThreads && !(MODE == kF32Local && C == 16 && DK == 128 && DV == 128)) || tg < Cfg::kTG;
+    const bool copies = Cfg::kVStep * Cfg::kVQ == Cfg::kThreads || tv < Cfg::kVStep;
     // position in the segment of the token that sits at place x of the order the chunks are walked in
     auto at = [&](long long x) { return REV ? len - 1 - x : x; };
     auto start_of = [&](int n) { return n ? (long long)n * C - pad : 0ll; };
     double seg_prefix[4] = {0., 0., 0., 0.};     // log decay accumulated over previous chunks
-    if constexpr (MODE == kF32LocalInit) {       // .. and over the segment's earlier pieces
-        const f32x4 *G = reinterpret_cast<const f32x4 *>(p.G_off + 2 * (sbh * DK + 4 * cq));
-#pragma unroll
-        for (int a = 0; a < 4; ++a) seg_prefix[a] = (double)G[a / 2][2 * (a & 1)] + (double)G[a / 2][2 * (a & 1) + 1];
-    }
-
     // The raw rows of the chunk worked on next: fetched a whole chunk ahead, 16 bytes a load and all of a chunk's loads
     // in flight together.  (Loaded one by one where they were used, four bytes a lane, they took half of a chunk's time:
     // output pass, d = 128, C = 64, 32 us a chunk, now 17; its products alone are 9.)
@@ -188,6 +193,11 @@ __global__ __launch_bounds__(DV * 4, f32_waves(DV / 16, C)) void gla_chunk_f32_k
     };
     fetch_gv(0);
     fetch_qk(0);
+    if constexpr (MODE == kF32LocalInit) {       // .. and over the segment's earlier pieces
+        const f32x4 *G = reinterpret_cast<const f32x4 *>(p.G_off + 2 * (sbh * DK + 4 * cq));
+#pragma unroll
+        for (int a = 0; a < 4; ++a) seg_prefix[a] = (double)G[a / 2][2 * (a & 1)] + (double)G[a / 2][2 * (a & 1) + 1];
+    }
 
     for (int n = 0; n < n_chunks; ++n) {
         const long long t0 = start_of(n);

@@ -1100,11 +1100,12 @@ zeco_status zeco_gla_bwd_from_state_varlen(const zeco_gla_desc *d, const int64_t
 // scan, output pass) and of the backward (forward states and their scan, dQ pass with the segments' state
 // gradients, reverse scan, dV and dK passes).
 //
-// Segments of up to 33 chunks are worked on as given: their chains are short, and the call then repeats the separate
-// calls bit for bit.  Longer ones are cut: the segments together are one run of tokens, whose pieces need not end where
-// they do, so the run is cut as in zeco_gla_fused_fwd, on the device (launch_plan), where the table is.  Measured with
-// 8 segments of 1160 .. 9287 tokens and 16 heads, forward and backward: 3.15 ms as given (the longest segment's
-// chain), 1.05 ms in 16 pieces.
+// Segments of up to 33 chunks are worked on as given, so that the call repeats the separate calls over the table bit for
+// bit; that is what the bound is for, and not that a cut would not pay.  Longer ones are cut: the segments together are
+// one run of tokens, whose pieces need not end where they do, so the run is cut as in zeco_gla_fused_fwd, on the device
+// (launch_plan), where the table is.  Forward and backward, d = 128, segments of up to 2112 (whole) / 2113 (cut) tokens: 16
+// segments, 1 head 628 / 170 us, 4 heads 626 / 345 us, 16 heads 1044 / 1069 us; 3 segments, 16 heads 631 / 274 us.  8 segments of
+// 1160 .. 9287 tokens, 16 heads: 3.15 ms as given (the longest segment's chain), 1.02 ms in 16 pieces.
 constexpr int kWholeSegments = 33 * 64;
 struct VarlenLayout {   // workspace carve-up, in floats
     int slots;          // pieces, or segments
