@@ -362,76 +362,87 @@ zeco_status zeco_gla_fwd_from_state(const zeco_gla_desc *d, const void *q, const
 // so neither the caller's segments nor a length without a small factor decide how many compute units work.  A piece
 // is a workgroup's serial chain of chunks.  More pieces shorten the chain; each costs a prologue and its states
 // (written by the first phase, scanned, read by the second), and a chunk takes the longer the more workgroups share
-// the memory system.  The estimate, in microseconds, is fitted to sweeps of the piece count over 491 shapes (1 .. 1024
-// (batch, head) pairs x 128 .. 131072 tokens, the widths, gate layouts and precisions, up to 20 counts each); the count
-// it picks takes 0.3 % (forward, a tenth at worst) and 0.9 % (training step) more than the best one.  Some of them, d = 128,
-// bf16, one / two phases: 64 pairs x 1024 tokens whole 41, in 4 pieces 50 us; 16 x 1024 whole 41, in 8 27 us; 256 x
-// 32768 whole 2363, in 2 3687 us; 640 x 16384 whole 3140, in 2 4611 us; gradient passes of 400 x 4096 in 3 / 4 / 16
-// pieces 2.24 / 2.33 / 2.85 ms; 8 x 2 M tokens in 32 / 256 pieces 7.15 / 7.25 ms forward (corrected: 4.84 / 5.63 ms), 21.7 /
-// 21.7 ms backward: a chain may be as long as it comes.
+// the memory system.  The estimate, in microseconds, has two sets of constants, both fitted to sweeps of the piece count:
+// for few (batch, head) pairs (d = 128, bf16, forward: 16 pairs x 16384 tokens, 8 / 16 / 32 pieces 157 / 130 / 147 us, 2048 tokens
+// 46 (4) / 36 (8) / 36 (16) / 52 (32) us; training step over 131072 tokens, 12 / 16 / 32 pieces 3.72 / 3.29 / 3.50 ms), and for
+// pairs that fill half of the compute units by themselves, where a piece's prologue and the last round of workgroups decide
+// (256 pairs x 32768 tokens whole 2.36, in 2 3.69 ms; 640 x 16384 whole 3.14, in 2 4.61 ms; gradient passes of 400 x
+// 4096 in 3 / 4 / 16 pieces 2.24 / 2.33 / 2.85 ms).  The count it picks takes 0.7 % (forward) and 1.6 % (training step) more than the
+// best of up to 25 counts in the mean over 596 shapes of 1 .. 1024 pairs.  A chain may be as long as it comes: 8 pairs x 2 M
+// tokens in 32 / 256 pieces 7.15 / 7.25 ms forward (corrected: 4.84 / 5.63 ms), 21.7 / 21.7 ms backward.
 struct PassCost {
     double chunk, bytes, hidden, start;   // a chunk's chain alone on the chip [us]; its traffic, divided by what of it is hidden; a piece's prologue and epilogue [us]
 };
 struct CostModel {
-    // Single pass, two phases, gradient passes; with up to `few` workgroups and with more (bf16: half as many as compute
-    // units, where the kernels take sibling workgroups; fp32 with short chunks: one for every compute unit).
-    PassCost one[2], two[2], grad[2];
-    double fixed1 = 0., fixed2 = 8.7, fixedb = 8.4;
+    PassCost one, two, grad;           // single pass, two phases, gradient passes
+    double fixed1, fixed2, fixedb;
     double state;                      // bytes of a state
-    double states1 = 0.6, states2 = 3.7, statesb = 4.9;   // states moved per piece
+    double states2, statesb;           // states moved per piece
+    double step2, stepb;               // of the scans, per piece
+    double even, one_piece;            // factors in favour of equal pieces, and a margin for a single one
     double slots = kComputeUnits;      // workgroups in flight
-    double few = kComputeUnits / 2;
-    double step = 0.043;               // of a scan, per piece
+    bool partial;                      // price a last round of fewer workgroups as such
     bool bound = false;                // no chunk faster than its traffic at `rate`
     double rate = 5.9e6;               // bytes per microsecond of the chip
 };
-static CostModel cost_model(const zeco_gla_desc *d) {
-    const bool f32 = d->io_dtype == ZECO_F32, wide = d->d_k == 128;
+static CostModel cost_model(const zeco_gla_desc *d, long long pairs) {
+    const bool f32 = d->io_dtype == ZECO_F32, wide = d->d_k == 128, many = pairs >= kComputeUnits / 2;
     const double io = f32 ? 4. : 2., k = io * d->d_k, v = io * d->d_v;
     const double g = d->g_per_head ? 4. : (d->g_dtype == ZECO_BF16 ? 2. : 4.) * d->d_k, f = (d->d_k * d->d_v) / 16384.;
     const double bytes1 = 64. * (2. * k + 2. * v + g), bytes2 = bytes1 + 64. * (k + v + g);
     const double bytesb = 64. * (9. * k + 8. * v + 3. * g + (d->g_per_head ? 12. : 12. * d->d_k));
     CostModel m;
     m.state = 4. * d->d_k * d->d_v;
-    if (f32) {
-        const double small = d->C == 16 ? 1.3 : 1., two = d->C == 64 ? 1. : 1.75;   // (C < 64: two workgroups share a compute unit)
-        m.one[0] = {3. + 11. * f, bytes1, 5., 3.};
-        m.two[0] = {small * (4. + 15. * f), bytes2, 5., 5. * f};
-        m.grad[0] = {small * (12. + 43. * f), bytesb, 7., 25. * f};
-        m.one[1] = {two * m.one[0].chunk, bytes1, 5., 3.};
-        m.two[1] = {two * m.two[0].chunk, bytes2, 5., 5. * f};
-        m.grad[1] = {two * m.grad[0].chunk, bytesb, 7., 25. * f};
-        if (d->C < 64) { m.slots = 2 * kComputeUnits; m.few = kComputeUnits; }
+    m.partial = many;
+    if (many) {
+        m.fixed1 = 5.; m.fixed2 = 9.5; m.fixedb = 7.2;
+        m.states2 = 3.8; m.statesb = 4.5; m.step2 = m.stepb = 0.04;
+        m.even = 0.97; m.one_piece = 1.;
     } else {
-        const double one = d->g_per_head ? 1.15 : 1.;
-        m.one[0] = {(wide ? 2.3 : d->d_v == 128 ? 1.35 : 1.5) * one, bytes1, 5.5, 3.7 + 1.7 * f};
-        m.one[1] = {wide ? 1.9 : 1.15, bytes1, 1.75, 3.7 + 1.7 * f};
-        m.two[0] = {wide ? 3.4 : 2.25, bytes2, 3.4, 1.6 + 2.9 * f};
-        m.two[1] = {wide ? 2.7 : 1.65, bytes2, 1.7, 1.6 + 2.9 * f};
-        m.grad[0] = {wide ? 12.1 : 11., bytesb, 12., wide ? 11. : 4.};
-        m.grad[1] = {wide ? 9.5 : 7.35, bytesb, 2., wide ? 11. : 4.};
+        m.fixed1 = 8.; m.fixed2 = 13.; m.fixedb = 30.;
+        m.states2 = 6.; m.statesb = 7.; m.step2 = 0.07; m.stepb = 0.14;
+        m.even = 0.92; m.one_piece = 0.93;
+    }
+    if (f32 && many) {
+        // (one workgroup on a compute unit: a second one, which fits at C < 64, takes as long again)
+        const double small = d->C == 16 ? 1.45 : 1.;
+        m.one = {4.4 + 11. * f, bytes1, 5., 3.};
+        m.two = {small * (4. + 16. * f), bytes2, 5., 4. * f};
+        m.grad = {small * (12. + 41. * f), bytesb, 7., 25. * f};
+    } else if (f32) {
+        m.one = {4. + 13. * f, bytes1, 2.6, 0.};
+        m.two = {6. + 20. * f, bytes2, 2.6, 0.};
+        m.grad = {15. + 55. * f, bytesb, 2.6, 0.};
+        m.slots = kComputeUnits * (d->C == 64 ? 1. : 2.);
+    } else if (many) {
+        m.one = {wide ? 1.9 : 1.15, bytes1, 1.75, 3.7 + 1.7 * f};
+        m.two = {wide ? 2.6 : 1.65, bytes2, 1.83, 2. + 3.35 * f};
+        m.grad = {wide ? 10.6 : 6.7, bytesb, 2.7, wide ? 14. : 2.5};
+    } else {
+        m.one = {wide ? 2.0 : 1.3, bytes1, 2.6, 0.};
+        m.two = {wide ? 3.5 : 2.2, bytes2, 2.6, 0.};
+        m.grad = {wide ? 13.5 : 9., bytesb, 2.6, 0.};
     }
     return m;
 }
-// Full rounds of workgroups, and a last one in which fewer share the memory system.
-static double cost_chain(const CostModel &m, const PassCost (&pass)[2], double wgs, double longest) {
-    const PassCost &c = pass[wgs > m.few];
+static double cost_chain(const CostModel &m, const PassCost &c, double wgs, double longest) {
     auto round = [&](double share) {
         const double traffic = share * c.bytes / m.rate, alone = c.chunk + traffic / c.hidden;
         return c.start + longest * (m.bound && traffic > alone ? traffic : alone);
     };
     const double full = (double)(long long)(wgs / m.slots), rest = wgs - full * m.slots;
-    return full * round(m.slots) + (rest > 0. ? round(rest) : 0.);
+    if (rest <= 0.) return full * round(m.slots);
+    return full * round(m.slots) + round(m.partial || full == 0. ? rest : m.slots);
 }
 static double cost_forward(const CostModel &m, double BH, double n, double longest, bool correct) {
-    if (n == 1.) return m.fixed1 + cost_chain(m, m.one, BH, longest) + m.states1 * BH * m.state / m.rate;
+    if (n == 1.) return m.fixed1 + cost_chain(m, m.one, BH, longest);
     // Pieces the AUTO schedule corrects instead of reading k, v, g twice: their first 35 chunks or so, what the decays of
     // a trained layer leave of a state, are then worked on again.
-    const double part = correct ? 0.55 + 12. / longest : 1.;
-    return m.fixed2 + part * cost_chain(m, m.two, n * BH, longest) + m.states2 * n * BH * m.state / m.rate + m.step * n;
+    const double part = correct ? (m.partial ? 0.55 + 12. / longest : 0.55 + 0.5 * 35. / longest) : 1.;
+    return m.fixed2 + part * cost_chain(m, m.two, n * BH, longest) + m.states2 * n * BH * m.state / m.rate + m.step2 * n;
 }
 static double cost_backward(const CostModel &m, double BH, double n, double longest) {
-    return m.fixedb + cost_chain(m, m.grad, n * BH, longest) + m.statesb * n * BH * m.state / m.rate + m.step * n;
+    return m.fixedb + cost_chain(m, m.grad, n * BH, longest) + m.statesb * n * BH * m.state / m.rate + m.stepb * n;
 }
 
 // Does ZECO_SCHEDULE_AUTO take the correction?  It rounds o twice and its time depends on the decays (with decays near 1
@@ -456,41 +467,32 @@ static bool corrects(bool may, long long chunks) { return may && chunks >= 64; }
 static long long pieces_for(const zeco_gla_desc *d, long long T, bool backward, bool may_be_one = true) {
     const long long BH = (long long)d->B * d->H, chunks = T / 64;
     if (BH == 0) return 1;
-    const CostModel m = cost_model(d);
+    const CostModel m = cost_model(d, BH);
     const bool may = may_be_one && may_correct(d);   // (the calls over a table, which take two pieces at least, do not correct)
-    const long long least = (chunks >> 22) + 1;   // (a piece's length is an int)
+    const long long least = (chunks >> 22) + 1;      // (a piece's length is an int)
     long long best = 0, seen = 0;
-    double cost = 0., cost_f = 0.;
-    auto count = [&](long long n) {
+    double cost = 0., cost_f = 0., cost_b = 0.;
+    auto consider = [&](long long n) {
+        if (n > chunks) n = chunks;
         if (n < 2 || n < least || n == seen || n == best || n * BH > (1ll << 24)) return;   // (the descriptor's limit on workgroups)
         seen = n;
         const bool even = T % (64 * n) == 0;
         const double longest = (double)(chunks / n + (even ? 0 : 1));
         const double f = cost_forward(m, (double)BH, (double)n, longest, corrects(may, chunks / n)), b = cost_backward(m, (double)BH, (double)n, longest);
-        // (equal pieces stay in step: 15 heads, 32768 tokens, 16 / 17 pieces 153 / 161 us; pieces of one chunk, 8 heads x
-        // 1024 tokens in 8 / 16: forward 24.5 / 26.1 us)
-        const double c = (backward ? b : f + 0.1 * b) * (even ? 0.97 : 1.) * (longest < 2. ? 1.05 : 1.);
-        if (best == 0 || c < cost) { cost = c; cost_f = backward ? b : f; best = n; }
+        // (equal pieces stay in step: 15 heads, 32768 tokens, 16 / 17 pieces 153 / 161 us)
+        const double c = (backward ? b : f + 0.1 * b) * (even ? m.even : 1.);
+        if (best == 0 || c < cost) { cost = c; cost_f = f; cost_b = b; best = n; }
     };
-    // .. and the fewest pieces whose longest chain is no longer (24 pairs x 4001 tokens in 8 / 9 / 10 pieces, chains of 8 / 7 /
-    // 7 chunks: training step 160 / 148 / 151 us)
-    auto consider = [&](long long n) {
-        if (n > chunks) n = chunks;
-        if (n < 2) return;
-        count(n);
-        const long long longest = chunks / n + (T % (64 * n) == 0 ? 0 : 1);
-        count((chunks + longest - 1) / longest + (chunks % longest == 0 && T % 64 ? 1 : 0));
-    };
-    // a quarter of the slots filled, .., four times over; the segments as they are, halved, ..; pieces of eight chunks or
-    // more; of two to four, where there are compute units for them
+    // a quarter of the slots filled, .., four times over; the segments as they are, halved, ..; two to four chunks each, where
+    // there are compute units for them, or eight and more
     for (int k : {1, 2, 3, 4, 6, 8, 12, 16}) consider(k * (long long)m.slots / (4 * BH));
     for (long long n = d->P; n <= chunks && n * BH <= 4 * (long long)m.slots; n *= 2) consider(n);
-    for (long long n = 2; n <= chunks / 8; n *= 2) consider(n);
     if (BH < kComputeUnits) for (int k = 2; k <= 4; ++k) consider((chunks + k - 1) / k);
+    if (m.partial) for (long long n = 2; n <= chunks / 8; n *= 2) consider(n);
     if (may) consider(chunks / 64);   // just enough for the correction
     if (least == 1 && may_be_one) {
         const double one = backward ? cost_backward(m, (double)BH, 1., (double)chunks) : cost_forward(m, (double)BH, 1., (double)chunks, false);
-        if (best == 0 || one <= cost_f) best = 1;
+        if (best == 0 || one <= m.one_piece * (backward ? cost_b : cost_f)) best = 1;
     }
     return best ? best : least;
 }
@@ -504,8 +506,8 @@ static long long pieces_for(const zeco_gla_desc *d, long long T, bool backward, 
 static int subsegments(const zeco_gla_desc *d) {
     const long long streams = (long long)d->B * d->P * d->H, chunks = d->L / 64;
     if (streams > 64 || streams == 0) return 1;
-    CostModel m = cost_model(d);
-    for (PassCost &c : m.two) c.bytes += 64. * (d->g_per_head ? 4. : 4. * d->d_k);   // G_cum
+    CostModel m = cost_model(d, streams);
+    m.two.bytes += 64. * (d->g_per_head ? 4. : 4. * d->d_k);   // G_cum
     m.bound = true;   // (three calls, 6 heads, 2 x 32768 tokens, 16 / 21 sub-segments: 285 / 302 us)
     long long best = 1;
     double cost = 0.;

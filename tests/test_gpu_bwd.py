@@ -17,11 +17,11 @@ pytestmark = pytest.mark.gpu
 CASES = [
     ("bwd_split", 1, 4, 2, 320, 128, 128, "f32"),          # 8 streams: d_v split in the dV pass, 5 chunks
     ("bwd_whole", 2, 16, 8, 128, 128, 128, "f32"),         # 256 streams
-    ("bwd_pieces", 1, 2, 2, 1024, 128, 128, "f32"),        # fused call cuts each segment in 4
+    ("bwd_pieces", 1, 2, 2, 1024, 128, 128, "f32"),        # pieces of one chunk
     ("bwd_pieces_d64", 1, 1, 1, 2048, 64, 64, "bf16"),
     ("bwd_gbf16", 1, 3, 2, 256, 128, 128, "bf16"),
-    ("bwd_pieces_odd", 1, 1, 1, 1920, 128, 128, "f32"),    # 30 chunks: forward 2 pieces, backward 6 of 5 chunks
-    ("bwd_pieces_prime", 1, 2, 1, 1664, 64, 128, "f32"),   # 26 chunks: 2 pieces of 13, which no factor divides
+    ("bwd_pieces_odd", 1, 1, 1, 1920, 128, 128, "f32"),    # 30 chunks, which no power of two divides
+    ("bwd_pieces_prime", 1, 2, 1, 1664, 64, 128, "f32"),   # 26 chunks
     ("bwd_onechunk", 1, 2, 4, 64, 128, 128, "f32"),
     ("bwd_dk64_dv128", 1, 2, 2, 192, 64, 128, "f32"),
     ("bwd_dk128_dv64", 1, 2, 2, 192, 128, 64, "bf16"),
@@ -164,8 +164,8 @@ def test_backward_from_states_saved_by_the_forward(case):
 @pytest.mark.parametrize("H", [1, 2])
 def test_few_heads_long_sequence_scans_the_pieces_as_a_tree(H):
     """One or two heads and 32768 tokens per segment: the fused calls cut the sequence into 128 pieces and more
-    and scan them with the two-level scan (a serial chain that short on width is latency-bound).  Forward by
-    both schedules and backward against the oracle, with a state entering and a state gradient leaving."""
+    and scan them (from 512 pieces of one head on with the two-level scan: a serial chain that short on width is
+    latency-bound).  Forward by both schedules and backward against the oracle, with a state entering and a state gradient leaving."""
     B, P, L, dk, dv = 1, 2, 32768, 64, 64
     print("few heads", H, flush=True)
     inp = synth.make_inputs(B, P * L, H, dk, dv, seed=500 + H, io="bf16", g="f32", device="cuda", gate_div=64.0)

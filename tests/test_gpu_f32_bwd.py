@@ -23,9 +23,9 @@ CASES = [
     ("f32bwd_ragged_c16", 1, 2, 2, 203, 64, 128, 16),
     ("f32bwd_d64", 1, 2, 2, 256, 64, 64, 32),
     ("f32bwd_dk128_dv64", 1, 2, 1, 257, 128, 64, 64),
-    ("f32bwd_anchor", 1, 2, 2, 1100, 128, 128, 64),        # two checkpoints of the forward state per segment
-    ("f32bwd_anchor_c16", 1, 1, 1, 1601, 64, 64, 16),      # three, 32 chunks apart; the last chunk holds one token
-    ("f32bwd_pieces_c16", 2, 16, 4, 1024, 128, 128, 16),   # 128 streams cut into 4 pieces each (four workgroups share a compute unit at C = 16)
+    ("f32bwd_anchor", 1, 2, 2, 1100, 128, 128, 64),        # pieces of a chunk or two (building blocks: two checkpoints of the forward state per segment)
+    ("f32bwd_anchor_c16", 1, 1, 1, 1601, 64, 64, 16),      # 13 pieces (building blocks: three checkpoints, 32 chunks apart; the last chunk holds one token)
+    ("f32bwd_pieces_c16", 2, 16, 4, 1024, 128, 128, 16),   # 32 (batch, head) pairs in 16 pieces (two workgroups share a compute unit at C = 16)
 ]
 GRADS = ("dq", "dk", "dv", "dg")
 AXES = (0, 2)

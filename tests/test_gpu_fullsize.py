@@ -195,7 +195,7 @@ def test_fullsize_backward_building_blocks_sampled_slices():
 
 def test_fullsize_ragged_segment_length_sampled_slices():
     """c3's tensors cut to 8 segments of 16380 tokens (255 chunks and one of 60 tokens per segment; the
-    fused backward cuts each into 35 pieces of 468): every forward route and the backward on sampled slices."""
+    fused calls cut the run into 16 uneven pieces): every forward route and the backward on sampled slices."""
     inp, c = synth.config_inputs("c3", device="cuda")
     P, H, L = c["P"], c["H"], 16380
     gen = torch.Generator(device="cuda").manual_seed(4243)

@@ -252,3 +252,78 @@ def test_local_pass_runs_whole_with_a_workspace_it_cannot_use(io, L):
         torch.cuda.synchronize()
         for a, b in zip(got, whole):
             assert torch.equal(a, b)
+
+
+def checkpoints_per_piece(q, v, g, P, C):
+    """(pieces, checkpoints of the forward state a piece has) of a one-call backward, from what its workspace holds:
+    four states a piece, one more and the pieces' log decays, and a state per checkpoint, one every eight chunks of 64
+    tokens (the count that gives that size)."""
+    B, T, H, dk = q.shape
+    dv, chunks, ws = v.shape[-1], T // 64, zeco.fused_bwd_workspace_bytes(q, v, g, P, C) // 4
+    found = []
+    for n in range(1, chunks + 1):
+        longest = 64 * (chunks // n + 1) if chunks % n else 64 * (chunks // n) + T % 64
+        ck = ((longest + 63) // 64 - 1) // 8
+        if B * H * (n * (4 * dk * dv + dk + ck * dk * dv) + dk * dv) == ws:
+            found.append((n, ck))
+    assert len(found) == 1, found
+    return found[0]
+
+
+CHECKPOINTED = [(1, 16, 1, 9507, 64, 64, "bf16", "f32", 64), (1, 16, 3, 3169, 64, 128, "bf16", "head", 64), (1, 16, 1, 9507, 64, 64, "f32", "f32", 64),
+                (1, 64, 1, 4901, 64, 64, "f32", "f32", 32), (1, 64, 1, 4901, 64, 64, "f32", "f32", 16)]
+
+
+@pytest.mark.parametrize("case", CHECKPOINTED, ids=lambda c: "B%d_H%d_P%d_L%d_%dx%d_%s_%s_C%d" % c)
+def test_one_call_backward_over_pieces_with_checkpoints(case):
+    """Uneven pieces of nine chunks or more, so that dG is re-anchored inside them from the forward states the dQ pass
+    left (and the saved states, with bf16, start the backward), against the oracle."""
+    B, H, P, L, dk, dv, io, gate, C = case
+    print("case", case, flush=True)
+    tol, head = TOL[io], gate == "head"
+    seed = zlib.crc32(repr(case).encode()) % 10000
+    inp = synth.make_inputs(B, P * L, H, dk, dv, seed=seed, io=io, g="f32", device="cuda", gate_div=64.0, per_head_gate=head)
+    q, k, v, g = (inp[n] for n in "qkvg")
+    n, ck = checkpoints_per_piece(q, v, g, P, C)
+    assert ck >= 1 and (P * L // 64) % n
+    gen = torch.Generator(device="cuda").manual_seed(seed + 1)
+    dO = torch.randn(v.shape, generator=gen, device="cuda").to(v.dtype)
+    S0 = torch.randn(B, H, dk, dv, device="cuda", generator=gen) * 0.3
+    dS_T = torch.randn(B, H, dk, dv, device="cuda", generator=gen) * 0.3
+    hg = np.repeat(host(g)[..., None], dk, axis=-1) if head else host(g)
+    ref = oracle.gla_recurrent_bwd(host(q), host(k), host(v), hg, host(dO), 0.5, host(S0), host(dS_T))
+    ref_dg = ref[3].sum(axis=-1) if head else ref[3]
+    save = None
+    if io == "bf16":
+        save = torch.empty(zeco.saved_states_bytes(q, v, g, P, C), dtype=torch.uint8, device="cuda")
+        zeco.gla_fused_fwd(q, k, v, g, P, scale=0.5, S0=S0, C=C, save=save)
+    for saved in {None, save}:
+        got = zeco.gla_fused_bwd(q, k, v, g, dO, P, scale=0.5, S0=None if saved is not None else S0, dS_T=dS_T, C=C, saved=saved)
+        torch.cuda.synchronize()
+        for nm, x, r in zip(("dq", "dk", "dv", "dg"), got[:4], ref[:3] + (ref_dg,)):
+            assert rel_err_bh(host(x), r, (0, 2)) <= tol, nm
+        assert rel_err_bh(host(got[4]), ref[4], (0, 1)) <= tol, "dS0"
+
+
+@pytest.mark.parametrize("lengths,lead,H,dk,dv,io,gate,C", [((3001, 64, 2113, 700, 3629), 37, 16, 64, 64, "bf16", "f32", 64),
+                                                           ((2500, 64, 2337), 5, 64, 64, 64, "f32", "f32", 16)])
+def test_one_call_backward_over_a_table_with_checkpoints(lengths, lead, H, dk, dv, io, gate, C):
+    """The same over a table of unequal segments: the checkpoints a piece has, and their places, come from the device."""
+    print("case", lengths, lead, H, dk, dv, io, gate, C, flush=True)
+    tol, T = TOL[io], lead + sum(lengths) + 11
+    inp = synth.make_inputs(1, T, H, dk, dv, seed=len(lengths), io=io, g="f32", device="cuda", gate_div=64.0)
+    q, k, v, g = (inp[n] for n in "qkvg")
+    a, e = lead, lead + sum(lengths)
+    run = [x[:, a:e] for x in (q, v, g)]
+    n, ck = checkpoints_per_piece(*run, 1, C)     # the run's pieces: the table's calls cut it by the same estimate
+    assert ck >= 1 and (sum(lengths) // 64) % n
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    dO = torch.randn(v.shape, generator=gen, device="cuda").to(v.dtype)
+    S0 = torch.randn(1, H, dk, dv, device="cuda", generator=gen) * 0.3
+    seg = torch.tensor([lead] + [lead + int(x) for x in np.cumsum(lengths)], dtype=torch.int64, device="cuda")
+    ref = oracle.gla_recurrent_bwd(*(np.ascontiguousarray(host(x)[:, a:e]) for x in (q, k, v, g, dO)), 0.5, host(S0))
+    got = zeco.gla_fused_bwd_varlen(q, k, v, g, dO, seg, max(lengths), scale=0.5, C=C, S0=S0)
+    torch.cuda.synchronize()
+    for nm, x, r in zip(("dq", "dk", "dv", "dg"), got, ref):
+        assert rel_err_bh(host(x)[:, a:e], r, (0, 2)) <= tol, nm
+    assert rel_err_bh(host(got[4]), ref[4], (0, 1)) <= tol

@@ -166,8 +166,8 @@ BWD_CASES = [
     ("rb_100", 1, 4, 2, 100, 128, 128, "f32"),            # d_v split in the dV pass; chunks of 36 + 64
     ("rb_65", 1, 2, 3, 65, 128, 128, "f32"),              # one token in the short chunk
     ("rb_whole_127", 2, 16, 5, 127, 128, 128, "f32"),     # 160 streams
-    ("rb_1000", 1, 2, 2, 1000, 128, 128, "bf16"),         # fused call: 2 pieces of 500 tokens per segment
-    ("rb_1046", 1, 1, 2, 1046, 64, 64, "f32"),            # 1046 = 2 x 523: no divisor gives pieces of 64..512 tokens, left whole
+    ("rb_1000", 1, 2, 2, 1000, 128, 128, "bf16"),         # 31 chunks and 16 tokens over both segments
+    ("rb_1046", 1, 1, 2, 1046, 64, 64, "f32"),            # pieces of one chunk, the first with 44 tokens on top
     ("rb_dk64_dv128_200", 1, 2, 2, 200, 64, 128, "f32"),
     ("rb_dk128_dv64_129", 1, 2, 2, 129, 128, 64, "bf16"),
 ]
