@@ -190,7 +190,7 @@ __global__ __launch_bounds__(256) void apply_init_bf16_kernel(ApplyParams p) {
     const long long T = p.T;                                     // tokens per batch entry
     int n_chunks = p.n_chunks, pad = p.pad;
     const int c0 = tb * (p.tokens_per_wg / 64);                  // this workgroup's first block
-    if (__builtin_expect(p.seg_start != nullptr, 0)) {
+    if (p.seg_start) {
         // segments of unequal length: bounds from the table; the grid is sized for the longest segment allowed,
         // so workgroups past this segment's end leave, and so do those of a segment that cannot be taken
         tok0 = p.seg_start[seg];
@@ -200,7 +200,7 @@ __global__ __launch_bounds__(256) void apply_init_bf16_kernel(ApplyParams p) {
         pad = 64 * n_chunks - (int)len;
         if (c0 >= n_chunks) return;
     }
-    if (__builtin_expect(p.cut.n != 0, 0)) {   // (the grid is sized for the longest piece)
+    if (p.cut.n) {   // (the grid is sized for the longest piece)
         long long len;
         piece_range(p.cut, seg, p.P, tok0, len);
         n_chunks = (int)((len + 63) >> 6);
@@ -307,7 +307,7 @@ __global__ __launch_bounds__(256) void apply_init_cd_bf16_kernel(ApplyParams p) 
     long long tok0 = (long long)seg * p.L;                       // the segment's first token
     int n_chunks = p.n_chunks, pad = p.pad;
     const int c0 = tb * (p.tokens_per_wg / 64);                  // this workgroup's first block (= chunk)
-    if (__builtin_expect(p.cut.n != 0, 0)) {   // (the grid is sized for the longest piece)
+    if (p.cut.n) {   // (the grid is sized for the longest piece)
         long long len;
         piece_range(p.cut, seg, p.P, tok0, len);
         n_chunks = (int)((len + 63) >> 6);
@@ -416,7 +416,7 @@ __global__ __launch_bounds__(DV * 4) void apply_init_f32_kernel(ApplyParams p) {
     const long long T = p.T;                                     // tokens per batch entry
     int n_chunks = p.n_chunks, pad = p.pad;
     const int c0 = tb * (p.tokens_per_wg / 64);                  // this workgroup's first block
-    if (__builtin_expect(p.seg_start != nullptr, 0)) {   // segments of unequal length, as in the bf16 kernel
+    if (p.seg_start) {   // segments of unequal length, as in the bf16 kernel
         tok0 = p.seg_start[seg];
         const long long len = p.seg_start[seg + 1] - tok0;
         if (tok0 < 0 || len < 64 || len > p.L || tok0 > T - len) return;   // (in this order: no sum can overflow)

@@ -166,7 +166,7 @@ __global__ __launch_bounds__(DK * 4) void gla_bwd_qk_kernel(BwdQKParams p) {
     const int b = sidx % p.B, seg = sidx / p.B;
     long long tok0 = (long long)seg * p.L;   // first token
     const long long T = p.T;                 // tokens per batch entry
-    if (__builtin_expect(p.seg_start != nullptr, 0)) {
+    if (p.seg_start) {
         // segments of unequal length: this one's bounds from the table; a segment that cannot be taken (under
         // 64 tokens, over the bound L, outside the tensor) is left alone: the whole workgroup leaves
         long long bound = p.L;
@@ -180,7 +180,7 @@ __global__ __launch_bounds__(DK * 4) void gla_bwd_qk_kernel(BwdQKParams p) {
         N = (int)((len + 63) >> 6);
         pad = 64 * N - (int)len;
     }
-    if (__builtin_expect(p.cut.n != 0, 0)) {
+    if (p.cut.n) {
         long long len;
         piece_range(p.cut, seg, p.P, tok0, len);
         N = (int)((len + 63) >> 6);

@@ -157,7 +157,7 @@ __global__ __launch_bounds__(chunk_threads(DK, DV, GM, MODE)) void gla_chunk_bf1
     constexpr bool REV = MODE == kDState || MODE == kDV;          // chunks and tokens in reverse
     constexpr bool NOQ = MODE == kStates || MODE == kDState;      // only the state is computed
     constexpr bool OUT = MODE == kOutput || MODE == kOutputRun;
-    constexpr bool FROM_INIT = OUT || MODE == kDV || MODE == kLocalInit;   // start from S_init (no state emitted, but see kOutput)
+    constexpr bool FROM_INIT = OUT || MODE == kDV || MODE == kLocalInit;   // start from S_init (no state emitted, but see kOutputRun)
     constexpr bool EMIT_G = MODE == kLocal || MODE == kLocalInit;  // per-token cumulative log decay
     constexpr float SGN = REV ? -1.f : 1.f;                       // sign of the decay exponents
     constexpr float kLog2e = 1.4426950408889634f;
@@ -198,7 +198,7 @@ __global__ __launch_bounds__(chunk_threads(DK, DV, GM, MODE)) void gla_chunk_bf1
     long long tok0 = (long long)seg * p.L;   // first token
     const long long T = p.T;                 // tokens per batch entry
     if constexpr (MODE != kLocalInit && MODE != kLocalCD) {
-        if (__builtin_expect(p.seg_start != nullptr, 0)) {
+        if (p.seg_start) {
             // segments of unequal length: this one's bounds from the table.  A segment the kernel cannot take
             // (under 64 tokens, over the bound L, outside the tensor) is left alone: the whole workgroup leaves.
             long long bound = p.L;
@@ -213,7 +213,7 @@ __global__ __launch_bounds__(chunk_threads(DK, DV, GM, MODE)) void gla_chunk_bf1
             pad = 64 * N - (int)len;
         }
     }
-    if (__builtin_expect(p.cut.n != 0, 0)) {
+    if (p.cut.n) {
         long long len;
         piece_range(p.cut, seg, p.P, tok0, len);
         N = (int)((len + 63) >> 6);
