@@ -283,8 +283,8 @@ zeco_status zeco_gla_fwd_from_state(const zeco_gla_desc *desc, const void *q, co
                                     void *stream);
 
 /* The whole forward in one call, for all P segments resident on this device.  The library cuts the P * L tokens
- * into pieces of its own (as many as keep the compute units busy, whatever P and L are; a short run stays whole
- * and takes a single launch); the states of those pieces live in the workspace.
+ * into pieces of its own (as many as keep the compute units busy, wherever the segments end; a run that is short, or
+ * whose B * H streams keep them busy by themselves, stays whole and takes a single launch); the states of those pieces live in the workspace.
  *   in   S0 [B,H,d_k,d_v] fp32 or NULL: state entering the first segment
  *   out  o;  S_last [B,H,d_k,d_v] fp32 or NULL: state after the last token
  *   out  S_save: NULL, or zeco_gla_saved_states_bytes(desc) bytes of device memory that receive the
