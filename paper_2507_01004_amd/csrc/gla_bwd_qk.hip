@@ -1,27 +1,49 @@
-// Backward of the chunkwise GLA forward for the two gated operands (App. A.4): dQ and dK, and the
-// gate gradient dG.  bf16 inputs and outputs, bf16 MFMA operands, fp32 accumulation and states.
+// Backward of the chunkwise GLA forward (App. A.4): dQ, and dK, dV and the gate gradient dG.  bf16 inputs and outputs,
+// bf16 MFMA operands, fp32 accumulation and states.
 //
-// Both gradients have the shape of the forward output pass with the operands in other roles.  With
+// The gradients of the two gated operands have the shape of the forward output pass with the operands in other roles.  With
 // Lambda the in-chunk cumulative decay, gamma the chunk decay, S the forward state entering a chunk,
 // dS the state gradient entering it from the later chunks, dA = mask(dO V^T) (shared by both):
 //   dQ_t = Lambda_t   .* [ dO_t S^T                    + sum_{s<=t} dA_ts (K_s / Lambda_s) ]      forward over chunks
 //   dK_s = 1/Lambda_s .* [ V_s ((gamma^T 1) .* dS)^T   + sum_{t>=s} dA_ts (Q_t .* Lambda_t) ]    backward over chunks
-// i.e.  out_r = F_r .* [ X_r W + sum_{r'<=r} (X_r . Y_r') Z~_r' ]  with
-//   dQ: X = dO, Y = V, Z~ = K / Lambda, F = Lambda,     W = S^T,   W <- (W + Y^T Z~) .* gamma (columns)
-//   dK: X = V, Y = dO, Z~ = Q .* Lambda, F = 1/Lambda,  W = dS^T,  W <- gamma .* W first, then W += Y^T Z~
+// i.e.  out_r = F_r .* [ X_r W + sum_{r'<=r} (X_r . Y_r') Z_r' ]  with
+//   dQ: X = dO, Y = V, Z = K / Lambda, F = Lambda,     W = S^T,   W <- (W + Y^T Z) .* gamma (columns)
+//   dK: X = V, Y = dO, Z = Q .* Lambda, F = 1/Lambda,  W = dS^T,  W <- gamma .* W first, then W += Y^T Z
 // (as built, Lambda is counted from HALF the chunk's total log decay and gamma is applied as two factors
 // sqrt(gamma), one before the chunk's products and one after its update: the same products with half the
 // range of exponents)
 // where for dK the chunks are visited last to first and token t of a chunk sits at tile row 63 - t,
-// which turns "t >= s" into the causal mask of the forward pass.  W (d_v x d_k, the transposed state)
-// stays in MFMA accumulators; wave w owns the 16 output channels [16w, 16w+16).  The gated dimension
-// d_k is the OUTPUT dimension here, so the decay acts on the columns of W (one scalar per lane) and
-// the factor F must be applied to the finished tile element by element: the gate pass leaves it in
-// LDS in fp32.
+// which turns "t >= s" into the causal mask of the forward pass.  The gated dimension d_k is the OUTPUT dimension here,
+// so the decay acts on the columns of W (one scalar per lane) and the factor F must be applied to the finished tile
+// element by element: the matrix waves leave the tile in LDS in fp32 and the gate waves, which computed F, multiply it.
 //
-// One workgroup of d_k/16 waves owns a (batch, segment, head) stream; all waves take part in the gate
-// pass and in the matrix products of a chunk, one after the other, on single-buffered LDS tiles; the
-// raw inputs of the next chunk are fetched into registers while the current one is processed.
+// dV needs the same operands as dK and one more product of each kind,
+//   dV_s = U_s ((gamma^T 1) .* dS) + sum_{t>=s} (U_s . Z_t) dO_t      with U = K / Lambda,
+// so the reverse pass computes it as well (it reads q, k, v, dO, g once for both: 3072 bytes per token-head at d = 128
+// with fp32 gates per channel, where a pass for dV alone and one for dK and dG together move 4352).  Its first product
+// contracts over d_k where dK's contracts over d_v, so this pass keeps dS twice, in both orientations.
+//
+// One workgroup owns a (batch, segment, head) stream, split into two kinds of waves that meet at two barriers a chunk:
+//   * four gate waves (VALU, transcendentals, global memory): the gated tiles Z, U of the next chunk, and the rows
+//     of the finished one: factor, dG bookkeeping, stores;
+//   * max(d_k, d_v) / 32 matrix waves: wave w owns 32 columns of W and of the second state; they also fetch X and Y straight
+//     from HBM to LDS, a chunk ahead, which takes neither registers nor LDS write instructions.
+//   phase 1 of chunk n   matrix: scores of the 10 lower 16 x 16 tiles -> LDS, inter-chunk products from the accumulators
+//                        gate: rows of chunk n - 1; sums of the log decays of chunk n + 1; dQ pass: U of chunk n
+//   phase 2 of chunk n   matrix: intra-chunk products; finished tile -> LDS; dV rows -> HBM; states
+//                        gate: dG of chunk n - 1; Z of chunk n + 1, dK pass: U of chunk n + 1; fetch of chunk n + 2
+// Y and Z live through both phases of a chunk and are double buffered; so is X in the dQ pass, where the by-product below
+// needs it in phase 2; in the dK pass X and U are dead after phase 1, in the dQ pass U before it.  151 - 160 KB of LDS at
+// d = 128, one workgroup a compute unit, two waves a SIMD with 256 registers each.
+//
+// What bounds it.  At 256 workgroups with fp32 gates per channel, HBM: dQ pass 1050 -> 960 us, dV 555 and dK 1094 -> one
+// pass of 1210 us for 16 heads x 131072 tokens, 5.2 TB/s of their 11.3 GB (the kernel before, with all waves at the gate pass
+// and then all at the products, took 8.2 - 8.6 us a chunk and pass whatever the bytes; per-head gates, 32768 tokens: dQ 250 -> 175, dV and dK
+// 337 -> 205 us).  On few compute units, what one of them can have in flight: 33 GB/s (64 streams: dQ 4.5, dK and dV 5.7 us
+// a chunk), because its outstanding reads fill the 32 KB of its vector cache.  The chain of the matrix waves is 4.1 us a
+// chunk in the dK pass, 1.9 in the dQ pass (cycle stamps), of which products 1.2; that of the gate waves 3.6 - 4.2.
+// What it took to get there: every wave's loop free of spilled registers, since the wait for a spilled value is also
+// a wait for the fetches issued before it (6.3 -> 8 us a chunk with a dozen spills), and operands read several products ahead.
 //
 // dG (last line of the backward listing of App. A.4): dG_t = sum over later tokens s >= t of
 // (Q_s .* dQ_s - K_s .* dK_s).  Inside one segment this is a reverse cumulative sum; what the later
@@ -31,8 +53,7 @@
 // formed from the fp32 gradients before those are rounded to bf16: summing rounded terms over
 // thousands of tokens is a random walk that reaches several percent of dG.  The dQ pass leaves
 // Q .* dQ (fp32) in the dG array; the dK pass, which walks the tokens from the last to the first
-// anyway, subtracts K .* dK, accumulates and overwrites the array with dG.  Both do this one chunk
-// late, from the fp32 result tile left in LDS, in the gate pass's thread layout (coalesced rows).
+// anyway, subtracts K .* dK, accumulates and overwrites the array with dG.
 //
 // Re-anchoring.  What is left in that running sum is the rounding noise of the bf16 MFMA operands, a random
 // walk that grows with the square root of the tokens summed (about 1 % of max|dG| after 512 tokens, 4 % after
@@ -48,103 +69,143 @@
 // state entering it is  dS_loc = scale * sum_t (Q_t .* exp(G_t))^T dO_t  with G_t the log decay from
 // the segment's first token through t: the first loop of the backward listing run from dS = 0.  The
 // listing walks the chunks backwards; the sum itself has no order, so the dQ pass, which reads q, g
-// and dO anyway, accumulates it in a second set of accumulators (transposed like W) from two more
-// tiles, dO^T and (Q .* exp(G))^T, and the separate pass over q, g, dO is not needed.
+// and dO anyway, accumulates it in a second set of accumulators (transposed like W) from U = Q .* exp(G),
+// and the separate pass over q, g, dO is not needed.
 #include "zeco_device.h"
 #include "zeco_internal.h"
 
 namespace zeco {
 
-template <int DK, int DV, bool EMIT = false> struct QKCfg {
-    static constexpr int NW = DK / 16;             // waves, 16 output channels each
-    static constexpr int NT = 64 * NW;
-    static constexpr int NIT = DV / 16;            // row tiles of W per wave
-    // gate pass over the gated operand: 4 channels x TPT consecutive tokens per thread
-    static constexpr int CQ = DK / 4;
-    static constexpr int GW = 64 / CQ;             // token groups inside one wave
-    static constexpr int TG = NT / CQ;             // token groups
-    static constexpr int TPT = 64 / TG;
-    // copy pass over X and Y: 4 channels x TPTV consecutive tokens per thread
-    static constexpr int VQ = DV / 4;
-    static constexpr int TPTV = 64 / (NT / VQ);
-    // LDS (bytes)
-    static constexpr int XS = DV * 2 + 16;         // row stride of Xs, Ys (token-major)
-    static constexpr int TS = 64 * 2 + 16;         // row stride of Yt, Zt, Ps (64 tokens per row)
-    static constexpr int FS = DK * 4 + 16;         // row stride of Fs (fp32)
-    static constexpr int kOffX = 0;
-    static constexpr int kOffY = kOffX + 64 * XS;
-    static constexpr int kOffYT = kOffY + 64 * XS;
-    static constexpr int kOffZT = kOffYT + DV * TS;
-    static constexpr int kOffP = kOffZT + DK * TS;
-    static constexpr int kOffF = kOffP + 64 * TS;
-    static constexpr int kOffTot = kOffF + 64 * FS;
-    static constexpr int kOffGam = kOffTot + NW * DK * 4;
-    static constexpr int kOffTot2 = kOffGam + DK * 4;        // [wave][channel] sums of the dG terms
-    static constexpr int kOffCarry = kOffTot2 + NW * DK * 4; // [channel] dG contribution of later segments
-    static constexpr int kOffAnchor = kOffCarry + DK * 4;    // [channel] exact dG contribution at the last checkpoint passed
-    static constexpr int kOffXT = kOffAnchor + DK * 4;       // EMIT: X^T (channel-major) and (Q .* exp(G))^T
-    static constexpr int kOffQT = kOffXT + (EMIT ? DV * TS : 0);
-    static constexpr int kBytes = kOffQT + (EMIT ? DK * TS : 0);
+// waves of a workgroup: four gate waves, d_k / 4 channels each, and matrix waves, 32 state columns each
+constexpr int bwd_matrix_waves(int dk, int dv) { return (dk > dv ? dk : dv) / 32; }
+constexpr int bwd_threads(int dk, int dv) { return 64 * (4 + bwd_matrix_waves(dk, dv)); }
 
-    // LDS position of contraction channel j inside an Xs / Ys row.  A lane of a 16x16 accumulator
-    // tile owns rows 4 kg .. 4 kg + 3; the rows it owns in two adjacent tiles of W serve as its eight
-    // k-slots of the 16x16x32 MFMA, so channel 16 q + 4 kg + m of a block of 32 sits at 8 kg + 4 q + m.
-    __device__ static __forceinline__ constexpr int pos_of_channel(int j) {
-        const int jl = j % 32;
-        return (j - jl) + 8 * ((jl / 4) % 4) + 4 * (jl / 16) + (jl % 4);
-    }
+template <int DK, int DV, bool REV> struct BwdCfg {
+    static constexpr int NWG = 4;
+    static constexpr int NWM = bwd_matrix_waves(DK, DV);
+    static constexpr int NT = bwd_threads(DK, DV);
+    static constexpr int CQ = DK / 4;                        // gate pass: lanes of a token, 4 channels each ..
+    static constexpr int GW = 64 / CQ;                       // .. token groups inside a wave ..
+    static constexpr int TPT = 64 / (NWG * GW);              // .. of this many consecutive tokens
+    // Tiles X, Y, Z, U: token-major, unpadded, the 16-byte pieces of row r swapped around by swizzle(r)
+    static constexpr int PPR = DV / 8;                       // pieces of a row of X, Y
+    static constexpr int RPI = 64 / PPR;                     // rows of X, Y that one instruction of a wave fetches
+    static constexpr int NXY = 64 / RPI / NWM;               // such instructions per tile and wave
+    static constexpr int XS = DV * 2, ZS = DK * 2;           // row strides of X, Y and of Z, U (bytes)
+    static constexpr int PS = 64 * 2 + 16;                   // row stride of the score tiles
+    static constexpr int OS = DK * 4 + 16;                   // row stride of the finished tile (fp32)
+    static constexpr int XB = 64 * XS, ZB = 64 * ZS;
+    static constexpr int kOffX = 0;
+    static constexpr int kOffY = kOffX + (REV ? 1 : 2) * XB;
+    static constexpr int kOffZ = kOffY + 2 * XB;
+    static constexpr int kOffU = kOffZ + 2 * ZB;
+    static constexpr int kOffP = kOffU + ZB;
+    static constexpr int kOffP2 = kOffP + 64 * PS;
+    static constexpr int kOffO = kOffP2 + (REV ? 64 * PS : 0);
+    static constexpr int kOffGam = kOffO + 64 * OS;          // [2][channel] e^(total / 2) of a chunk
+    static constexpr int kOffCarry = kOffGam + 2 * DK * 4;   // [channel] dG contribution of later segments
+    static constexpr int kOffAnchor = kOffCarry + DK * 4;    // [channel] exact dG contribution at the last checkpoint passed
+    static constexpr int kOffSum = kOffAnchor + DK * 4;      // [token] channel sums (per-head gates)
+    static constexpr int kOffTot = kOffSum + 64 * 4;         // [gate wave][channel] sums of the log decays
+    static constexpr int kOffTot2 = kOffTot + NWG * DK * 4;  // [gate wave][channel] sums of the dG terms
+    static constexpr int kBytes = kOffTot2 + (REV ? NWG * DK * 4 : 0);
+    static_assert(kBytes <= 160 * 1024, "LDS of a compute unit");
 };
+
+// Where piece c of row r lies: at c ^ swizzle(r).  Sixteen consecutive rows then have the same piece on 64 different banks
+// (16-byte reads: a lane per row), and so have four consecutive rows the same pair of pieces (transposing reads), without
+// padding, which a fetch straight to LDS could not leave.
+template <int D> __device__ __forceinline__ constexpr int swizzle(int r) {
+    return D == 128 ? ((r & 3) << 2) | ((r >> 2) & 3) : (((r >> 1) & 1) << 2) | ((r >> 2) & 3);
+}
+// 16 bytes a lane from `base` + `off` (bytes) straight to LDS, to `at` + 16 * lane.  The compiler does not see these
+// loads: lds_fetch_wait before the barrier that publishes them.
+__device__ __forceinline__ void lds_fetch(const unsigned char *base, unsigned off, unsigned at) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(at), "v"(off), "s"(base) : "memory");
+}
+__device__ __forceinline__ void lds_fetch_wait() { asm volatile("s_waitcnt vmcnt(0)" : : : "memory"); }
+
+// Keeps what is derived from x inside the loop: hoisted out of it, the dozens of LDS addresses that differ from a few by an
+// exclusive or would take registers that are not there.
+__device__ __forceinline__ void keep_in_loop(unsigned &x) { asm volatile("" : "+v"(x)); }
+
+// A chain of N matrix products, each with one operand `rd(s)` from LDS, kept D reads ahead of the products `mm(s, operand)`.
+// With nothing but its own instructions to hide an LDS read of some 130 cycles behind, a matrix wave has to issue it four
+// products early; left to itself the compiler, short of registers, waits for every read right after issuing it (scores and
+// products of a chunk of the dK pass, d = 128, alone on the chip: 6.3 us).
+template <int N, int D, class R, class F> __device__ __forceinline__ void pipelined(R rd, F mm) {
+    decltype(rd(0)) f[D];
+#pragma unroll
+    for (int s = 0; s < D && s < N; ++s) f[s] = rd(s);
+#pragma unroll
+    for (int s = 0; s < N; ++s) {
+        __builtin_amdgcn_sched_barrier(0x6);   // (VALU and SALU instructions may pass, matrix products and reads may not)
+        mm(s, f[s % D]);
+        if (s + D < N) f[s % D] = rd(s + D);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+}
+struct FragPair { bf16x8 a, b; };
+
+// Sum over the N lanes (16 or 32, aligned) that share a token, in all of them.
+template <int N> __device__ __forceinline__ float lane_sum(float x) {
+    auto add = [&](auto ctrl) __attribute__((always_inline)) {
+        x += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), decltype(ctrl)::value, 0xf, 0xf, true));
+    };
+    add(std::integral_constant<int, 0xb1>{});    // lane ^ 1 (quad_perm)
+    add(std::integral_constant<int, 0x4e>{});    // lane ^ 2 (quad_perm)
+    add(std::integral_constant<int, 0x141>{});   // the other quad of eight lanes (row_half_mirror)
+    add(std::integral_constant<int, 0x140>{});   // the other eight of sixteen (row_mirror)
+    if constexpr (N == 32)   // lane ^ 16
+        x += __builtin_bit_cast(float, __builtin_amdgcn_ds_swizzle(__builtin_bit_cast(int, x), (16 << 10) | 0x1f));
+    return x;
+}
 
 constexpr int kAnchor = 8;   // chunks between two checkpoints of the forward state (512 tokens)
 
-__device__ __forceinline__ bf16x8 pack2x4(f32x4 a, f32x4 b) {
-    u32x4 w = {pack_bf16(a[0], a[1]), pack_bf16(a[2], a[3]), pack_bf16(b[0], b[1]),
-               pack_bf16(b[2], b[3])};
+__device__ __forceinline__ bf16x8 pack8_bwd(const f32x16 &a, int base) {
+    u32x4 w = {pack_bf16(a[base + 0], a[base + 1]), pack_bf16(a[base + 2], a[base + 3]),
+               pack_bf16(a[base + 4], a[base + 5]), pack_bf16(a[base + 6], a[base + 7])};
     return __builtin_bit_cast(bf16x8, w);
 }
 
-// REV = false: dQ (x = dO, y = v, z = k, W_init = forward states; the query scale multiplies the
-// output).  REV = true: dK (x = v, y = dO, z = q, W_init = state gradients entering each segment's
+// REV = false: dQ (x = dO, y = v, z = k, z2 = q, W_init = forward states; the query scale multiplies the
+// output).  REV = true: dK, dV, dG (x = v, y = dO, z = q, z2 = k, W_init = state gradients entering each segment's
 // final state; the query scale rides on Q .* Lambda, so that the running dS is the true gradient).
 // EMIT (dQ pass only): also accumulate the segment's state gradient dS_loc and emit it (and, when asked,
 // the segment's total log decay).
-// NS > 1 (per-channel gates): NS sibling workgroups share a stream, each with DK of its NS * DK channels - columns of W,
-// of the outputs and of everything gated; X, Y and the scores, which contract over d_v, each of them has whole.
-// Taken with at most 128 streams, half as many as compute units: 64 streams of 8192 tokens, d = 128: dK 769 -> 627 us,
-// dQ 681 -> 581 us; from 129 streams on one workgroup a stream leaves no compute unit idle for a sibling.
-template <int DK, int DV, int NS, bool REV, int GM, bool EMIT>
-__global__ __launch_bounds__(DK * 4) void gla_bwd_qk_kernel(BwdQKParams p) {
+// NT: the rows that the gate waves read and write carry the non-temporal hint (see streams_past_caches).
+template <int DK, int DV, bool REV, int GM, bool EMIT, bool NT_>
+__global__ __launch_bounds__(bwd_threads(DK, DV)) void gla_bwd_bf16_kernel(BwdQKParams p) {
     static_assert(!(REV && EMIT), "the state gradient is a by-product of the forward-direction pass");
-    static_assert(NS == 1 || GM != kGateHead, "one decay per head sums over all channels");
-    constexpr int DKF = DK * NS;
-    typedef QKCfg<DK, DV, EMIT> Cfg;
-    typedef Mma<16> M;
+    typedef BwdCfg<DK, DV, REV> Cfg;
+    typedef Mma<32> M;
     typedef GateVal<GM> GV;
-    constexpr int XS = Cfg::XS, TS = Cfg::TS, FS = Cfg::FS, NW = Cfg::NW, NT = Cfg::NT;
-    constexpr int TPT = Cfg::TPT, TPTV = Cfg::TPTV, CQ = Cfg::CQ, GW = Cfg::GW;
+    constexpr int XS = Cfg::XS, ZS = Cfg::ZS, PS = Cfg::PS, OS = Cfg::OS, NWM = Cfg::NWM, NWG = Cfg::NWG, NT = Cfg::NT;
+    constexpr int TPT = Cfg::TPT, CQ = Cfg::CQ, GW = Cfg::GW;
     constexpr int GB = GM == kGateBF16 ? 2 : 4;
     constexpr bool GH = GM == kGateHead;
+    constexpr bool HAS_U = REV || EMIT;
+    constexpr int NG = GH ? 1 : 4;           // decays of a thread's four channels
     constexpr float kLog2e = 1.4426950408889634f;
-    constexpr float SZ = REV ? 1.f : -1.f;   // exponent sign of the operand Z~; the factor F takes the other
+    constexpr float SZ = REV ? 1.f : -1.f;   // exponent sign of the operand Z; the factor F takes the other
     extern __shared__ __align__(16) unsigned char lds[];
-    unsigned char *Xs = lds + Cfg::kOffX, *Ys = lds + Cfg::kOffY, *Yt = lds + Cfg::kOffYT;
-    unsigned char *Zt = lds + Cfg::kOffZT, *Ps = lds + Cfg::kOffP, *Fs = lds + Cfg::kOffF;
-    float *wtot = reinterpret_cast<float *>(lds + Cfg::kOffTot);   // [wave][channel] gate sums
-    float *gam = reinterpret_cast<float *>(lds + Cfg::kOffGam);    // e^(total / 2) of the chunk [channel]
-    float *wtot2 = reinterpret_cast<float *>(lds + Cfg::kOffTot2);
+    unsigned char *Ps = lds + Cfg::kOffP, *P2s = lds + Cfg::kOffP2, *Os = lds + Cfg::kOffO;
+    float *gam = reinterpret_cast<float *>(lds + Cfg::kOffGam);
     float *carry0 = reinterpret_cast<float *>(lds + Cfg::kOffCarry);
     float *anchor = reinterpret_cast<float *>(lds + Cfg::kOffAnchor);
-    unsigned char *Xt = lds + Cfg::kOffXT, *Qt = lds + Cfg::kOffQT;
+    float *hsum = reinterpret_cast<float *>(lds + Cfg::kOffSum);
+    float *wtot = reinterpret_cast<float *>(lds + Cfg::kOffTot);
+    float *wtot2 = reinterpret_cast<float *>(lds + Cfg::kOffTot2);
 
     const int tid = threadIdx.x, lane = tid & 63;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int l16 = lane & 15, kg = lane >> 4;
+    const int pw = __builtin_amdgcn_readfirstlane(tid >> 6);
     int N = p.n_chunks, pad = p.pad;   // (per segment when the segments differ in length, see below)
     auto chunk_of = [&](int m) { return REV ? N - 1 - m : m; };
     auto pos_of = [](int t) { return REV ? 63 - t : t; };
     // When L is no multiple of 64 the chunk processed FIRST is the short one, 64 - pad tokens: the segment's
     // first tokens in the dQ pass, its last ones in the dK pass.  It is loaded as a full window inside the
-    // segment, [0, 64) or [L - 64, L); the gated operand, the log decays and the dG terms of the window's
+    // segment, [0, 64) or [L - 64, L); the operands, the log decays and the dG terms of the window's
     // surplus rows are taken as zero - they then touch no state, no decay and no other row - and their
     // gradient rows are not stored.
     // (With checkpoints the dQ pass cuts like the dK pass: the short chunk is the segment's last one.)
@@ -155,11 +216,8 @@ __global__ __launch_bounds__(DK * 4) void gla_bwd_qk_kernel(BwdQKParams p) {
     auto dead = [&](int t) { return short_last ? t < pad : t >= 64 - pad; };
     auto is_short = [&](int c) { return c == (short_last ? N - 1 : 0); };   // chunk c is the short one (if any is)
 
-    // workgroup -> stream, dealt so that consecutive streams land on different XCDs
-    // (siblings in consecutive slots of one XCD, whose L2 they share for X and Y)
-    const int slice = NS == 1 ? 0 : (int)(blockIdx.x >> 3) % NS;
-    int sidx = NS == 1 ? (int)blockIdx.x : (int)(blockIdx.x >> 3) / NS * 8 + (int)(blockIdx.x & 7);
-    if (NS > 1 && sidx >= p.B * p.P * p.H) return;
+    // consecutive streams land on different XCDs (workgroup ids are dealt round-robin)
+    int sidx = (int)blockIdx.x;
     const size_t sbh = sidx;                        // (seg * B + b) * H + h
     const int h = sidx % p.H;
     sidx /= p.H;
@@ -187,531 +245,806 @@ __global__ __launch_bounds__(DK * 4) void gla_bwd_qk_kernel(BwdQKParams p) {
         pad = (int)(64ll * N - len);
     }
     const int n_ck = p.plan ? (int)p.seg_start[p.plan + 3] : p.n_ck;
-    const long long kbase = b * p.sb + tok0 * p.st + h * p.sh + slice * DK;
+    const long long kbase = b * p.sb + tok0 * p.st + h * p.sh;
     const long long vbase = b * p.vb + tok0 * p.vt + h * p.vh;
-    const unsigned char *xb = (const unsigned char *)p.x + vbase * 2;
-    const unsigned char *yb = (const unsigned char *)p.y + vbase * 2;
-    const unsigned char *zb = (const unsigned char *)p.z + kbase * 2;
-    const long long hbase = ((long long)b * T + tok0) * p.H + h;   // per-head arrays [B,T,H]
-    const unsigned char *gb = (const unsigned char *)p.g + (GH ? hbase : kbase) * GB;
-    const long long gst = GH ? (long long)p.H : p.st;                       // gate elements between tokens
-    const unsigned char *z2b = (const unsigned char *)p.z2 + kbase * 2;
-    unsigned char *ob = (unsigned char *)p.out + kbase * 2;
-    const long long st = p.st, vt = p.vt;
-    float *dgb = p.dg + hbase * (GH ? 1 : DKF) + slice * DK;   // [B,T,H,d_k] contiguous ([B,T,H] with per-head gates)
-    const long long gcs = (long long)p.H * (GH ? 1 : DKF);
-
-    // gate-pass coordinates (z, g) and copy-pass coordinates (x, y)
-    const int cq = lane % CQ, gl = lane / CQ, tq = w * GW + gl;
-    const int vq = tid % Cfg::VQ, tv = tid / Cfg::VQ;
-    const int xpos = Cfg::pos_of_channel(4 * vq);
-
-    // W^T tile init: Sacc[it][rr] = W[row 16 it + 4 kg + rr][col 16 w + l16] = W_init[col][row]
-    f32x4 Sacc[Cfg::NIT];
-    {
-        const float *Wi = p.W_init + sbh * DKF * DV + (size_t)(slice * DK + w * 16 + l16) * DV + 4 * kg;
-#pragma unroll
-        for (int it = 0; it < Cfg::NIT; ++it) Sacc[it] = *reinterpret_cast<const f32x4 *>(Wi + it * 16);
-    }
-
-    // EMIT: dS_loc^T in the layout of W, and the log decay of the chunks done so far (this thread's channels)
-    f32x4 Dacc[EMIT ? Cfg::NIT : 1];
-    f32x4 gpre = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int it = 0; it < (EMIT ? Cfg::NIT : 1); ++it) Dacc[it] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const unsigned st = (unsigned)p.st, vt = (unsigned)p.vt;
 
     // Score tiles above the diagonal are never computed: zero them once.
-    for (int e = tid; e < 64 * TS / 16; e += NT)
+    for (int e = tid; e < (REV ? 2 : 1) * 64 * PS / 16; e += NT)
         *reinterpret_cast<u32x4 *>(Ps + e * 16) = u32x4{0u, 0u, 0u, 0u};
 
-    // dG carried in from the later segments: c[i] = sum_j dS_end[i][j] S_end[i][j]  (4 threads per row)
-    f32x4 carry = {0.f, 0.f, 0.f, 0.f};
-    if constexpr (REV) {
-        const float *A = p.W_init + (sbh * DKF + slice * DK) * DV;
-        const float *Bm = (seg + 1 < (p.plan ? (int)p.seg_start[p.plan + 1] : p.P)) ? p.S_init + ((sbh + (size_t)p.B * p.H) * DKF + slice * DK) * DV
-                                          : p.S_last + (((size_t)b * p.H + h) * DKF + slice * DK) * DV;
-        const int i = tid >> 2, part = tid & 3;
-        float acc = 0.f;
-        for (int j = part * 4; j < DV; j += 16) {
-            const f32x4 x = *reinterpret_cast<const f32x4 *>(A + (size_t)i * DV + j);
-            const f32x4 y = *reinterpret_cast<const f32x4 *>(Bm + (size_t)i * DV + j);
-            acc += x[0] * y[0] + x[1] * y[1] + x[2] * y[2] + x[3] * y[3];
-        }
-        acc += __shfl_xor(acc, 1, 64);
-        acc += __shfl_xor(acc, 2, 64);
-        if (part == 0) carry0[i] = acc;
-        __syncthreads();
-        carry = *reinterpret_cast<const f32x4 *>(carry0 + 4 * (lane % CQ));
-    }
+    if (pw >= NWM) {
+        // ================================ gate waves ===========================================
+        const int gw = pw - NWM;
+        const int cq = lane % CQ, gl = lane / CQ, tg = gw * GW + gl;
+        const int ch = 4 * cq;             // first of this thread's four channels
+        const long long hbase = ((long long)b * T + tok0) * p.H + h;   // per-head arrays [B,T,H]
+        const unsigned char *zb = (const unsigned char *)p.z + kbase * 2;
+        const unsigned char *z2b = (const unsigned char *)p.z2 + kbase * 2;
+        const unsigned char *gb = (const unsigned char *)p.g + (GH ? hbase : kbase) * GB;
+        unsigned char *ob = (unsigned char *)p.out + kbase * 2;
+        const unsigned gst = GH ? (unsigned)p.H : st;                         // gate elements between tokens
+        float *dgb = p.dg + hbase * (GH ? 1 : DK);   // [B,T,H,d_k] contiguous ([B,T,H] with per-head gates)
+        const long long gcs = (long long)p.H * (GH ? 1 : DK);
+        // per-thread byte offsets of its first token inside a chunk
+        unsigned z_b0 = ((unsigned)(tg * TPT) * st + ch) * 2;
+        unsigned g_b0 = ((unsigned)(tg * TPT) * gst + (GH ? 0 : ch)) * GB;
+        float *dgt = dgb + (long long)(tg * TPT) * gcs + ch;     // (not with per-head gates)
+        auto dg_rows = [&](int c) __attribute__((always_inline)) -> float * {
+            float *r = dgt;
+            asm volatile("" : "+v"(r));   // (keep_in_loop)
+            return r + cstart(c) * gcs;
+        };
 
-    // raw inputs of the chunk worked on next
-    u32x2 rx[TPTV], ry[TPTV], rz[TPT];
-    u32x2 rq[EMIT ? TPT : 1];   // EMIT: q of the chunk worked on next (otherwise q is fetched late, for dG only)
-    typename GV::raw_t rg[TPT];
-    {
-        const long long c0 = cstart(chunk_of(0));
-#pragma unroll
-        for (int u = 0; u < TPT; ++u) {
-            if constexpr (EMIT) rq[u] = *reinterpret_cast<const u32x2 *>(z2b + ((c0 + tq * TPT + u) * st + 4 * cq) * 2);
-            rz[u] = *reinterpret_cast<const u32x2 *>(zb + ((c0 + tq * TPT + u) * st + 4 * cq) * 2);
-            rg[u] = *reinterpret_cast<const typename GV::raw_t *>(gb + ((c0 + tq * TPT + u) * gst + (GH ? 0 : 4 * cq)) * GB);
-        }
-#pragma unroll
-        for (int u = 0; u < TPTV; ++u) {
-            rx[u] = *reinterpret_cast<const u32x2 *>(xb + ((c0 + tv * TPTV + u) * vt + 4 * vq) * 2);
-            ry[u] = *reinterpret_cast<const u32x2 *>(yb + ((c0 + tv * TPTV + u) * vt + 4 * vq) * 2);
-        }
-    }
+        // raw rows of the chunk computed next; each piece is reloaded right after its last use
+        u32x2 rz[TPT], rk[TPT];
+        typename GV::raw_t rg[TPT];
+        auto load = [](auto *ptr) __attribute__((always_inline)) {
+            if constexpr (NT_) return __builtin_nontemporal_load(ptr);
+            else return *ptr;
+        };
+        auto store = [](auto val, auto *ptr) __attribute__((always_inline)) {
+            if constexpr (NT_) __builtin_nontemporal_store(val, ptr);
+            else *ptr = val;
+        };
+        auto load_raw = [&](int u, long long t0) __attribute__((always_inline)) {
+            rz[u] = load(reinterpret_cast<const u32x2 *>(zb + (t0 + u) * st * 2 + z_b0));
+            rk[u] = load(reinterpret_cast<const u32x2 *>(z2b + (t0 + u) * st * 2 + z_b0));
+            rg[u] = load(reinterpret_cast<const typename GV::raw_t *>(gb + (t0 + u) * gst * GB + g_b0));
+        };
+        // factor F and raw z2 of the chunk computed last (1) and of the one before it (0), whose rows are finished next
+        float F0[TPT][NG], F1[TPT][NG];
+        u32x2 k0[TPT], k1[TPT];
+        f32x4 gpre = {0.f, 0.f, 0.f, 0.f};                      // EMIT: log decay of the chunks done so far
+        float epre[NG];                                         // EMIT: scale * decay of the chunks before the one computed last, to its middle
 
-    // sum over the d_k channels of a token: the 4 of this thread, then the CQ lanes that share the token
-    auto channel_sum = [&](f32x4 x) __attribute__((always_inline)) {
-        float tot = (x[0] + x[1]) + (x[2] + x[3]);
+        // (channel and token group for addresses inside the loop, see keep_in_loop)
+        unsigned tgo = tg, cho = ch;
+        auto fresh = [&]() __attribute__((always_inline)) { keep_in_loop(tgo), keep_in_loop(cho), keep_in_loop(z_b0), keep_in_loop(g_b0); };
+        auto tile_at = [&](int u) __attribute__((always_inline)) -> int {
+            const int r = pos_of((int)tgo * TPT + u);
+            return r * ZS + ((((int)cho >> 3) ^ swizzle<DK>(r)) << 4) + 2 * ((int)cho & 4);
+        };
+        auto scaled = [&](u32x2 w, const float *e) __attribute__((always_inline)) {
+            constexpr int A1 = GH ? 0 : 1, A2 = GH ? 0 : 2, A3 = GH ? 0 : 3;
+            return u32x2{pack_bf16(bf16_lo(w[0]) * e[0], bf16_hi(w[0]) * e[A1]), pack_bf16(bf16_lo(w[1]) * e[A2], bf16_hi(w[1]) * e[A3])};
+        };
+        // sums of the log decays of the m-th chunk: this thread's tokens, the wave's earlier ones, the wave's total -> LDS
+        float excl[NG];
+        auto part1 = [&](int m, bool sh) __attribute__((always_inline)) {
+            fresh();
+            float run[NG];
 #pragma unroll
-        for (int d = 1; d < CQ; d <<= 1) tot += __shfl_xor(tot, d, 64);
-        return tot;
-    };
-    // dG bookkeeping of the chunk finished last: raw z2 (q for dQ, k for dK) and, for dK, the Q .* dQ terms
-    u32x2 rz2[TPT];
-    f32x4 rqd[TPT], dterm[TPT];
-    f32x4 later_in_wave = {0.f, 0.f, 0.f, 0.f};
-
-    // first half: the finished chunk's gradient rows go to HBM, and the dG terms are formed from the fp32
-    // result tile in Fs; dQ stores them, dK starts the reverse sums
-    auto dg_first = [&](long long tc, bool first) __attribute__((always_inline)) {
-        float *row = dgb + (tc + tq * TPT) * gcs + (GH ? 0 : 4 * cq);
-        f32x4 run = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int u = TPT - 1; u >= 0; --u) {
-            if (first && dead(tq * TPT + u)) {   // surplus row: nothing stored, no dG term
-                if constexpr (REV) dterm[u] = run;
-                continue;
-            }
-            const f32x4 val = *reinterpret_cast<const f32x4 *>(Fs + pos_of(tq * TPT + u) * FS + 16 * cq);
-            // the gradient itself: 32 lanes write one contiguous row (the accumulator layout of the
-            // products would give 32-byte pieces)
-            __builtin_nontemporal_store(u32x2{pack_bf16(val[0], val[1]), pack_bf16(val[2], val[3])},
-                                        reinterpret_cast<u32x2 *>(ob + ((tc + tq * TPT + u) * st + 4 * cq) * 2));
-            const u32x2 zw = rz2[u];
-            const f32x4 pr = {bf16_lo(zw[0]) * val[0], bf16_hi(zw[0]) * val[1],
-                              bf16_lo(zw[1]) * val[2], bf16_hi(zw[1]) * val[3]};
-            if constexpr (!REV && GH) {
-                const float tot = channel_sum(pr);
-                if (cq == 0) row[u * gcs] = tot;
-            } else if constexpr (!REV) {
-                *reinterpret_cast<f32x4 *>(row + u * gcs) = pr;
-            } else {
-#pragma unroll
-                for (int a = 0; a < 4; ++a) run[a] += rqd[u][a] - pr[a];
-                dterm[u] = run;   // sum over this thread's tokens >= u
-            }
-        }
-        if constexpr (REV) {
-            f32x4 inc = run;   // inclusive suffix scan over the wave's token groups
-#pragma unroll
-            for (int s = 1; s < GW; s <<= 1) {
-#pragma unroll
-                for (int a = 0; a < 4; ++a) {
-                    const float dn = __shfl_down(inc[a], s * CQ, 64);
-                    if (gl + s < GW) inc[a] += dn;
-                }
-            }
-#pragma unroll
-            for (int a = 0; a < 4; ++a) later_in_wave[a] = inc[a] - run[a];
-            if (gl == 0) *reinterpret_cast<f32x4 *>(wtot2 + w * DK + 4 * cq) = inc;
-        }
-    };
-    // second half (dK, after a barrier): add the later waves and the later chunks, store dG
-    auto dg_second = [&](long long tc, bool first, int c) __attribute__((always_inline)) {
-        float *row = dgb + (tc + tq * TPT) * gcs + (GH ? 0 : 4 * cq);
-        // chunk c ends at a checkpoint: what the later tokens contribute is known exactly (left in `anchor`
-        // when the pass crossed that boundary, two iterations ago)
-        if (p.S_ck && (c + 1) % kAnchor == 0 && c + 1 < N) carry = *reinterpret_cast<const f32x4 *>(anchor + 4 * cq);
-        f32x4 later = carry, total = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int a = 0; a < 4; ++a) later[a] += later_in_wave[a];
-#pragma unroll
-        for (int u = 0; u < NW; ++u) {
-            const f32x4 x = *reinterpret_cast<const f32x4 *>(wtot2 + u * DK + 4 * cq);
-            const float sel = (u > w) ? 1.f : 0.f;   // wave-uniform
-#pragma unroll
-            for (int a = 0; a < 4; ++a) {
-                later[a] = __builtin_fmaf(sel, x[a], later[a]);
-                total[a] += x[a];
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < TPT; ++u) {
-            if (first && dead(tq * TPT + u)) continue;
-            f32x4 o;
-#pragma unroll
-            for (int a = 0; a < 4; ++a) o[a] = dterm[u][a] + later[a];
-            if constexpr (GH) {
-                const float tot = channel_sum(o);
-                if (cq == 0) row[u * gcs] = tot;
-            } else {
-                __builtin_nontemporal_store(o, reinterpret_cast<f32x4 *>(row + u * gcs));
-            }
-        }
-#pragma unroll
-        for (int a = 0; a < 4; ++a) carry[a] += total[a];
-    };
-
-    for (int n = 0; n < N; ++n) {
-        const long long t0 = cstart(chunk_of(n));                          // this chunk
-        const long long t1 = cstart(chunk_of((n + 1 < N) ? n + 1 : n));    // chunk fetched meanwhile
-        const long long tp = cstart(chunk_of((n > 0) ? n - 1 : 0));        // chunk finished last
-        const bool first = is_short(chunk_of(n));                          // the short chunk, if there is one
-        if (n > 0) dg_first(tp, is_short(chunk_of(n - 1)));
-        if constexpr (!REV) {
-            // checkpoint: the forward state entering this chunk, for the dK pass to re-anchor dG with
-            if (p.S_ck && n > 0 && n % kAnchor == 0) {
-                float *ck = p.S_ck + (sbh * n_ck + (n / kAnchor - 1)) * DKF * DV + (size_t)(slice * DK + w * 16 + l16) * DV + 4 * kg;
-#pragma unroll
-                for (int it = 0; it < Cfg::NIT; ++it) *reinterpret_cast<f32x4 *>(ck + it * 16) = Sacc[it];
-            }
-        }
-
-        // ---- gate pass, part 1: per-thread cumulative sums of g; X, Y, Y^T -> LDS -----------------
-        f32x4 cs[TPT];
-        f32x4 excl = {0.f, 0.f, 0.f, 0.f};
-        {
-            f32x4 run = {0.f, 0.f, 0.f, 0.f};
+            for (int a = 0; a < NG; ++a) run[a] = 0.f;
 #pragma unroll
             for (int u = 0; u < TPT; ++u) {
-                f32x4 gv = GV::get(rg[u]);
-                if (first && dead(tq * TPT + u)) gv = f32x4{0.f, 0.f, 0.f, 0.f};
-                rg[u] = *reinterpret_cast<const typename GV::raw_t *>(gb + ((t1 + tq * TPT + u) * gst + (GH ? 0 : 4 * cq)) * GB);
+                const f32x4 gv = GV::get(rg[u]);
 #pragma unroll
-                for (int a = 0; a < 4; ++a) run[a] += gv[a];
-                cs[u] = run;
+                for (int a = 0; a < NG; ++a) run[a] += (sh && dead(tg * TPT + u)) ? 0.f : gv[a];
             }
-            f32x4 inc = run;   // inclusive scan of the group sums over the wave's GW token groups
+            f32x4 wave = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int d = 1; d < GW; d <<= 1) {
+            for (int a = 0; a < NG; ++a) {
+                float inc = run[a];
 #pragma unroll
-                for (int a = 0; a < 4; ++a) {
-                    const float up = __shfl_up(inc[a], d * CQ, 64);
-                    if (gl >= d) inc[a] += up;
+                for (int d = 1; d < GW; d <<= 1) {
+                    const float up = __shfl_up(inc, d * CQ, 64);
+                    if (gl >= d) inc += up;
                 }
+                excl[a] = inc - run[a];
+                wave[a] = inc;
             }
-#pragma unroll
-            for (int a = 0; a < 4; ++a) excl[a] = inc[a] - run[a];
-            if (gl == GW - 1) *reinterpret_cast<f32x4 *>(wtot + w * DK + 4 * cq) = inc;
-        }
-        {
-            TokenRun<TPTV> ch[4];
-#pragma unroll
-            for (int u = 0; u < TPTV; ++u) {
-                const int r = pos_of(tv * TPTV + u);
-                *reinterpret_cast<u32x2 *>(Xs + r * XS + xpos * 2) = rx[u];
-                *reinterpret_cast<u32x2 *>(Ys + r * XS + xpos * 2) = ry[u];
+            if (gl == GW - 1) {
+                if constexpr (GH) wtot[gw * DK + (cho >> 2)] = wave[0];   // (the same from every lane of a token)
+                else *reinterpret_cast<f32x4 *>(wtot + gw * DK + cho) = wave;
             }
-            if constexpr (EMIT) {   // X^T, channel-major (forward direction: tokens in order)
-                TokenRun<TPTV> cx[4];
+        };
+        // after a barrier: Z, U, F and gamma of the m-th chunk; raw rows of the next one are fetched
+        auto part2 = [&](int m, bool sh) __attribute__((always_inline)) {
+            fresh();
+            const long long t1 = cstart(chunk_of(m + 1 < N ? m + 1 : N - 1));
+            float run[NG], total[NG], off[NG], mid[NG];
 #pragma unroll
-                for (int m = 0; m < TPTV / 2; ++m) {
-                    cx[0].w[m] = pair_lo(rx[2 * m][0], rx[2 * m + 1][0]);
-                    cx[1].w[m] = pair_hi(rx[2 * m][0], rx[2 * m + 1][0]);
-                    cx[2].w[m] = pair_lo(rx[2 * m][1], rx[2 * m + 1][1]);
-                    cx[3].w[m] = pair_hi(rx[2 * m][1], rx[2 * m + 1][1]);
-                }
+            for (int a = 0; a < NG; ++a) run[a] = excl[a], total[a] = 0.f;
 #pragma unroll
-                for (int a = 0; a < 4; ++a) cx[a].store(Xt + (4 * vq + a) * TS + tv * TPTV * 2);
-            }
+            for (int u = 0; u < NWG; ++u) {
+                f32x4 x;
+                if constexpr (GH) x[0] = wtot[u * DK + (cho >> 2)];
+                else x = *reinterpret_cast<const f32x4 *>(wtot + u * DK + cho);
+                const float sel = (u < gw) ? 1.f : 0.f;   // wave-uniform
 #pragma unroll
-            for (int m = 0; m < TPTV / 2; ++m) {
-                // tokens (2m, 2m+1) of the run share a word; reversed, the run is written back to front
-                const u32x2 a0 = REV ? ry[2 * m + 1] : ry[2 * m], a1 = REV ? ry[2 * m] : ry[2 * m + 1];
-                const int wd = REV ? TPTV / 2 - 1 - m : m;
-                ch[0].w[wd] = pair_lo(a0[0], a1[0]);
-                ch[1].w[wd] = pair_hi(a0[0], a1[0]);
-                ch[2].w[wd] = pair_lo(a0[1], a1[1]);
-                ch[3].w[wd] = pair_hi(a0[1], a1[1]);
-            }
-#pragma unroll
-            for (int u = 0; u < TPTV; ++u) {
-                rx[u] = *reinterpret_cast<const u32x2 *>(xb + ((t1 + tv * TPTV + u) * vt + 4 * vq) * 2);
-                ry[u] = *reinterpret_cast<const u32x2 *>(yb + ((t1 + tv * TPTV + u) * vt + 4 * vq) * 2);
-            }
-            const int c0 = REV ? 64 - (tv + 1) * TPTV : tv * TPTV;
-#pragma unroll
-            for (int a = 0; a < 4; ++a) ch[a].store(Yt + (4 * vq + a) * TS + c0 * 2);
-        }
-        __syncthreads();
-        if constexpr (REV) {
-            if (n > 0) dg_second(tp, is_short(chunk_of(n - 1)), chunk_of(n - 1));
-        }
-
-        // ---- gate pass, part 2: stitch waves; Z~^T and the factor tile -> LDS ----------------------
-        {
-            // The decay factors of Z~ and F are taken relative to half the chunk's total log decay, as in the forward
-            // kernel: no exponent then exceeds |total| / 2.  W is decayed in two equal steps to match: by e^(total/2)
-            // before the chunk's products and again after its update.
-            f32x4 pre = excl, total = {0.f, 0.f, 0.f, 0.f}, mid;
-#pragma unroll
-            for (int u = 0; u < NW; ++u) {
-                const f32x4 x = *reinterpret_cast<const f32x4 *>(wtot + u * DK + 4 * cq);
-                const float sel = (u < w) ? 1.f : 0.f;   // wave-uniform
-#pragma unroll
-                for (int a = 0; a < 4; ++a) {
-                    pre[a] = __builtin_fmaf(sel, x[a], pre[a]);
+                for (int a = 0; a < NG; ++a) {
+                    run[a] = __builtin_fmaf(sel, x[a], run[a]);
                     total[a] += x[a];
                 }
             }
 #pragma unroll
-            for (int a = 0; a < 4; ++a) {
+            for (int a = 0; a < NG; ++a) {
+                // the factors are taken relative to half the chunk's total log decay: no exponent exceeds |total| / 2
                 mid[a] = 0.5f * total[a];
-                pre[a] -= mid[a];
+                off[a] = run[a] - mid[a];
+                run[a] = 0.f;
             }
-            TokenRun<TPT> zt[4];
-            u32x2 zprev = {0u, 0u};
-            TokenRun<TPT> qt[EMIT ? 4 : 1];
-            u32x2 qprev = {0u, 0u};
-            f32x4 epre = {0.f, 0.f, 0.f, 0.f};   // EMIT: scale * decay of the earlier chunks of the segment
             if constexpr (EMIT) {
 #pragma unroll
-                for (int a = 0; a < 4; ++a) epre[a] = __builtin_amdgcn_exp2f((gpre[GH ? 0 : a] + mid[GH ? 0 : a]) * kLog2e) * p.qscale;
+                for (int a = 0; a < NG; ++a) epre[a] = __builtin_amdgcn_exp2f((gpre[a] + mid[a]) * kLog2e) * p.qscale;
             }
 #pragma unroll
             for (int u = 0; u < TPT; ++u) {
-                const int t = tq * TPT + u;
-                f32x4 ez, ef;
-                if constexpr (GH) {   // one decay per token: one pair of exponentials for the four channels
-                    const float y = (cs[u][0] + pre[0]) * kLog2e;
-                    const float z = __builtin_amdgcn_exp2f(SZ * y) * p.zscale, f = __builtin_amdgcn_exp2f(-SZ * y);
-                    ez = f32x4{z, z, z, z};
-                    ef = f32x4{f, f, f, f};
-                } else {
+                float ez[NG], ef[NG];
+                const f32x4 gv = GV::get(rg[u]);
 #pragma unroll
-                    for (int a = 0; a < 4; ++a) {
-                        const float y = (cs[u][a] + pre[a]) * kLog2e;   // in-chunk cumulative log2 decay
-                        ez[a] = __builtin_amdgcn_exp2f(SZ * y) * p.zscale;
-                        ef[a] = __builtin_amdgcn_exp2f(-SZ * y);
-                    }
+                for (int a = 0; a < NG; ++a) {
+                    run[a] += (sh && dead(tg * TPT + u)) ? 0.f : gv[a];
+                    const float y = (run[a] + off[a]) * kLog2e;   // in-chunk cumulative log2 decay
+                    ez[a] = __builtin_amdgcn_exp2f(SZ * y);
+                    if constexpr (REV) ez[a] *= p.zscale;
+                    ef[a] = __builtin_amdgcn_exp2f(-SZ * y);
+                    F0[u][a] = F1[u][a];
+                    F1[u][a] = ef[a];
                 }
-                u32x2 zw = rz[u];
-                if (first && dead(t)) zw = u32x2{0u, 0u};
-                rz[u] = *reinterpret_cast<const u32x2 *>(zb + ((t1 + t) * st + 4 * cq) * 2);
-                const u32x2 zq = {pack_bf16(bf16_lo(zw[0]) * ez[0], bf16_hi(zw[0]) * ez[1]),
-                                  pack_bf16(bf16_lo(zw[1]) * ez[2], bf16_hi(zw[1]) * ez[3])};
-                *reinterpret_cast<f32x4 *>(Fs + pos_of(t) * FS + 16 * cq) = ef;
-                if constexpr (EMIT) {   // (Q .* exp(G))^T: F = Lambda here, times the earlier chunks' decay
-                    u32x2 qw = rq[u];
-                    if (first && dead(t)) qw = u32x2{0u, 0u};
-                    rq[u] = *reinterpret_cast<const u32x2 *>(z2b + ((t1 + t) * st + 4 * cq) * 2);
-                    rz2[u] = qw;   // kept for this chunk's dG terms
-                    const u32x2 qh = {pack_bf16(bf16_lo(qw[0]) * ef[0] * epre[0], bf16_hi(qw[0]) * ef[1] * epre[1]),
-                                      pack_bf16(bf16_lo(qw[1]) * ef[2] * epre[2], bf16_hi(qw[1]) * ef[3] * epre[3])};
-                    if (u % 2 == 1) {
-                        qt[0].w[u / 2] = pair_lo(qprev[0], qh[0]);
-                        qt[1].w[u / 2] = pair_hi(qprev[0], qh[0]);
-                        qt[2].w[u / 2] = pair_lo(qprev[1], qh[1]);
-                        qt[3].w[u / 2] = pair_hi(qprev[1], qh[1]);
-                    }
-                    qprev = qh;
-                }
-                if (u % 2 == 1) {
-                    const u32x2 a0 = REV ? zq : zprev, a1 = REV ? zprev : zq;
-                    const int wd = REV ? (TPT - 1 - u) / 2 : u / 2;
-                    zt[0].w[wd] = pair_lo(a0[0], a1[0]);
-                    zt[1].w[wd] = pair_hi(a0[0], a1[0]);
-                    zt[2].w[wd] = pair_lo(a0[1], a1[1]);
-                    zt[3].w[wd] = pair_hi(a0[1], a1[1]);
-                }
-                zprev = zq;
+                u32x2 zw = rz[u], kw = rk[u];
+                if (sh && dead(tg * TPT + u)) zw = kw = u32x2{0u, 0u};
+                load_raw(u, t1);
+                k0[u] = k1[u];
+                k1[u] = kw;
+                *reinterpret_cast<u32x2 *>(lds + Cfg::kOffZ + (m & 1) * Cfg::ZB + tile_at(u)) = scaled(zw, ez);
+                if constexpr (REV) *reinterpret_cast<u32x2 *>(lds + Cfg::kOffU + tile_at(u)) = scaled(kw, ef);
             }
-            const int c0 = REV ? 64 - (tq + 1) * TPT : tq * TPT;
-#pragma unroll
-            for (int a = 0; a < 4; ++a) zt[a].store(Zt + (4 * cq + a) * TS + c0 * 2);
-            if constexpr (EMIT) {
-#pragma unroll
-                for (int a = 0; a < 4; ++a) {
-                    qt[a].store(Qt + (4 * cq + a) * TS + c0 * 2);
-                    gpre[a] += total[a];
-                }
-            }
-            if (tq == 0) {
+            if (tg == 0) {
                 f32x4 gh;
 #pragma unroll
-                for (int a = 0; a < 4; ++a) gh[a] = __builtin_amdgcn_exp2f(mid[a] * kLog2e);
-                *reinterpret_cast<f32x4 *>(gam + 4 * cq) = gh;
+                for (int a = 0; a < 4; ++a) gh[a] = __builtin_amdgcn_exp2f(mid[GH ? 0 : a] * kLog2e);
+                *reinterpret_cast<f32x4 *>(gam + (m & 1) * DK + cho) = gh;
             }
-        }
-        __syncthreads();
+            if constexpr (EMIT) {
+#pragma unroll
+                for (int a = 0; a < NG; ++a) gpre[a] += total[a];
+            }
+        };
+        // EMIT: U of the chunk computed last, in its own phase 1 (U is single)
+        auto put_u = [&]() __attribute__((always_inline)) {
+            if constexpr (EMIT) {
+                fresh();
+#pragma unroll
+                for (int u = 0; u < TPT; ++u) {
+                    float e[NG];
+#pragma unroll
+                    for (int a = 0; a < NG; ++a) e[a] = F1[u][a] * epre[a];
+                    *reinterpret_cast<u32x2 *>(lds + Cfg::kOffU + tile_at(u)) = scaled(k1[u], e);
+                }
+            }
+        };
 
-        // operands of this chunk's dG terms, consumed one iteration later
+        // dK pass: the Q .* dQ terms of the chunk whose rows are finished next
+        f32x4 rqd[REV && !GH ? TPT : 1];   // (then the chunk's dG terms, until the sums of the other waves are there)
+        f32x4 later_in_wave = {0.f, 0.f, 0.f, 0.f};
+        float hqd = 0.f, hcarry = 0.f;   // per-head gates: lane = token (every gate wave does the sums, the first one stores)
+        f32x4 carry = {0.f, 0.f, 0.f, 0.f};
+        auto fetch_qd = [&](int m) __attribute__((always_inline)) {
+            if constexpr (REV && !GH) {
+                const float *row = dg_rows(chunk_of(m));
+#pragma unroll
+                for (int u = 0; u < TPT; ++u) rqd[u] = load(reinterpret_cast<const f32x4 *>(row + u * gcs));
+            }
+        };
+        // rows of the m-th chunk, from the fp32 tile the matrix waves left: factor, store, dG terms
+        // (sh: it is the short chunk; the literal false of the loop leaves no branch around the stores, at whose joins the
+        // compiler would wait for the loads in flight)
+        auto finish = [&](int m, bool sh) __attribute__((always_inline)) {
+            const int c = chunk_of(m);
+            const long long t0 = cstart(c);
+            unsigned char *orow = ob + t0 * st * 2;
+            float *drow = REV || GH ? nullptr : dg_rows(c);
+            fresh();
+            f32x4 run = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int u = TPT - 1; u >= 0; --u) {
+                const int t = tg * TPT + u;
+                f32x4 val = *reinterpret_cast<const f32x4 *>(Os + pos_of((int)tgo * TPT + u) * OS + cho * 4);
+#pragma unroll
+                for (int a = 0; a < 4; ++a) {
+                    val[a] *= F0[u][GH ? 0 : a];
+                    if constexpr (!REV) val[a] *= p.oscale;
+                }
+                const bool live = !(sh && dead(t));
+                if (live)
+                    store(u32x2{pack_bf16(val[0], val[1]), pack_bf16(val[2], val[3])},
+                          reinterpret_cast<u32x2 *>(orow + (size_t)(u * st) * 2 + z_b0));
+                const u32x2 kw = k0[u];
+                const f32x4 pr = {bf16_lo(kw[0]) * val[0], bf16_hi(kw[0]) * val[1],
+                                  bf16_lo(kw[1]) * val[2], bf16_hi(kw[1]) * val[3]};
+                if constexpr (GH) {
+                    const float tot = lane_sum<CQ>((pr[0] + pr[1]) + (pr[2] + pr[3]));
+                    if (cq == 0) hsum[t] = tot;
+                } else if constexpr (!REV) {
+                    if (live) store(pr, reinterpret_cast<f32x4 *>(drow + u * gcs));
+                } else {
+#pragma unroll
+                    for (int a = 0; a < 4; ++a) run[a] += live ? rqd[u][a] - pr[a] : 0.f;
+                    rqd[u] = run;   // sum over this thread's tokens >= u
+                }
+            }
+            if constexpr (REV && !GH) {
+                f32x4 wave;
+#pragma unroll
+                for (int a = 0; a < 4; ++a) {   // suffix scan over the wave's token groups
+                    float inc = run[a];
+#pragma unroll
+                    for (int d = 1; d < GW; d <<= 1) {
+                        const float dn = __shfl_down(inc, d * CQ, 64);
+                        if (gl + d < GW) inc += dn;
+                    }
+                    later_in_wave[a] = inc - run[a];
+                    wave[a] = inc;
+                }
+                if (gl == 0) *reinterpret_cast<f32x4 *>(wtot2 + gw * DK + cho) = wave;
+            }
+        };
+        // after a barrier: the later waves' and the later chunks' share, dG of the m-th chunk
+        auto finish_dg = [&](int m, bool sh) __attribute__((always_inline)) {
+            if constexpr (REV && !GH) {
+                fresh();
+                const int c = chunk_of(m);
+                // chunk c ends at a checkpoint: what the later tokens contribute is known exactly (left in `anchor`
+                // when the matrix waves crossed that boundary)
+                if (p.S_ck && (c + 1) % kAnchor == 0 && c + 1 < N) carry = *reinterpret_cast<const f32x4 *>(anchor + cho);
+                f32x4 later = carry;
+#pragma unroll
+                for (int a = 0; a < 4; ++a) later[a] += later_in_wave[a];
+#pragma unroll
+                for (int u = 0; u < NWG; ++u) {
+                    const f32x4 x = *reinterpret_cast<const f32x4 *>(wtot2 + u * DK + cho);
+                    const float sel = (u > gw) ? 1.f : 0.f;   // wave-uniform
+#pragma unroll
+                    for (int a = 0; a < 4; ++a) {
+                        later[a] = __builtin_fmaf(sel, x[a], later[a]);
+                        carry[a] += x[a];
+                    }
+                }
+                float *row = dg_rows(c);
+#pragma unroll
+                for (int u = 0; u < TPT; ++u) {
+                    if (sh && dead(tg * TPT + u)) continue;
+                    f32x4 o;
+#pragma unroll
+                    for (int a = 0; a < 4; ++a) o[a] = rqd[u][a] + later[a];
+                    __builtin_nontemporal_store(o, reinterpret_cast<f32x4 *>(row + u * gcs));
+                }
+            }
+        };
+        // the same with per-head gates, lane = token, from the channel sums
+        auto finish_head = [&](int m) __attribute__((always_inline)) {
+            if constexpr (GH) {
+                const int c = chunk_of(m);
+                const bool live = !(is_short(c) && dead(lane));
+                float *row = dgb + (cstart(c) + lane) * gcs;
+                float x = hsum[lane];
+                if constexpr (!REV) {
+                    if (live && gw == 0) *row = x;
+                } else {
+                    x = live ? hqd - x : 0.f;
+                    float inc = x;   // sum over the tokens >= lane
+#pragma unroll
+                    for (int d = 1; d < 64; d <<= 1) {
+                        const float dn = __shfl_down(inc, d, 64);
+                        if (lane + d < 64) inc += dn;
+                    }
+                    if (p.S_ck && (c + 1) % kAnchor == 0 && c + 1 < N) {
+                        hcarry = 0.f;
+                        for (int i = 0; i < DK; i += 64) hcarry += anchor[i + lane];
+#pragma unroll
+                        for (int d = 1; d < 64; d <<= 1) hcarry += __shfl_xor(hcarry, d, 64);
+                    }
+                    if (live && gw == 0) *row = inc + hcarry;
+                    hcarry += __shfl(inc, 0, 64);
+                }
+            }
+        };
+        auto fetch_head = [&](int m) __attribute__((always_inline)) {
+            if constexpr (REV && GH) {
+                hqd = dgb[(cstart(chunk_of(m)) + lane) * gcs];
+            }
+        };
+
+        {
+            const long long t0 = cstart(chunk_of(0));
+#pragma unroll
+            for (int u = 0; u < TPT; ++u) load_raw(u, t0);
+        }
 #pragma unroll
         for (int u = 0; u < TPT; ++u) {
-            if constexpr (!EMIT) rz2[u] = *reinterpret_cast<const u32x2 *>(z2b + ((t0 + tq * TPT + u) * st + 4 * cq) * 2);
-            if constexpr (REV && GH) {   // the channel sum of q .* dq, booked on the first channel
-                const float x = dgb[(t0 + tq * TPT + u) * gcs];
-                rqd[u] = f32x4{cq == 0 ? x : 0.f, 0.f, 0.f, 0.f};
-            } else if constexpr (REV) {
-                rqd[u] = *reinterpret_cast<const f32x4 *>(dgb + (t0 + tq * TPT + u) * gcs + 4 * cq);
-            }
+            k1[u] = u32x2{0u, 0u};
+#pragma unroll
+            for (int a = 0; a < NG; ++a) F1[u][a] = 0.f;
         }
-
-        // ---- scores: P^T tiles (r' <= r), 16x16x32 over the d_v channels -----------------------------
-        // half the decay of this lane's column of W: once before the chunk's products, once after its update
-        const float gcol = gam[w * 16 + l16];
+        const bool sh0 = is_short(chunk_of(0));
+        part1(0, sh0);
+        __syncthreads();
+        part2(0, sh0);
+        __syncthreads();   // chunk 0 ready
+        if constexpr (REV && !GH) carry = *reinterpret_cast<const f32x4 *>(carry0 + ch);
+        if constexpr (REV && GH) {
+            for (int i = 0; i < DK; i += 64) hcarry += carry0[i + lane];
 #pragma unroll
-        for (int it = 0; it < Cfg::NIT; ++it)
-#pragma unroll
-            for (int rr = 0; rr < 4; ++rr) Sacc[it][rr] *= gcol;
-#pragma unroll
-        for (int i = 0; i < (10 + NW - 1) / NW; ++i) {
-            const int idx = w + NW * i;   // wave-uniform
-            if (idx < 10) {
-                const int tt = (idx >= 6) ? 3 : (idx >= 3) ? 2 : (idx >= 1) ? 1 : 0;
-                const int ts = idx - tt * (tt + 1) / 2;
-                const unsigned char *ya = Ys + (16 * ts + l16) * XS + 16 * kg;
-                const unsigned char *xf = Xs + (16 * tt + l16) * XS + 16 * kg;
-                bf16x8 fa[DV / 32], fb[DV / 32];
-#pragma unroll
-                for (int ks = 0; ks < DV / 32; ++ks) {
-                    fa[ks] = lds_frag(ya, 64 * ks);
-                    fb[ks] = lds_frag(xf, 64 * ks);
-                }
-                f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int ks = 0; ks < DV / 32; ++ks) acc = M::run(fa[ks], fb[ks], acc);
-                if (ts == tt) {
-#pragma unroll
-                    for (int rr = 0; rr < 4; ++rr)
-                        if (4 * kg + rr > l16) acc[rr] = 0.f;
-                }
-                *reinterpret_cast<u32x2 *>(Ps + (16 * tt + l16) * TS + (16 * ts + 4 * kg) * 2) =
-                    u32x2{pack_bf16(acc[0], acc[1]), pack_bf16(acc[2], acc[3])};
-            }
+            for (int d = 1; d < 64; d <<= 1) hcarry += __shfl_xor(hcarry, d, 64);
         }
-        // ---- inter: O^T = W^T X^T with W fed from the accumulators -----------------------------------
-        f32x4 Oacc[4];
+        put_u();
+        // (in the dQ pass the short chunk may be the last one)
+        auto short_ahead = [&](int m) __attribute__((always_inline)) { return !REV && m < N && is_short(chunk_of(m)); };
+        part1(1, short_ahead(1));
+        auto step = [&](int n, bool first, bool second) __attribute__((always_inline)) {
+            __syncthreads();   // phase 2 of chunk n
+            if (!first) finish_dg(n - 1, second && sh0), finish_head(n - 1);
+            __builtin_amdgcn_sched_barrier(0);   // (neither those terms nor the next ones take registers during the gate pass)
+            part2(n + 1, short_ahead(n + 1));
+            __builtin_amdgcn_sched_barrier(0);
+            fetch_qd(n);
+            fetch_head(n);
+            __syncthreads();   // phase 1 of chunk n + 1
+            put_u();
+            finish(n, first && sh0);
+            part1(n + 2, short_ahead(n + 2));
+        };
+        for (int n = 0; n + 1 < N; ++n) step(n, n == 0, n == 1);
+        __syncthreads();       // phase 2 of the last chunk
+        if (N > 1) finish_dg(N - 2, N == 2 && sh0), finish_head(N - 2);
+        fetch_qd(N - 1);
+        fetch_head(N - 1);
 #pragma unroll
-        for (int mt = 0; mt < 4; ++mt) Oacc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int u = 0; u < TPT; ++u) {
+            k0[u] = k1[u];
 #pragma unroll
-        for (int ks = 0; ks < DV / 32; ++ks) {
-            const bf16x8 sf = pack2x4(Sacc[2 * ks], Sacc[2 * ks + 1]);
-#pragma unroll
-            for (int mt = 0; mt < 4; ++mt)
-                Oacc[mt] = M::run(sf, lds_frag(Xs, (mt * 16 + l16) * XS + (ks * 32 + 8 * kg) * 2), Oacc[mt]);
+            for (int a = 0; a < NG; ++a) F0[u][a] = F1[u][a];
         }
         __syncthreads();
-
-        // ---- intra: O^T += Zt Ps^T over the causal range; factor, scale, store ------------------------
-        bf16x8 zf[2];
-#pragma unroll
-        for (int ks = 0; ks < 2; ++ks) zf[ks] = lds_frag(Zt, (w * 16 + l16) * TS + (ks * 32 + 8 * kg) * 2);
-#pragma unroll
-        for (int mt = 0; mt < 4; ++mt) {
-#pragma unroll
-            for (int ks = 0; ks <= mt / 2; ++ks)
-                Oacc[mt] = M::run(zf[ks], lds_frag(Ps, (mt * 16 + l16) * TS + (ks * 32 + 8 * kg) * 2), Oacc[mt]);
-            const int r = mt * 16 + l16;
-            float *fr = reinterpret_cast<float *>(Fs + r * FS + (w * 16 + 4 * kg) * 4);
-            const f32x4 f = *reinterpret_cast<const f32x4 *>(fr);
-            const f32x4 val = {Oacc[mt][0] * f[0] * p.oscale, Oacc[mt][1] * f[1] * p.oscale,
-                               Oacc[mt][2] * f[2] * p.oscale, Oacc[mt][3] * f[3] * p.oscale};
-            *reinterpret_cast<f32x4 *>(fr) = val;   // fp32 gradient; stored and used for dG one chunk later
+        finish(N - 1, is_short(chunk_of(N - 1)));
+        if constexpr (REV || GH) {
+            __syncthreads();
+            finish_dg(N - 1, is_short(chunk_of(N - 1)));
+            finish_head(N - 1);
         }
-        // ---- state: W += Yt Zt^T (then the column decay in the forward direction) ---------------------
+        if constexpr (EMIT) {
+            if (p.G_tot_out && tg == 0) {   // total log decay of the segment
+                if constexpr (GH) {
+                    if (cq == 0) p.G_tot_out[sbh] = gpre[0];
+                } else {
+                    *reinterpret_cast<f32x4 *>(p.G_tot_out + sbh * DK + ch) = gpre;
+                }
+            }
+        }
+    } else {
+        // ================================ matrix waves =========================================
+        const int w = pw;
+        // Lane coordinates of the 32x32x16 and (score tiles) 16x16x32 products, and all LDS addresses, are worked out where they
+        // are used, from a lane number that changes for all the compiler knows (keep_in_loop).
+        unsigned ln = lane;
+        auto LT = [&]() __attribute__((always_inline)) { return (int)(ln & 31); };
+        auto KG = [&]() __attribute__((always_inline)) { return (int)(ln >> 5); };
+        auto L16 = [&]() __attribute__((always_inline)) { return (int)(ln & 15); };
+        auto KG16 = [&]() __attribute__((always_inline)) { return (int)(ln >> 4); };
+        const bool has_k = DK >= 32 * NWM || w < DK / 32;   // this wave owns columns of W ..
+        const bool has_v = DV >= 32 * NWM || w < DV / 32;   // .. and, in the dK pass, of the second state (d_k x d_v)
+        const unsigned char *xb = (const unsigned char *)p.x + vbase * 2;
+        const unsigned char *yb = (const unsigned char *)p.y + vbase * 2;
+
+        // X, Y of the m-th chunk -> LDS: an instruction of a wave fetches RPI whole rows
+        auto XR = [&]() __attribute__((always_inline)) { return (int)(Cfg::RPI * w + ln / Cfg::PPR); };   // tile row of the lane's first piece
+        auto fetch = [&](const unsigned char *src, int m, unsigned tile) __attribute__((always_inline)) {
+            const int xr = XR(), xpc = (ln % Cfg::PPR) ^ swizzle<DV>(xr);
+            const unsigned x_off = ((unsigned)pos_of(REV ? xr + Cfg::RPI * NWM * (Cfg::NXY - 1) : xr) * vt + 8 * xpc) * 2;
+            const unsigned char *base = src + cstart(chunk_of(m < N ? m : N - 1)) * vt * 2;
 #pragma unroll
-        for (int it = 0; it < Cfg::NIT; ++it) {
-            f32x4 acc = Sacc[it];
+            for (int i = 0; i < Cfg::NXY; ++i)
+                lds_fetch(base + (size_t)(Cfg::RPI * NWM * (REV ? Cfg::NXY - 1 - i : i)) * vt * 2, x_off,
+                          tile + (w + NWM * i) * 1024);
+        };
+        // surplus rows of the short chunk: zero (so that nothing in them, infinities included, reaches other rows)
+        auto clear_dead = [&](int m, unsigned tile) __attribute__((always_inline)) {
+            if (pad && m < N && is_short(chunk_of(m))) {
 #pragma unroll
-            for (int ks = 0; ks < 2; ++ks)
-                acc = M::run(lds_frag(Yt, (it * 16 + l16) * TS + (ks * 32 + 8 * kg) * 2), zf[ks], acc);
+                for (int i = 0; i < Cfg::NXY; ++i)
+                    if (dead(pos_of(XR() + Cfg::RPI * NWM * i)))
+                        *reinterpret_cast<u32x4 *>(lds + tile + (w + NWM * i) * 1024 + 16 * lane) = u32x4{0u, 0u, 0u, 0u};
+            }
+        };
+        auto x_tile = [](int m) { return (unsigned)(Cfg::kOffX + (REV ? 0 : (m & 1) * Cfg::XB)); };
+        auto y_tile = [](int m) { return (unsigned)(Cfg::kOffY + (m & 1) * Cfg::XB); };
+        fetch(xb, 0, x_tile(0));
+        fetch(yb, 0, y_tile(0));
+
+        // W: this lane holds column d_k = 32 w + lt; register 4 q + m of W[it] is row d_v = 32 it + row_of(q) + m.  (The rows of
+        // an accumulator tile are assigned to channels so that the eight rows a lane owns in half a tile are eight
+        // consecutive channels: they serve as its eight k-slots of the next product.)
+        auto row_of = [&](int q) __attribute__((always_inline)) { return 16 * (q >> 1) + 8 * KG() + 4 * (q & 1); };
+        f32x16 W[DV / 32], W2[REV ? DK / 32 : (EMIT ? DV / 32 : 1)];
+        const size_t wo = sbh * DK * DV + (size_t)(w * 32 + LT()) * DV;   // of its column in [d_k, d_v]
+        auto row_dot = [&](const float *S) __attribute__((always_inline)) {      // row_sum(W^T .* S) of this lane's d_k row
+            float acc = 0.f;
 #pragma unroll
-            for (int rr = 0; rr < 4; ++rr) acc[rr] *= gcol;
-            Sacc[it] = acc;
+            for (int it = 0; it < DV / 32; ++it)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const f32x4 x = *reinterpret_cast<const f32x4 *>(S + it * 32 + row_of(q));
+                    acc += (W[it][4 * q] * x[0] + W[it][4 * q + 1] * x[1]) + (W[it][4 * q + 2] * x[2] + W[it][4 * q + 3] * x[3]);
+                }
+            return acc + __shfl_xor(acc, 32, 64);
+        };
+        auto store_w = [&](float *S, const f32x16 *A) __attribute__((always_inline)) {
+#pragma unroll
+            for (int it = 0; it < DV / 32; ++it)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    *reinterpret_cast<f32x4 *>(S + it * 32 + row_of(q)) =
+                        f32x4{A[it][4 * q], A[it][4 * q + 1], A[it][4 * q + 2], A[it][4 * q + 3]};
+        };
+#pragma unroll
+        for (int it = 0; it < DV / 32; ++it)
+#pragma unroll
+            for (int rr = 0; rr < 16; ++rr) W[it][rr] = 0.f;
+        if (has_k) {
+#pragma unroll
+            for (int it = 0; it < DV / 32; ++it)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const f32x4 x = *reinterpret_cast<const f32x4 *>(p.W_init + wo + it * 32 + row_of(q));
+#pragma unroll
+                    for (int m = 0; m < 4; ++m) W[it][4 * q + m] = x[m];
+                }
         }
         if constexpr (REV) {
-            // W is now the gradient of the state entering this chunk.  At a checkpoint: the exact dG
-            // contribution of this chunk and everything after it to the earlier tokens, row_sum(dS .* S)
-            const int c = chunk_of(n);
-            if (p.S_ck && c > 0 && c % kAnchor == 0) {
-                const float *ck = p.S_ck + (sbh * n_ck + (c / kAnchor - 1)) * DKF * DV + (size_t)(slice * DK + w * 16 + l16) * DV + 4 * kg;
-                float acc = 0.f;
 #pragma unroll
-                for (int it = 0; it < Cfg::NIT; ++it) {
-                    const f32x4 x = *reinterpret_cast<const f32x4 *>(ck + it * 16);
-                    acc += (Sacc[it][0] * x[0] + Sacc[it][1] * x[1]) + (Sacc[it][2] * x[2] + Sacc[it][3] * x[3]);
+            for (int it = 0; it < DK / 32; ++it)
+#pragma unroll
+                for (int rr = 0; rr < 16; ++rr) W2[it][rr] = 0.f;
+            if (has_v) {   // rows d_k, columns d_v
+                const float *Si = p.W_init + sbh * DK * DV + w * 32 + LT();
+#pragma unroll
+                for (int it = 0; it < DK / 32; ++it)
+#pragma unroll
+                    for (int rr = 0; rr < 16; ++rr) W2[it][rr] = Si[(size_t)(it * 32 + row_of(rr / 4) + rr % 4) * DV];
+            }
+            if (has_k) {   // dG carried in from the later segments: c[i] = sum_j dS_end[i][j] S_end[i][j]
+                const bool inner = seg + 1 < (p.plan ? (int)p.seg_start[p.plan + 1] : p.P);
+                const float *S_end = inner ? p.S_init + wo + (size_t)p.B * p.H * DK * DV
+                                           : p.S_last + ((size_t)b * p.H + h) * DK * DV + (size_t)(w * 32 + LT()) * DV;
+                const float acc = row_dot(S_end);
+                if (KG() == 0) carry0[w * 32 + LT()] = acc;
+            }
+        } else {
+#pragma unroll
+            for (int it = 0; it < (EMIT ? DV / 32 : 1); ++it)
+#pragma unroll
+                for (int rr = 0; rr < 16; ++rr) W2[it][rr] = 0.f;
+        }
+        lds_fetch_wait();
+        clear_dead(0, x_tile(0));
+        clear_dead(0, y_tile(0));
+
+        // Byte addresses in the tiles: 16-byte reads of rows, row lt (+ 32 mt), piece kg (+ 2 ks); for scores, row l16 (+ 16 t),
+        // piece kg16 (+ 4 ks).
+        auto row_at = [&](auto d) __attribute__((always_inline)) -> unsigned {
+            constexpr int D = decltype(d)::value;
+            return (ln & 31) * (2 * D) + (((ln >> 5) ^ swizzle<D>(ln & 15)) << 4);
+        };
+        auto score_at = [&](auto d) __attribute__((always_inline)) -> unsigned {
+            constexpr int D = decltype(d)::value;
+            return (ln & 15) * (2 * D) + (((ln >> 4) ^ swizzle<D>(ln & 15)) << 4);
+        };
+        // Transposing reads, eight tokens 8 kg .. of a 16-token step: a lane supplies row tr_k of four, a quad of channels;
+        // the second read, four rows on, has the low bit of the piece flipped (swizzle).  As columns of a state (own 32
+        // channels, in order) and as rows (all channels, in the order of row_of).
+        auto col_at = [&](auto d) __attribute__((always_inline)) -> unsigned {
+            constexpr int D = decltype(d)::value;
+            const unsigned row = 8 * (ln >> 5) + ((ln >> 2) & 3), r = ln & 3;
+            return row * (2 * D) + (((4 * w + 2 * ((ln >> 4) & 1) + (r >> 1)) ^ swizzle<D>(row)) << 4) + 8 * (r & 1);
+        };
+        auto tr_at = [&](auto d) __attribute__((always_inline)) -> unsigned {
+            constexpr int D = decltype(d)::value;
+            const unsigned row = 8 * (ln >> 5) + ((ln >> 2) & 3), r = ln & 3;
+            return row * (2 * D) + (((2 * ((ln >> 4) & 1) + (r & 1)) ^ swizzle<D>(row)) << 4) + 8 * (r >> 1);
+        };
+        typedef std::integral_constant<int, DV> CV;
+        typedef std::integral_constant<int, DK> CK;
+        auto frag_tr = [](const unsigned char *tile, unsigned at, int stride, int ks) __attribute__((always_inline)) {
+            const unsigned second = (at ^ 16u) + 4 * stride;
+            return lds_frag_tr(tile + at + ks * 16 * stride, tile + second + ks * 16 * stride);
+        };
+        unsigned char *dvb = REV ? (unsigned char *)p.out2 + vbase * 2 : nullptr;
+
+        // the second state's rows of the ks-th step of 16 channels times a chunk's half decay
+        struct Rows8 { f32x4 lo, hi; };
+        auto rd_gam = [&](const float *gm, int ks) __attribute__((always_inline)) {
+            const float *x = gm + ks * 16 + 8 * KG();   // (row_of)
+            return Rows8{*reinterpret_cast<const f32x4 *>(x), *reinterpret_cast<const f32x4 *>(x + 4)};
+        };
+        auto decay_w2 = [&](int ks, const Rows8 &x) __attribute__((always_inline)) {
+            if constexpr (REV) {
+#pragma unroll
+                for (int m = 0; m < 4; ++m) {
+                    W2[ks / 2][8 * (ks % 2) + m] *= x.lo[m];
+                    W2[ks / 2][8 * (ks % 2) + 4 + m] *= x.hi[m];
                 }
-                acc += __shfl_xor(acc, 16, 64);
-                acc += __shfl_xor(acc, 32, 64);
-                if (kg == 0) anchor[w * 16 + l16] = acc;
             }
-        }
-        if constexpr (EMIT) {   // dS_loc^T += X^T (Q .* exp(G))
-            bf16x8 qf[2];
+        };
+        // 16 x 16 tiles of scores, NTL of the lower ten, i0 + step * i: P[r][r'] = A_r . B_r', r in row tile tt, r' in ts <= tt
+        auto scores = [&](auto ntl, auto steps, const unsigned char *A, const unsigned char *Bt, unsigned at, int i0, int step,
+                          unsigned char *P) __attribute__((always_inline)) {
+            constexpr int NTL = decltype(ntl)::value, K = decltype(steps)::value, S = K * 64;   // (row stride)
+            auto tile = [&](int i, int &tt, int &ts) __attribute__((always_inline)) {   // wave-uniform
+                const int idx = i0 + step * i;
+                tt = (idx >= 6) ? 3 : (idx >= 3) ? 2 : (idx >= 1) ? 1 : 0;
+                ts = idx - tt * (tt + 1) / 2;
+            };
+            f32x4 acc;
+            pipelined<NTL * K, 4>(
+                [&](int s) __attribute__((always_inline)) {
+                    int tt, ts;
+                    tile(s / K, tt, ts);
+                    const unsigned o = at ^ (64 * (s % K));
+                    return FragPair{lds_frag(A + 16 * tt * S + o, 0), lds_frag(Bt + 16 * ts * S + o, 0)};
+                },
+                [&](int s, const FragPair &f) __attribute__((always_inline)) {
+                    if (s % K == 0) acc = f32x4{0.f, 0.f, 0.f, 0.f};
+                    acc = Mma<16>::run(f.b, f.a, acc);
+                    if (s % K == K - 1) {
+                        int tt, ts;
+                        tile(s / K, tt, ts);
+                        const int last = L16() + 16 * (tt - ts) - 4 * KG16();   // r' <= r
 #pragma unroll
-            for (int ks = 0; ks < 2; ++ks) qf[ks] = lds_frag(Qt, (w * 16 + l16) * TS + (ks * 32 + 8 * kg) * 2);
-#pragma unroll
-            for (int it = 0; it < Cfg::NIT; ++it)
-#pragma unroll
-                for (int ks = 0; ks < 2; ++ks)
-                    Dacc[it] = M::run(lds_frag(Xt, (it * 16 + l16) * TS + (ks * 32 + 8 * kg) * 2), qf[ks], Dacc[it]);
-        }
-        __syncthreads();
-    }
-    if constexpr (EMIT) {
-        float *Dl = p.dS_loc + sbh * DKF * DV + (size_t)(slice * DK + w * 16 + l16) * DV + 4 * kg;
-#pragma unroll
-        for (int it = 0; it < Cfg::NIT; ++it) *reinterpret_cast<f32x4 *>(Dl + it * 16) = Dacc[it];
-        if (p.G_tot_out && tq == 0) {   // total log decay of the segment
-            if constexpr (GH) {
-                if (cq == 0) p.G_tot_out[sbh] = gpre[0];
+                        for (int rr = 0; rr < 4; ++rr) acc[rr] = rr > last ? 0.f : acc[rr];
+                        *reinterpret_cast<u32x2 *>(P + (16 * tt + L16()) * PS + (16 * ts + 4 * KG16()) * 2) =
+                            u32x2{pack_bf16(acc[0], acc[1]), pack_bf16(acc[2], acc[3])};
+                    }
+                });
+        };
+        __syncthreads();   // (the gate waves' sums)
+        __syncthreads();   // chunk 0 ready
+        auto step = [&](int n, bool first) __attribute__((always_inline)) {
+            const unsigned char *Xs = lds + x_tile(n), *Ys = lds + y_tile(n);
+            const unsigned char *Zs = lds + Cfg::kOffZ + (n & 1) * Cfg::ZB, *Us = lds + Cfg::kOffU;
+            const float *gm = gam + (n & 1) * DK;
+            keep_in_loop(ln);
+            // ---- phase 1 --------------------------------------------------------------------------
+            fetch(yb, n + 1, y_tile(n + 1));
+            if constexpr (!REV) fetch(xb, n + 1, x_tile(n + 1));
+            if constexpr (!REV) {
+                // checkpoint: the forward state entering this chunk, for the dK pass to re-anchor dG with
+                if (p.S_ck && n > 0 && n % kAnchor == 0 && has_k)
+                    store_w(p.S_ck + (sbh * n_ck + (n / kAnchor - 1)) * DK * DV + (size_t)(w * 32 + LT()) * DV, W);
+            }
+            const unsigned x_sc = score_at(CV{}), z_sc = score_at(CK{}), x_row = row_at(CV{}), z_row = row_at(CK{});
+            const float gcol = gm[has_k ? w * 32 + LT() : LT()];
+            typedef std::integral_constant<int, DV / 32> KV;   // steps of a contraction over d_v, over d_k
+            typedef std::integral_constant<int, DK / 32> KK;
+            if constexpr (REV) {   // one half of the waves takes X Y^T, the other U Z^T
+                constexpr int HW = NWM / 2;
+                typedef std::integral_constant<int, 10 / HW> NTL;
+                const bool second = w >= HW;
+                if constexpr (DK == DV) scores(NTL{}, KV{}, second ? Us : Xs, second ? Zs : Ys, x_sc, w % HW, HW, second ? P2s : Ps);
+                else if (second) scores(NTL{}, KK{}, Us, Zs, z_sc, w % HW, HW, P2s);
+                else scores(NTL{}, KV{}, Xs, Ys, x_sc, w % HW, HW, Ps);
             } else {
-                *reinterpret_cast<f32x4 *>(p.G_tot_out + sbh * DKF + slice * DK + 4 * cq) = gpre;
+                scores(std::integral_constant<int, 10 / NWM>{}, KV{}, Xs, Ys, x_sc, w, NWM, Ps);
+                if (10 % NWM && w < 10 % NWM) scores(std::integral_constant<int, 1>{}, KV{}, Xs, Ys, x_sc, w + 10 / NWM * NWM, NWM, Ps);
             }
+            // O^T = W^T X^T with W, decayed on the way, fed from the accumulators, and the same for dV
+            f32x16 O[2], O2[REV ? 2 : 1];
+#pragma unroll
+            for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+                for (int rr = 0; rr < 16; ++rr) {
+                    O[mt][rr] = 0.f;
+                    if constexpr (REV) O2[mt][rr] = 0.f;
+                }
+            constexpr int NKI = DV / 8, NVI = DK / 8;   // products of the two
+            bf16x8 sf;
+            Rows8 gx;
+            auto rd_k = [&](int s) __attribute__((always_inline)) { return lds_frag(Xs + (x_row ^ (32 * (s / 2))), (s % 2) * 32 * XS); };
+            auto mm_k = [&](int s, bf16x8 f) __attribute__((always_inline)) {
+                const int ks = s / 2, b0 = 8 * (ks % 2);
+                if (s % 2 == 0) {
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) W[ks / 2][b0 + i] *= gcol;
+                    sf = pack8_bwd(W[ks / 2], b0);
+                }
+                O[s % 2] = M::run(sf, f, O[s % 2]);
+            };
+            auto rd_v = [&](int s) __attribute__((always_inline)) { return lds_frag(Us + (z_row ^ (32 * (s / 2))), (s % 2) * 32 * ZS); };
+            auto mm_v = [&](int s, bf16x8 f) __attribute__((always_inline)) {
+                if constexpr (REV) {
+                    const int ks = s / 2, b0 = 8 * (ks % 2);
+                    if (s == 0) gx = rd_gam(gm, 0);
+                    if (s % 2 == 0) {
+                        decay_w2(ks, gx);
+                        sf = pack8_bwd(W2[ks / 2], b0);
+                        if (ks + 1 < DK / 16) gx = rd_gam(gm, ks + 1);
+                    }
+                    O2[s % 2] = M::run(sf, f, O2[s % 2]);
+                }
+            };
+            if constexpr (REV && DK == DV) {
+                pipelined<NKI + NVI, 4>([&](int s) __attribute__((always_inline)) { return s < NKI ? rd_k(s) : rd_v(s - NKI); },
+                                        [&](int s, bf16x8 f) __attribute__((always_inline)) { if (s < NKI) mm_k(s, f); else mm_v(s - NKI, f); });
+            } else {
+                if (has_k) pipelined<NKI, 5>(rd_k, mm_k);
+                if constexpr (REV) {
+                    if (has_v) pipelined<NVI, 5>(rd_v, mm_v);
+                }
+            }
+            __syncthreads();
+            // ---- phase 2 --------------------------------------------------------------------------
+            keep_in_loop(ln);
+            if constexpr (REV) fetch(xb, n + 1, x_tile(n + 1));
+            const unsigned x_col = col_at(CV{}), z_col = col_at(CK{}), x_tr = tr_at(CV{}), z_tr = tr_at(CK{});
+            // Phase 2 contracts over tokens, 16 at a time: with the step's rows of this wave's own columns of Z (Y) in hand, the
+            // intra-chunk products of the one or two 32-token tiles the step reaches (the scores' upper part is zero), then
+            // the state's row tiles: NR + 1 or NR + 2 products a step, two steps of each kind.
+            auto own_at = [&](int s, int NR, int &ks, int &j) __attribute__((always_inline)) {   // s-th product -> step, place in it
+                ks = s < 2 * (NR + 2) ? s / (NR + 2) : 2 + (s - 2 * (NR + 2)) / (NR + 1);
+                j = s < 2 * (NR + 2) ? s % (NR + 2) : 1 + (s - 2 * (NR + 2)) % (NR + 1);   // 0, 1: tile; 2 ..: state row tile
+            };
+            auto rd_p = [&](const unsigned char *P, int mt, int ks) __attribute__((always_inline)) {
+                return lds_frag(P, (mt * 32 + LT()) * PS + (ks * 16 + 8 * KG()) * 2);
+            };
+            if constexpr (REV) {
+                if (has_v) {   // dV += P2 Y, dS += Z^T Y
+                    constexpr int NR = DK / 32;
+                    bf16x8 own = frag_tr(Ys, x_col, XS, 0), next;
+                    pipelined<4 * NR + 6, 4>(
+                        [&](int s) __attribute__((always_inline)) {
+                            int ks, j;
+                            own_at(s, NR, ks, j);
+                            return j < 2 ? rd_p(P2s, j, ks) : frag_tr(Zs, z_tr ^ (64 * (j - 2)), ZS, ks);
+                        },
+                        [&](int s, bf16x8 f) __attribute__((always_inline)) {
+                            int ks, j;
+                            own_at(s, NR, ks, j);
+                            if (j == 2 && ks < 3) next = frag_tr(Ys, x_col, XS, ks + 1);
+                            if (j < 2) O2[j] = M::run(own, f, O2[j]);
+                            else W2[j - 2] = M::run(f, own, W2[j - 2]);
+                            if (j == NR + 1) own = next;
+                        });
+                    // rows of dV: the two halves of the wave exchange four channels each, so that a lane stores 16 bytes
+                    const int c = chunk_of(n);
+                    unsigned char *dvr = dvb + cstart(c) * vt * 2;
+                    const bool sh = first && is_short(c);
+#pragma unroll
+                    for (int mt = 0; mt < 2; ++mt) {
+                        const int t = pos_of(mt * 32 + LT());
+#pragma unroll
+                        for (int hq = 0; hq < 2; ++hq) {
+                            const f32x16 &o = O2[mt];
+                            u32x4 row;
+#pragma unroll
+                            for (int i = 0; i < 2; ++i) {
+                                const auto sw = __builtin_amdgcn_permlane32_swap(
+                                    pack_bf16(o[8 * hq + 2 * i], o[8 * hq + 2 * i + 1]),
+                                    pack_bf16(o[8 * hq + 4 + 2 * i], o[8 * hq + 4 + 2 * i + 1]), false, false);
+                                row[i] = sw[0];
+                                row[2 + i] = sw[1];
+                            }
+                            if (!(sh && dead(t)))
+                                *reinterpret_cast<u32x4 *>(dvr + ((unsigned)t * vt + w * 32 + 16 * hq + 8 * KG()) * 2) = row;
+                        }
+                    }
+#pragma unroll
+                    for (int ks = 0; ks < DK / 16; ++ks) decay_w2(ks, rd_gam(gm, ks));
+#pragma unroll
+                    for (int it = 0; it < NR; ++it) asm volatile("" : "+v"(W2[it]));   // (here, not at the end of the loop with the factors in registers till then)
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            if (has_k) {   // O += P Z -> LDS, W += Y^T Z, dQ pass: dS_loc^T += X^T U
+                constexpr int NR = DV / 32;
+                bf16x8 own = frag_tr(Zs, z_col, ZS, 0), next;
+                pipelined<4 * NR + 6, 4>(
+                    [&](int s) __attribute__((always_inline)) {
+                        int ks, j;
+                        own_at(s, NR, ks, j);
+                        return j < 2 ? rd_p(Ps, j, ks) : frag_tr(Ys, x_tr ^ (64 * (j - 2)), XS, ks);
+                    },
+                    [&](int s, bf16x8 f) __attribute__((always_inline)) {
+                        int ks, j;
+                        own_at(s, NR, ks, j);
+                        if (j == 2 && ks < 3) next = frag_tr(Zs, z_col, ZS, ks + 1);
+                        if (j < 2) O[j] = M::run(own, f, O[j]);
+                        else W[j - 2] = M::run(f, own, W[j - 2]);
+                        if (j == NR + 1) own = next;
+                    });
+                if constexpr (EMIT) {
+                    own = frag_tr(Us, z_col, ZS, 0);
+                    pipelined<4 * NR, 4>(
+                        [&](int s) __attribute__((always_inline)) { return frag_tr(Xs, x_tr ^ (64 * (s % NR)), XS, s / NR); },
+                        [&](int s, bf16x8 f) __attribute__((always_inline)) {
+                            if (s % NR == 0 && s / NR < 3) next = frag_tr(Us, z_col, ZS, s / NR + 1);
+                            W2[s % NR] = M::run(f, own, W2[s % NR]);
+                            if (s % NR == NR - 1) own = next;
+                        });
+                }
+#pragma unroll
+                for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        *reinterpret_cast<f32x4 *>(Os + (mt * 32 + LT()) * OS + (w * 32 + 8 * q + 4 * KG()) * 4) =
+                            f32x4{O[mt][4 * q], O[mt][4 * q + 1], O[mt][4 * q + 2], O[mt][4 * q + 3]};
+#pragma unroll
+                for (int it = 0; it < NR; ++it)
+#pragma unroll
+                    for (int rr = 0; rr < 16; ++rr) W[it][rr] *= gcol;
+            }
+            if constexpr (REV) {
+                // W is now the gradient of the state entering this chunk.  At a checkpoint: the exact dG
+                // contribution of this chunk and everything after it to the earlier tokens, row_sum(dS .* S)
+                const int c = chunk_of(n);
+                if (p.S_ck && c > 0 && c % kAnchor == 0 && has_k) {
+                    const float acc = row_dot(p.S_ck + (sbh * n_ck + (c / kAnchor - 1)) * DK * DV + (size_t)(w * 32 + LT()) * DV);
+                    if (KG() == 0) anchor[w * 32 + LT()] = acc;
+                }
+            }
+            lds_fetch_wait();
+            clear_dead(n + 1, y_tile(n + 1));
+            clear_dead(n + 1, x_tile(n + 1));
+            __syncthreads();
+        };
+        if constexpr (REV) {
+            step(0, true);
+            for (int n = 1; n < N; ++n) step(n, false);
+        } else {
+            for (int n = 0; n < N; ++n) step(n, false);
         }
-    }
-    // dG terms of the last chunk processed
-    const long long tl = cstart(chunk_of(N - 1));
-    dg_first(tl, is_short(chunk_of(N - 1)));
-    if constexpr (REV) {
-        __syncthreads();
-        dg_second(tl, is_short(chunk_of(N - 1)), chunk_of(N - 1));
+        if constexpr (EMIT) {
+            if (has_k) store_w(p.dS_loc + wo, W2);
+        }
+        if constexpr (REV || GH) __syncthreads();   // (the gate waves' last sums)
     }
 }
 
-template <int DK, int DV, int NS, bool REV, int GM, bool EMIT>
-static hipError_t launch_qk2(const BwdQKParams &p, hipStream_t s) {
-    typedef QKCfg<DK, DV, EMIT> Cfg;
-    auto kern = gla_bwd_qk_kernel<DK, DV, NS, REV, GM, EMIT>;
+template <int DK, int DV, bool REV, int GM, bool EMIT, bool NT>
+static hipError_t launch_bwd2(const BwdQKParams &p, hipStream_t s) {
+    typedef BwdCfg<DK, DV, REV> Cfg;
+    auto kern = gla_bwd_bf16_kernel<DK, DV, REV, GM, EMIT, NT>;
     static LdsLimit limit;   // one per instantiation
     hipError_t e = limit.raise((const void *)kern, Cfg::kBytes);
     if (e != hipSuccess) return e;
-    const int streams = p.B * p.P * p.H, grid = NS == 1 ? streams : (streams + 7) / 8 * 8 * NS;
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(Cfg::NT), Cfg::kBytes, s, p);
+    hipLaunchKernelGGL(kern, dim3(p.B * p.P * p.H), dim3(Cfg::NT), Cfg::kBytes, s, p);
     return hipGetLastError();
 }
-template <int DK, int DV, int NS, bool REV, int GM>
-static hipError_t launch_qk(const BwdQKParams &p, hipStream_t s) {
+// Do the passes' tensors outgrow the 256 MB Infinity Cache?  What a pass reads is then not there from the pass before, and rows
+// that are touched once are better read and written past the caches; below, the hint costs hits.  Training step, d = 128, one
+// run of 16 heads, without / with the hint: 4096 tokens 149 / 155 us, 8192 (q, k, v, dO, g: 201 MB) 249 / 250, 16384 456 / 423,
+// 131072 2974 / 2881; per-head gates 8192 (134 MB) 182 / 185, 16384 (268 MB) 326 / 311; d_k = 64, bf16 gates 16384 (235 MB) 270 / 256.
+static bool streams_past_caches(const BwdQKParams &p, int dk, int dv, int gm) {
+    const double gate = gm == kGateHead ? 4. : gm == kGateBF16 ? 2. * dk : 4. * dk;
+    return (double)p.B * p.T * p.H * (4. * (dk + dv) + gate) > 215e6;
+}
+template <int DK, int DV, bool REV, int GM, bool EMIT>
+static hipError_t launch_bwd1(const BwdQKParams &p, hipStream_t s) {
+    return streams_past_caches(p, DK, DV, GM) ? launch_bwd2<DK, DV, REV, GM, EMIT, true>(p, s) : launch_bwd2<DK, DV, REV, GM, EMIT, false>(p, s);
+}
+template <int DK, int DV, bool REV, int GM>
+static hipError_t launch_bwd(const BwdQKParams &p, hipStream_t s) {
     if constexpr (!REV) {
-        if (p.dS_loc) return launch_qk2<DK, DV, NS, false, GM, true>(p, s);
+        if (p.dS_loc) return launch_bwd1<DK, DV, false, GM, true>(p, s);
     }
-    return launch_qk2<DK, DV, NS, REV, GM, false>(p, s);
+    return launch_bwd1<DK, DV, REV, GM, false>(p, s);
 }
 
 template <bool REV, int GM>
-static hipError_t dispatch_qk(const BwdQKParams &p, int d_k, int d_v, hipStream_t s) {
-    if constexpr (GM != kGateHead) {
-        if (d_k == 128 && p.B * p.P * p.H * 2 <= 256)
-            return d_v == 64 ? launch_qk<64, 64, 2, REV, GM>(p, s) : launch_qk<64, 128, 2, REV, GM>(p, s);
-    }
-    if (d_k == 64 && d_v == 64) return launch_qk<64, 64, 1, REV, GM>(p, s);
-    if (d_k == 128 && d_v == 64) return launch_qk<128, 64, 1, REV, GM>(p, s);
-    if (d_k == 64 && d_v == 128) return launch_qk<64, 128, 1, REV, GM>(p, s);
-    if (d_k == 128 && d_v == 128) return launch_qk<128, 128, 1, REV, GM>(p, s);
+static hipError_t dispatch_bwd(const BwdQKParams &p, int d_k, int d_v, hipStream_t s) {
+    if (d_k == 64 && d_v == 64) return launch_bwd<64, 64, REV, GM>(p, s);
+    if (d_k == 128 && d_v == 64) return launch_bwd<128, 64, REV, GM>(p, s);
+    if (d_k == 64 && d_v == 128) return launch_bwd<64, 128, REV, GM>(p, s);
+    if (d_k == 128 && d_v == 128) return launch_bwd<128, 128, REV, GM>(p, s);
     return hipErrorInvalidValue;
 }
 
 hipError_t launch_bwd_qk(const BwdQKParams &p, int d_k, int d_v, int gate_mode, bool reverse, hipStream_t s) {
     if (gate_mode == kGateBF16)
-        return reverse ? dispatch_qk<true, kGateBF16>(p, d_k, d_v, s) : dispatch_qk<false, kGateBF16>(p, d_k, d_v, s);
+        return reverse ? dispatch_bwd<true, kGateBF16>(p, d_k, d_v, s) : dispatch_bwd<false, kGateBF16>(p, d_k, d_v, s);
     if (gate_mode == kGateHead)
-        return reverse ? dispatch_qk<true, kGateHead>(p, d_k, d_v, s) : dispatch_qk<false, kGateHead>(p, d_k, d_v, s);
-    return reverse ? dispatch_qk<true, kGateF32>(p, d_k, d_v, s) : dispatch_qk<false, kGateF32>(p, d_k, d_v, s);
+        return reverse ? dispatch_bwd<true, kGateHead>(p, d_k, d_v, s) : dispatch_bwd<false, kGateHead>(p, d_k, d_v, s);
+    return reverse ? dispatch_bwd<true, kGateF32>(p, d_k, d_v, s) : dispatch_bwd<false, kGateF32>(p, d_k, d_v, s);
 }
 
 }  // namespace zeco

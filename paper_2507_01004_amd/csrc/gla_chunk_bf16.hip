@@ -105,17 +105,13 @@ __device__ __forceinline__ bf16x8 pack8(const f32x16 &a, int base) {
 //            given offsets G_off[p]: o, G_cum (second pass of the local pass when a segment is cut
 //            into sub-segments; S_init[p] and G_off[p] then hold what precedes sub-segment p inside
 //            its segment)
-// and two passes of the backward (App. A.4), which walk the chunks of a segment from the last to the
-// first and keep dS, the gradient of the running state, in the accumulators:
+// and a pass of the backward (App. A.4), which walks the chunks of a segment from the last to the first and keeps dS, the
+// gradient of the running state, in the accumulators:
 //   kDState  dS <- (gamma^T 1) .* dS + (Q .* Lambda)^T dO from zero; S_loc receives the gradient that
 //            leaves the segment towards the state entering it (first loop of the backward listing)
-//   kDV      dV = (K / Lambda) ((gamma^T 1) .* dS) + (intra-chunk scores)^T dO, with dS started from
-//            S_init[p] = the gradient entering the segment's final state
-// The backward modes are called with the tensors in other roles (kDState: k := q, v := dO;
-// kDV: q := k, k := q, v := dO, o := dV), flip the sign of the decay exponents, apply gamma before the
-// chunk's products instead of after, and store token t of a chunk at tile row 63 - t, so that the
-// causal structure of the tiles is the one of the forward pass.
-enum ChunkMode { kLocal = 0, kStates = 1, kOutput = 2, kDState = 3, kDV = 4, kLocalInit = 5, kLocalCD = 6, kOutputRun = 7 };
+// It is called with the tensors in other roles (k := q, v := dO), flips the sign of the decay exponents, applies gamma before the
+// chunk's products instead of after, and stores token t of a chunk at tile row 63 - t.  (dQ, dK, dV, dG: gla_bwd_qk.hip.)
+enum ChunkMode { kLocal = 0, kStates = 1, kOutput = 2, kDState = 3, kLocalInit = 5, kLocalCD = 6, kOutputRun = 7 };
 
 // Gate waves per workgroup: 4, one per SIMD beside an MFMA wave; 8 in the local pass with per-channel
 // gates at d_k = 128, which moves the most bytes per chunk and gains 2-3 % from the second set of
@@ -154,10 +150,10 @@ __global__ __launch_bounds__(chunk_threads(DK, DV, GM, MODE)) void gla_chunk_bf1
     constexpr int TPT = Cfg::TPT, TPTV = Cfg::TPTV, CQ = Cfg::CQ, GW = Cfg::GW;
     constexpr int GB = GM == kGateBF16 ? 2 : 4;   // bytes per gate element
     constexpr bool GH = GM == kGateHead;
-    constexpr bool REV = MODE == kDState || MODE == kDV;          // chunks and tokens in reverse
+    constexpr bool REV = MODE == kDState;                         // chunks and tokens in reverse
     constexpr bool NOQ = MODE == kStates || MODE == kDState;      // only the state is computed
     constexpr bool OUT = MODE == kOutput || MODE == kOutputRun;
-    constexpr bool FROM_INIT = OUT || MODE == kDV || MODE == kLocalInit;   // start from S_init (no state emitted, but see kOutputRun)
+    constexpr bool FROM_INIT = OUT || MODE == kLocalInit;   // start from S_init (no state emitted, but see kOutputRun)
     constexpr bool EMIT_G = MODE == kLocal || MODE == kLocalInit;  // per-token cumulative log decay
     constexpr float SGN = REV ? -1.f : 1.f;                       // sign of the decay exponents
     constexpr float kLog2e = 1.4426950408889634f;
@@ -451,7 +447,7 @@ __global__ __launch_bounds__(chunk_threads(DK, DV, GM, MODE)) void gla_chunk_bf1
             }
             // decay outputs: the local pass and the two state passes (the backward one emits G_tot when
             // asked, so that the reverse scan does not need the forward state pass)
-            if constexpr (OUT || MODE == kDV) return;
+            if constexpr (OUT) return;
             if constexpr (MODE == kDState) {
                 if (!p.G_tot) return;
             }
@@ -585,7 +581,7 @@ __global__ __launch_bounds__(chunk_threads(DK, DV, GM, MODE)) void gla_chunk_bf1
         // part 1: scores -> Ps, inter-chunk product -> Oacc
         auto mfma_a = [&](const unsigned char *tile, const float *gam_n) __attribute__((always_inline)) {
             const unsigned char *Qs = tile + Cfg::kOffQ, *Ks = tile + Cfg::kOffK;
-            if constexpr (MODE == kDV || (WIDE && !REV)) decay_state(gam_n);
+            if constexpr (WIDE) decay_state(gam_n);
             // P^T tiles (ts <= tt), 16x16x32; all operand reads of a tile are issued up front
 #pragma unroll
             for (int i = 0; i < (10 + NWM - 1) / NWM; ++i) {
@@ -746,7 +742,6 @@ hipError_t launch_chunk_bf16(const ChunkParams &p, int d_k, int d_v, int gate_mo
     if (mode == kStates) return dispatch_gate<kStates>(p, d_k, d_v, gate_mode, s);
     if (mode == kOutput) return dispatch_gate<kOutput>(p, d_k, d_v, gate_mode, s);
     if (mode == kDState) return dispatch_gate<kDState>(p, d_k, d_v, gate_mode, s);
-    if (mode == kDV) return dispatch_gate<kDV>(p, d_k, d_v, gate_mode, s);
     if (mode == kLocalInit) return dispatch_gate<kLocalInit>(p, d_k, d_v, gate_mode, s);
     if (mode == kLocalCD) return dispatch_gate<kLocalCD>(p, d_k, d_v, gate_mode, s);
     if (mode == kOutputRun) return dispatch_gate<kOutputRun>(p, d_k, d_v, gate_mode, s);

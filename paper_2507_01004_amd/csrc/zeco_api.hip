@@ -719,22 +719,22 @@ static zeco_status bwd_dv_dk_passes(const zeco_gla_desc *d, int P, int L, const 
                                     const float *S_last, const float *dS_in, void *dk, void *dv,
                                     float *dg, float *S_ck, hipStream_t s, const int64_t *seg_start = nullptr,
                                     int64_t T = 0, const zeco::Cut *cut = nullptr, int plan = 0) {
-    const int gb = gate_mode(d);
-    zeco::ChunkParams c;
-    fill_chunk_params(c, d);
-    c.P = P; set_length(c, L);
-    if (cut) set_cut(c, *cut);
-    if (seg_start) { c.seg_start = reinterpret_cast<const long long *>(seg_start); c.T = T; c.plan = plan; }
-    c.q = k; c.k = q; c.v = dO; c.g = g; c.o = dv; c.S_init = dS_in; c.scale = 1.f; c.kscale = d->scale;
-    if (launch_phase(c, d, 4, s) != hipSuccess) return ZECO_ERR_HIP;
-
+    if (d->io_dtype == ZECO_F32) {
+        zeco::ChunkParams c;
+        fill_chunk_params(c, d);
+        c.P = P; set_length(c, L);
+        if (cut) set_cut(c, *cut);
+        if (seg_start) { c.seg_start = reinterpret_cast<const long long *>(seg_start); c.T = T; c.plan = plan; }
+        c.q = k; c.k = q; c.v = dO; c.g = g; c.o = dv; c.S_init = dS_in; c.scale = 1.f; c.kscale = d->scale;
+        if (launch_phase(c, d, 4, s) != hipSuccess) return ZECO_ERR_HIP;
+    }
     zeco::BwdQKParams b;
     fill_bwd_params(b, d, P, L, g, dg, S_init, S_last, cut);
     if (seg_start) { b.seg_start = reinterpret_cast<const long long *>(seg_start); b.T = T; b.plan = plan; }
-    b.x = v; b.y = dO; b.z = q; b.z2 = k; b.out = dk; b.W_init = dS_in; b.zscale = d->scale; b.oscale = 1.f;
+    b.x = v; b.y = dO; b.z = q; b.z2 = k; b.out = dk; b.out2 = dv; b.W_init = dS_in; b.zscale = d->scale; b.oscale = 1.f;
     if (S_ck && bwd_checkpoints(L) > 0) { b.S_ck = S_ck; b.n_ck = bwd_checkpoints(L); }
     if (d->io_dtype == ZECO_F32) return from_hip(zeco::launch_bwd_qk_f32(b, d->d_k, d->d_v, d->C, true, s));
-    return from_hip(zeco::launch_bwd_qk(b, d->d_k, d->d_v, gb, true, s));
+    return from_hip(zeco::launch_bwd_qk(b, d->d_k, d->d_v, gate_mode(d), true, s));   // (dV in the same pass)
 }
 
 zeco_status zeco_gla_bwd_dstate(const zeco_gla_desc *d, const void *q, const void *g, const void *dO,

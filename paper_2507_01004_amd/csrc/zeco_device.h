@@ -139,13 +139,14 @@ __device__ __forceinline__ uint32_t pair_hi(uint32_t x, uint32_t y) {
 // is up to the caller: a contraction does not care about the order of its k-slots as long as both
 // operands agree.
 typedef __attribute__((ext_vector_type(4))) short s16x4;
-__device__ __forceinline__ bf16x8 lds_frag_tr(const unsigned char *addr, int second) {
+__device__ __forceinline__ bf16x8 lds_frag_tr(const unsigned char *addr, const unsigned char *second) {
     typedef __attribute__((address_space(3))) s16x4 *lds_ptr;
     const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(addr));
-    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(addr + second));
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(second));
     typedef __attribute__((ext_vector_type(8))) short s16x8;
     const s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
     return __builtin_bit_cast(bf16x8, v);
 }
+__device__ __forceinline__ bf16x8 lds_frag_tr(const unsigned char *addr, int second) { return lds_frag_tr(addr, addr + second); }
 
 }  // namespace zeco

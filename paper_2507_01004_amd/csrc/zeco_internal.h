@@ -44,7 +44,7 @@ struct ChunkParams {
     int plan = 0;              // slots of a table written by launch_plan (SegPlan); 0: seg_start is the caller's own table
     float scale;
     Cut cut;                   // P counts pieces, n_chunks is the longest piece's (the stride of G_chunk), L and pad are unused
-    // Segments of unequal length (modes 0 to 4 of the bf16 kernel, and the fp32 kernel): segment p covers tokens
+    // Segments of unequal length (modes 0 to 3 of the bf16 kernel, and the fp32 kernel): segment p covers tokens
     // [seg_start[p], seg_start[p+1]) of the T tokens of every batch entry; L is then the upper bound of the
     // lengths, n_chunks and pad are unused.
     const long long *seg_start = nullptr;
@@ -105,7 +105,7 @@ struct ScanParams {
     int gate_per_head = 0;       // 1: G_tot [groups*P, BH], one log decay per head
 };
 
-// dQ / dK pass (gla_bwd_qk.hip).  x, y: [B,T,H,d_v] operands (strides vb, vt, vh); z, z2, g, out:
+// dQ pass; dK, dV and dG pass (gla_bwd_qk.hip).  x, y: [B,T,H,d_v] operands (strides vb, vt, vh); z, z2, g, out:
 // [B,T,H,d_k] (strides sb, st, sh); W_init [P,B,H,d_k,d_v] fp32; dg [B,T,H,d_k] fp32 contiguous (the dQ
 // pass leaves q .* dq there, the dK pass turns it into dG); S_init, S_last: forward states (dK pass).
 // With per-head gates g and dg are [B,T,H] and the channel sums are taken before anything is stored.
@@ -120,6 +120,7 @@ struct BwdQKParams {
     long long sb, st, sh, vb, vt, vh;
     const void *x, *y, *z, *z2, *g;
     void *out;
+    void *out2 = nullptr;        // dK pass: dv, [B,T,H,d_v] (strides vb, vt, vh)
     float *dg;
     const float *W_init, *S_init, *S_last;
     float zscale, oscale;        // multipliers of the gated operand and of the output
@@ -156,8 +157,7 @@ struct LdsLimit {
 // 1 states only, 2 output pass from S_init, 3 backward state pass, 4 dV pass, 5 (as in the bf16 kernel below)
 hipError_t launch_chunk_f32(const ChunkParams &p, int d_k, int d_v, int C, int mode, hipStream_t s);
 // mode: 0 local pass (o, S_loc, G_cum, G_tot), 1 states only (S_loc, G_tot), 2 output pass from S_init (o),
-// 3 backward state pass (k := q, v := dO; S_loc := dS leaving the segment), 4 dV pass (q := k, k := q,
-// v := dO, S_init := dS entering the segment's final state, o := dV), 5 output pass from S_init that also
+// 3 backward state pass (k := q, v := dO; S_loc := dS leaving the segment), 5 output pass from S_init that also
 // writes G_cum counted from G_off (o, G_cum), 6 local pass with the cumulative decay
 // per chunk instead of per token (o, S_loc, G_chunk, G_tot; per-channel gates only), 7 mode 2 over whole runs:
 // S_init may be null (zero), also the end states (S_loc) and, for a backward, S_emit and S_loc2, each if given
@@ -169,7 +169,7 @@ hipError_t launch_apply_cd_bf16(const ApplyParams &p, int d_k, int d_v, hipStrea
 hipError_t launch_scan(const ScanParams &p, hipStream_t s);
 hipError_t launch_plan(const SegPlan &p, hipStream_t s);
 // reverse = false: dQ (x = dO, y = v, z = k, z2 = q, W_init = forward states); true: dK (x = v, y = dO,
-// z = q, z2 = k, W_init = state gradients; must run after the dQ pass, whose q .* dq it consumes)
+// z = q, z2 = k, W_init = state gradients, out2 = dv; must run after the dQ pass, whose q .* dq it consumes)
 hipError_t launch_bwd_qk(const BwdQKParams &p, int d_k, int d_v, int gate_mode, bool reverse, hipStream_t s);
 // the same two passes on fp32 tensors (gla_bwd_f32.hip), chunk length C in {16, 32, 64}; no by-products
 hipError_t launch_bwd_qk_f32(const BwdQKParams &p, int d_k, int d_v, int C, bool reverse, hipStream_t s);
