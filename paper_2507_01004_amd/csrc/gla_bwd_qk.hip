@@ -174,10 +174,15 @@ __device__ __forceinline__ bf16x8 pack8_bwd(const f32x16 &a, int base) {
 // final state; the query scale rides on Q .* Lambda, so that the running dS is the true gradient).
 // EMIT (dQ pass only): also accumulate the segment's state gradient dS_loc and emit it (and, when asked,
 // the segment's total log decay).
+// NS > 1 (dQ pass, gates per channel): NS sibling workgroups share a stream, each with DK of its NS * DK channels - columns of
+// W, of the output and of everything gated; X, Y and the scores, which contract over d_v, each of them has whole.
+// (dV contracts over d_k, so the dK pass is not split.)
 // NT: the rows that the gate waves read and write carry the non-temporal hint (see streams_past_caches).
-template <int DK, int DV, bool REV, int GM, bool EMIT, bool NT_>
+template <int DK, int DV, int NS, bool REV, int GM, bool EMIT, bool NT_>
 __global__ __launch_bounds__(bwd_threads(DK, DV)) void gla_bwd_bf16_kernel(BwdQKParams p) {
     static_assert(!(REV && EMIT), "the state gradient is a by-product of the forward-direction pass");
+    static_assert(NS == 1 || (!REV && GM != kGateHead), "dV, and one decay per head, sum over all channels");
+    constexpr int DKF = DK * NS;
     typedef BwdCfg<DK, DV, REV> Cfg;
     typedef Mma<32> M;
     typedef GateVal<GM> GV;
@@ -216,8 +221,11 @@ __global__ __launch_bounds__(bwd_threads(DK, DV)) void gla_bwd_bf16_kernel(BwdQK
     auto dead = [&](int t) { return short_last ? t < pad : t >= 64 - pad; };
     auto is_short = [&](int c) { return c == (short_last ? N - 1 : 0); };   // chunk c is the short one (if any is)
 
-    // consecutive streams land on different XCDs (workgroup ids are dealt round-robin)
-    int sidx = (int)blockIdx.x;
+    // consecutive streams land on different XCDs (workgroup ids are dealt round-robin), siblings in consecutive slots of
+    // one, whose L2 they share for X and Y
+    const int slice = NS == 1 ? 0 : (int)(blockIdx.x >> 3) % NS;
+    int sidx = NS == 1 ? (int)blockIdx.x : (int)(blockIdx.x >> 3) / NS * 8 + (int)(blockIdx.x & 7);
+    if (NS > 1 && sidx >= p.B * p.P * p.H) return;
     const size_t sbh = sidx;                        // (seg * B + b) * H + h
     const int h = sidx % p.H;
     sidx /= p.H;
@@ -245,7 +253,7 @@ __global__ __launch_bounds__(bwd_threads(DK, DV)) void gla_bwd_bf16_kernel(BwdQK
         pad = (int)(64ll * N - len);
     }
     const int n_ck = p.plan ? (int)p.seg_start[p.plan + 3] : p.n_ck;
-    const long long kbase = b * p.sb + tok0 * p.st + h * p.sh;
+    const long long kbase = b * p.sb + tok0 * p.st + h * p.sh + slice * DK;
     const long long vbase = b * p.vb + tok0 * p.vt + h * p.vh;
     const unsigned st = (unsigned)p.st, vt = (unsigned)p.vt;
 
@@ -264,8 +272,8 @@ __global__ __launch_bounds__(bwd_threads(DK, DV)) void gla_bwd_bf16_kernel(BwdQK
         const unsigned char *gb = (const unsigned char *)p.g + (GH ? hbase : kbase) * GB;
         unsigned char *ob = (unsigned char *)p.out + kbase * 2;
         const unsigned gst = GH ? (unsigned)p.H : st;                         // gate elements between tokens
-        float *dgb = p.dg + hbase * (GH ? 1 : DK);   // [B,T,H,d_k] contiguous ([B,T,H] with per-head gates)
-        const long long gcs = (long long)p.H * (GH ? 1 : DK);
+        float *dgb = p.dg + hbase * (GH ? 1 : DKF) + slice * DK;   // [B,T,H,d_k] contiguous ([B,T,H] with per-head gates)
+        const long long gcs = (long long)p.H * (GH ? 1 : DKF);
         // per-thread byte offsets of its first token inside a chunk
         unsigned z_b0 = ((unsigned)(tg * TPT) * st + ch) * 2;
         unsigned g_b0 = ((unsigned)(tg * TPT) * gst + (GH ? 0 : ch)) * GB;
@@ -609,7 +617,7 @@ __global__ __launch_bounds__(bwd_threads(DK, DV)) void gla_bwd_bf16_kernel(BwdQK
                 if constexpr (GH) {
                     if (cq == 0) p.G_tot_out[sbh] = gpre[0];
                 } else {
-                    *reinterpret_cast<f32x4 *>(p.G_tot_out + sbh * DK + ch) = gpre;
+                    *reinterpret_cast<f32x4 *>(p.G_tot_out + sbh * DKF + slice * DK + ch) = gpre;
                 }
             }
         }
@@ -658,7 +666,7 @@ __global__ __launch_bounds__(bwd_threads(DK, DV)) void gla_bwd_bf16_kernel(BwdQK
         // consecutive channels: they serve as its eight k-slots of the next product.)
         auto row_of = [&](int q) __attribute__((always_inline)) { return 16 * (q >> 1) + 8 * KG() + 4 * (q & 1); };
         f32x16 W[DV / 32], W2[REV ? DK / 32 : (EMIT ? DV / 32 : 1)];
-        const size_t wo = sbh * DK * DV + (size_t)(w * 32 + LT()) * DV;   // of its column in [d_k, d_v]
+        const size_t wo = sbh * DKF * DV + (size_t)(slice * DK + w * 32 + LT()) * DV;   // of its column in [d_k, d_v]
         auto row_dot = [&](const float *S) __attribute__((always_inline)) {      // row_sum(W^T .* S) of this lane's d_k row
             float acc = 0.f;
 #pragma unroll
@@ -811,7 +819,7 @@ __global__ __launch_bounds__(bwd_threads(DK, DV)) void gla_bwd_bf16_kernel(BwdQK
             if constexpr (!REV) {
                 // checkpoint: the forward state entering this chunk, for the dK pass to re-anchor dG with
                 if (p.S_ck && n > 0 && n % kAnchor == 0 && has_k)
-                    store_w(p.S_ck + (sbh * n_ck + (n / kAnchor - 1)) * DK * DV + (size_t)(w * 32 + LT()) * DV, W);
+                    store_w(p.S_ck + (sbh * n_ck + (n / kAnchor - 1)) * DKF * DV + (size_t)(slice * DK + w * 32 + LT()) * DV, W);
             }
             const unsigned x_sc = score_at(CV{}), z_sc = score_at(CK{}), x_row = row_at(CV{}), z_row = row_at(CK{});
             const float gcol = gm[has_k ? w * 32 + LT() : LT()];
@@ -1000,14 +1008,15 @@ __global__ __launch_bounds__(bwd_threads(DK, DV)) void gla_bwd_bf16_kernel(BwdQK
     }
 }
 
-template <int DK, int DV, bool REV, int GM, bool EMIT, bool NT>
+template <int DK, int DV, int NS, bool REV, int GM, bool EMIT, bool NT>
 static hipError_t launch_bwd2(const BwdQKParams &p, hipStream_t s) {
     typedef BwdCfg<DK, DV, REV> Cfg;
-    auto kern = gla_bwd_bf16_kernel<DK, DV, REV, GM, EMIT, NT>;
+    auto kern = gla_bwd_bf16_kernel<DK, DV, NS, REV, GM, EMIT, NT>;
     static LdsLimit limit;   // one per instantiation
     hipError_t e = limit.raise((const void *)kern, Cfg::kBytes);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3(p.B * p.P * p.H), dim3(Cfg::NT), Cfg::kBytes, s, p);
+    const int streams = p.B * p.P * p.H, grid = NS == 1 ? streams : (streams + 7) / 8 * 8 * NS;
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(Cfg::NT), Cfg::kBytes, s, p);
     return hipGetLastError();
 }
 // Do the passes' tensors outgrow the 256 MB Infinity Cache?  What a pass reads is then not there from the pass before, and rows
@@ -1018,24 +1027,32 @@ static bool streams_past_caches(const BwdQKParams &p, int dk, int dv, int gm) {
     const double gate = gm == kGateHead ? 4. : gm == kGateBF16 ? 2. * dk : 4. * dk;
     return (double)p.B * p.T * p.H * (4. * (dk + dv) + gate) > 215e6;
 }
-template <int DK, int DV, bool REV, int GM, bool EMIT>
+template <int DK, int DV, int NS, bool REV, int GM, bool EMIT>
 static hipError_t launch_bwd1(const BwdQKParams &p, hipStream_t s) {
-    return streams_past_caches(p, DK, DV, GM) ? launch_bwd2<DK, DV, REV, GM, EMIT, true>(p, s) : launch_bwd2<DK, DV, REV, GM, EMIT, false>(p, s);
+    return streams_past_caches(p, DK * NS, DV, GM) ? launch_bwd2<DK, DV, NS, REV, GM, EMIT, true>(p, s)
+                                                    : launch_bwd2<DK, DV, NS, REV, GM, EMIT, false>(p, s);
 }
-template <int DK, int DV, bool REV, int GM>
+template <int DK, int DV, int NS, bool REV, int GM>
 static hipError_t launch_bwd(const BwdQKParams &p, hipStream_t s) {
     if constexpr (!REV) {
-        if (p.dS_loc) return launch_bwd1<DK, DV, false, GM, true>(p, s);
+        if (p.dS_loc) return launch_bwd1<DK, DV, NS, false, GM, true>(p, s);
     }
-    return launch_bwd1<DK, DV, REV, GM, false>(p, s);
+    return launch_bwd1<DK, DV, NS, REV, GM, false>(p, s);
 }
 
 template <bool REV, int GM>
 static hipError_t dispatch_bwd(const BwdQKParams &p, int d_k, int d_v, hipStream_t s) {
-    if (d_k == 64 && d_v == 64) return launch_bwd<64, 64, REV, GM>(p, s);
-    if (d_k == 128 && d_v == 64) return launch_bwd<128, 64, REV, GM>(p, s);
-    if (d_k == 64 && d_v == 128) return launch_bwd<64, 128, REV, GM>(p, s);
-    if (d_k == 128 && d_v == 128) return launch_bwd<128, 128, REV, GM>(p, s);
+    if constexpr (!REV && GM != kGateHead) {
+        // At most half as many streams as compute units: two siblings each, which fetch half of q, k, g each and all of v, dO - the
+        // bytes a compute unit can have in flight set the pace there (64 streams of 8192 tokens, d = 128: 579 -> 379 us;
+        // training steps of 1 - 16 heads x 512 - 8192 tokens: 4 - 11 %).  Beyond that they would take a second round.
+        if (d_k == 128 && p.B * p.P * p.H * 2 <= 256)
+            return d_v == 64 ? launch_bwd<64, 64, 2, REV, GM>(p, s) : launch_bwd<64, 128, 2, REV, GM>(p, s);
+    }
+    if (d_k == 64 && d_v == 64) return launch_bwd<64, 64, 1, REV, GM>(p, s);
+    if (d_k == 128 && d_v == 64) return launch_bwd<128, 64, 1, REV, GM>(p, s);
+    if (d_k == 64 && d_v == 128) return launch_bwd<64, 128, 1, REV, GM>(p, s);
+    if (d_k == 128 && d_v == 128) return launch_bwd<128, 128, 1, REV, GM>(p, s);
     return hipErrorInvalidValue;
 }
 
