@@ -141,7 +141,9 @@ constexpr int chunk_threads(int dk, int dv, int gm, int mode) {
 //            so |total| may reach 160.  The state takes e^(total/2) twice, before the chunk's products with
 //            it and after its update (in either walking direction), which costs the MFMA waves a second
 //            multiplication of the state per chunk: about 3 % of the local pass.
-template <int DK, int DV, int NS, int GM, int MODE, bool WIDE>
+//
+// NSK > 1 (states only): NSK sibling workgroups each own DK of the stream's NSK * DK key channels - rows of the state, of k and of g.
+template <int DK, int DV, int NS, int GM, int MODE, bool WIDE, int NSK>
 __global__ __launch_bounds__(chunk_threads(DK, DV, GM, MODE)) void gla_chunk_bf16_kernel(ChunkParams p) {
     typedef B16Cfg<DK, DV, gate_waves(DK, GM, MODE), idle_waves(DK, DV, GM, MODE)> Cfg;
     typedef Mma<32> M;
@@ -152,6 +154,8 @@ __global__ __launch_bounds__(chunk_threads(DK, DV, GM, MODE)) void gla_chunk_bf1
     constexpr bool GH = GM == kGateHead;
     constexpr bool REV = MODE == kDState;                         // chunks and tokens in reverse
     constexpr bool NOQ = MODE == kStates || MODE == kDState;      // only the state is computed
+    static_assert(NSK == 1 || NOQ, "scores contract over all key channels");
+    constexpr int DKF = DK * NSK;
     constexpr bool OUT = MODE == kOutput || MODE == kOutputRun;
     constexpr bool FROM_INIT = OUT || MODE == kLocalInit;   // start from S_init (no state emitted, but see kOutputRun)
     constexpr bool EMIT_G = MODE == kLocal || MODE == kLocalInit;  // per-token cumulative log decay
@@ -184,8 +188,8 @@ __global__ __launch_bounds__(chunk_threads(DK, DV, GM, MODE)) void gla_chunk_bf1
     // Workgroup -> (stream, slice).  Workgroup ids are dealt round-robin to the 8 XCDs, so sibling
     // slices of a stream take consecutive slots of one XCD and share its L2 for q, k, g.
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-    int sidx = (slot / NS) * 8 + xcd;
-    const int slice = slot % NS;
+    int sidx = (slot / (NS * NSK)) * 8 + xcd;
+    const int slice = slot % NS, kslice = NSK == 1 ? 0 : slot / NS % NSK;
     if (sidx >= p.B * p.P * p.H) return;
     const size_t sbh = sidx;                        // (seg * B + b) * H + h  (S_loc / G_tot order)
     const int h = sidx % p.H;
@@ -215,7 +219,7 @@ __global__ __launch_bounds__(chunk_threads(DK, DV, GM, MODE)) void gla_chunk_bf1
         N = (int)((len + 63) >> 6);
         pad = (int)(64ll * N - len);
     }
-    const long long kbase = b * p.sb + tok0 * p.st + h * p.sh;
+    const long long kbase = b * p.sb + tok0 * p.st + h * p.sh + kslice * DK;
     const long long vbase = b * p.vb + tok0 * p.vt + h * p.vh + slice * DV;
     const unsigned st = (unsigned)p.st, vt = (unsigned)p.vt;
 
@@ -477,16 +481,16 @@ __global__ __launch_bounds__(chunk_threads(DK, DV, GM, MODE)) void gla_chunk_bf1
 #pragma unroll
                     for (int a = 0; a < 4; ++a) lo[a] = (seg_hi[a] - gt[a]) + seg_lo[a];
                     if constexpr (GH) {
-                        if (cq == 0) p.G_tot[2 * sbh] = gt[0], p.G_tot[2 * sbh + 1] = lo[0];
+                        if (cq == 0 && kslice == 0) p.G_tot[2 * sbh] = gt[0], p.G_tot[2 * sbh + 1] = lo[0];
                     } else {
-                        f32x4 *G = reinterpret_cast<f32x4 *>(p.G_tot + 2 * (sbh * DK + 4 * cq));
+                        f32x4 *G = reinterpret_cast<f32x4 *>(p.G_tot + 2 * (sbh * DKF + kslice * DK + 4 * cq));
                         G[0] = f32x4{gt[0], lo[0], gt[1], lo[1]};
                         G[1] = f32x4{gt[2], lo[2], gt[3], lo[3]};
                     }
                 } else if constexpr (GH) {
-                    if (cq == 0) p.G_tot[sbh] = gt[0];
+                    if (cq == 0 && kslice == 0) p.G_tot[sbh] = gt[0];
                 } else {
-                    *reinterpret_cast<f32x4 *>(p.G_tot + sbh * DK + 4 * cq) = gt;
+                    *reinterpret_cast<f32x4 *>(p.G_tot + sbh * DKF + kslice * DK + 4 * cq) = gt;
                 }
             }
         };
@@ -553,7 +557,7 @@ __global__ __launch_bounds__(chunk_threads(DK, DV, GM, MODE)) void gla_chunk_bf1
         const unsigned k_tr0 = Cfg::kOffK + (8 * kg + tr_k) * QS + (16 * tr_h + 8 * (tr_r & 1) + 4 * (tr_r >> 1)) * 2;
 
         f32x16 Sacc[Cfg::NIT], Oacc[2];
-        float *Sl = p.S_loc + sbh * DK * (DV * NS) + slice * DV + w * 32 + lt;   // this lane's state column
+        float *Sl = p.S_loc + (sbh * DKF + kslice * DK) * (DV * NS) + slice * DV + w * 32 + lt;   // this lane's state column
         const float *Si = p.S_init + sbh * DK * (DV * NS) + slice * DV + w * 32 + lt;
 #pragma unroll
         for (int it = 0; it < Cfg::NIT; ++it)
@@ -692,15 +696,15 @@ __global__ __launch_bounds__(chunk_threads(DK, DV, GM, MODE)) void gla_chunk_bf1
     }
 }
 
-template <int DK, int DV, int NS, int GM, int MODE, bool WIDE>
+template <int DK, int DV, int NS, int GM, int MODE, bool WIDE, int NSK = 1>
 static hipError_t launch_b16(const ChunkParams &p, hipStream_t s) {
     typedef B16Cfg<DK, DV, gate_waves(DK, GM, MODE), idle_waves(DK, DV, GM, MODE)> Cfg;
-    auto kern = gla_chunk_bf16_kernel<DK, DV, NS, GM, MODE, WIDE>;
+    auto kern = gla_chunk_bf16_kernel<DK, DV, NS, GM, MODE, WIDE, NSK>;
     static LdsLimit limit;   // one per instantiation
     hipError_t e = limit.raise((const void *)kern, Cfg::kBytes);
     if (e != hipSuccess) return e;
     const int streams = p.B * p.P * p.H;
-    const int grid = ((streams + 7) / 8) * 8 * NS;
+    const int grid = ((streams + 7) / 8) * 8 * NS * NSK;
     hipLaunchKernelGGL(kern, dim3(grid), dim3(Cfg::NT), Cfg::kBytes, s, p);
     return hipGetLastError();
 }
@@ -711,7 +715,17 @@ static hipError_t dispatch_dims(const ChunkParams &p, int d_k, int d_v, hipStrea
     // more compute units stream memory; the gate pass is then computed twice.  Between 128 and 256 streams
     // one workgroup per stream on part of the chip is faster than two rounds of siblings (192 streams:
     // 1.21 ms against 1.58 ms for the local pass of 16384 tokens).
-    const bool split = d_v == 128 && p.B * p.P * p.H * 2 <= 256;
+    const int streams = p.B * p.P * p.H;
+    const bool split = d_v == 128 && streams * 2 <= 256;
+    if constexpr (MODE == kStates || MODE == kDState) {
+        // The states alone split over the key channels as well, and better: a sibling then reads half of k and g, not all of
+        // them and half of v (64 streams of 8192 tokens, d = 128, in 256 instead of 128 workgroups: 230 -> 172 us, state gradients
+        // 233 -> 169)
+        if (d_k == 128 && streams * 2 <= 256) {
+            if (d_v == 64) return launch_b16<64, 64, 1, GM, MODE, WIDE, 2>(p, s);
+            return streams * 4 <= 256 ? launch_b16<64, 64, 2, GM, MODE, WIDE, 2>(p, s) : launch_b16<64, 128, 1, GM, MODE, WIDE, 2>(p, s);
+        }
+    }
     if (d_k == 64 && d_v == 64) return launch_b16<64, 64, 1, GM, MODE, WIDE>(p, s);
     if (d_k == 128 && d_v == 64) return launch_b16<128, 64, 1, GM, MODE, WIDE>(p, s);
     if (d_k == 64 && d_v == 128)

@@ -57,3 +57,31 @@ def test_surplus_rows_reach_nothing(dk, dv, bad):
     assert torch.equal(got[0][:, :40], clean[0][:, :40]) and torch.equal(got[0][:, 41:], clean[0][:, 41:])
     for a, b in zip(got[1:], clean[1:]):   # what depends on later tokens only
         assert torch.equal(a[:, 64:], b[:, 64:])
+
+
+@pytest.mark.parametrize("gate", ["f32", "bf16", "head"])
+@pytest.mark.parametrize("dv", [64, 128])
+@pytest.mark.parametrize("streams", [64, 65, 128, 129])
+def test_state_passes_and_dq_around_the_sibling_rules(streams, dv, gate):
+    # 64 and 128 streams are the last that run as four and as two workgroups a stream (state passes; dQ: two)
+    P, L, dk = streams, 96, 128
+    inp = make(1, P * L, dk, dv, gate, 40 + streams)
+    h = {n: host(t) for n, t in inp.items()}
+    if gate == "head":
+        h["g"] = np.repeat(h["g"][..., None], dk, axis=-1)
+    q, k, v, g, dO = (inp[n] for n in ("q", "k", "v", "g", "dO"))
+    S_loc, G_tot = zeco.gla_local_state(k, v, g, P)
+    S_init, S_last = zeco.state_scan(S_loc, G_tot)
+    dS_loc = zeco.gla_bwd_dstate(q, g, dO, P, scale=0.5)
+    dS_in, dS0 = zeco.state_scan(dS_loc, G_tot, direction=1)
+    got = zeco.gla_bwd_from_state(q, k, v, g, dO, S_init, S_last, dS_in, P, scale=0.5)
+    torch.cuda.synchronize()
+    _, S_ref = oracle.gla_recurrent(h["q"], h["k"], h["v"], h["g"], 0.5)
+    ref = oracle.gla_recurrent_bwd(h["q"], h["k"], h["v"], h["g"], h["dO"], 0.5, None, None)
+    assert rel_err_bh(host(S_last), S_ref, (0, 1)) <= TOLB
+    assert rel_err_bh(host(dS0), ref[4], (0, 1)) <= TOLB
+    assert rel_err_bh(host(G_tot).sum(axis=0)[..., None], h["g"][..., 0].sum(axis=1)[..., None] if gate == "head" else h["g"].sum(axis=1)[..., None],
+                      (0, 1)) <= 1e-5
+    for nm, x, r in zip(("dq", "dk", "dv"), got[:3], ref[:3]):
+        assert rel_err_bh(host(x), r, (0, 2)) <= TOLB, nm
+    assert rel_err_bh(host(got[3]), ref[3].sum(axis=-1) if gate == "head" else ref[3], (0, 2)) <= TOLB, "dg"
