@@ -152,6 +152,7 @@ __global__ __launch_bounds__(256) void state_scan_kernel(ScanParams p, int parts
         }
     }
     if (p.S_last) *reinterpret_cast<vec_t *>(p.S_last + grp * seg_stride + off) = s;
+    if (p.S_last2) *reinterpret_cast<vec_t *>(p.S_last2 + grp * seg_stride + off) = s;
     if (prefix && p.G_sum) p.G_sum[grp * g_stride + gcol] = (float)gsum;
 }
 

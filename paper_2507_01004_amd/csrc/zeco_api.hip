@@ -115,13 +115,13 @@ hipError_t launch_scan_tree(zeco::ScanParams sp, float *scratch, hipStream_t s) 
     float *T = scratch, *I = T + J * state, *Gt = I + J * state;
     zeco::ScanParams p = sp;
     p.G_pre = nullptr;
-    p.S0 = nullptr; p.S_init = nullptr; p.S_last = T; p.G_sum = Gt; p.P = g; p.groups = J;
+    p.S0 = nullptr; p.S_init = nullptr; p.S_last = T; p.S_last2 = nullptr; p.G_sum = Gt; p.P = g; p.groups = J;
     hipError_t e = zeco::launch_scan(p, s);
     if (e != hipSuccess) return e;
-    p.S_loc = T; p.G_tot = Gt; p.S0 = sp.S0; p.S_init = I; p.S_last = sp.S_last; p.G_sum = nullptr;
+    p.S_loc = T; p.G_tot = Gt; p.S0 = sp.S0; p.S_init = I; p.S_last = sp.S_last; p.S_last2 = sp.S_last2; p.G_sum = nullptr;
     p.P = J; p.groups = 1;
     if ((e = zeco::launch_scan(p, s)) != hipSuccess) return e;
-    p.S_loc = sp.S_loc; p.G_tot = sp.G_tot; p.S0 = I; p.S_init = sp.S_init; p.S_last = nullptr;
+    p.S_loc = sp.S_loc; p.G_tot = sp.G_tot; p.S0 = I; p.S_init = sp.S_init; p.S_last = p.S_last2 = nullptr;
     p.P = g; p.groups = J;
     return zeco::launch_scan(p, s);
 }
@@ -636,13 +636,10 @@ zeco_status zeco_gla_fused_fwd(const zeco_gla_desc *d, const void *q, const void
 
     zeco::ScanParams sp;
     sp.S_loc = Sloc; sp.G_tot = Gtot; sp.S0 = S0; sp.S_init = Sinit; sp.S_last = S_save ? save_last : S_last;
+    sp.S_last2 = S_save ? S_last : nullptr;   // (by the scan, not a copy of its own: 16 heads, d = 128, 2.4 us and a launch)
     sp.P = p.P; sp.groups = 1; sp.BH = d->B * d->H; sp.d_k = d->d_k; sp.d_v = d->d_v;
     sp.rows_per_block = d->d_k / 16; sp.gate_per_head = d->g_per_head;
     if ((e = launch_scan_chain(sp, tree, s)) != hipSuccess) return ZECO_ERR_HIP;
-    if (S_save && S_last) {
-        e = zeco::launch_copy(S_last, save_last, (size_t)d->B * d->H * d->d_k * d->d_v * sizeof(float), s);
-        if (e != hipSuccess) return ZECO_ERR_HIP;
-    }
 
     if (correct) {   // correction of the pieces' heads
         zeco::ApplyParams ap;

@@ -95,6 +95,7 @@ struct ApplyParams {
 struct ScanParams {
     const float *S_loc, *G_tot, *S0;
     float *S_init, *S_last;      // either may be null (not stored)
+    float *S_last2 = nullptr;    // optional: the end states a second time
     int P, BH, d_k, d_v, rows_per_block, groups;
     const long long *P_used = nullptr;   // optional, one chain only: its length, on the device (at most P)
     int reverse = 0;             // 1: chain runs from segment P-1 down to 0
