@@ -129,24 +129,6 @@ __device__ __forceinline__ void lds_fetch_wait() { asm volatile("s_waitcnt vmcnt
 // exclusive or would take registers that are not there.
 __device__ __forceinline__ void keep_in_loop(unsigned &x) { asm volatile("" : "+v"(x)); }
 
-// A chain of N matrix products, each with one operand `rd(s)` from LDS, kept D reads ahead of the products `mm(s, operand)`.
-// With nothing but its own instructions to hide an LDS read of some 130 cycles behind, a matrix wave has to issue it four
-// products early; left to itself the compiler, short of registers, waits for every read right after issuing it (scores and
-// products of a chunk of the dK pass, d = 128, alone on the chip: 6.3 us).
-template <int N, int D, class R, class F> __device__ __forceinline__ void pipelined(R rd, F mm) {
-    decltype(rd(0)) f[D];
-#pragma unroll
-    for (int s = 0; s < D && s < N; ++s) f[s] = rd(s);
-#pragma unroll
-    for (int s = 0; s < N; ++s) {
-        __builtin_amdgcn_sched_barrier(0x6);   // (VALU and SALU instructions may pass, matrix products and reads may not)
-        mm(s, f[s % D]);
-        if (s + D < N) f[s % D] = rd(s + D);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-}
-struct FragPair { bf16x8 a, b; };
-
 // Sum over the N lanes (16 or 32, aligned) that share a token, in all of them.
 template <int N> __device__ __forceinline__ float lane_sum(float x) {
     auto add = [&](auto ctrl) __attribute__((always_inline)) {

@@ -149,4 +149,22 @@ __device__ __forceinline__ bf16x8 lds_frag_tr(const unsigned char *addr, const u
 }
 __device__ __forceinline__ bf16x8 lds_frag_tr(const unsigned char *addr, int second) { return lds_frag_tr(addr, addr + second); }
 
+// A chain of N matrix products, each with one operand `rd(s)` from LDS, kept D reads ahead of the products `mm(s, operand)`.
+// With nothing but its own instructions to hide an LDS read of some 130 cycles behind, a matrix wave has to issue it four
+// products early; left to itself the compiler, short of registers, waits for every read right after issuing it (six times the
+// products' own time in the dK pass).
+template <int N, int D, class R, class F> __device__ __forceinline__ void pipelined(R rd, F mm) {
+    decltype(rd(0)) f[D];
+#pragma unroll
+    for (int s = 0; s < D && s < N; ++s) f[s] = rd(s);
+#pragma unroll
+    for (int s = 0; s < N; ++s) {
+        __builtin_amdgcn_sched_barrier(0x6);   // (VALU and SALU instructions may pass, matrix products and reads may not)
+        mm(s, f[s % D]);
+        if (s + D < N) f[s % D] = rd(s + D);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+}
+struct FragPair { bf16x8 a, b; };
+
 }  // namespace zeco
