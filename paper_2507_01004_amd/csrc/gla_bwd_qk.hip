@@ -606,6 +606,9 @@ __global__ __launch_bounds__(bwd_threads(DK, DV)) void gla_bwd_bf16_kernel(BwdQK
     } else {
         // ================================ matrix waves =========================================
         const int w = pw;
+        // before the gate wave on the same SIMD, whose turn comes while products run (0.3 - 1 %: per-head training step 575 -> 569 us,
+        // packed segments 914 -> 909; the gate waves first: 0.7 % slower there, 1 % faster on 64 streams)
+        __builtin_amdgcn_s_setprio(2);
         // Lane coordinates of the 32x32x16 and (score tiles) 16x16x32 products, and all LDS addresses, are worked out where they
         // are used, from a lane number that changes for all the compiler knows (keep_in_loop).
         unsigned ln = lane;
