@@ -443,11 +443,11 @@ def run_workload(args, workload, with_cpu):
             bms = timed(lambda: zeco.gla_fused_bwd(q, k, v, g, dO, P, out=grads, workspace=ws),
                         warm=max(1, args.warmup // 2), reps=nb)
             th = B * T * H
-            # bytes of the four passes as built: forward states (k, v, g), dQ (dO, v, k, q, g in; dq and fp32 q.*dq
-            # out; it also leaves the pieces' state gradients), dV (k, q, dO, g in; dv out), dK (v, dO, q, k, g, fp32
-            # q.*dq in; dk and fp32 dg out)
+            # bytes of the three passes as built: forward states (k, v, g), dQ (dO, v, k, q, g in; dq and fp32 q.*dq
+            # out; it also leaves the pieces' state gradients), dK and dV (v, dO, q, k, g, fp32 q.*dq in; dk, dv and
+            # fp32 dg out)
             io = dk * 2
-            pb = th * ((2 * io + g_in) + (5 * io + g_in + g_cum) + (4 * io + g_in) + (5 * io + g_in + 2 * g_cum))
+            pb = th * ((2 * io + g_in) + (5 * io + g_in + g_cum) + (6 * io + g_in + 2 * g_cum))
             # training pair: the forward leaves the states at the backward's piece boundaries, the backward
             # starts from them instead of recomputing them
             save = torch.empty(zeco.saved_states_bytes(q, v, g, P), dtype=torch.uint8, device="cuda:0")

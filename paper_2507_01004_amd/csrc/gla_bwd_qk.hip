@@ -39,8 +39,8 @@
 // What bounds it.  At 256 workgroups with fp32 gates per channel, HBM: dQ pass 1050 -> 960 us, dV 555 and dK 1094 -> one
 // pass of 1210 us for 16 heads x 131072 tokens, 5.2 TB/s of their 11.3 GB (the kernel before, with all waves at the gate pass
 // and then all at the products, took 8.2 - 8.6 us a chunk and pass whatever the bytes; per-head gates, 32768 tokens: dQ 250 -> 175, dV and dK
-// 337 -> 205 us).  On few compute units, what one of them can have in flight: 33 GB/s (64 streams: dQ 4.5, dK and dV 5.7 us
-// a chunk), because its outstanding reads fill the 32 KB of its vector cache.  The chain of the matrix waves is 4.1 us a
+// 337 -> 205 us).  On few compute units, what one of them can have in flight: 33 GB/s (64 streams of 128 chunks: dQ 579 us, 379 in
+// two workgroups a stream; dK and dV 819 us in one), because its outstanding reads fill the 32 KB of its vector cache.  The chain of the matrix waves is 4.1 us a
 // chunk in the dK pass, 1.9 in the dQ pass (cycle stamps), of which products 1.2; that of the gate waves 3.6 - 4.2.
 // What it took to get there: every wave's loop free of spilled registers, since the wait for a spilled value is also
 // a wait for the fetches issued before it (6.3 -> 8 us a chunk with a dozen spills), and operands read several products ahead.

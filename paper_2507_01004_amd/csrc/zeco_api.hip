@@ -72,7 +72,7 @@ void set_length_c(zeco::ChunkParams &p, int L, int C) {
 int gate_mode(const zeco_gla_desc *d);
 int chunk_gate(const zeco_gla_desc *d);
 // One of the phases both precisions have (0 local pass, 1 states only, 2 output pass from S_init, 3 backward
-// state pass, 4 dV pass), on the segments p describes (p.L tokens each, or the table p.seg_start).
+// state pass; fp32 only: 4 dV pass), on the segments p describes (p.L tokens each, or the table p.seg_start).
 hipError_t launch_phase(zeco::ChunkParams &p, const zeco_gla_desc *d, int mode, hipStream_t s) {
     if (d->io_dtype == ZECO_F32) {
         if (!p.cut.n) set_length_c(p, p.L, d->C);
