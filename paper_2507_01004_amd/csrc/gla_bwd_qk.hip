@@ -110,6 +110,7 @@ template <int DK, int DV, bool REV> struct BwdCfg {
     static constexpr int kOffTot2 = kOffTot + NWG * DK * 4;  // [gate wave][channel] sums of the dG terms
     static constexpr int kBytes = kOffTot2 + (REV ? NWG * DK * 4 : 0);
     static_assert(kBytes <= 160 * 1024, "LDS of a compute unit");
+    static_assert(kOffZ <= 64 * 1024, "the fetched tiles, X and Y, are addressed with the 16 bits of M0");
 };
 
 // Where piece c of row r lies: at c ^ swizzle(r).  Sixteen consecutive rows then have the same piece on 64 different banks
@@ -118,10 +119,25 @@ template <int DK, int DV, bool REV> struct BwdCfg {
 template <int D> __device__ __forceinline__ constexpr int swizzle(int r) {
     return D == 128 ? ((r & 3) << 2) | ((r >> 2) & 3) : (((r >> 1) & 1) << 2) | ((r >> 2) & 3);
 }
-// 16 bytes a lane from `base` + `off` (bytes) straight to LDS, to `at` + 16 * lane.  The compiler does not see these
-// loads: lds_fetch_wait before the barrier that publishes them.
-__device__ __forceinline__ void lds_fetch(const unsigned char *base, unsigned off, unsigned at) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(at), "v"(off), "s"(base) : "memory");
+// N times 16 bytes a lane straight to LDS, from `base` + `off` + i * step (the offset in 32 bits, modulo 2^32) to `at` + i * STEP +
+// 16 * lane.  The compiler does not see that these are loads: lds_fetch_wait before the barrier that publishes them.  Nor does it see
+// that a load reads `base`, which it may have restored from a vector register's lane right before the block (the kernels keep up to a
+// hundred scalars there): five wait states have to lie between a vector instruction that writes a scalar register and a vector
+// memory instruction that reads it, here the first two instructions.  The loads of a group share the base, so the wait is there
+// once, and the address arithmetic of the rest is one vector addition each (16 heads x 4096 tokens, 64 x 64, per-head gates:
+// gradients 270 us with a base for each load and no wait, 276 with the wait before each, 265 so).  M0 is the compiler's to reserve and is
+// written again before every use, so it is no clobber.
+template <int N, int STEP> __device__ __forceinline__ void lds_fetch(const unsigned char *base, unsigned off, unsigned step, unsigned at) {
+    static_assert(N == 2 || N == 4, "");
+#define ZECO_FETCH_NEXT "v_add_u32 %0, %3, %0\n\ts_add_u32 m0, m0, %4\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2\n\t"
+#define ZECO_FETCH_FIRST "s_mov_b32 m0, %1\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %0, %2\n\t"
+    if constexpr (N == 2)
+        asm volatile(ZECO_FETCH_FIRST ZECO_FETCH_NEXT : "+&v"(off) : "s"(at), "s"(base), "s"(step), "n"(STEP) : "memory", "scc");
+    else
+        asm volatile(ZECO_FETCH_FIRST ZECO_FETCH_NEXT ZECO_FETCH_NEXT ZECO_FETCH_NEXT
+                     : "+&v"(off) : "s"(at), "s"(base), "s"(step), "n"(STEP) : "memory", "scc");
+#undef ZECO_FETCH_NEXT
+#undef ZECO_FETCH_FIRST
 }
 __device__ __forceinline__ void lds_fetch_wait() { asm volatile("s_waitcnt vmcnt(0)" : : : "memory"); }
 
@@ -625,12 +641,8 @@ __global__ __launch_bounds__(bwd_threads(DK, DV)) void gla_bwd_bf16_kernel(BwdQK
         auto XR = [&]() __attribute__((always_inline)) { return (int)(Cfg::RPI * w + ln / Cfg::PPR); };   // tile row of the lane's first piece
         auto fetch = [&](const unsigned char *src, int m, unsigned tile) __attribute__((always_inline)) {
             const int xr = XR(), xpc = (ln % Cfg::PPR) ^ swizzle<DV>(xr);
-            const unsigned x_off = ((unsigned)pos_of(REV ? xr + Cfg::RPI * NWM * (Cfg::NXY - 1) : xr) * vt + 8 * xpc) * 2;
-            const unsigned char *base = src + cstart(chunk_of(m < N ? m : N - 1)) * vt * 2;
-#pragma unroll
-            for (int i = 0; i < Cfg::NXY; ++i)
-                lds_fetch(base + (size_t)(Cfg::RPI * NWM * (REV ? Cfg::NXY - 1 - i : i)) * vt * 2, x_off,
-                          tile + (w + NWM * i) * 1024);
+            const unsigned off = ((unsigned)pos_of(xr) * vt + 8 * xpc) * 2, step = (unsigned)(Cfg::RPI * NWM) * vt * 2;
+            lds_fetch<Cfg::NXY, NWM * 1024>(src + cstart(chunk_of(m < N ? m : N - 1)) * vt * 2, off, REV ? 0u - step : step, tile + w * 1024);
         };
         // surplus rows of the short chunk: zero (so that nothing in them, infinities included, reaches other rows)
         auto clear_dead = [&](int m, unsigned tile) __attribute__((always_inline)) {

@@ -1,0 +1,63 @@
+"""What the compiler made of the kernels, read from the library as built: the instructions and the resources that correctness or
+speed rest on and that no test of results would show.  Needs no GPU."""
+import os
+import re
+import struct
+import subprocess
+
+import pytest
+
+from paper_2507_01004_amd import zeco
+
+OBJDUMP = "/opt/rocm/llvm/bin/llvm-objdump"
+
+
+def code_objects():
+    """The gfx950 code objects in the library, one per source file with kernels."""
+    if not os.path.exists(zeco.LIB_PATH):
+        from paper_2507_01004_amd.build import build_lib
+        build_lib()
+    data = open(zeco.LIB_PATH, "rb").read()
+    out = []
+    for m in re.finditer(b"__CLANG_OFFLOAD_BUNDLE__", data):
+        entries, at = struct.unpack_from("<Q", data, m.start() + 24)[0], m.start() + 32
+        for _ in range(entries):
+            offset, size, n = struct.unpack_from("<QQQ", data, at)
+            if b"gfx950" in data[at + 24:at + 24 + n]:
+                out.append(data[m.start() + offset:m.start() + offset + size])
+            at += 24 + n
+    assert out
+    return out
+
+
+def instructions(path):
+    """(mnemonic, operands) of every instruction of a code object."""
+    text = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", str(path)], check=True, capture_output=True, text=True).stdout
+    for line in text.splitlines():
+        if line.startswith("\t"):
+            yield tuple((line.split("//")[0].strip() + " ").split(" ", 1))
+
+
+@pytest.mark.skipif(not os.path.exists(OBJDUMP), reason="no disassembler")
+def test_fetches_to_lds_wait_for_their_base(tmp_path):
+    """A vector-memory instruction may read a scalar register five wait states after a vector instruction wrote it, and the compiler,
+    which restores scalars from vector lanes, does not know of the loads inside an asm block: each has to bring the wait along, or
+    share the base of a load just before it."""
+    seen = 0
+    for i, obj in enumerate(code_objects()):
+        path = tmp_path / ("%d.elf" % i)
+        path.write_bytes(obj)
+        before = []
+        for op, args in instructions(path):
+            if op.startswith("global_load_lds"):
+                seen += 1
+                base = args.split(",")[1].strip()
+                assert before[-1][0] == "s_nop"
+                if before[-2][0] == "s_mov_b32":   # first of a group
+                    assert before[-2][1].startswith("m0") and int(before[-1][1]) >= 3
+                else:
+                    assert before[-2][0] == "s_add_u32" and before[-2][1].startswith("m0")
+                    assert before[-3][0].startswith("v_add_u32")
+                    assert before[-4][0].startswith("global_load_lds") and before[-4][1].split(",")[1].strip() == base
+            before = (before + [(op, args)])[-4:]
+    assert seen > 0
