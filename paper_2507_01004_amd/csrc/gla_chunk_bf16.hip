@@ -131,6 +131,21 @@ constexpr int chunk_threads(int dk, int dv, int gm, int mode) {
     return 64 * (dv / 32 + gate_waves(dk, gm, mode) + idle_waves(dk, dv, gm, mode));
 }
 
+// LDS reads of the scores and of the inter-chunk product issued ahead of their products (see pipelined; 0: in the compiler's
+// order).  Four where there are registers for them and the matrix waves are the ones waited for: d_k = 64 (16 heads x 8192
+// tokens as one segment, output pass: 64 x 128 193 -> 183 us, 64 x 64 with bf16 gates 198 -> 187), the wide range of gates, whose state is
+// decayed twice (16 heads, 8 x 4096 tokens, d = 128: per-head gates local 205 -> 161, output 206 -> 155; bf16 gates local in siblings
+// 224 -> 203), output passes with per-head gates (16 heads x 8192, 249 -> 235).  None at d_k = 128 otherwise: the twelve waves of the
+// local pass with gates per channel and all 128 columns have 168 registers each, and the wide form spills 23 inside its loop (16 heads,
+// 16 x 4096 tokens: 365 -> 430 us, bf16 gates 352 -> 420); per-head local pass of 192 segments of 2240 tokens 110 -> 114; output passes of few streams
+// with gates per channel 278 -> 282.
+constexpr int read_ahead(int dk, int dv, int gm, int mode, bool wide) {
+    const bool local = mode == kLocal || mode == kLocalInit;
+    if (dk == 64) return 4;
+    if (gm == kGateHead) return wide || !(local || mode == kLocalCD) ? 4 : 0;
+    return wide && local && dv == 64 ? 4 : 0;
+}
+
 //
 // WIDE selects the reference point of the decay factors in the operand tiles.  With c the in-chunk cumulative
 // log decay and total its value at the chunk's end, the tiles hold Q .* e^(c - ref) and K .* e^(ref - c); any
@@ -155,7 +170,7 @@ __global__ __launch_bounds__(chunk_threads(DK, DV, GM, MODE)) void gla_chunk_bf1
     constexpr bool REV = MODE == kDState;                         // chunks and tokens in reverse
     constexpr bool NOQ = MODE == kStates || MODE == kDState;      // only the state is computed
     static_assert(NSK == 1 || NOQ, "scores contract over all key channels");
-    constexpr int DKF = DK * NSK;
+    constexpr int DKF = DK * NSK, AHEAD = read_ahead(DK, DV, GM, MODE, WIDE);
     constexpr bool OUT = MODE == kOutput || MODE == kOutputRun;
     constexpr bool FROM_INIT = OUT || MODE == kLocalInit;   // start from S_init (no state emitted, but see kOutputRun)
     constexpr bool EMIT_G = MODE == kLocal || MODE == kLocalInit;  // per-token cumulative log decay
@@ -586,9 +601,8 @@ __global__ __launch_bounds__(chunk_threads(DK, DV, GM, MODE)) void gla_chunk_bf1
         auto mfma_a = [&](const unsigned char *tile, const float *gam_n) __attribute__((always_inline)) {
             const unsigned char *Qs = tile + Cfg::kOffQ, *Ks = tile + Cfg::kOffK;
             if constexpr (WIDE) decay_state(gam_n);
-            // P^T tiles (ts <= tt), 16x16x32.  Reads four products ahead here and in the inter-chunk product (500 tokens, 8 heads,
-            // d_k = 64: 16.0 -> 15.7 us; 16 heads x 16384 tokens, d_v = 64: 115.4 -> 112.4).  Not in part 2, whose state update then has its
-            // decays behind it instead of between its tiles (16 heads x 16384 tokens 145.5 -> 150 us).
+            // P^T tiles (ts <= tt), 16x16x32.  (Part 2 is left to the compiler everywhere: read ahead, its state update has its
+            // decays behind it instead of between its tiles, 16 heads x 16384 tokens 145.5 -> 150 us.)
             auto scores = [&](auto tiles, int i0) __attribute__((always_inline)) {   // tiles i0, i0 + NWM, .. of the lower ten
                 constexpr int NTL = decltype(tiles)::value, K = DK / 32;
                 auto tile_of = [&](int i, int &tt, int &ts) __attribute__((always_inline)) {   // wave-uniform
@@ -597,7 +611,7 @@ __global__ __launch_bounds__(chunk_threads(DK, DV, GM, MODE)) void gla_chunk_bf1
                     ts = idx - tt * (tt + 1) / 2;
                 };
                 f32x4 acc;
-                pipelined<NTL * K, 4>(
+                pipelined<NTL * K, AHEAD>(
                     [&](int s) __attribute__((always_inline)) {
                         int tt, ts;
                         tile_of(s / K, tt, ts);
@@ -610,9 +624,11 @@ __global__ __launch_bounds__(chunk_threads(DK, DV, GM, MODE)) void gla_chunk_bf1
                         if (s % K == K - 1) {
                             int tt, ts;
                             tile_of(s / K, tt, ts);
-                            const int last = l16 + 16 * (tt - ts) - 4 * kg16;   // s <= t
+                            if (AHEAD || ts == tt) {   // s <= t (a branch would be a fence between the reads)
+                                const int last = l16 + 16 * (tt - ts) - 4 * kg16;
 #pragma unroll
-                            for (int rr = 0; rr < 4; ++rr) acc[rr] = rr > last ? 0.f : acc[rr];
+                                for (int rr = 0; rr < 4; ++rr) acc[rr] = rr > last ? 0.f : acc[rr];
+                            }
                             *reinterpret_cast<u32x2 *>(Ps + (16 * tt + l16) * TS + (16 * ts + 4 * kg16) * 2) =
                                 u32x2{pack_bf16(acc[0], acc[1]), pack_bf16(acc[2], acc[3])};
                         }
@@ -626,7 +642,7 @@ __global__ __launch_bounds__(chunk_threads(DK, DV, GM, MODE)) void gla_chunk_bf1
 #pragma unroll
                 for (int rr = 0; rr < 16; ++rr) Oacc[mt][rr] = 0.f;
             bf16x8 sf;
-            pipelined<DK / 8, 4>(
+            pipelined<DK / 8, AHEAD>(
                 [&](int s) __attribute__((always_inline)) { return lds_frag(Qs, ((s % 2) * 32 + lt) * QS + (s / 2 * 16 + 8 * kg) * 2); },
                 [&](int s, bf16x8 f) __attribute__((always_inline)) {
                     if (s % 2 == 0) sf = pack8(Sacc[s / 4], 8 * (s / 2 % 2));

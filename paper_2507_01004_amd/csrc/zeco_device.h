@@ -154,16 +154,21 @@ __device__ __forceinline__ bf16x8 lds_frag_tr(const unsigned char *addr, int sec
 // products early; left to itself the compiler, short of registers, waits for every read right after issuing it (six times the
 // products' own time in the dK pass).
 template <int N, int D, class R, class F> __device__ __forceinline__ void pipelined(R rd, F mm) {
-    decltype(rd(0)) f[D];
+    if constexpr (D == 0) {   // left to the compiler
 #pragma unroll
-    for (int s = 0; s < D && s < N; ++s) f[s] = rd(s);
+        for (int s = 0; s < N; ++s) mm(s, rd(s));
+    } else {
+        decltype(rd(0)) f[D];
 #pragma unroll
-    for (int s = 0; s < N; ++s) {
-        __builtin_amdgcn_sched_barrier(0x6);   // (VALU and SALU instructions may pass, matrix products and reads may not)
-        mm(s, f[s % D]);
-        if (s + D < N) f[s % D] = rd(s + D);
+        for (int s = 0; s < D && s < N; ++s) f[s] = rd(s);
+#pragma unroll
+        for (int s = 0; s < N; ++s) {
+            __builtin_amdgcn_sched_barrier(0x6);   // (VALU and SALU instructions may pass, matrix products and reads may not)
+            mm(s, f[s % D]);
+            if (s + D < N) f[s % D] = rd(s + D);
+        }
+        __builtin_amdgcn_sched_barrier(0);
     }
-    __builtin_amdgcn_sched_barrier(0);
 }
 struct FragPair { bf16x8 a, b; };
 

@@ -30,6 +30,25 @@ def code_objects():
     return out
 
 
+def kernels():
+    """Name -> metadata of every kernel in the library (the ELF note the runtime itself launches by)."""
+    msgpack = pytest.importorskip("msgpack")
+    out = {}
+    for obj in code_objects():
+        table, = struct.unpack_from("<Q", obj, 0x28)
+        size, count = struct.unpack_from("<HH", obj, 0x3a)
+        for at in range(table, table + size * count, size):
+            kind, = struct.unpack_from("<I", obj, at + 4)
+            offset, = struct.unpack_from("<Q", obj, at + 24)
+            if kind == 7:   # SHT_NOTE: one note, name padded to four bytes
+                name, desc = struct.unpack_from("<II", obj, offset)
+                start = offset + 12 + (name + 3) // 4 * 4
+                for k in msgpack.unpackb(obj[start:start + desc], strict_map_key=False)["amdhsa.kernels"]:
+                    out[k[".name"]] = k
+    assert out
+    return out
+
+
 def instructions(path):
     """(mnemonic, operands) of every instruction of a code object."""
     text = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", str(path)], check=True, capture_output=True, text=True).stdout
@@ -61,3 +80,11 @@ def test_fetches_to_lds_wait_for_their_base(tmp_path):
                     assert before[-4][0].startswith("global_load_lds") and before[-4][1].split(",")[1].strip() == base
             before = (before + [(op, args)])[-4:]
     assert seen > 0
+
+
+def test_chunk_kernels_keep_their_registers():
+    """A spilled register of the chunk kernel is reloaded in its loop, and the wait for it is a wait for the rows fetched ahead as well.
+    Two or three, saved around the loop's tail, are what the twelve-wave forms need at their 168 registers."""
+    spilled = {n: k[".vgpr_spill_count"] for n, k in kernels().items() if "gla_chunk_bf16_kernel" in n}
+    assert len(spilled) > 100
+    assert {n: v for n, v in spilled.items() if v > 3} == {}
