@@ -270,12 +270,17 @@ __global__ __launch_bounds__(chunk_threads(DK, DV, GM, MODE)) void gla_chunk_bf1
         const unsigned v_b0 = ((unsigned)(tv * TPTV) * vt + 4 * vq) * 2;
         const unsigned g_b0 = ((unsigned)(tq * TPT) * gcs + (GH ? 0 : 4 * cq)) * 4;   // G_cum: contiguous [.., H, d_k]
 
-        // Reloads of the streamed inputs: read once by this workgroup, so non-temporal - unless sibling
-        // workgroups share them through the XCD's L2 (NS = 2), where the hint would cost HBM re-reads.
-        auto stream_load = [](auto *ptr) __attribute__((always_inline)) {
-            if constexpr (NS == 1) return __builtin_nontemporal_load(ptr);
+        // Reloads of the streamed inputs: read once, so non-temporal - unless sibling workgroups share them through the XCD's L2,
+        // where the hint would cost HBM re-reads: all of them with siblings over the columns (NS = 2).  Siblings over the key channels share v,
+        // and with one decay per head g: with the hint on these the forward states of 96 streams x 4096 tokens, d = 128, take 79.3 us
+        // instead of 70.3 (112 x 8192 153 / 136, state gradients 79.3 / 72.5).  With gates per channel, where v is a quarter of the bytes,
+        // it is as long either way (128 x 4096 100 / 98 us, 128 x 16384 with bf16 gates 352 / 357): the hint stays.
+        auto stream_load = [](auto *ptr, auto shared) __attribute__((always_inline)) {
+            if constexpr (NS == 1 && !(GH && NSK > 1 && decltype(shared)::value)) return __builtin_nontemporal_load(ptr);
             else return *ptr;
         };
+        typedef std::false_type Own;      // this workgroup's channels
+        typedef std::true_type Shared;    // the stream's
 
         // Raw q, k, g, v of the chunk worked on next; each piece is reloaded with the following
         // chunk's data right after its last use (clamped to the last chunk).
@@ -316,7 +321,7 @@ __global__ __launch_bounds__(chunk_threads(DK, DV, GM, MODE)) void gla_chunk_bf1
             for (int u = 0; u < TPT; ++u) {
                 f32x4 gv = GV::get(rg[u]);
                 if (first && dead(tq * TPT + u)) gv = f32x4{0.f, 0.f, 0.f, 0.f};
-                rg[u] = stream_load(reinterpret_cast<const typename GV::raw_t *>(gn + (size_t)(u * gst) * GB + g_in_b0));
+                rg[u] = stream_load(reinterpret_cast<const typename GV::raw_t *>(gn + (size_t)(u * gst) * GB + g_in_b0), Shared{});
 #pragma unroll
                 for (int a = 0; a < 4; ++a) run[a] += gv[a];
                 cs[u] = run;
@@ -342,7 +347,7 @@ __global__ __launch_bounds__(chunk_threads(DK, DV, GM, MODE)) void gla_chunk_bf1
             for (int u = 0; u < TPTV; ++u) {
                 if (first && dead(tv * TPTV + u)) rv[u] = u32x2{0u, 0u};
                 *reinterpret_cast<u32x2 *>(tile + Cfg::kOffV + pos_of(tv * TPTV + u) * VS + 8 * vq) = rv[u];
-                rv[u] = stream_load(reinterpret_cast<const u32x2 *>(vn + (size_t)(u * vt) * 2 + v_b0));
+                rv[u] = stream_load(reinterpret_cast<const u32x2 *>(vn + (size_t)(u * vt) * 2 + v_b0), Shared{});
             }
         };
 
@@ -425,7 +430,7 @@ __global__ __launch_bounds__(chunk_threads(DK, DV, GM, MODE)) void gla_chunk_bf1
                 }
                 u32x2 kw = rk[u];
                 if (first && dead(t)) kw = u32x2{0u, 0u};
-                rk[u] = stream_load(reinterpret_cast<const u32x2 *>(kn + (size_t)(u * st) * 2 + q_b0));
+                rk[u] = stream_load(reinterpret_cast<const u32x2 *>(kn + (size_t)(u * st) * 2 + q_b0), Own{});
                 const u32x2 kq = {pack_bf16(bf16_lo(kw[0]) * ilam[0], bf16_hi(kw[0]) * ilam[1]),
                                   pack_bf16(bf16_lo(kw[1]) * ilam[2], bf16_hi(kw[1]) * ilam[3])};
                 if constexpr (!NOQ) {   // scores and outputs need Q .* Lambda
@@ -438,7 +443,7 @@ __global__ __launch_bounds__(chunk_threads(DK, DV, GM, MODE)) void gla_chunk_bf1
                         for (int a = 0; a < 4; ++a) lam[a] = __builtin_amdgcn_exp2f(SGN * yv[a]);
                     }
                     const u32x2 qw = rq[u];
-                    rq[u] = stream_load(reinterpret_cast<const u32x2 *>(qn + (size_t)(u * st) * 2 + q_b0));
+                    rq[u] = stream_load(reinterpret_cast<const u32x2 *>(qn + (size_t)(u * st) * 2 + q_b0), Own{});
                     *reinterpret_cast<u32x2 *>(Qs + pos_of(t) * QS + qpos * 2) =
                         u32x2{pack_bf16(bf16_lo(qw[0]) * lam[0], bf16_hi(qw[0]) * lam[1]),
                               pack_bf16(bf16_lo(qw[1]) * lam[2], bf16_hi(qw[1]) * lam[3])};

@@ -49,12 +49,16 @@ def kernels():
     return out
 
 
-def instructions(path):
-    """(mnemonic, operands) of every instruction of a code object."""
+def instructions(obj, path):
+    """(kernel, mnemonic, operands) of every instruction of a code object."""
+    path.write_bytes(obj)
     text = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", str(path)], check=True, capture_output=True, text=True).stdout
+    kernel = None
     for line in text.splitlines():
-        if line.startswith("\t"):
-            yield tuple((line.split("//")[0].strip() + " ").split(" ", 1))
+        if line.endswith(">:"):
+            kernel = line.split("<")[1][:-2]
+        elif line.startswith("\t"):
+            yield (kernel,) + tuple((line.split("//")[0].strip() + " ").split(" ", 1))
 
 
 @pytest.mark.skipif(not os.path.exists(OBJDUMP), reason="no disassembler")
@@ -63,11 +67,9 @@ def test_fetches_to_lds_wait_for_their_base(tmp_path):
     which restores scalars from vector lanes, does not know of the loads inside an asm block: each has to bring the wait along, or
     share the base of a load just before it."""
     seen = 0
-    for i, obj in enumerate(code_objects()):
-        path = tmp_path / ("%d.elf" % i)
-        path.write_bytes(obj)
+    for obj in code_objects():
         before = []
-        for op, args in instructions(path):
+        for _, op, args in instructions(obj, tmp_path / "code.elf"):
             if op.startswith("global_load_lds"):
                 seen += 1
                 base = args.split(",")[1].strip()
@@ -88,3 +90,18 @@ def test_chunk_kernels_keep_their_registers():
     spilled = {n: k[".vgpr_spill_count"] for n, k in kernels().items() if "gla_chunk_bf16_kernel" in n}
     assert len(spilled) > 100
     assert {n: v for n, v in spilled.items() if v > 3} == {}
+
+
+@pytest.mark.skipif(not os.path.exists(OBJDUMP), reason="no disassembler")
+def test_what_key_channel_siblings_share_is_not_streamed(tmp_path):
+    """Two workgroups that own half of the key channels each read the same v, and the same g with one decay per head.  Read with the
+    non-temporal hint these come from HBM twice: only the four-byte g and the rows of k are told apart here, by width and number."""
+    hinted, plain = {}, {}
+    for obj in code_objects():
+        for kernel, op, args in instructions(obj, tmp_path / "code.elf"):
+            if op.startswith("global_load") and re.search(r"gla_chunk_bf16_kernelILi64ELi\d+ELi1ELi2ELi[13]ELb[01]ELi2EE", kernel):
+                (hinted if args.split()[-1] == "nt" else plain).setdefault(kernel, []).append(op)
+    assert len(plain) == 8   # two widths of v, forward and backward states, two ranges of gates
+    for kernel, ops in plain.items():
+        assert set(hinted[kernel]) == {"global_load_dwordx2"}, kernel
+        assert len(hinted[kernel]) < ops.count("global_load_dwordx2"), kernel
