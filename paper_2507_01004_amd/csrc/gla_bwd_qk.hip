@@ -79,8 +79,13 @@ namespace zeco {
 // waves of a workgroup: four gate waves, d_k / 4 channels each, and matrix waves, 32 state columns each
 constexpr int bwd_matrix_waves(int dk, int dv) { return (dk > dv ? dk : dv) / 32; }
 constexpr int bwd_threads(int dk, int dv) { return 64 * (4 + bwd_matrix_waves(dk, dv)); }
+// Two workgroups share a compute unit in the dQ pass alone at d = 64, and with them the wait of a short segment's prologue
+// (2048 streams of 64 tokens, gradients: 138 -> 120 us, bf16 gates 134 -> 118; 320 of 1024 226 -> 212): 80 KB of LDS and, for
+// two sets of six waves to fit the four SIMDs wherever they land, 128 registers.  The other forms have no room for a second.
+constexpr bool bwd_pairs(int dk, int dv, bool rev, bool emit) { return dk == 64 && dv == 64 && !rev && !emit; }
+constexpr int bwd_min_waves(int dk, int dv, bool rev, bool emit) { return bwd_pairs(dk, dv, rev, emit) ? 4 : 1; }
 
-template <int DK, int DV, bool REV> struct BwdCfg {
+template <int DK, int DV, bool REV, bool HAS_U> struct BwdCfg {
     static constexpr int NWG = 4;
     static constexpr int NWM = bwd_matrix_waves(DK, DV);
     static constexpr int NT = bwd_threads(DK, DV);
@@ -99,7 +104,7 @@ template <int DK, int DV, bool REV> struct BwdCfg {
     static constexpr int kOffY = kOffX + (REV ? 1 : 2) * XB;
     static constexpr int kOffZ = kOffY + 2 * XB;
     static constexpr int kOffU = kOffZ + 2 * ZB;
-    static constexpr int kOffP = kOffU + ZB;
+    static constexpr int kOffP = kOffU + (HAS_U ? ZB : 0);
     static constexpr int kOffP2 = kOffP + 64 * PS;
     static constexpr int kOffO = kOffP2 + (REV ? 64 * PS : 0);
     static constexpr int kOffGam = kOffO + 64 * OS;          // [2][channel] e^(total / 2) of a chunk
@@ -110,6 +115,7 @@ template <int DK, int DV, bool REV> struct BwdCfg {
     static constexpr int kOffTot2 = kOffTot + NWG * DK * 4;  // [gate wave][channel] sums of the dG terms
     static constexpr int kBytes = kOffTot2 + (REV ? NWG * DK * 4 : 0);
     static_assert(kBytes <= 160 * 1024, "LDS of a compute unit");
+    static_assert(HAS_U || DK > 64 || DV > 64 || kBytes <= 80 * 1024, "half of it, see bwd_pairs");
     static_assert(kOffZ <= 64 * 1024, "the fetched tiles, X and Y, are addressed with the 16 bits of M0");
 };
 
@@ -177,18 +183,18 @@ __device__ __forceinline__ bf16x8 pack8_bwd(const f32x16 &a, int base) {
 // (dV contracts over d_k, so the dK pass is not split.)
 // NT: the rows that the gate waves read and write carry the non-temporal hint (see streams_past_caches).
 template <int DK, int DV, int NS, bool REV, int GM, bool EMIT, bool NT_>
-__global__ __launch_bounds__(bwd_threads(DK, DV)) void gla_bwd_bf16_kernel(BwdQKParams p) {
+__global__ __launch_bounds__(bwd_threads(DK, DV), bwd_min_waves(DK, DV, REV, EMIT)) void gla_bwd_bf16_kernel(BwdQKParams p) {
     static_assert(!(REV && EMIT), "the state gradient is a by-product of the forward-direction pass");
     static_assert(NS == 1 || (!REV && GM != kGateHead), "dV, and one decay per head, sum over all channels");
     constexpr int DKF = DK * NS;
-    typedef BwdCfg<DK, DV, REV> Cfg;
+    constexpr bool HAS_U = REV || EMIT;
+    typedef BwdCfg<DK, DV, REV, HAS_U> Cfg;
     typedef Mma<32> M;
     typedef GateVal<GM> GV;
     constexpr int XS = Cfg::XS, ZS = Cfg::ZS, PS = Cfg::PS, OS = Cfg::OS, NWM = Cfg::NWM, NWG = Cfg::NWG, NT = Cfg::NT;
     constexpr int TPT = Cfg::TPT, CQ = Cfg::CQ, GW = Cfg::GW;
     constexpr int GB = GM == kGateBF16 ? 2 : 4;
     constexpr bool GH = GM == kGateHead;
-    constexpr bool HAS_U = REV || EMIT;
     constexpr int NG = GH ? 1 : 4;           // decays of a thread's four channels
     constexpr float kLog2e = 1.4426950408889634f;
     constexpr float SZ = REV ? 1.f : -1.f;   // exponent sign of the operand Z; the factor F takes the other
@@ -255,9 +261,11 @@ __global__ __launch_bounds__(bwd_threads(DK, DV)) void gla_bwd_bf16_kernel(BwdQK
     const long long vbase = b * p.vb + tok0 * p.vt + h * p.vh;
     const unsigned st = (unsigned)p.st, vt = (unsigned)p.vt;
 
-    // Score tiles above the diagonal are never computed: zero them once.
-    for (int e = tid; e < (REV ? 2 : 1) * 64 * PS / 16; e += NT)
-        *reinterpret_cast<u32x4 *>(Ps + e * 16) = u32x4{0u, 0u, 0u, 0u};
+    // Score tiles above the diagonal are never computed: zero them once, before the first barrier, with the first loads under way.
+    auto clear_scores = [&]() __attribute__((always_inline)) {
+        for (int e = tid; e < (REV ? 2 : 1) * 64 * PS / 16; e += NT)
+            *reinterpret_cast<u32x4 *>(Ps + e * 16) = u32x4{0u, 0u, 0u, 0u};
+    };
 
     if (pw >= NWM) {
         // ================================ gate waves ===========================================
@@ -558,6 +566,7 @@ __global__ __launch_bounds__(bwd_threads(DK, DV)) void gla_bwd_bf16_kernel(BwdQK
 #pragma unroll
             for (int u = 0; u < TPT; ++u) load_raw(u, t0);
         }
+        clear_scores();
 #pragma unroll
         for (int u = 0; u < TPT; ++u) {
             k1[u] = u32x2{0u, 0u};
@@ -722,6 +731,7 @@ __global__ __launch_bounds__(bwd_threads(DK, DV)) void gla_bwd_bf16_kernel(BwdQK
 #pragma unroll
                 for (int rr = 0; rr < 16; ++rr) W2[it][rr] = 0.f;
         }
+        clear_scores();
         lds_fetch_wait();
         clear_dead(0, x_tile(0));
         clear_dead(0, y_tile(0));
@@ -1007,7 +1017,7 @@ __global__ __launch_bounds__(bwd_threads(DK, DV)) void gla_bwd_bf16_kernel(BwdQK
 
 template <int DK, int DV, int NS, bool REV, int GM, bool EMIT, bool NT>
 static hipError_t launch_bwd2(const BwdQKParams &p, hipStream_t s) {
-    typedef BwdCfg<DK, DV, REV> Cfg;
+    typedef BwdCfg<DK, DV, REV, REV || EMIT> Cfg;
     auto kern = gla_bwd_bf16_kernel<DK, DV, NS, REV, GM, EMIT, NT>;
     static LdsLimit limit;   // one per instantiation
     hipError_t e = limit.raise((const void *)kern, Cfg::kBytes);

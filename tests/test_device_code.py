@@ -92,6 +92,15 @@ def test_chunk_kernels_keep_their_registers():
     assert {n: v for n, v in spilled.items() if v > 3} == {}
 
 
+def test_two_workgroups_of_the_narrow_dq_pass_share_a_compute_unit():
+    """Six waves of a workgroup on four SIMDs: a second one fits for certain at four waves a SIMD, 128 registers.  (Its LDS is asserted
+    at compile time.)"""
+    found = [k for n, k in kernels().items() if re.search(r"gla_bwd_bf16_kernelILi64ELi64ELi[12]ELb0ELi[012]ELb0E", n)]
+    assert len(found) == 10   # gate layouts, siblings (not with per-head gates), cache hints
+    for k in found:
+        assert k[".vgpr_count"] <= 128 and k[".vgpr_spill_count"] == 0
+
+
 @pytest.mark.skipif(not os.path.exists(OBJDUMP), reason="no disassembler")
 def test_what_key_channel_siblings_share_is_not_streamed(tmp_path):
     """Two workgroups that own half of the key channels each read the same v, and the same g with one decay per head.  Read with the
