@@ -1,6 +1,6 @@
 """GPU parity of the backward pass (App. A.4): the HIP path through the C ABI against the fp64 oracle's
 token-by-token reverse recurrence, on seeded synthetic inputs spanning several chunks, segments, the
-d_v split and the cut into shorter pieces."""
+sibling workgroups and the cut into shorter pieces."""
 import zlib
 
 import numpy as np
@@ -15,7 +15,7 @@ pytestmark = pytest.mark.gpu
 
 # (name, B, H, P, L, d_k, d_v, g dtype)
 CASES = [
-    ("bwd_split", 1, 4, 2, 320, 128, 128, "f32"),          # 8 streams: d_v split in the dV pass, 5 chunks
+    ("bwd_split", 1, 4, 2, 320, 128, 128, "f32"),          # 8 streams: siblings in the state and dQ passes, 5 chunks
     ("bwd_whole", 2, 16, 8, 128, 128, 128, "f32"),         # 256 streams
     ("bwd_pieces", 1, 2, 2, 1024, 128, 128, "f32"),        # pieces of one chunk
     ("bwd_pieces_d64", 1, 1, 1, 2048, 64, 64, "bf16"),

@@ -13,8 +13,8 @@ pytestmark = pytest.mark.gpu
 TOLB = TOL["bf16"]   # bf16 operands, fp32 accumulation: the bound of every bf16 test
 
 
-def make(H, L, dk, dv, gate, seed):
-    inp = synth.make_inputs(1, L, H, dk, dv, seed=seed, io="bf16", g="bf16" if gate == "bf16" else "f32", device="cuda",
+def make(H, L, dk, dv, gate, seed, B=1):
+    inp = synth.make_inputs(B, L, H, dk, dv, seed=seed, io="bf16", g="bf16" if gate == "bf16" else "f32", device="cuda",
                             per_head_gate=gate == "head", gate_div=64.0 if gate == "head" else 16.0)
     gen = torch.Generator(device="cuda").manual_seed(seed + 1)
     inp["dO"] = torch.randn(inp["v"].shape, generator=gen, device="cuda").to(torch.bfloat16)
@@ -85,3 +85,56 @@ def test_state_passes_and_dq_around_the_sibling_rules(streams, dv, gate):
     for nm, x, r in zip(("dq", "dk", "dv"), got[:3], ref[:3]):
         assert rel_err_bh(host(x), r, (0, 2)) <= TOLB, nm
     assert rel_err_bh(host(got[3]), ref[3].sum(axis=-1) if gate == "head" else ref[3], (0, 2)) <= TOLB, "dg"
+
+
+def check_batch(inp, gate, got, samples, scale):
+    """Gradients (and the initial state's, if given) of a few batch entries of one segment each, against the oracle."""
+    for b in samples:
+        h = {n: host(t[b:b + 1]) for n, t in inp.items()}
+        if gate == "head":
+            h["g"] = np.repeat(h["g"][..., None], h["q"].shape[-1], axis=-1)
+        ref = list(oracle.gla_recurrent_bwd(h["q"], h["k"], h["v"], h["g"], h["dO"], scale, None, None))
+        if gate == "head":
+            ref[3] = ref[3].sum(axis=-1)
+        for nm, x, r in zip(("dq", "dk", "dv", "dg", "dS0"), got, ref):
+            assert rel_err_bh(host(x[b:b + 1]), r, (0, 1) if nm == "dS0" else (0, 2)) <= TOLB, (nm, b)
+
+
+def from_state(inp, L, dk, dv, scale):
+    B, H = inp["q"].shape[0], inp["q"].shape[2]
+    zero = torch.zeros(1, B, H, dk, dv, device="cuda")
+    S, _ = zeco.gla_local_state(inp["k"], inp["v"], inp["g"], 1)
+    return zeco.gla_bwd_from_state(*(inp[n] for n in ("q", "k", "v", "g", "dO")), zero, S[0], zero, 1, scale=scale)
+
+
+@pytest.mark.parametrize("gate", ["f32", "bf16", "head"])
+@pytest.mark.parametrize("dv", [64, 128])
+@pytest.mark.parametrize("L", [513, 640])
+def test_more_streams_than_siblings_take_with_checkpoints(L, dv, gate):
+    """130 streams: one workgroup each in the dQ pass too, with a checkpoint behind the eighth chunk and a short or whole last one."""
+    inp = make(1, L, 128, dv, gate, 510 + L, B=130)
+    got = from_state(inp, L, 128, dv, 0.5)
+    torch.cuda.synchronize()
+    check_batch(inp, gate, got, (0, 64, 129), 0.5)
+
+
+@pytest.mark.parametrize("B,dk,dv,gate", [
+    (130, 128, 128, "f32"), (130, 128, 128, "bf16"), (130, 128, 128, "head"),
+    (130, 64, 64, "f32"), (130, 64, 64, "bf16"), (130, 64, 64, "head"),
+    (130, 64, 128, "f32"), (130, 64, 128, "bf16"), (130, 64, 128, "head"),
+    (130, 128, 64, "f32"), (130, 128, 64, "bf16"), (130, 128, 64, "head"),
+    (100, 128, 128, "bf16"), (100, 128, 64, "f32"),          # dQ pass of from_state in siblings
+])
+def test_gradients_past_the_caches(B, dk, dv, gate):
+    """Tensors of over 215e6 bytes (q, k, v, dO and the gates) take the kernels with non-temporal rows; the length leaves a short chunk."""
+    per_token = 4 * (dk + dv) + {"f32": 4 * dk, "bf16": 2 * dk, "head": 4}[gate]
+    L = int(215e6 / (B * per_token)) + 8
+    L += 1 - L % 2
+    assert B * L * per_token > 215e6 and L % 64
+    inp = make(1, L, dk, dv, gate, 70 + B + dv, B=B)
+    q, k, v, g, dO = (inp[n] for n in ("q", "k", "v", "g", "dO"))
+    got = from_state(inp, L, dk, dv, 0.5)
+    fused = zeco.gla_fused_bwd(q, k, v, g, dO, 1, scale=0.5)
+    torch.cuda.synchronize()
+    check_batch(inp, gate, got, (0, B - 1), 0.5)
+    check_batch(inp, gate, fused, (0, B - 1), 0.5)

@@ -163,7 +163,7 @@ def test_ragged_per_head_gates():
 
 BWD_CASES = [
     # (name, B, H, P, L, d_k, d_v, g dtype)
-    ("rb_100", 1, 4, 2, 100, 128, 128, "f32"),            # d_v split in the dV pass; chunks of 36 + 64
+    ("rb_100", 1, 4, 2, 100, 128, 128, "f32"),            # siblings in the dQ pass; chunks of 36 + 64
     ("rb_65", 1, 2, 3, 65, 128, 128, "f32"),              # one token in the short chunk
     ("rb_whole_127", 2, 16, 5, 127, 128, 128, "f32"),     # 160 streams
     ("rb_1000", 1, 2, 2, 1000, 128, 128, "bf16"),         # 31 chunks and 16 tokens over both segments
