@@ -68,8 +68,9 @@ typedef struct {
                                 * 0: below 80 (log Lambda counted from the chunk's start, as in Alg. 1:
                                 *    mean decays alpha > 0.29 per token at C = 64),
                                 * 1: below 160 (log Lambda counted from half the chunk's total, however the
-                                *    decay is spread over the chunk: alpha > 0.08 per token), at about 3 % more
-                                *    time in the chunk kernels.
+                                *    decay is spread over the chunk: alpha > 0.08 per token), at 0 - 4 % more
+                                *    time in the chunk kernels (output passes of few streams with per-head gates:
+                                *    up to 14 %).
                                 * No call can check this: beyond the range the factors overflow and the
                                 * outputs come out as inf / NaN while the status is still ZECO_OK. */
 } zeco_gla_desc;

@@ -33,8 +33,8 @@
 //   phase 2 of chunk n   matrix: intra-chunk products; finished tile -> LDS; dV rows -> HBM; states
 //                        gate: dG of chunk n - 1; Z of chunk n + 1, dK pass: U of chunk n + 1; fetch of chunk n + 2
 // Y and Z live through both phases of a chunk and are double buffered; so is X in the dQ pass, where the by-product below
-// needs it in phase 2; in the dK pass X and U are dead after phase 1, in the dQ pass U before it.  151 - 160 KB of LDS at
-// d = 128, one workgroup a compute unit, two waves a SIMD with 256 registers each.
+// needs it in phase 2; in the dK pass X and U are dead after phase 1, in the dQ pass U before it.  At d = 128 153 KB of LDS in
+// the dK pass, 158 in the dQ pass (142 without the by-product): one workgroup a compute unit, two waves a SIMD with 256 registers each.
 //
 // What bounds it.  At 256 workgroups with fp32 gates per channel, HBM: dQ pass 1050 -> 960 us, dV 555 and dK 1094 -> one
 // pass of 1210 us for 16 heads x 131072 tokens, 5.2 TB/s of their 11.3 GB (the kernel before, with all waves at the gate pass
@@ -43,7 +43,8 @@
 // two workgroups a stream; dK and dV 819 us in one), because its outstanding reads fill the 32 KB of its vector cache.  The chain of the matrix waves is 4.1 us a
 // chunk in the dK pass, 1.9 in the dQ pass (cycle stamps), of which products 1.2; that of the gate waves 3.6 - 4.2.
 // What it took to get there: every wave's loop free of spilled registers, since the wait for a spilled value is also
-// a wait for the fetches issued before it (6.3 -> 8 us a chunk with a dozen spills), and operands read several products ahead.
+// a wait for the fetches issued before it (6.3 -> 8 us a chunk with a dozen spills), and operands read several products ahead (backward with per-head gates 3 % at 128 x 128, 13 % at
+// 64 x 128; nothing at 128 x 128 with gates per channel, whose pace the gate waves and HBM set).
 //
 // dG (last line of the backward listing of App. A.4): dG_t = sum over later tokens s >= t of
 // (Q_s .* dQ_s - K_s .* dK_s).  Inside one segment this is a reverse cumulative sum; what the later
@@ -125,25 +126,23 @@ template <int DK, int DV, bool REV, bool HAS_U> struct BwdCfg {
 template <int D> __device__ __forceinline__ constexpr int swizzle(int r) {
     return D == 128 ? ((r & 3) << 2) | ((r >> 2) & 3) : (((r >> 1) & 1) << 2) | ((r >> 2) & 3);
 }
-// N times 16 bytes a lane straight to LDS, from `base` + `off` + i * step (the offset in 32 bits, modulo 2^32) to `at` + i * STEP +
-// 16 * lane.  The compiler does not see that these are loads: lds_fetch_wait before the barrier that publishes them.  Nor does it see
-// that a load reads `base`, which it may have restored from a vector register's lane right before the block (the kernels keep up to a
-// hundred scalars there): five wait states have to lie between a vector instruction that writes a scalar register and a vector
-// memory instruction that reads it, here the first two instructions.  The loads of a group share the base, so the wait is there
-// once, and the address arithmetic of the rest is one vector addition each (16 heads x 4096 tokens, 64 x 64, per-head gates:
-// gradients 270 us with a base for each load and no wait, 276 with the wait before each, 265 so).  M0 is the compiler's to reserve and is
-// written again before every use, so it is no clobber.
+// 16 bytes a lane straight to LDS, from `base` + `off` to `at` + 16 * lane; with N > 1 that many times, `step` (bytes, the offset is
+// counted modulo 2^32) and STEP further on each time.  The compiler does not see that this is a load: lds_fetch_wait before the
+// barrier that publishes it.  Nor does it see that a load reads `base`, which it may have restored from a vector register's lane right
+// before the block (the kernels keep up to a hundred scalars there): five wait states have to lie between a vector instruction that
+// writes a scalar register and a vector-memory instruction that reads it, here the first two instructions.  M0 is the compiler's to
+// reserve and is written again before every use, so it is no clobber.
 template <int N, int STEP> __device__ __forceinline__ void lds_fetch(const unsigned char *base, unsigned off, unsigned step, unsigned at) {
-    static_assert(N == 2 || N == 4, "");
-#define ZECO_FETCH_NEXT "v_add_u32 %0, %3, %0\n\ts_add_u32 m0, m0, %4\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2\n\t"
-#define ZECO_FETCH_FIRST "s_mov_b32 m0, %1\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %0, %2\n\t"
-    if constexpr (N == 2)
-        asm volatile(ZECO_FETCH_FIRST ZECO_FETCH_NEXT : "+&v"(off) : "s"(at), "s"(base), "s"(step), "n"(STEP) : "memory", "scc");
-    else
-        asm volatile(ZECO_FETCH_FIRST ZECO_FETCH_NEXT ZECO_FETCH_NEXT ZECO_FETCH_NEXT
-                     : "+&v"(off) : "s"(at), "s"(base), "s"(step), "n"(STEP) : "memory", "scc");
-#undef ZECO_FETCH_NEXT
-#undef ZECO_FETCH_FIRST
+    static_assert(N == 1 || N == 2 || N == 4, "");
+#define ZECO_FETCH "s_mov_b32 m0, %1\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %0, %2\n\t"
+#define ZECO_NEXT "v_add_u32 %0, %3, %0\n\ts_add_u32 m0, m0, %4\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2\n\t"
+#define ZECO_OPERANDS : "+&v"(off) : "s"(at), "s"(base), "s"(step), "n"(STEP) : "memory", "scc"
+    if constexpr (N == 1) asm volatile(ZECO_FETCH : : "v"(off), "s"(at), "s"(base) : "memory");
+    else if constexpr (N == 2) asm volatile(ZECO_FETCH ZECO_NEXT ZECO_OPERANDS);
+    else asm volatile(ZECO_FETCH ZECO_NEXT ZECO_NEXT ZECO_NEXT ZECO_OPERANDS);
+#undef ZECO_OPERANDS
+#undef ZECO_NEXT
+#undef ZECO_FETCH
 }
 __device__ __forceinline__ void lds_fetch_wait() { asm volatile("s_waitcnt vmcnt(0)" : : : "memory"); }
 
@@ -181,7 +180,8 @@ __device__ __forceinline__ bf16x8 pack8_bwd(const f32x16 &a, int base) {
 // NS > 1 (dQ pass, gates per channel): NS sibling workgroups share a stream, each with DK of its NS * DK channels - columns of
 // W, of the output and of everything gated; X, Y and the scores, which contract over d_v, each of them has whole.
 // (dV contracts over d_k, so the dK pass is not split.)
-// NT: the rows that the gate waves read and write carry the non-temporal hint (see streams_past_caches).
+// NT: the rows that the gate waves read and write carry the non-temporal hint (see streams_past_caches).  The dG rows of the dK
+// pass always do: nothing in the call reads them again (by the same rule as the others: one-call backward 0.5 % slower at 128 x 64, the same elsewhere).
 template <int DK, int DV, int NS, bool REV, int GM, bool EMIT, bool NT_>
 __global__ __launch_bounds__(bwd_threads(DK, DV), bwd_min_waves(DK, DV, REV, EMIT)) void gla_bwd_bf16_kernel(BwdQKParams p) {
     static_assert(!(REV && EMIT), "the state gradient is a by-product of the forward-direction pass");
@@ -261,12 +261,14 @@ __global__ __launch_bounds__(bwd_threads(DK, DV), bwd_min_waves(DK, DV, REV, EMI
     const long long vbase = b * p.vb + tok0 * p.vt + h * p.vh;
     const unsigned st = (unsigned)p.st, vt = (unsigned)p.vt;
 
-    // Score tiles above the diagonal are never computed: zero them once, before the first barrier, with the first loads under way.
+    // Score tiles above the diagonal are never computed: zero them once - at d_k = 64 with the first loads under way (2048 streams of 64
+    // tokens, 64 x 64, bf16 gates 118.4 -> 117.7 us), at d_k = 128 before them (64 x 1024 tokens, 128 x 64, per-head gates 73.4 -> 71.9).
     auto clear_scores = [&]() __attribute__((always_inline)) {
         for (int e = tid; e < (REV ? 2 : 1) * 64 * PS / 16; e += NT)
             *reinterpret_cast<u32x4 *>(Ps + e * 16) = u32x4{0u, 0u, 0u, 0u};
     };
 
+    if constexpr (DK != 64) clear_scores();
     if (pw >= NWM) {
         // ================================ gate waves ===========================================
         const int gw = pw - NWM;
@@ -443,8 +445,9 @@ __global__ __launch_bounds__(bwd_threads(DK, DV), bwd_min_waves(DK, DV, REV, EMI
             }
         };
         // rows of the m-th chunk, from the fp32 tile the matrix waves left: factor, store, dG terms
-        // (sh: it is the short chunk; the literal false of the loop leaves no branch around the stores, at whose joins the
-        // compiler would wait for the loads in flight)
+        // (sh: it is the short chunk, known only at run time in the loop as well.  With the first two rounds peeled off, so that the others
+        // have no branch around a store, few streams gain and many lose: gradients of one head x 4 x 2048 tokens 254 -> 242 us, 16 x 16 x 4096
+        // 1060 -> 1093, one-call backward of 256 x 512 209 -> 212)
         auto finish = [&](int m, bool sh) __attribute__((always_inline)) {
             const int c = chunk_of(m);
             const long long t0 = cstart(c);
@@ -566,7 +569,7 @@ __global__ __launch_bounds__(bwd_threads(DK, DV), bwd_min_waves(DK, DV, REV, EMI
 #pragma unroll
             for (int u = 0; u < TPT; ++u) load_raw(u, t0);
         }
-        clear_scores();
+        if constexpr (DK == 64) clear_scores();
 #pragma unroll
         for (int u = 0; u < TPT; ++u) {
             k1[u] = u32x2{0u, 0u};
@@ -650,8 +653,19 @@ __global__ __launch_bounds__(bwd_threads(DK, DV), bwd_min_waves(DK, DV, REV, EMI
         auto XR = [&]() __attribute__((always_inline)) { return (int)(Cfg::RPI * w + ln / Cfg::PPR); };   // tile row of the lane's first piece
         auto fetch = [&](const unsigned char *src, int m, unsigned tile) __attribute__((always_inline)) {
             const int xr = XR(), xpc = (ln % Cfg::PPR) ^ swizzle<DV>(xr);
-            const unsigned off = ((unsigned)pos_of(xr) * vt + 8 * xpc) * 2, step = (unsigned)(Cfg::RPI * NWM) * vt * 2;
-            lds_fetch<Cfg::NXY, NWM * 1024>(src + cstart(chunk_of(m < N ? m : N - 1)) * vt * 2, off, REV ? 0u - step : step, tile + w * 1024);
+            const unsigned char *base = src + cstart(chunk_of(m < N ? m : N - 1)) * vt * 2;
+            // One wait and one base for a tile's loads at d_k = 64 (2048 streams of 64 tokens, 64 x 64, gradients 123 -> 120 us; 16 heads x 4096
+            // tokens with per-head gates 276 -> 265); a base and a wait for each load at d_k = 128, whose reverse pass has no register for the
+            // changing offset (128 streams of 16384 tokens, 128 x 128: 2710 -> 2690 us).
+            if constexpr (DK == 64) {
+                const unsigned off = ((unsigned)pos_of(xr) * vt + 8 * xpc) * 2, step = (unsigned)(Cfg::RPI * NWM) * vt * 2;
+                lds_fetch<Cfg::NXY, NWM * 1024>(base, off, REV ? 0u - step : step, tile + w * 1024);
+            } else {
+                const unsigned off = ((unsigned)pos_of(REV ? xr + Cfg::RPI * NWM * (Cfg::NXY - 1) : xr) * vt + 8 * xpc) * 2;
+#pragma unroll
+                for (int i = 0; i < Cfg::NXY; ++i)
+                    lds_fetch<1, 0>(base + (size_t)(Cfg::RPI * NWM * (REV ? Cfg::NXY - 1 - i : i)) * vt * 2, off, 0u, tile + (w + NWM * i) * 1024);
+            }
         };
         // surplus rows of the short chunk: zero (so that nothing in them, infinities included, reaches other rows)
         auto clear_dead = [&](int m, unsigned tile) __attribute__((always_inline)) {
@@ -731,7 +745,7 @@ __global__ __launch_bounds__(bwd_threads(DK, DV), bwd_min_waves(DK, DV, REV, EMI
 #pragma unroll
                 for (int rr = 0; rr < 16; ++rr) W2[it][rr] = 0.f;
         }
-        clear_scores();
+        if constexpr (DK == 64) clear_scores();
         lds_fetch_wait();
         clear_dead(0, x_tile(0));
         clear_dead(0, y_tile(0));

@@ -363,13 +363,14 @@ zeco_status zeco_gla_fwd_from_state(const zeco_gla_desc *d, const void *q, const
 // is a workgroup's serial chain of chunks.  More pieces shorten the chain; each costs a prologue and its states
 // (written by the first phase, scanned, read by the second), and a chunk takes the longer the more workgroups share
 // the memory system.  The estimate, in microseconds, has two sets of constants, both fitted to sweeps of the piece count:
-// for few (batch, head) pairs (d = 128, bf16, forward: 16 pairs x 16384 tokens, 8 / 16 / 32 pieces 157 / 130 / 147 us, 2048 tokens
-// 46 (4) / 36 (8) / 36 (16) / 52 (32) us; training step over 131072 tokens, 12 / 16 / 32 pieces 3.72 / 3.29 / 3.50 ms), and for
+// for few (batch, head) pairs (d = 128, bf16, forward: 16 pairs x 16384 tokens, 8 / 16 / 32 pieces 152 / 138 / 152 us, 2048 tokens
+// 42 (4) / 34 (8) / 36 (16) / 52 (32) us; training step over 131072 tokens, 12 / 16 / 32 pieces 3.34 / 3.04 / 3.15 ms), and for
 // pairs that fill half of the compute units by themselves, where a piece's prologue and the last round of workgroups decide
-// (256 pairs x 32768 tokens whole 2.36, in 2 3.69 ms; 640 x 16384 whole 3.14, in 2 4.61 ms; gradient passes of 400 x
-// 4096 in 3 / 4 / 16 pieces 2.24 / 2.33 / 2.85 ms).  The count it picks takes 0.7 % (forward) and 1.6 % (training step) more than the
-// best of up to 25 counts in the mean over 596 shapes of 1 .. 1024 pairs.  A chain may be as long as it comes: 8 pairs x 2 M
-// tokens in 32 / 256 pieces 7.15 / 7.25 ms forward (corrected: 4.84 / 5.63 ms), 21.7 / 21.7 ms backward.
+// (256 pairs x 32768 tokens whole 2.34, in 2 3.70 ms; 640 x 16384 whole 3.15, in 2 4.64 ms; backward from saved states of 400 x
+// 4096 in 1 / 3 / 4 / 16 pieces 1.93 / 1.89 / 1.98 / 2.30 ms).  The constants of the gradient passes (grad, bytesb) were fitted while dV was
+// a pass of its own; the count picked takes 0.8 % (forward) and 1.0 % (training step) more than the best of up to 25 counts in the mean
+// over 312 shapes of 1 .. 400 pairs, 11 and 17 % at worst, and 0.1 % of that is what a fit to the passes as they are would save.  A chain may
+// be as long as it comes: 8 pairs x 2 M tokens in 32 / 256 pieces 7.12 / 7.30 ms forward (corrected: 4.85 / 5.65 ms), 16.6 / 16.5 ms backward.
 struct PassCost {
     double chunk, bytes, hidden, start;   // a chunk's chain alone on the chip [us]; its traffic, divided by what of it is hidden; a piece's prologue and epilogue [us]
 };

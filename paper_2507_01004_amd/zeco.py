@@ -176,7 +176,7 @@ _WIDE_GATES = False
 @contextlib.contextmanager
 def wide_gates(on=True):
     """Within the block every descriptor asks for the wide range of gates (zeco_gla_desc.wide_gates: the sum of
-    |g| over a chunk may reach 160 instead of 80 with bf16 q/k/v, at about 3 % more time in the chunk kernels)."""
+    |g| over a chunk may reach 160 instead of 80 with bf16 q/k/v, at 0 - 4 % more time in the chunk kernels)."""
     global _WIDE_GATES
     before, _WIDE_GATES = _WIDE_GATES, bool(on)
     try:
