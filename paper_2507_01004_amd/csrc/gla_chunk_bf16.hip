@@ -135,14 +135,15 @@ constexpr int chunk_threads(int dk, int dv, int gm, int mode) {
 // order).  Four where there are registers for them and the matrix waves are the ones waited for: d_k = 64 (16 heads x 8192
 // tokens as one segment, output pass: 64 x 128 193 -> 183 us, 64 x 64 with bf16 gates 198 -> 187), the wide range of gates, whose state is
 // decayed twice (16 heads, 8 x 4096 tokens, d = 128: per-head gates local 205 -> 161, output 206 -> 155; bf16 gates local in siblings
-// 224 -> 203), output passes with per-head gates (16 heads x 8192, 249 -> 235).  None at d_k = 128 otherwise: the twelve waves of the
+// 224 -> 203), runs in one launch, whose inputs the caches hold (64 x 512 tokens 24.3 -> 24.0, saving states 27.2 -> 26.1), output passes with
+// per-head gates (16 heads x 8192, 249 -> 235).  None at d_k = 128 otherwise: the twelve waves of the
 // local pass with gates per channel and all 128 columns have 168 registers each, and the wide form spills 23 inside its loop (16 heads,
 // 16 x 4096 tokens: 365 -> 430 us, bf16 gates 352 -> 420); per-head local pass of 192 segments of 2240 tokens 110 -> 114; output passes of few streams
 // with gates per channel 278 -> 282.
 constexpr int read_ahead(int dk, int dv, int gm, int mode, bool wide) {
     const bool local = mode == kLocal || mode == kLocalInit;
-    if (dk == 64) return 4;
-    if (gm == kGateHead) return wide || !(local || mode == kLocalCD) ? 4 : 0;
+    if (dk == 64 || mode == kOutputRun) return 4;
+    if (gm == kGateHead) return wide || mode == kOutput ? 4 : 0;
     return wide && local && dv == 64 ? 4 : 0;
 }
 
