@@ -43,9 +43,11 @@ template <int V> __device__ __forceinline__ void scan_store(float *ptr, const Sc
 // The steady-state loop is free of branches (a branch makes the compiler wait for all outstanding loads at
 // the join): STORE (S_init is written), BYP (1: the by-products G_pre / G_sum are wanted, 2: with G_tot and G_pre as pairs) and PD (the chain's length is
 // on the device) are template flags, and the rounds whose refills would run past the chain's end are peeled off into a guarded tail.
+// So is TWICE (the end states are stored to S_last2 as well): a pointer tested at the kernel's end costs every scan 0.3 us (16 segments
+// x 16 heads behind the state pass 7.8 -> 8.1).
 // Loads, the gate loads and the stores all count against the 63 memory operations a wave can have
 // outstanding, so D beyond 20 buys nothing.
-template <int V, int D, bool STORE, int BYP, bool PD>
+template <int V, int D, bool STORE, int BYP, bool PD, bool TWICE = false>
 __global__ __launch_bounds__(256) void state_scan_kernel(ScanParams p, int parts) {
     typedef ScanVec<V> vec_t;
     const int blocks_per_head = p.d_k / p.rows_per_block;
@@ -152,7 +154,7 @@ __global__ __launch_bounds__(256) void state_scan_kernel(ScanParams p, int parts
         }
     }
     if (p.S_last) *reinterpret_cast<vec_t *>(p.S_last + grp * seg_stride + off) = s;
-    if (p.S_last2) *reinterpret_cast<vec_t *>(p.S_last2 + grp * seg_stride + off) = s;
+    if constexpr (TWICE) *reinterpret_cast<vec_t *>(p.S_last2 + grp * seg_stride + off) = s;
     if (prefix && p.G_sum) p.G_sum[grp * g_stride + gcol] = (float)gsum;
 }
 
@@ -165,7 +167,10 @@ template <int V, int D> static hipError_t launch_scan_vd(const ScanParams &p, hi
     if (blocks > 0x7fffffffll) return hipErrorInvalidValue;
     const dim3 grid((unsigned)blocks, p.groups), block(threads);
     const bool byp = p.G_pre || p.G_sum;
-    if (p.S_init) {
+    if (p.S_last2) {
+        if (!p.S_init || p.pairs || byp || p.P_used) return hipErrorInvalidValue;
+        hipLaunchKernelGGL((state_scan_kernel<V, D, true, 0, false, true>), grid, block, 0, s, p, parts);
+    } else if (p.S_init) {
         if (p.pairs) hipLaunchKernelGGL((state_scan_kernel<V, D, true, 2, false>), grid, block, 0, s, p, parts);
         else if (byp) hipLaunchKernelGGL((state_scan_kernel<V, D, true, 1, false>), grid, block, 0, s, p, parts);
         else if (p.P_used) hipLaunchKernelGGL((state_scan_kernel<V, D, true, 0, true>), grid, block, 0, s, p, parts);

@@ -114,3 +114,18 @@ def test_what_key_channel_siblings_share_is_not_streamed(tmp_path):
     for kernel, ops in plain.items():
         assert set(hinted[kernel]) == {"global_load_dwordx2"}, kernel
         assert len(hinted[kernel]) < ops.count("global_load_dwordx2"), kernel
+
+
+@pytest.mark.skipif(not os.path.exists(OBJDUMP), reason="no disassembler")
+def test_scan_stores_its_end_states_twice_only_where_asked(tmp_path):
+    """The second copy of the end states (a forward that saves its states) has kernels of its own: a pointer tested at the end of the
+    others would cost every scan its load."""
+    stores = {}
+    for obj in code_objects():
+        for kernel, op, _ in instructions(obj, tmp_path / "code.elf"):
+            m = kernel and re.search(r"state_scan_kernelILi(\d+)ELi\d+ELb1ELi0ELb0ELb([01])E", kernel)
+            if m and op.startswith("global_store"):
+                key = (m.group(1), m.group(2))
+                stores[key] = stores.get(key, 0) + 1
+    for v in ("4", "2", "1"):
+        assert stores[v, "1"] == stores[v, "0"] + 1
