@@ -10,7 +10,8 @@
  *     _SCRATCH_LIMIT mean that nothing was launched and no output was touched.  ZECO_ERR_HIP means that the
  *     runtime refused a launch (or a kernel attribute); entry points that launch several kernels may then
  *     have enqueued the earlier ones, and the outputs are unspecified.
- *   - Results are deterministic (no atomics) and independent of launch-shape heuristics.
+ *   - Results are deterministic (no atomics): the same arguments give the same bits.  (How a call cuts its work depends on
+ *     its shape, and for the calls that may run without their workspace on the size of the one they are given.)
  *   - Notation: B batch, P segments (the paper's devices), L tokens per segment, T = P*L, H heads,
  *     C chunk length, g = log(alpha) <= 0 the LOG decay of Eq. (1), scale multiplies q
  *     (1.0 reproduces the paper).  Decay scales row i (the d_k index) of a d_k x d_v state.
@@ -287,8 +288,9 @@ zeco_status zeco_gla_fwd_from_state(const zeco_gla_desc *desc, const void *q, co
  * these calls, given zeco_gla_block_workspace(desc, call) bytes of device memory, cuts every segment into pieces of its
  * own whose states live there (as zeco_gla_local_fwd does); the results are the same up to rounding.  A size of 0 says that
  * the call is not cut.  With a workspace that is null, unaligned or smaller than that the segments are run whole, as by the
- * calls without one; zeco_gla_bwd_from_state, whose checkpoints need one, takes either size: that of
- * zeco_gla_bwd_from_state_workspace or, to be cut, that of ZECO_BLOCK_BWD_FROM_STATE (never the smaller one). */
+ * calls without one; zeco_gla_bwd_from_state_ws (below), whose checkpoints need one, takes at least
+ * zeco_gla_bwd_from_state_workspace(desc) bytes and, to be cut, those of ZECO_BLOCK_BWD_FROM_STATE (never fewer).
+ * The size that is passed therefore decides the order of the sums, and so the last bits: pass the same one for the same bits. */
 enum { ZECO_BLOCK_LOCAL_STATE = 0, ZECO_BLOCK_FWD_FROM_STATE = 1, ZECO_BLOCK_BWD_DSTATE = 2, ZECO_BLOCK_BWD_FROM_STATE = 3 };
 size_t zeco_gla_block_workspace(const zeco_gla_desc *desc, int32_t call);
 zeco_status zeco_gla_local_state_ws(const zeco_gla_desc *desc, const void *k, const void *v, const void *g,
@@ -365,6 +367,12 @@ zeco_status zeco_gla_bwd_from_state(const zeco_gla_desc *desc, const void *q, co
                                     const float *S_last, const float *dS_in, void *dq, void *dk,
                                     void *dv, float *dg, void *workspace, size_t workspace_bytes,
                                     void *stream);
+/* The same, and with zeco_gla_block_workspace(desc, ZECO_BLOCK_BWD_FROM_STATE) bytes or more the segments may be cut. */
+zeco_status zeco_gla_bwd_from_state_ws(const zeco_gla_desc *desc, const void *q, const void *k,
+                                       const void *v, const void *g, const void *dO, const float *S_init,
+                                       const float *S_last, const float *dS_in, void *dq, void *dk,
+                                       void *dv, float *dg, void *workspace, size_t workspace_bytes,
+                                       void *stream);
 
 /* The whole backward in one call: recomputes the forward segment states (phase 1 and its scan, from
  * S0), runs the state-gradient pass and its reverse scan (from dS_T), then the gradient passes.  Like

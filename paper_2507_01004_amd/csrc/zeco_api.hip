@@ -940,10 +940,11 @@ size_t zeco_gla_bwd_from_state_workspace(const zeco_gla_desc *desc) {
     return bwd_checkpoint_floats(desc, desc->P, desc->L) * sizeof(float);
 }
 
-zeco_status zeco_gla_bwd_from_state(const zeco_gla_desc *d, const void *q, const void *k, const void *v,
-                                    const void *g, const void *dO, const float *S_init, const float *S_last,
-                                    const float *dS_in, void *dq, void *dk, void *dv, float *dg,
-                                    void *workspace, size_t workspace_bytes, void *stream) {
+// `may_cut`: the _ws form, which takes more than its checkpoints' workspace for leave to cut the segments (the other one never
+// writes past its own size, however much it is given).
+static zeco_status bwd_from_state(const zeco_gla_desc *d, const void *q, const void *k, const void *v, const void *g, const void *dO,
+                                  const float *S_init, const float *S_last, const float *dS_in, void *dq, void *dk, void *dv,
+                                  float *dg, void *workspace, size_t workspace_bytes, void *stream, bool may_cut) {
     const zeco_status st = check_desc(d, true);
     if (st != ZECO_OK) return st;
     if (d->B == 0) return ZECO_OK;   // empty batch: nothing to do
@@ -958,7 +959,7 @@ zeco_status zeco_gla_bwd_from_state(const zeco_gla_desc *d, const void *q, const
         return ZECO_ERR_INVALID_ARG;
     hipStream_t s = static_cast<hipStream_t>(stream);
     BlockLayout w;
-    if (block_cut(w, d, ZECO_BLOCK_BWD_FROM_STATE, workspace, workspace_bytes)) {
+    if (may_cut && block_cut(w, d, ZECO_BLOCK_BWD_FROM_STATE, workspace, workspace_bytes)) {
         // as in zeco_gla_fused_bwd, with the states and gradients entering the segments given: forward states of the
         // pieces, dQ with the pieces' state gradients, their scan inside the segments, dK, dV and dG
         float *ws = static_cast<float *>(workspace), *Sin = ws + w.off_Sinit, *dSin = ws + w.off_dSin;
@@ -982,6 +983,20 @@ zeco_status zeco_gla_bwd_from_state(const zeco_gla_desc *d, const void *q, const
     const zeco_status sq = bwd_dq_pass(d, d->P, d->L, q, k, v, g, dO, S_init, S_last, dq, dg, nullptr, nullptr, S_ck, s);
     if (sq != ZECO_OK) return sq;
     return bwd_dv_dk_passes(d, d->P, d->L, q, k, v, g, dO, S_init, S_last, dS_in, dk, dv, dg, S_ck, s);
+}
+
+zeco_status zeco_gla_bwd_from_state(const zeco_gla_desc *d, const void *q, const void *k, const void *v,
+                                    const void *g, const void *dO, const float *S_init, const float *S_last,
+                                    const float *dS_in, void *dq, void *dk, void *dv, float *dg,
+                                    void *workspace, size_t workspace_bytes, void *stream) {
+    return bwd_from_state(d, q, k, v, g, dO, S_init, S_last, dS_in, dq, dk, dv, dg, workspace, workspace_bytes, stream, false);
+}
+
+zeco_status zeco_gla_bwd_from_state_ws(const zeco_gla_desc *d, const void *q, const void *k, const void *v,
+                                       const void *g, const void *dO, const float *S_init, const float *S_last,
+                                       const float *dS_in, void *dq, void *dk, void *dv, float *dg,
+                                       void *workspace, size_t workspace_bytes, void *stream) {
+    return bwd_from_state(d, q, k, v, g, dO, S_init, S_last, dS_in, dq, dk, dv, dg, workspace, workspace_bytes, stream, true);
 }
 
 // zeco_gla_fused_bwd works on the forward's pieces (bwd_cut), whose entering states the forward can save for it.  The

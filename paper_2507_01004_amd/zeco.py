@@ -31,6 +31,7 @@ EXPORTS = ("zeco_gla_local_fwd_workspace", "zeco_gla_local_fwd", "zeco_state_sca
            "zeco_gla_local_fwd_chunk_decay", "zeco_apply_init_state_chunk_decay",
            "zeco_gla_local_state", "zeco_gla_fwd_from_state",
            "zeco_gla_block_workspace", "zeco_gla_local_state_ws", "zeco_gla_fwd_from_state_ws", "zeco_gla_bwd_dstate_ws",
+           "zeco_gla_bwd_from_state_ws",
            "zeco_gla_fused_fwd_workspace", "zeco_gla_saved_states_bytes", "zeco_gla_fused_fwd", "zeco_gla_bwd_dstate",
            "zeco_gla_bwd_from_state_workspace", "zeco_gla_bwd_from_state", "zeco_gla_fused_bwd_workspace", "zeco_gla_fused_bwd",
            "zeco_hbm_copy", "zeco_hbm_mix", "zeco_status_string", "zeco_version")
@@ -130,6 +131,8 @@ def lib():
         L.zeco_gla_bwd_from_state_workspace.argtypes = [dp]
         L.zeco_gla_bwd_from_state_workspace.restype = ctypes.c_size_t
         L.zeco_gla_bwd_from_state.restype = i32
+        L.zeco_gla_bwd_from_state_ws.argtypes = L.zeco_gla_bwd_from_state.argtypes
+        L.zeco_gla_bwd_from_state_ws.restype = i32
         L.zeco_gla_fused_bwd_workspace.argtypes = [dp]
         L.zeco_gla_fused_bwd_workspace.restype = ctypes.c_size_t
         L.zeco_gla_fused_bwd.argtypes = [dp] + [vp] * 5 + [fp] * 3 + [vp] * 3 + [fp, fp, vp, ctypes.c_size_t, vp]
@@ -700,21 +703,21 @@ def _grad_outputs(q, v, g):
 
 def gla_bwd_from_state(q, k, v, g, dO, S_init, S_last, dS_in, P, scale=1.0, C=64, out=None, workspace=None):
     """zeco_gla_bwd_from_state: dq, dk, dv, dg of every segment from the scanned forward states and
-    state gradients.  Returns (dq, dk, dv, dg)."""
+    state gradients.  With a workspace of the caller's the segments are run whole.  Returns (dq, dk, dv, dg)."""
     if not q.is_cuda:
         raise RuntimeError("zeco kernels run on the GPU only")
     _check_same_layout(q, k)
     _check_same_layout(v, dO)
     desc = _gate_desc(q, v, g, P, C, scale)
     dq, dk, dv, dg = _grad_outputs(q, v, g) if out is None else out
-    ws_bytes = 0
+    call, ws_bytes = lib().zeco_gla_bwd_from_state_ws, 0
     if workspace is None:
         workspace, ws_bytes = _block_workspace(desc, BLOCK_BWD_FROM_STATE, q.shape[0] * P * q.shape[2], q.shape[1] // P, q.device)
     if not ws_bytes:
+        call = lib().zeco_gla_bwd_from_state
         workspace, ws_bytes = _bwd_from_state_workspace(desc, workspace, q.device)
-    st = lib().zeco_gla_bwd_from_state(desc, _ptr(q), _ptr(k), _ptr(v), _ptr(g), _ptr(dO),
-                                       _ptr(S_init), _ptr(S_last), _ptr(dS_in), _ptr(dq), _ptr(dk),
-                                       _ptr(dv), _ptr(dg), _ptr(workspace), ws_bytes, _stream())
+    st = call(desc, _ptr(q), _ptr(k), _ptr(v), _ptr(g), _ptr(dO), _ptr(S_init), _ptr(S_last), _ptr(dS_in), _ptr(dq), _ptr(dk),
+              _ptr(dv), _ptr(dg), _ptr(workspace), ws_bytes, _stream())
     if st != ZECO_OK:
         raise ZecoError(st, "zeco_gla_bwd_from_state")
     return dq, dk, dv, dg

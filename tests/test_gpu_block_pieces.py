@@ -98,6 +98,34 @@ def test_cut_calls_give_what_whole_segments_give(case):
         assert rel_err_bh(host(x), host(ref), axes) <= t, name
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("io", ["bf16", "f32"])
+def test_the_call_without_leave_to_cut_keeps_to_its_own_size(io):
+    """zeco_gla_bwd_from_state with more workspace than it asks for: the same bits as with exactly that, and not a byte past it."""
+    case = (1, 2, 2, 2048, 128, 128, "f32", io, 64, False, False)
+    B, H, P, L, dk, dv = case[:6]
+    print("arena", io, flush=True)
+    q, k, v, g, dO, gd = _inputs(case)
+    desc = zeco.make_desc(q, v, g, P, 64, 0.5)
+    need = zeco.lib().zeco_gla_bwd_from_state_workspace(ctypes.byref(desc))
+    more = zeco.lib().zeco_gla_block_workspace(ctypes.byref(desc), zeco.BLOCK_BWD_FROM_STATE)
+    assert 0 < need < more
+    S, S_last, dS = (0.3 * randn_seeded(s, i) for i, s in enumerate([(P, B, H, dk, dv), (B, H, dk, dv), (P, B, H, dk, dv)], 50))
+    arena = torch.full((more + 4096,), 171, dtype=torch.uint8, device="cuda")
+    out = []
+    for ws in (torch.empty(need, dtype=torch.uint8, device="cuda"), arena):
+        grads = tuple(torch.empty_like(x) for x in (q, k, v)) + (torch.empty(g.shape, device="cuda"),)
+        st = zeco.lib().zeco_gla_bwd_from_state(ctypes.byref(desc), *[x.data_ptr() for x in (q, k, v, g, dO, S, S_last, dS) + grads + (ws,)],
+                                                ws.numel(), zeco._stream())
+        assert st == zeco.ZECO_OK
+        out.append(grads)
+    by_binding = zeco.gla_bwd_from_state(q, k, v, g, dO, S, S_last, dS, P, scale=0.5, workspace=arena)
+    torch.cuda.synchronize()
+    assert (arena[need:] == 171).all()
+    for x, y, z in zip(*out, by_binding):
+        assert torch.equal(x, y) and torch.equal(x, z)
+
+
 def _desc(**kw):
     d = dict(B=1, P=2, H=2, L=4096, d_k=128, d_v=128, C=64, io_dtype=zeco.ZECO_BF16, g_dtype=zeco.ZECO_F32, scale=1.0,
              stride_b=2 * 4096 * 128 * 2, stride_t=256, stride_h=128, vstride_b=2 * 4096 * 128 * 2, vstride_t=256,
