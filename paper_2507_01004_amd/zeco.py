@@ -590,10 +590,22 @@ def apply_init_state_chunk_decay(q, g, G_chunk, S_init, o, P, scale=1.0, C=64, f
     return o
 
 
-def _block_workspace(desc, call, streams, tokens, device):
-    """Workspace with which a building block over few streams is cut (from torch's pool, so its lifetime follows the
-    current stream), or None: the call then runs every segment whole.  Returns (tensor, bytes)."""
-    if streams > 128 or tokens < 512:   # (never cut: spare the call the question)
+_BLOCK_STREAMS, _BLOCK_TOKENS = 128, 512   # the library cuts no building block over more streams, or with shorter segments
+
+
+def block_workspace_bytes(q, v, g, P, call, C=64):
+    """Bytes with which a building block (`call`: BLOCK_LOCAL_STATE with k for q, BLOCK_FWD_FROM_STATE, BLOCK_BWD_DSTATE with dO for v,
+    BLOCK_BWD_FROM_STATE) may cut its segments, for the `block_workspace` of its function; 0: it does not."""
+    return int(lib().zeco_gla_block_workspace(_gate_desc(q, v, g, P, C, 1.0), call))
+
+
+def _block_workspace(given, desc, call, streams, tokens, device):
+    """Workspace with which a building block over few streams is cut, and its bytes: the caller's, or one from torch's pool (so that its
+    lifetime follows the current stream).  None: the call runs every segment whole, as it does where the pool has no room - a call
+    that needs no memory is not refused for want of it, at the price of other last bits (see the functions that take one)."""
+    if given is not None:
+        return given, given.numel()
+    if streams > _BLOCK_STREAMS or tokens < _BLOCK_TOKENS:   # (never cut: spare the call the question)
         return None, 0
     need = int(lib().zeco_gla_block_workspace(desc, call))
     if not need:
@@ -604,8 +616,12 @@ def _block_workspace(desc, call, streams, tokens, device):
         return None, 0
 
 
-def gla_local_state(k, v, g, P, C=64, out=None):
-    """zeco_gla_local_state (phase 1 of the two-phase forward).  Returns (S_loc, G_tot)."""
+def gla_local_state(k, v, g, P, C=64, out=None, block_workspace=None):
+    """zeco_gla_local_state (phase 1 of the two-phase forward).  Returns (S_loc, G_tot).
+
+    Over few streams the segments are cut into pieces whose states live in a workspace.  By default it comes from torch's
+    pool, at every call; a program that keeps one (block_workspace_bytes(), uint8), because it may not allocate or wants the same
+    last bits whatever memory is free, hands it in.  With one that is too small, or empty, the segments are run whole."""
     if not k.is_cuda:
         raise RuntimeError("zeco kernels run on the GPU only")
     B, T, H, dk = k.shape
@@ -616,7 +632,7 @@ def gla_local_state(k, v, g, P, C=64, out=None):
         G_tot = torch.empty((P, B, H) + _gate_dims(g, dk), dtype=torch.float32, device=k.device)
     else:
         S_loc, G_tot = out
-    ws, ws_bytes = _block_workspace(desc, BLOCK_LOCAL_STATE, B * P * H, T // P, k.device)
+    ws, ws_bytes = _block_workspace(block_workspace, desc, BLOCK_LOCAL_STATE, B * P * H, T // P, k.device)
     st = lib().zeco_gla_local_state_ws(desc, _ptr(k), _ptr(v), _ptr(g), _ptr(S_loc),
                                        _ptr(G_tot), _ptr(ws), ws_bytes, _stream())
     if st != ZECO_OK:
@@ -624,14 +640,15 @@ def gla_local_state(k, v, g, P, C=64, out=None):
     return S_loc, G_tot
 
 
-def gla_fwd_from_state(q, k, v, g, S_init, P, scale=1.0, C=64, out=None):
-    """zeco_gla_fwd_from_state (phase 2): forward of each segment p started from S_init[p].  Returns o."""
+def gla_fwd_from_state(q, k, v, g, S_init, P, scale=1.0, C=64, out=None, block_workspace=None):
+    """zeco_gla_fwd_from_state (phase 2): forward of each segment p started from S_init[p].  Returns o.
+    `block_workspace`: as in gla_local_state."""
     if not q.is_cuda:
         raise RuntimeError("zeco kernels run on the GPU only")
     _check_same_layout(q, k)
     desc = _gate_desc(q, v, g, P, C, scale)
     o = torch.empty_strided(v.shape, v.stride(), dtype=v.dtype, device=v.device) if out is None else out
-    ws, ws_bytes = _block_workspace(desc, BLOCK_FWD_FROM_STATE, q.shape[0] * P * q.shape[2], q.shape[1] // P, q.device)
+    ws, ws_bytes = _block_workspace(block_workspace, desc, BLOCK_FWD_FROM_STATE, q.shape[0] * P * q.shape[2], q.shape[1] // P, q.device)
     st = lib().zeco_gla_fwd_from_state_ws(desc, _ptr(q), _ptr(k), _ptr(v), _ptr(g),
                                           _ptr(S_init), _ptr(o), _ptr(ws), ws_bytes, _stream())
     if st != ZECO_OK:
@@ -677,16 +694,16 @@ def gla_fused_fwd(q, k, v, g, P, scale=1.0, S0=None, C=64, out=None, workspace=N
     return o, S_last
 
 
-def gla_bwd_dstate(q, g, dO, P, scale=1.0, C=64, out=None):
+def gla_bwd_dstate(q, g, dO, P, scale=1.0, C=64, out=None, block_workspace=None):
     """zeco_gla_bwd_dstate: per segment, the state gradient it sends to the segment before it.
-    Returns dS_loc [P,B,H,d_k,d_v]."""
+    Returns dS_loc [P,B,H,d_k,d_v].  `block_workspace`: as in gla_local_state."""
     if not q.is_cuda:
         raise RuntimeError("zeco kernels run on the GPU only")
     B, T, H, dk = q.shape
     dv = dO.shape[-1]
     desc = _gate_desc(q, dO, g, P, C, scale)
     dS_loc = torch.empty(P, B, H, dk, dv, dtype=torch.float32, device=q.device) if out is None else out
-    ws, ws_bytes = _block_workspace(desc, BLOCK_BWD_DSTATE, B * P * H, T // P, q.device)
+    ws, ws_bytes = _block_workspace(block_workspace, desc, BLOCK_BWD_DSTATE, B * P * H, T // P, q.device)
     st = lib().zeco_gla_bwd_dstate_ws(desc, _ptr(q), _ptr(g), _ptr(dO), _ptr(dS_loc), _ptr(ws), ws_bytes, _stream())
     if st != ZECO_OK:
         raise ZecoError(st, "zeco_gla_bwd_dstate")
@@ -701,9 +718,10 @@ def _grad_outputs(q, v, g):
     return dq, dk, dv, dg
 
 
-def gla_bwd_from_state(q, k, v, g, dO, S_init, S_last, dS_in, P, scale=1.0, C=64, out=None, workspace=None):
+def gla_bwd_from_state(q, k, v, g, dO, S_init, S_last, dS_in, P, scale=1.0, C=64, out=None, workspace=None, block_workspace=None):
     """zeco_gla_bwd_from_state: dq, dk, dv, dg of every segment from the scanned forward states and
-    state gradients.  With a workspace of the caller's the segments are run whole.  Returns (dq, dk, dv, dg)."""
+    state gradients.  Returns (dq, dk, dv, dg).  `workspace`: one for the checkpoints of whole segments
+    (zeco_gla_bwd_from_state_workspace); `block_workspace`: as in gla_local_state."""
     if not q.is_cuda:
         raise RuntimeError("zeco kernels run on the GPU only")
     _check_same_layout(q, k)
@@ -712,12 +730,14 @@ def gla_bwd_from_state(q, k, v, g, dO, S_init, S_last, dS_in, P, scale=1.0, C=64
     dq, dk, dv, dg = _grad_outputs(q, v, g) if out is None else out
     call, ws_bytes = lib().zeco_gla_bwd_from_state_ws, 0
     if workspace is None:
-        workspace, ws_bytes = _block_workspace(desc, BLOCK_BWD_FROM_STATE, q.shape[0] * P * q.shape[2], q.shape[1] // P, q.device)
-    if not ws_bytes:
+        ws, ws_bytes = _block_workspace(block_workspace, desc, BLOCK_BWD_FROM_STATE, q.shape[0] * P * q.shape[2], q.shape[1] // P, q.device)
+        if block_workspace is not None and ws_bytes < lib().zeco_gla_bwd_from_state_workspace(desc):
+            ws_bytes = 0
+    if not ws_bytes:   # whole segments: a workspace for their checkpoints alone
         call = lib().zeco_gla_bwd_from_state
-        workspace, ws_bytes = _bwd_from_state_workspace(desc, workspace, q.device)
+        ws, ws_bytes = _bwd_from_state_workspace(desc, workspace, q.device)
     st = call(desc, _ptr(q), _ptr(k), _ptr(v), _ptr(g), _ptr(dO), _ptr(S_init), _ptr(S_last), _ptr(dS_in), _ptr(dq), _ptr(dk),
-              _ptr(dv), _ptr(dg), _ptr(workspace), ws_bytes, _stream())
+              _ptr(dv), _ptr(dg), _ptr(ws), ws_bytes, _stream())
     if st != ZECO_OK:
         raise ZecoError(st, "zeco_gla_bwd_from_state")
     return dq, dk, dv, dg

@@ -126,6 +126,95 @@ def test_the_call_without_leave_to_cut_keeps_to_its_own_size(io):
         assert torch.equal(x, y) and torch.equal(x, z)
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("io", ["bf16", "f32"])
+def test_a_workspace_of_the_programs_own(io, monkeypatch):
+    """The binding's `block_workspace`: with one of the size asked for the bits are those of a call that takes it from the pool, and nothing
+    is allocated; with an empty one, and where the pool has no room, they are those of whole segments."""
+    case = (1, 2, 2, 2048, 128, 64, "f32", io, 64, False, False)
+    B, H, P, L, dk, dv = case[:6]
+    print("kept workspace", io, flush=True)
+    q, k, v, g, dO, gd = _inputs(case)
+    f32 = lambda *s: torch.empty(s, device="cuda")
+    S, S_last, dS = (0.3 * randn_seeded(s, i) for i, s in enumerate([(P, B, H, dk, dv), (B, H, dk, dv), (P, B, H, dk, dv)], 60))
+    outs = lambda: (f32(P, B, H, dk, dv), f32(P, B, H, *gd), torch.empty_like(v), f32(P, B, H, dk, dv),
+                    (torch.empty_like(q), torch.empty_like(k), torch.empty_like(v), f32(*g.shape)))
+
+    def run(out, ws):
+        zeco.gla_local_state(k, v, g, P, out=out[:2], block_workspace=ws[0])
+        zeco.gla_fwd_from_state(q, k, v, g, S, P, scale=0.5, out=out[2], block_workspace=ws[1])
+        zeco.gla_bwd_dstate(q, g, dO, P, scale=0.5, out=out[3], block_workspace=ws[2])
+        zeco.gla_bwd_from_state(q, k, v, g, dO, S, S_last, dS, P, scale=0.5, out=out[4], block_workspace=ws[3])
+        torch.cuda.synchronize()
+        return out[:4] + out[4]
+
+    sizes = [zeco.block_workspace_bytes(x, y, g, P, c) for c, (x, y) in enumerate([(k, v), (q, v), (q, dO), (q, v)])]
+    assert all(n > 0 for n in sizes)
+    kept = [torch.empty(n, dtype=torch.uint8, device="cuda") for n in sizes]
+    none = torch.empty(0, dtype=torch.uint8, device="cuda")
+    pool, whole = run(outs(), [None] * 4), run(outs(), [none] * 4)
+    own, poor = outs(), outs()
+    real = torch.empty
+
+    def refuse(*a, **kw):
+        raise AssertionError("allocated")
+
+    def no_room(n, *a, **kw):
+        if n in sizes:   # (the checkpoints of whole segments are another, smaller request)
+            raise torch.cuda.OutOfMemoryError("no room")
+        return real(n, *a, **kw)
+
+    monkeypatch.setattr(torch, "empty", refuse)
+    own = run(own, kept)
+    monkeypatch.setattr(torch, "empty", no_room)
+    poor = run(poor, [None] * 4)
+    monkeypatch.setattr(torch, "empty", real)
+    assert all(torch.equal(x, y) for x, y in zip(pool, own))
+    assert all(torch.equal(x, y) for x, y in zip(whole, poor))
+    assert not all(torch.equal(x, y) for x, y in zip(pool, whole))   # (cut and whole differ in the last bits: something was cut)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("io", ["bf16", "f32"])
+def test_workspaces_the_calls_cannot_use(io):
+    """The _ws forms with no workspace, one byte too few or a misaligned one: whole segments, as the calls without one run them."""
+    case = (1, 2, 2, 2048, 128, 128, "f32", io, 64, False, False)
+    B, H, P, L, dk, dv = case[:6]
+    print("unusable workspaces", io, flush=True)
+    q, k, v, g, dO, gd = _inputs(case)
+    f32 = lambda *s: torch.empty(s, device="cuda")
+    S, S_last, dS = (0.3 * randn_seeded(s, i) for i, s in enumerate([(P, B, H, dk, dv), (B, H, dk, dv), (P, B, H, dk, dv)], 70))
+    desc = zeco.make_desc(q, v, g, P, 64, 0.5)
+    L_ = zeco.lib()
+    calls = [("zeco_gla_local_state", (k, v, g), lambda: (f32(P, B, H, dk, dv), f32(P, B, H, dk))),
+             ("zeco_gla_fwd_from_state", (q, k, v, g, S), lambda: (torch.empty_like(v),)),
+             ("zeco_gla_bwd_dstate", (q, g, dO), lambda: (f32(P, B, H, dk, dv),)),
+             ("zeco_gla_bwd_from_state", (q, k, v, g, dO, S, S_last, dS),
+              lambda: (torch.empty_like(q), torch.empty_like(k), torch.empty_like(v), f32(*g.shape)))]
+    for c, (name, ins, outs) in enumerate(calls):
+        need = L_.zeco_gla_block_workspace(ctypes.byref(desc), c)
+        arena = torch.empty(need + 16, dtype=torch.uint8, device="cuda")
+        ref = outs()
+        _whole(desc, name, ins + ref)
+        few = [(arena.data_ptr(), need - 1)]
+        if c < 3:   # (the fourth needs one for its checkpoints: null or misaligned is refused)
+            few += [(None, 0), (None, need), (arena.data_ptr() + 4, need), (arena.data_ptr(), 0)]
+        for ptr, n in few:
+            got = outs()
+            st = getattr(L_, name + "_ws")(ctypes.byref(desc), *[x.data_ptr() for x in ins + got], ptr, n, zeco._stream())
+            torch.cuda.synchronize()
+            assert st == zeco.ZECO_OK and all(torch.equal(x, y) for x, y in zip(got, ref)), (name, n)
+        got = outs()
+        st = getattr(L_, name + "_ws")(ctypes.byref(desc), *[x.data_ptr() for x in ins + got], arena.data_ptr(), need, zeco._stream())
+        torch.cuda.synchronize()
+        assert st == zeco.ZECO_OK and not all(torch.equal(x, y) for x, y in zip(got, ref)), name   # (that size does cut)
+    args = [x.data_ptr() for x in calls[3][1] + calls[3][2]()]
+    ck = L_.zeco_gla_bwd_from_state_workspace(ctypes.byref(desc))
+    for ptr, n, status in ((None, need, zeco.ZECO_ERR_INVALID_ARG), (arena.data_ptr() + 4, need, zeco.ZECO_ERR_INVALID_ARG),
+                           (arena.data_ptr(), ck - 1, zeco.ZECO_ERR_WORKSPACE)):
+        assert L_.zeco_gla_bwd_from_state_ws(ctypes.byref(desc), *args, ptr, n, zeco._stream()) == status
+
+
 def _desc(**kw):
     d = dict(B=1, P=2, H=2, L=4096, d_k=128, d_v=128, C=64, io_dtype=zeco.ZECO_BF16, g_dtype=zeco.ZECO_F32, scale=1.0,
              stride_b=2 * 4096 * 128 * 2, stride_t=256, stride_h=128, vstride_b=2 * 4096 * 128 * 2, vstride_t=256,
@@ -145,6 +234,13 @@ def test_workspace_of_the_blocks():
         n = ws(call)
         assert n >= 2 * 2 * 2 * state                            # two pieces a segment at least
         assert n <= (256 * 3 + 64 * 4) * state + (1 << 20)       # states of one round of workgroups; 512 tokens a checkpoint
+    # the binding does not even ask beyond these
+    for io, C in ((zeco.ZECO_BF16, 64), (zeco.ZECO_F32, 16), (zeco.ZECO_F32, 64)):
+        for dk in (64, 128):
+            for kw in (dict(P=zeco._BLOCK_STREAMS // 2 + 1), dict(P=1, H=zeco._BLOCK_STREAMS + 1), dict(L=zeco._BLOCK_TOKENS - 1), dict(P=1, H=1, L=64)):
+                kw = dict(kw, io_dtype=io, C=C, d_k=dk)
+                assert [ws(c, **kw) for c in range(3)] == [0, 0, 0]
+                assert ws(3, **kw) == L.zeco_gla_bwd_from_state_workspace(ctypes.byref(_desc(**kw)))
     # nothing to cut: enough streams, short segments, an empty batch; and what is no call or no descriptor
     for kw in (dict(P=65), dict(L=448), dict(B=0)):
         for call in range(3):
