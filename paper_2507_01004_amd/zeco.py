@@ -55,98 +55,110 @@ class ZecoError(RuntimeError):
         super().__init__("%s: %s (status %d)" % (where, status_string(status), status))
 
 
-_lib = None
+_lib = _own_lib = None
 
 
 def lib():
     """The loaded library.  Raises if it has not been built (python -m paper_2507_01004_amd.build)."""
     global _lib
     if _lib is None:
-        if not os.path.exists(LIB_PATH):
-            raise RuntimeError("libzeco.so is not built: run __graft_entry__.build() "
-                               "(expected at %s); there is no fallback path" % LIB_PATH)
-        L = ctypes.CDLL(LIB_PATH)
-        vp, i32, fp = ctypes.c_void_p, ctypes.c_int32, ctypes.c_void_p
-        dp = vp   # (a GlaDesc by reference, or its bytes)
-        L.zeco_gla_local_fwd_workspace.argtypes = [dp]
-        L.zeco_gla_local_fwd_workspace.restype = ctypes.c_size_t
-        L.zeco_gla_local_fwd.argtypes = [dp, vp, vp, vp, vp, vp, fp, fp, fp, vp, ctypes.c_size_t, vp]
-        L.zeco_gla_local_fwd.restype = i32
-        L.zeco_state_scan.argtypes = [i32, i32, i32, i32, i32, fp, fp, fp, fp, fp, i32, i32, vp]
-        L.zeco_state_scan.restype = i32
-        L.zeco_state_scan_tree_workspace.argtypes = [i32, i32, i32, i32, i32]
-        L.zeco_state_scan_tree_workspace.restype = ctypes.c_size_t
-        L.zeco_state_scan_tree.argtypes = [i32, i32, i32, i32, fp, fp, fp, fp, fp, i32, i32, vp, ctypes.c_size_t, vp]
-        L.zeco_state_scan_tree.restype = i32
-        L.zeco_state_scan_tree_static_limit.argtypes = []
-        L.zeco_state_scan_tree_static_limit.restype = ctypes.c_size_t
-        L.zeco_state_scan_tree_static.argtypes = [i32, i32, i32, i32, fp, fp, fp, fp, fp, i32, i32, vp]
-        L.zeco_state_scan_tree_static.restype = i32
-        L.zeco_apply_init_state.argtypes = [dp, vp, fp, fp, vp, i32, vp]
-        L.zeco_apply_init_state.restype = i32
-        L.zeco_gla_local_fwd_varlen.argtypes = [dp, vp, ctypes.c_int64, vp, vp, vp, vp, vp, fp, fp, fp, vp]
-        L.zeco_gla_local_fwd_varlen.restype = i32
-        L.zeco_apply_init_state_varlen.argtypes = [dp, vp, ctypes.c_int64, vp, fp, fp, vp, i32, vp]
-        L.zeco_apply_init_state_varlen.restype = i32
-        L.zeco_gla_local_state_varlen.argtypes = [dp, vp, ctypes.c_int64, vp, vp, vp, fp, fp, vp]
-        L.zeco_gla_local_state_varlen.restype = i32
-        L.zeco_gla_fwd_from_state_varlen.argtypes = [dp, vp, ctypes.c_int64, vp, vp, vp, vp, fp, vp, vp]
-        L.zeco_gla_fwd_from_state_varlen.restype = i32
-        L.zeco_gla_bwd_dstate_varlen.argtypes = [dp, vp, ctypes.c_int64, vp, vp, vp, fp, vp]
-        L.zeco_gla_bwd_dstate_varlen.restype = i32
-        L.zeco_gla_bwd_from_state_varlen.argtypes = [dp, vp, ctypes.c_int64] + [vp] * 5 + [fp] * 3 + [vp] * 3 + [fp, vp, ctypes.c_size_t, vp]
-        L.zeco_gla_bwd_from_state_varlen.restype = i32
-        for nm in ("zeco_gla_fused_fwd_varlen_workspace", "zeco_gla_fused_bwd_varlen_workspace"):
-            getattr(L, nm).argtypes = [dp]
-            getattr(L, nm).restype = ctypes.c_size_t
-        L.zeco_gla_fused_fwd_varlen.argtypes = [dp, vp, ctypes.c_int64] + [vp] * 4 + [fp, vp, fp, vp, ctypes.c_size_t, vp]
-        L.zeco_gla_fused_fwd_varlen.restype = i32
-        L.zeco_gla_fused_bwd_varlen.argtypes = [dp, vp, ctypes.c_int64] + [vp] * 5 + [fp, fp] + [vp] * 3 + [fp, fp, vp, ctypes.c_size_t, vp]
-        L.zeco_gla_fused_bwd_varlen.restype = i32
-        L.zeco_gla_local_fwd_chunk_decay.argtypes = [dp, vp, vp, vp, vp, vp, fp, fp, fp, vp]
-        L.zeco_gla_local_fwd_chunk_decay.restype = i32
-        L.zeco_apply_init_state_chunk_decay.argtypes = [dp, vp, vp, fp, fp, vp, i32, vp]
-        L.zeco_apply_init_state_chunk_decay.restype = i32
-        L.zeco_gla_local_state.argtypes = [dp, vp, vp, vp, fp, fp, vp]
-        L.zeco_gla_local_state.restype = i32
-        L.zeco_gla_fwd_from_state.argtypes = [dp, vp, vp, vp, vp, fp, vp, vp]
-        L.zeco_gla_fwd_from_state.restype = i32
-        L.zeco_gla_block_workspace.argtypes = [dp, i32]
-        L.zeco_gla_block_workspace.restype = ctypes.c_size_t
-        L.zeco_gla_local_state_ws.argtypes = [dp, vp, vp, vp, fp, fp, vp, ctypes.c_size_t, vp]
-        L.zeco_gla_local_state_ws.restype = i32
-        L.zeco_gla_fwd_from_state_ws.argtypes = [dp, vp, vp, vp, vp, fp, vp, vp, ctypes.c_size_t, vp]
-        L.zeco_gla_fwd_from_state_ws.restype = i32
-        L.zeco_gla_bwd_dstate_ws.argtypes = [dp, vp, vp, vp, fp, vp, ctypes.c_size_t, vp]
-        L.zeco_gla_bwd_dstate_ws.restype = i32
-        L.zeco_gla_fused_fwd_workspace.argtypes = [dp]
-        L.zeco_gla_fused_fwd_workspace.restype = ctypes.c_size_t
-        L.zeco_gla_saved_states_bytes.argtypes = [dp]
-        L.zeco_gla_saved_states_bytes.restype = ctypes.c_size_t
-        L.zeco_gla_fused_fwd.argtypes = [dp, vp, vp, vp, vp, fp, vp, fp, fp, i32, vp, ctypes.c_size_t, vp]
-        L.zeco_gla_fused_fwd.restype = i32
-        L.zeco_gla_bwd_dstate.argtypes = [dp, vp, vp, vp, fp, vp]
-        L.zeco_gla_bwd_dstate.restype = i32
-        L.zeco_gla_bwd_from_state.argtypes = [dp] + [vp] * 5 + [fp] * 3 + [vp] * 3 + [fp, vp, ctypes.c_size_t, vp]
-        L.zeco_gla_bwd_from_state_workspace.argtypes = [dp]
-        L.zeco_gla_bwd_from_state_workspace.restype = ctypes.c_size_t
-        L.zeco_gla_bwd_from_state.restype = i32
-        L.zeco_gla_bwd_from_state_ws.argtypes = L.zeco_gla_bwd_from_state.argtypes
-        L.zeco_gla_bwd_from_state_ws.restype = i32
-        L.zeco_gla_fused_bwd_workspace.argtypes = [dp]
-        L.zeco_gla_fused_bwd_workspace.restype = ctypes.c_size_t
-        L.zeco_gla_fused_bwd.argtypes = [dp] + [vp] * 5 + [fp] * 3 + [vp] * 3 + [fp, fp, vp, ctypes.c_size_t, vp]
-        L.zeco_gla_fused_bwd.restype = i32
-        L.zeco_hbm_copy.argtypes = [vp, vp, ctypes.c_size_t, vp]
-        L.zeco_hbm_copy.restype = i32
-        L.zeco_hbm_mix.argtypes = [vp, vp, ctypes.c_size_t, i32, i32, vp]
-        L.zeco_hbm_mix.restype = i32
-        L.zeco_status_string.argtypes = [i32]
-        L.zeco_status_string.restype = ctypes.c_char_p
-        L.zeco_version.argtypes = []
-        L.zeco_version.restype = i32
-        _lib = L
+        _lib = _bind(ctypes.POINTER(GlaDesc))
     return _lib
+
+
+def _own():
+    """The same library for this module's own calls, which hand over a descriptor as its bytes."""
+    global _own_lib
+    if _own_lib is None:
+        _own_lib = _bind(ctypes.c_char_p)
+    return _own_lib
+
+
+def _bind(dp):
+    """A handle of the library whose functions take descriptors of type dp."""
+    if not os.path.exists(LIB_PATH):
+        raise RuntimeError("libzeco.so is not built: run __graft_entry__.build() "
+                           "(expected at %s); there is no fallback path" % LIB_PATH)
+    L = ctypes.CDLL(LIB_PATH)
+    vp, i32, fp = ctypes.c_void_p, ctypes.c_int32, ctypes.c_void_p
+    L.zeco_gla_local_fwd_workspace.argtypes = [dp]
+    L.zeco_gla_local_fwd_workspace.restype = ctypes.c_size_t
+    L.zeco_gla_local_fwd.argtypes = [dp, vp, vp, vp, vp, vp, fp, fp, fp, vp, ctypes.c_size_t, vp]
+    L.zeco_gla_local_fwd.restype = i32
+    L.zeco_state_scan.argtypes = [i32, i32, i32, i32, i32, fp, fp, fp, fp, fp, i32, i32, vp]
+    L.zeco_state_scan.restype = i32
+    L.zeco_state_scan_tree_workspace.argtypes = [i32, i32, i32, i32, i32]
+    L.zeco_state_scan_tree_workspace.restype = ctypes.c_size_t
+    L.zeco_state_scan_tree.argtypes = [i32, i32, i32, i32, fp, fp, fp, fp, fp, i32, i32, vp, ctypes.c_size_t, vp]
+    L.zeco_state_scan_tree.restype = i32
+    L.zeco_state_scan_tree_static_limit.argtypes = []
+    L.zeco_state_scan_tree_static_limit.restype = ctypes.c_size_t
+    L.zeco_state_scan_tree_static.argtypes = [i32, i32, i32, i32, fp, fp, fp, fp, fp, i32, i32, vp]
+    L.zeco_state_scan_tree_static.restype = i32
+    L.zeco_apply_init_state.argtypes = [dp, vp, fp, fp, vp, i32, vp]
+    L.zeco_apply_init_state.restype = i32
+    L.zeco_gla_local_fwd_varlen.argtypes = [dp, vp, ctypes.c_int64, vp, vp, vp, vp, vp, fp, fp, fp, vp]
+    L.zeco_gla_local_fwd_varlen.restype = i32
+    L.zeco_apply_init_state_varlen.argtypes = [dp, vp, ctypes.c_int64, vp, fp, fp, vp, i32, vp]
+    L.zeco_apply_init_state_varlen.restype = i32
+    L.zeco_gla_local_state_varlen.argtypes = [dp, vp, ctypes.c_int64, vp, vp, vp, fp, fp, vp]
+    L.zeco_gla_local_state_varlen.restype = i32
+    L.zeco_gla_fwd_from_state_varlen.argtypes = [dp, vp, ctypes.c_int64, vp, vp, vp, vp, fp, vp, vp]
+    L.zeco_gla_fwd_from_state_varlen.restype = i32
+    L.zeco_gla_bwd_dstate_varlen.argtypes = [dp, vp, ctypes.c_int64, vp, vp, vp, fp, vp]
+    L.zeco_gla_bwd_dstate_varlen.restype = i32
+    L.zeco_gla_bwd_from_state_varlen.argtypes = [dp, vp, ctypes.c_int64] + [vp] * 5 + [fp] * 3 + [vp] * 3 + [fp, vp, ctypes.c_size_t, vp]
+    L.zeco_gla_bwd_from_state_varlen.restype = i32
+    for nm in ("zeco_gla_fused_fwd_varlen_workspace", "zeco_gla_fused_bwd_varlen_workspace"):
+        getattr(L, nm).argtypes = [dp]
+        getattr(L, nm).restype = ctypes.c_size_t
+    L.zeco_gla_fused_fwd_varlen.argtypes = [dp, vp, ctypes.c_int64] + [vp] * 4 + [fp, vp, fp, vp, ctypes.c_size_t, vp]
+    L.zeco_gla_fused_fwd_varlen.restype = i32
+    L.zeco_gla_fused_bwd_varlen.argtypes = [dp, vp, ctypes.c_int64] + [vp] * 5 + [fp, fp] + [vp] * 3 + [fp, fp, vp, ctypes.c_size_t, vp]
+    L.zeco_gla_fused_bwd_varlen.restype = i32
+    L.zeco_gla_local_fwd_chunk_decay.argtypes = [dp, vp, vp, vp, vp, vp, fp, fp, fp, vp]
+    L.zeco_gla_local_fwd_chunk_decay.restype = i32
+    L.zeco_apply_init_state_chunk_decay.argtypes = [dp, vp, vp, fp, fp, vp, i32, vp]
+    L.zeco_apply_init_state_chunk_decay.restype = i32
+    L.zeco_gla_local_state.argtypes = [dp, vp, vp, vp, fp, fp, vp]
+    L.zeco_gla_local_state.restype = i32
+    L.zeco_gla_fwd_from_state.argtypes = [dp, vp, vp, vp, vp, fp, vp, vp]
+    L.zeco_gla_fwd_from_state.restype = i32
+    L.zeco_gla_block_workspace.argtypes = [dp, i32]
+    L.zeco_gla_block_workspace.restype = ctypes.c_size_t
+    L.zeco_gla_local_state_ws.argtypes = [dp, vp, vp, vp, fp, fp, vp, ctypes.c_size_t, vp]
+    L.zeco_gla_local_state_ws.restype = i32
+    L.zeco_gla_fwd_from_state_ws.argtypes = [dp, vp, vp, vp, vp, fp, vp, vp, ctypes.c_size_t, vp]
+    L.zeco_gla_fwd_from_state_ws.restype = i32
+    L.zeco_gla_bwd_dstate_ws.argtypes = [dp, vp, vp, vp, fp, vp, ctypes.c_size_t, vp]
+    L.zeco_gla_bwd_dstate_ws.restype = i32
+    L.zeco_gla_fused_fwd_workspace.argtypes = [dp]
+    L.zeco_gla_fused_fwd_workspace.restype = ctypes.c_size_t
+    L.zeco_gla_saved_states_bytes.argtypes = [dp]
+    L.zeco_gla_saved_states_bytes.restype = ctypes.c_size_t
+    L.zeco_gla_fused_fwd.argtypes = [dp, vp, vp, vp, vp, fp, vp, fp, fp, i32, vp, ctypes.c_size_t, vp]
+    L.zeco_gla_fused_fwd.restype = i32
+    L.zeco_gla_bwd_dstate.argtypes = [dp, vp, vp, vp, fp, vp]
+    L.zeco_gla_bwd_dstate.restype = i32
+    L.zeco_gla_bwd_from_state.argtypes = [dp] + [vp] * 5 + [fp] * 3 + [vp] * 3 + [fp, vp, ctypes.c_size_t, vp]
+    L.zeco_gla_bwd_from_state_workspace.argtypes = [dp]
+    L.zeco_gla_bwd_from_state_workspace.restype = ctypes.c_size_t
+    L.zeco_gla_bwd_from_state.restype = i32
+    L.zeco_gla_bwd_from_state_ws.argtypes = L.zeco_gla_bwd_from_state.argtypes
+    L.zeco_gla_bwd_from_state_ws.restype = i32
+    L.zeco_gla_fused_bwd_workspace.argtypes = [dp]
+    L.zeco_gla_fused_bwd_workspace.restype = ctypes.c_size_t
+    L.zeco_gla_fused_bwd.argtypes = [dp] + [vp] * 5 + [fp] * 3 + [vp] * 3 + [fp, fp, vp, ctypes.c_size_t, vp]
+    L.zeco_gla_fused_bwd.restype = i32
+    L.zeco_hbm_copy.argtypes = [vp, vp, ctypes.c_size_t, vp]
+    L.zeco_hbm_copy.restype = i32
+    L.zeco_hbm_mix.argtypes = [vp, vp, ctypes.c_size_t, i32, i32, vp]
+    L.zeco_hbm_mix.restype = i32
+    L.zeco_status_string.argtypes = [i32]
+    L.zeco_status_string.restype = ctypes.c_char_p
+    L.zeco_version.argtypes = []
+    L.zeco_version.restype = i32
+    return L
 
 
 def status_string(status):
@@ -211,8 +223,12 @@ def _desc(q, v, g_code, per_head, P, C, scale):
     qs, vs = q.stride(), v.stride()
     if qs[-1] != 1 or vs[-1] != 1:
         raise ValueError("innermost dimension must be contiguous")
-    return _pack_desc(B, P, H, T // P, dk, v.shape[-1], C, _dtype_code(q), g_code, float(scale), qs[0], qs[1], qs[2], vs[0], vs[1], vs[2],
-                      per_head, _WIDE_GATES)
+    fields = (B, P, H, T // P, dk, v.shape[-1], C, _dtype_code(q), g_code, float(scale), qs[0], qs[1], qs[2], vs[0], vs[1], vs[2],
+              int(per_head), int(_WIDE_GATES))
+    try:
+        return _pack_desc(*fields)
+    except struct.error:   # what does not fit, or is no integer, goes the structure's own way: to the library's check, or a TypeError
+        return bytes(GlaDesc(*fields))
 
 
 def _gate_desc(q, v, g, P, C, scale):
@@ -238,7 +254,7 @@ def _check_same_layout(ref, *others):
 
 
 def local_fwd_workspace_bytes(q, v, g, P, C=64):
-    return int(lib().zeco_gla_local_fwd_workspace(_gate_desc(q, v, g, P, C, 1.0)))
+    return int(_own().zeco_gla_local_fwd_workspace(_gate_desc(q, v, g, P, C, 1.0)))
 
 
 def gla_local_fwd(q, k, v, g, P, scale=1.0, C=64, out=None, workspace=None):
@@ -260,7 +276,7 @@ def gla_local_fwd(q, k, v, g, P, scale=1.0, C=64, out=None, workspace=None):
     else:
         o, S_loc, G_cum, G_tot = out
         _check_same_layout(v, o)
-    L = lib()
+    L = _own()
     ws_bytes = L.zeco_gla_local_fwd_workspace(desc)
     ws = workspace
     if ws is None and ws_bytes:
@@ -351,7 +367,7 @@ def apply_init_state(q, g_like, G_cum, S_init, o, P, scale=1.0, C=64, first_segm
     if not q.is_cuda:
         raise RuntimeError("zeco kernels run on the GPU only")
     desc = _desc(q, o, _dtype_code(g_like), G_cum.dim() == 3, P, C, scale)
-    st = lib().zeco_apply_init_state(desc, _ptr(q), _ptr(G_cum), _ptr(S_init), _ptr(o),
+    st = _own().zeco_apply_init_state(desc, _ptr(q), _ptr(G_cum), _ptr(S_init), _ptr(o),
                                      _apply_flags(first_segment_is_zero, dense), _stream())
     if st != ZECO_OK:
         raise ZecoError(st, "zeco_apply_init_state")
@@ -478,7 +494,8 @@ def gla_bwd_dstate_varlen(q, g, dO, seg_start, max_len, scale=1.0, C=64, out=Non
 
 
 def _bwd_from_state_workspace(desc, workspace, device):
-    need = int(lib().zeco_gla_bwd_from_state_workspace(desc if type(desc) is bytes else ctypes.byref(desc)))
+    """`desc`: as bytes."""
+    need = int(_own().zeco_gla_bwd_from_state_workspace(desc))
     if workspace is None and need:
         workspace = torch.empty(need, dtype=torch.uint8, device=device)
     return workspace, (workspace.numel() if workspace is not None else 0)
@@ -494,7 +511,7 @@ def gla_bwd_from_state_varlen(q, k, v, g, dO, S_init, S_last, dS_in, seg_start, 
     _check_same_layout(v, dO)
     desc = _varlen_desc(q, v, _dtype_code(g), _gate_per_head(q, g), seg_start, max_len, scale, C)
     dq, dk, dv, dg = _grad_outputs(q, v, g) if out is None else out
-    workspace, ws_bytes = _bwd_from_state_workspace(desc, workspace, q.device)
+    workspace, ws_bytes = _bwd_from_state_workspace(bytes(desc), workspace, q.device)
     st = lib().zeco_gla_bwd_from_state_varlen(ctypes.byref(desc), _ptr(seg_start), q.shape[1], _ptr(q), _ptr(k),
                                               _ptr(v), _ptr(g), _ptr(dO), _ptr(S_init), _ptr(S_last), _ptr(dS_in),
                                               _ptr(dq), _ptr(dk), _ptr(dv), _ptr(dg), _ptr(workspace), ws_bytes,
@@ -569,7 +586,7 @@ def gla_local_fwd_chunk_decay(q, k, v, g, P, scale=1.0, C=64, out=None):
     else:
         o, S_loc, G_chunk, G_tot = out
         _check_same_layout(v, o)
-    st = lib().zeco_gla_local_fwd_chunk_decay(desc, _ptr(q), _ptr(k), _ptr(v), _ptr(g), _ptr(o),
+    st = _own().zeco_gla_local_fwd_chunk_decay(desc, _ptr(q), _ptr(k), _ptr(v), _ptr(g), _ptr(o),
                                               _ptr(S_loc), _ptr(G_chunk), _ptr(G_tot), _stream())
     if st != ZECO_OK:
         raise ZecoError(st, "zeco_gla_local_fwd_chunk_decay")
@@ -582,7 +599,7 @@ def apply_init_state_chunk_decay(q, g, G_chunk, S_init, o, P, scale=1.0, C=64, f
     if not q.is_cuda:
         raise RuntimeError("zeco kernels run on the GPU only")
     desc = _gate_desc(q, o, g, P, C, scale)
-    st = lib().zeco_apply_init_state_chunk_decay(desc, _ptr(q), _ptr(g), _ptr(G_chunk),
+    st = _own().zeco_apply_init_state_chunk_decay(desc, _ptr(q), _ptr(g), _ptr(G_chunk),
                                                  _ptr(S_init), _ptr(o),
                                                  _apply_flags(first_segment_is_zero, dense), _stream())
     if st != ZECO_OK:
@@ -596,7 +613,7 @@ _BLOCK_STREAMS, _BLOCK_TOKENS = 128, 512   # the library cuts no building block 
 def block_workspace_bytes(q, v, g, P, call, C=64):
     """Bytes with which a building block (`call`: BLOCK_LOCAL_STATE with k for q, BLOCK_FWD_FROM_STATE, BLOCK_BWD_DSTATE with dO for v,
     BLOCK_BWD_FROM_STATE) may cut its segments, for the `block_workspace` of its function; 0: it does not."""
-    return int(lib().zeco_gla_block_workspace(_gate_desc(q, v, g, P, C, 1.0), call))
+    return int(_own().zeco_gla_block_workspace(_gate_desc(q, v, g, P, C, 1.0), call))
 
 
 def _block_workspace(given, desc, call, streams, tokens, device):
@@ -607,7 +624,7 @@ def _block_workspace(given, desc, call, streams, tokens, device):
         return given, given.numel()
     if streams > _BLOCK_STREAMS or tokens < _BLOCK_TOKENS:   # (never cut: spare the call the question)
         return None, 0
-    need = int(lib().zeco_gla_block_workspace(desc, call))
+    need = int(_own().zeco_gla_block_workspace(desc, call))
     if not need:
         return None, 0
     try:
@@ -633,7 +650,7 @@ def gla_local_state(k, v, g, P, C=64, out=None, block_workspace=None):
     else:
         S_loc, G_tot = out
     ws, ws_bytes = _block_workspace(block_workspace, desc, BLOCK_LOCAL_STATE, B * P * H, T // P, k.device)
-    st = lib().zeco_gla_local_state_ws(desc, _ptr(k), _ptr(v), _ptr(g), _ptr(S_loc),
+    st = _own().zeco_gla_local_state_ws(desc, _ptr(k), _ptr(v), _ptr(g), _ptr(S_loc),
                                        _ptr(G_tot), _ptr(ws), ws_bytes, _stream())
     if st != ZECO_OK:
         raise ZecoError(st, "zeco_gla_local_state")
@@ -649,7 +666,7 @@ def gla_fwd_from_state(q, k, v, g, S_init, P, scale=1.0, C=64, out=None, block_w
     desc = _gate_desc(q, v, g, P, C, scale)
     o = torch.empty_strided(v.shape, v.stride(), dtype=v.dtype, device=v.device) if out is None else out
     ws, ws_bytes = _block_workspace(block_workspace, desc, BLOCK_FWD_FROM_STATE, q.shape[0] * P * q.shape[2], q.shape[1] // P, q.device)
-    st = lib().zeco_gla_fwd_from_state_ws(desc, _ptr(q), _ptr(k), _ptr(v), _ptr(g),
+    st = _own().zeco_gla_fwd_from_state_ws(desc, _ptr(q), _ptr(k), _ptr(v), _ptr(g),
                                           _ptr(S_init), _ptr(o), _ptr(ws), ws_bytes, _stream())
     if st != ZECO_OK:
         raise ZecoError(st, "zeco_gla_fwd_from_state")
@@ -657,11 +674,11 @@ def gla_fwd_from_state(q, k, v, g, S_init, P, scale=1.0, C=64, out=None, block_w
 
 
 def fused_workspace_bytes(q, v, g, P, C=64):
-    return int(lib().zeco_gla_fused_fwd_workspace(_gate_desc(q, v, g, P, C, 1.0)))
+    return int(_own().zeco_gla_fused_fwd_workspace(_gate_desc(q, v, g, P, C, 1.0)))
 
 
 def saved_states_bytes(q, v, g, P, C=64):
-    return int(lib().zeco_gla_saved_states_bytes(_gate_desc(q, v, g, P, C, 1.0)))
+    return int(_own().zeco_gla_saved_states_bytes(_gate_desc(q, v, g, P, C, 1.0)))
 
 
 def gla_fused_fwd(q, k, v, g, P, scale=1.0, S0=None, C=64, out=None, workspace=None, want_last=True,
@@ -675,7 +692,7 @@ def gla_fused_fwd(q, k, v, g, P, scale=1.0, S0=None, C=64, out=None, workspace=N
     B, T, H, dk = q.shape
     dv = v.shape[-1]
     desc = _gate_desc(q, v, g, P, C, scale)
-    L = lib()
+    L = _own()
     need = L.zeco_gla_fused_fwd_workspace(desc)
     if workspace is None:
         workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=q.device)
@@ -704,7 +721,7 @@ def gla_bwd_dstate(q, g, dO, P, scale=1.0, C=64, out=None, block_workspace=None)
     desc = _gate_desc(q, dO, g, P, C, scale)
     dS_loc = torch.empty(P, B, H, dk, dv, dtype=torch.float32, device=q.device) if out is None else out
     ws, ws_bytes = _block_workspace(block_workspace, desc, BLOCK_BWD_DSTATE, B * P * H, T // P, q.device)
-    st = lib().zeco_gla_bwd_dstate_ws(desc, _ptr(q), _ptr(g), _ptr(dO), _ptr(dS_loc), _ptr(ws), ws_bytes, _stream())
+    st = _own().zeco_gla_bwd_dstate_ws(desc, _ptr(q), _ptr(g), _ptr(dO), _ptr(dS_loc), _ptr(ws), ws_bytes, _stream())
     if st != ZECO_OK:
         raise ZecoError(st, "zeco_gla_bwd_dstate")
     return dS_loc
@@ -728,13 +745,13 @@ def gla_bwd_from_state(q, k, v, g, dO, S_init, S_last, dS_in, P, scale=1.0, C=64
     _check_same_layout(v, dO)
     desc = _gate_desc(q, v, g, P, C, scale)
     dq, dk, dv, dg = _grad_outputs(q, v, g) if out is None else out
-    call, ws_bytes = lib().zeco_gla_bwd_from_state_ws, 0
+    call, ws_bytes = _own().zeco_gla_bwd_from_state_ws, 0
     if workspace is None:
         ws, ws_bytes = _block_workspace(block_workspace, desc, BLOCK_BWD_FROM_STATE, q.shape[0] * P * q.shape[2], q.shape[1] // P, q.device)
-        if block_workspace is not None and ws_bytes < lib().zeco_gla_bwd_from_state_workspace(desc):
+        if block_workspace is not None and ws_bytes < _own().zeco_gla_bwd_from_state_workspace(desc):
             ws_bytes = 0
     if not ws_bytes:   # whole segments: a workspace for their checkpoints alone
-        call = lib().zeco_gla_bwd_from_state
+        call = _own().zeco_gla_bwd_from_state
         ws, ws_bytes = _bwd_from_state_workspace(desc, workspace, q.device)
     st = call(desc, _ptr(q), _ptr(k), _ptr(v), _ptr(g), _ptr(dO), _ptr(S_init), _ptr(S_last), _ptr(dS_in), _ptr(dq), _ptr(dk),
               _ptr(dv), _ptr(dg), _ptr(ws), ws_bytes, _stream())
@@ -744,7 +761,7 @@ def gla_bwd_from_state(q, k, v, g, dO, S_init, S_last, dS_in, P, scale=1.0, C=64
 
 
 def fused_bwd_workspace_bytes(q, v, g, P, C=64):
-    return int(lib().zeco_gla_fused_bwd_workspace(_gate_desc(q, v, g, P, C, 1.0)))
+    return int(_own().zeco_gla_fused_bwd_workspace(_gate_desc(q, v, g, P, C, 1.0)))
 
 
 def gla_fused_bwd(q, k, v, g, dO, P, scale=1.0, S0=None, dS_T=None, C=64, out=None, workspace=None,
@@ -757,7 +774,7 @@ def gla_fused_bwd(q, k, v, g, dO, P, scale=1.0, S0=None, dS_T=None, C=64, out=No
     B, T, H, dk_ = q.shape
     dv_ = v.shape[-1]
     desc = _gate_desc(q, v, g, P, C, scale)
-    L = lib()
+    L = _own()
     need = L.zeco_gla_fused_bwd_workspace(desc)
     if workspace is None:
         workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=q.device)

@@ -333,3 +333,28 @@ def test_workspace_over_a_table_is_bounded_by_the_segments_or_the_compute_units(
     fwd = ((2 * slots + 1) * H + slots * H / 128) * state + 16 * (slots + 4) + 64
     assert zeco.lib().zeco_gla_fused_fwd_varlen_workspace(ctypes.byref(d)) <= fwd
     assert zeco.lib().zeco_gla_fused_bwd_varlen_workspace(ctypes.byref(d)) <= fwd + (2 * slots + P * L // 512) * H * state
+
+
+def test_descriptors_are_taken_as_structures_only(L):
+    """The library's functions take a descriptor as itself or by reference and nothing else; the binding packs its own, and what does not
+    pack is what the structure makes of it."""
+    import torch
+
+    q = torch.zeros(1, 128, 2, 64)
+    d = zeco.make_desc(q, q, q, 1)
+    need = L.zeco_gla_fused_fwd_workspace(ctypes.byref(d))
+    assert need > 0 and L.zeco_gla_fused_fwd_workspace(d) == need == zeco.fused_workspace_bytes(q, q, q, 1)
+    assert L.zeco_gla_fused_fwd_workspace(ctypes.pointer(d)) == need
+    for other in (12345, b"x" * 4096, ctypes.byref(ctypes.c_int(0))):
+        with pytest.raises(ctypes.ArgumentError):
+            L.zeco_gla_fused_fwd_workspace(other)
+    for bad in (64.0, "64"):
+        with pytest.raises(TypeError):
+            zeco.make_desc(q, q, q, 1, C=bad)
+    assert zeco.fused_workspace_bytes(q, q, q, 1, C=2 ** 40) == 0     # (32 bits of it: no chunk length the library has)
+    with zeco.wide_gates():
+        w = zeco.make_desc(q, q, q, 2, C=64, scale=0.5)
+    for name, x in (("B", 1), ("P", 2), ("H", 2), ("L", 64), ("d_k", 64), ("d_v", 64), ("C", 64), ("io_dtype", zeco.ZECO_F32), ("g_dtype", zeco.ZECO_F32),
+                    ("scale", 0.5), ("stride_b", 128 * 128), ("stride_t", 128), ("stride_h", 64), ("vstride_b", 128 * 128), ("vstride_t", 128),
+                    ("vstride_h", 64), ("g_per_head", 0), ("wide_gates", 1)):
+        assert getattr(w, name) == x, name
