@@ -9,25 +9,29 @@ import torch
 from paper_2507_01004_amd import zeco
 from tests.gpu_util import host, randn_seeded, rel_err_bh
 
-# (B, H, P, L, d_k, d_v, gate, io, C, head-major storage, wide gates)
+# (B, H, P, L, d_k, d_v, gate, io, C, head-major storage, wide gates), the calls that are cut (0 states, 1 output pass, 2 state gradients,
+# 3 gradients), pieces per segment and checkpoints of dG inside the longest of them in the gradient call (as its workspace has them)
 CASES = [
-    (1, 1, 1, 512, 128, 128, "f32", "bf16", 64, False, False),     # one chunk a piece, the shortest segment that is cut
-    (2, 2, 3, 1000, 128, 128, "f32", "bf16", 64, False, False),    # ragged, pieces of two lengths, several batch entries
-    (1, 4, 4, 8191, 64, 128, "bf16", "bf16", 64, False, False),    # checkpoints inside the pieces, 63-token remainder
-    (1, 3, 2, 2048, 128, 64, "head", "bf16", 64, False, False),
-    (1, 8, 4, 1664, 64, 64, "f32", "bf16", 64, True, False),       # 26 chunks: pieces that do not come out even
-    (2, 16, 4, 2049, 128, 128, "f32", "bf16", 64, False, False),   # 128 streams: two pieces a segment at most
-    (1, 2, 2, 1100, 128, 128, "f32", "bf16", 64, False, True),     # twice the range of gates
-    (1, 2, 2, 1000, 128, 128, "f32", "f32", 64, False, False),
-    (1, 3, 2, 777, 64, 128, "f32", "f32", 32, True, False),
-    (2, 1, 2, 530, 128, 64, "f32", "f32", 16, False, False),
+    ((1, 1, 1, 512, 128, 128, "f32", "bf16", 64, False, False), "0123", 8, 0),     # one chunk a piece, the shortest segment that is cut
+    ((2, 2, 3, 1000, 128, 128, "f32", "bf16", 64, False, False), "0123", 8, 0),    # ragged, pieces of two lengths, several batch entries
+    ((1, 4, 4, 8191, 64, 128, "bf16", "bf16", 64, False, False), "0123", 16, 0),   # 63-token remainder
+    ((1, 3, 2, 2048, 128, 64, "head", "bf16", 64, False, False), "0123", 32, 0),
+    ((1, 8, 4, 1664, 64, 64, "f32", "bf16", 64, True, False), "0123", 8, 0),       # 26 chunks: pieces that do not come out even
+    ((2, 16, 4, 4099, 128, 128, "f32", "bf16", 64, False, False), "03", 2, 4),     # 128 streams: two pieces a segment at most
+    ((1, 16, 4, 5000, 128, 128, "f32", "bf16", 64, False, False), "0123", 4, 2),   # 256 pieces: whole streams, the last pieces left out
+    ((1, 16, 8, 4001, 64, 64, "head", "bf16", 64, False, False), "023", 2, 3),
+    ((1, 2, 2, 1100, 128, 128, "f32", "bf16", 64, False, True), "0123", 9, 0),     # twice the range of gates
+    ((1, 2, 2, 1000, 128, 128, "f32", "f32", 64, False, False), "0123", 8, 0),
+    ((1, 16, 4, 4200, 128, 128, "f32", "f32", 64, False, False), "0123", 8, 1),    # checkpoints inside unequal pieces
+    ((1, 20, 5, 3000, 128, 64, "f32", "f32", 32, False, False), "0123", 5, 1),
+    ((1, 3, 2, 777, 64, 128, "f32", "f32", 32, True, False), "0123", 8, 0),
+    ((2, 1, 2, 530, 128, 64, "f32", "f32", 16, False, False), "0123", 8, 0),
 ]
 
 
 def _inputs(case):
     B, H, P, L, dk, dv, gate, io, C, hm, wide = case
     T, dt = P * L, torch.bfloat16 if io == "bf16" else torch.float32
-
 
     def lay(x, dtype):   # [B,T,H,d], stored head-major or token-major
         return x.to(dtype).transpose(1, 2) if hm else x.to(dtype)
@@ -60,8 +64,8 @@ def _whole(desc, name, args):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("case", CASES, ids=lambda c: "x".join(map(str, c)))
-def test_cut_calls_give_what_whole_segments_give(case):
+@pytest.mark.parametrize("case, cut, pieces, ck", CASES, ids=["x".join(map(str, c[0])) for c in CASES])
+def test_cut_calls_give_what_whole_segments_give(case, cut, pieces, ck):
     B, H, P, L, dk, dv, gate, io, C, hm, wide = case
     print("block pieces", case, flush=True)
     q, k, v, g, dO, gd = _inputs(case)
@@ -72,7 +76,9 @@ def test_cut_calls_give_what_whole_segments_give(case):
     with zeco.wide_gates(wide):
         desc = zeco.make_desc(q, v, g, P, C, 0.5)
         sizes = [zeco.lib().zeco_gla_block_workspace(ctypes.byref(desc), c) for c in range(4)]
-        assert max(sizes[1], sizes[3]) > 0     # (something is cut in every case)
+        whole = [0, 0, 0, zeco.lib().zeco_gla_bwd_from_state_workspace(ctypes.byref(desc))]
+        assert "".join(str(c) for c in range(4) if sizes[c] > whole[c]) == cut
+        assert sizes[3] == 4 * P * B * H * pieces * ((3 + ck) * dk * dv + 2 * dk)
         S_loc, G_tot = zeco.gla_local_state(k, v, g, P, C=C)
         S_w, G_w = f32(P, B, H, dk, dv), f32(P, B, H, *gd)
         _whole(desc, "zeco_gla_local_state", (k, v, g, S_w, G_w))
