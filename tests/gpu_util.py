@@ -3,7 +3,7 @@ import numpy as np
 import torch
 
 from oracle import oracle
-from paper_2507_01004_amd import synth
+from paper_2507_01004_amd import synth, zeco
 
 # Tolerances: relative error per (batch, head) = max|x - ref| / max|ref|; 1e-4 for fp32 inputs,
 # 2e-2 for bf16 inputs with fp32 accumulation.  Cumulative log decays are compared as logs:
@@ -36,6 +36,14 @@ def oracle_local(inp, P, scale=1.0):
 
 def oracle_full(inp, scale=1.0, S0=None):
     return oracle.gla_recurrent(host(inp["q"]), host(inp["k"]), host(inp["v"]), host(inp["g"]), scale, S0)
+
+
+def checkpoints_only(q, v, g, P, C=64):
+    """A workspace with which zeco.gla_bwd_from_state runs segments whole, with a checkpoint of the forward state for every 512 tokens inside
+    one: (tensor, checkpoints a segment)."""
+    need = zeco.lib().zeco_gla_bwd_from_state_workspace(zeco.make_desc(q, v, g, P, C))
+    states = need // (4 * P * q.shape[0] * q.shape[2] * q.shape[3] * v.shape[3])
+    return torch.empty(need, dtype=torch.uint8, device=q.device), states
 
 
 def dev(a, dtype=torch.float32):

@@ -9,7 +9,7 @@ import torch
 
 from oracle import oracle
 from paper_2507_01004_amd import synth, zeco
-from tests.gpu_util import TOL, dev, host, rel_err_bh
+from tests.gpu_util import TOL, checkpoints_only, dev, host, rel_err_bh
 
 pytestmark = pytest.mark.gpu
 
@@ -99,11 +99,16 @@ def test_bwd_building_blocks_chain(case):
     S_init, S_last = zeco.state_scan(S_loc, G_tot)
     dS_loc = zeco.gla_bwd_dstate(q, g, dO, P, scale=0.7)
     dS_in, dS0 = zeco.state_scan(dS_loc, G_tot, direction=1)
-    got = zeco.gla_bwd_from_state(q, k, v, g, dO, S_init, S_last, dS_in, P, scale=0.7)
+    # whole segments, with the checkpoints of their length, and as the library cuts them
+    ws, checkpoints = checkpoints_only(q, v, g, P)
+    assert checkpoints == (L - 1) // 512
+    whole = zeco.gla_bwd_from_state(q, k, v, g, dO, S_init, S_last, dS_in, P, scale=0.7, workspace=ws)
+    cut = zeco.gla_bwd_from_state(q, k, v, g, dO, S_init, S_last, dS_in, P, scale=0.7)
     torch.cuda.synchronize()
     ref = oracle_bwd(inp, 0.7)
-    for name_, x, r in zip(GRADS, got, ref[:4]):
-        assert rel_err_bh(host(x), r, AXES) <= TOL["bf16"], name_
+    for got in (whole, cut):
+        for name_, x, r in zip(GRADS, got, ref[:4]):
+            assert rel_err_bh(host(x), r, AXES) <= TOL["bf16"], name_
     assert rel_err_bh(host(dS0), ref[4], (0, 1)) <= TOL["bf16"]
     # the reverse scan against the oracle's scan run on the flipped chain
     Si_r, Sl_r = oracle.state_scan(np.flip(host(dS_loc), 0).reshape(P, B * H, dk, dv),

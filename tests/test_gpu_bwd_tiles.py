@@ -7,7 +7,7 @@ import torch
 
 from oracle import oracle
 from paper_2507_01004_amd import synth, zeco
-from tests.gpu_util import TOL, host, rel_err_bh
+from tests.gpu_util import TOL, checkpoints_only, host, rel_err_bh
 
 pytestmark = pytest.mark.gpu
 TOLB = TOL["bf16"]   # bf16 operands, fp32 accumulation: the bound of every bf16 test
@@ -32,13 +32,15 @@ def test_gradients_of_one_segment(L, dk, dv, gate):
     q, k, v, g, dO = (inp[n] for n in ("q", "k", "v", "g", "dO"))
     zero = torch.zeros(1, 1, 2, dk, dv, device="cuda")
     S, G = zeco.gla_local_state(k, v, g, 1)
-    got = zeco.gla_bwd_from_state(q, k, v, g, dO, zero, S[0], zero, 1, scale=0.5)
+    whole = zeco.gla_bwd_from_state(q, k, v, g, dO, zero, S[0], zero, 1, scale=0.5, workspace=checkpoints_only(q, v, g, 1)[0])
+    cut = zeco.gla_bwd_from_state(q, k, v, g, dO, zero, S[0], zero, 1, scale=0.5)   # (from 512 tokens on)
     torch.cuda.synchronize()
     ref = oracle.gla_recurrent_bwd(h["q"], h["k"], h["v"], h["g"], h["dO"], 0.5, None, None)
-    for nm, x, r in zip(("dq", "dk", "dv"), got[:3], ref[:3]):
-        assert rel_err_bh(host(x), r, (0, 2)) <= TOLB, nm
     rg = ref[3].sum(axis=-1) if gate == "head" else ref[3]
-    assert rel_err_bh(host(got[3]), rg, (0, 2)) <= TOLB, "dg"
+    for got in (whole, cut):
+        for nm, x, r in zip(("dq", "dk", "dv"), got[:3], ref[:3]):
+            assert rel_err_bh(host(x), r, (0, 2)) <= TOLB, nm
+        assert rel_err_bh(host(got[3]), rg, (0, 2)) <= TOLB, "dg"
 
 
 @pytest.mark.parametrize("bad", [float("inf"), float("nan")])
@@ -104,7 +106,8 @@ def from_state(inp, L, dk, dv, scale):
     B, H = inp["q"].shape[0], inp["q"].shape[2]
     zero = torch.zeros(1, B, H, dk, dv, device="cuda")
     S, _ = zeco.gla_local_state(inp["k"], inp["v"], inp["g"], 1)
-    return zeco.gla_bwd_from_state(*(inp[n] for n in ("q", "k", "v", "g", "dO")), zero, S[0], zero, 1, scale=scale)
+    return zeco.gla_bwd_from_state(*(inp[n] for n in ("q", "k", "v", "g", "dO")), zero, S[0], zero, 1, scale=scale,
+                                   workspace=checkpoints_only(inp["q"], inp["v"], inp["g"], 1)[0])   # (whole segments)
 
 
 @pytest.mark.parametrize("gate", ["f32", "bf16", "head"])

@@ -1,4 +1,4 @@
-"""GPU parity of the fp32 backward pass (App. A.4 on fp32 tensors, fp32 MFMA): the one-call backward and the calls
+"""GPU parity of the fp32 backward pass (App. A.4 on fp32 tensors): the one-call backward and the calls
 a sequence-parallel run makes around the two All-Scans, against the fp64 oracle's token-by-token reverse
 recurrence at the fp32 tolerance; every chunk length the fp32 kernels take, whole and ragged segment lengths,
 lengths beyond a checkpoint of the forward state, both state shapes, unequal segments."""
@@ -10,7 +10,7 @@ import torch
 
 from oracle import oracle
 from paper_2507_01004_amd import synth, zeco
-from tests.gpu_util import TOL, host, rel_err_bh
+from tests.gpu_util import TOL, checkpoints_only, host, rel_err_bh
 
 pytestmark = pytest.mark.gpu
 
@@ -23,8 +23,8 @@ CASES = [
     ("f32bwd_ragged_c16", 1, 2, 2, 203, 64, 128, 16),
     ("f32bwd_d64", 1, 2, 2, 256, 64, 64, 32),
     ("f32bwd_dk128_dv64", 1, 2, 1, 257, 128, 64, 64),
-    ("f32bwd_anchor", 1, 2, 2, 1100, 128, 128, 64),        # pieces of a chunk or two (building blocks: two checkpoints of the forward state per segment)
-    ("f32bwd_anchor_c16", 1, 1, 1, 1601, 64, 64, 16),      # 13 pieces (building blocks: three checkpoints, 32 chunks apart; the last chunk holds one token)
+    ("f32bwd_anchor", 1, 2, 2, 1100, 128, 128, 64),        # pieces of a chunk or two (building blocks, whole: two checkpoints of the forward state per segment)
+    ("f32bwd_anchor_c16", 1, 1, 1, 1601, 64, 64, 16),      # 13 pieces (building blocks, whole: three checkpoints, 32 chunks apart; the last chunk holds one token)
     ("f32bwd_pieces_c16", 2, 16, 4, 1024, 128, 128, 16),   # 32 (batch, head) pairs in 16 pieces (two workgroups share a compute unit at C = 16)
 ]
 GRADS = ("dq", "dk", "dv", "dg")
@@ -66,7 +66,7 @@ def test_fused_bwd_fp32_matches_unsegmented_oracle(case):
         assert rel_err_bh(host(got[4]), ref[4], (0, 1)) <= TOL["f32"]
 
 
-@pytest.mark.parametrize("case", [CASES[0], CASES[2], CASES[3], CASES[7]], ids=lambda c: c[0])
+@pytest.mark.parametrize("case", [CASES[0], CASES[2], CASES[3], CASES[7], CASES[8]], ids=lambda c: c[0])
 def test_bwd_building_blocks_fp32(case):
     """Forward states, their scan, state gradients (checked per segment against the oracle run on that segment
     alone), the reverse scan, then the gradient passes, with P segments as given."""
@@ -78,14 +78,18 @@ def test_bwd_building_blocks_fp32(case):
     S_init, S_last = zeco.state_scan(S_loc, G_tot)
     dS_loc = zeco.gla_bwd_dstate(q, g, dO, P, scale=0.7, C=C)
     dS_in, dS0 = zeco.state_scan(dS_loc, G_tot, direction=1)
-    got = zeco.gla_bwd_from_state(q, k, v, g, dO, S_init, S_last, dS_in, P, scale=0.7, C=C)
+    ws, checkpoints = checkpoints_only(q, v, g, P, C)
+    assert checkpoints == (L - 1) // 512
+    whole = zeco.gla_bwd_from_state(q, k, v, g, dO, S_init, S_last, dS_in, P, scale=0.7, C=C, workspace=ws)
+    cut = zeco.gla_bwd_from_state(q, k, v, g, dO, S_init, S_last, dS_in, P, scale=0.7, C=C)
     torch.cuda.synchronize()
     for p in range(P):
         sl = {n: t[:, p * L:(p + 1) * L] for n, t in inp.items()}
         assert rel_err_bh(host(dS_loc[p]), oracle_bwd(sl, 0.7)[4], (0, 1)) <= TOL["f32"], p
     ref = oracle_bwd(inp, 0.7)
-    for name_, x, r in zip(GRADS, got, ref[:4]):
-        assert rel_err_bh(host(x), r, AXES) <= TOL["f32"], name_
+    for got in (whole, cut):
+        for name_, x, r in zip(GRADS, got, ref[:4]):
+            assert rel_err_bh(host(x), r, AXES) <= TOL["f32"], name_
     assert rel_err_bh(host(dS0), ref[4], (0, 1)) <= TOL["f32"]
 
 

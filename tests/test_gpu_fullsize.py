@@ -8,7 +8,7 @@ import torch
 
 from oracle import oracle
 from paper_2507_01004_amd import synth, zeco
-from tests.gpu_util import TOL, host, log_err, rel_err_bh
+from tests.gpu_util import TOL, checkpoints_only, host, log_err, rel_err_bh
 
 pytestmark = pytest.mark.gpu
 W = {"c2": 8192, "c3": 8192, "c4": 8192, "c5": 16384}   # warm-up tokens (slow heads of c5 decay 4x slower)
@@ -141,7 +141,7 @@ def test_fullsize_backward_c5_sampled_slices():
 
 def test_fullsize_backward_building_blocks_sampled_slices():
     """Config 3 through the calls a sequence-parallel rank makes around the two scans, with the segments as
-    given (16384 tokens each, not cut into pieces): forward states, scan, state gradients, reverse scan, gradient
+    given (16384 tokens each; the gradients with whole segments and as the library cuts them): forward states, scan, state gradients, reverse scan, gradient
     passes.  dG is a running sum over a whole segment there, re-anchored every 512 tokens.  Then the same over
     an unequal cut of the same tokens (three ragged lengths)."""
     inp, c = synth.config_inputs("c3", device="cuda")
@@ -155,12 +155,15 @@ def test_fullsize_backward_building_blocks_sampled_slices():
     S_init, S_last = zeco.state_scan(S_loc, G_tot)
     dS_loc = zeco.gla_bwd_dstate(q, g, dO, P)
     dS_in, dS0 = zeco.state_scan(dS_loc, G_tot, direction=1)
-    grads = zeco.gla_bwd_from_state(q, k, v, g, dO, S_init, S_last, dS_in, P)
+    ws, checkpoints = checkpoints_only(q, v, g, P)
+    assert checkpoints == 31
+    whole = zeco.gla_bwd_from_state(q, k, v, g, dO, S_init, S_last, dS_in, P, workspace=ws)
+    cut = zeco.gla_bwd_from_state(q, k, v, g, dO, S_init, S_last, dS_in, P)
     torch.cuda.synchronize()
     for (p, h) in [(0, 3), (4, 7), (7, 15)]:
         print("  sample segment %d head %d" % (p, h), flush=True)
         ref = slice_oracle_bwd(inp, dO, L, p, h, P, W["c3"])
-        for nm, x, r in zip(("dq", "dk", "dv", "dg"), grads, ref):
+        for nm, x, r in zip(("dq", "dk", "dv", "dg") * 2, whole + cut, tuple(ref[:4]) * 2):
             got = host(x[:1, p * L:(p + 1) * L, h:h + 1])
             print("    %s rel err %.4f" % (nm, rel_err_bh(got, r, (0, 2))), flush=True)
             assert rel_err_bh(got, r, (0, 2)) <= tol, nm

@@ -11,7 +11,7 @@ import torch
 
 from oracle import oracle
 from paper_2507_01004_amd import synth, zeco
-from tests.gpu_util import TOL, dev, host, log_err, oracle_full, oracle_local, rel_err_bh, randn_seeded
+from tests.gpu_util import TOL, checkpoints_only, dev, host, log_err, oracle_full, oracle_local, rel_err_bh, randn_seeded
 
 pytestmark = pytest.mark.gpu
 
@@ -214,11 +214,14 @@ def test_ragged_backward(case):
         sl = {n: t[:, p * L:(p + 1) * L] for n, t in inp.items()}
         assert rel_err_bh(host(dS_loc[p]), oracle_bwd(sl, 0.7)[4], (0, 1)) <= tol, p
     dS_in, dS0 = zeco.state_scan(dS_loc, G_tot, direction=1)
-    got = zeco.gla_bwd_from_state(q, k, v, g, dO, S_init, S_last, dS_in, P, scale=0.7)
+    ws, _ = checkpoints_only(q, v, g, P)   # whole segments, and as the library cuts them
+    whole = zeco.gla_bwd_from_state(q, k, v, g, dO, S_init, S_last, dS_in, P, scale=0.7, workspace=ws)
+    cut = zeco.gla_bwd_from_state(q, k, v, g, dO, S_init, S_last, dS_in, P, scale=0.7)
     torch.cuda.synchronize()
     ref = oracle_bwd(inp, 0.7)
-    for name_, x, r in zip(GRADS, got, ref[:4]):
-        assert rel_err_bh(host(x), r, (0, 2)) <= tol, name_
+    for got in (whole, cut):
+        for name_, x, r in zip(GRADS, got, ref[:4]):
+            assert rel_err_bh(host(x), r, (0, 2)) <= tol, name_
     assert rel_err_bh(host(dS0), ref[4], (0, 1)) <= tol
 
 
