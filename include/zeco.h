@@ -128,8 +128,9 @@ zeco_status zeco_state_scan(int32_t P, int32_t BH, int32_t d_k, int32_t d_v, int
  * state (its end state and total log decay), (2) the chain over the groups gives the state entering each
  * group and S_last, (3) every group is scanned again from the state entering it, which writes S_init.
  * The serial depth drops from P to about 2 g + P/g (g is chosen to minimise it over the divisors of P)
- * for one more read of S_loc: it pays where a single chain is latency-bound, i.e. one head and 512 segments
- * or more; from two heads on zeco_state_scan has enough chains in flight and is the faster one.
+ * for one more read of S_loc: it pays where the chains are few and small enough to be bound by the latency
+ * of a step, i.e. BH * d_k * d_v up to 8192 and 512 segments or more (1024 segments of 64 x 64: 19 against 34 us);
+ * with more elements zeco_state_scan is the faster one (1024 segments of 128 x 128: 41 against 46 us).
  * Same arguments and conventions as zeco_state_scan; the result differs from it by rounding only (the
  * groups re-associate the sums), it is deterministic; d_k % 16 == 0.  When P has no divisor that
  * shortens the chain (P prime, P <= 4) the call is zeco_state_scan and needs no workspace.
@@ -148,7 +149,7 @@ zeco_status zeco_state_scan_tree(int32_t P, int32_t BH, int32_t d_k, int32_t d_v
  * until the process ends.  The call allocates and frees nothing.
  *   - A problem whose zeco_state_scan_tree_workspace() exceeds the limit returns ZECO_ERR_SCRATCH_LIMIT and
  *     launches nothing (33 MiB covers 1024 segments of up to 4 heads, or 16384 segments of one head, at
- *     d_k = d_v = 128; the tree is the faster scan only for few heads).
+ *     d_k = d_v = 128; the tree is the faster scan only for few elements a segment).
  *   - The first call on a device looks up the array's address on that device (hipGetSymbolAddress, no
  *     allocation, no synchronisation); make that call with the device current, as for every other call.
  *   - All calls on one GPU share that GPU's array.  Nothing in it has to start at zero and nothing is kept

@@ -126,20 +126,20 @@ hipError_t launch_scan_tree(zeco::ScanParams sp, float *scratch, hipStream_t s) 
     return zeco::launch_scan(p, s);
 }
 
-// Inside the fused calls: is the chain of P pieces better scanned as a tree?  Only for a single head: its
-// serial chain (16384 threads at one float each) is bound by the latency of a step, 1024 segments take
-// 0.057 ms against 0.044 ms as a tree, 4096 take 0.227 against 0.198 ms; at 256 segments the two are even,
-// and from two heads on the serial scan is the faster one at every length (1024 x 2: 0.060 against 0.077 ms).
-bool chain_wants_tree(int P, int BH) {
-    if (!(BH == 1 && P >= 512)) return false;
+// Inside the fused calls: is the chain of P pieces better scanned as a tree?  Only for a single head of up to 8192
+// elements, whose chain, though split over the waves of a workgroup, is bound by the latency of its steps: scan / tree, us, 256,
+// 512, 1024, 4096 segments of 64 x 64 9.8 / 13.2, 17.5 / 15.9, 34 / 19, 135 / 52; of 128 x 64 10.4 / 13.9, 19.4 / 19.0, 38 / 28, 138 / 82; of
+// 128 x 128 12.1 / 17.6, 22.5 / 25.2, 41 / 46, 149 / 159.
+bool chain_wants_tree(int P, int BH, int d_k, int d_v) {
+    if (!(BH == 1 && P >= 512 && d_k * d_v <= 8192)) return false;
     const int g = tree_group(P);
     return g != P && P / g <= 65535;          // (the groups are the y dimension of the launch)
 }
 size_t chain_scratch_floats(int P, int BH, int d_k, int d_v, int gate_per_head) {
-    return chain_wants_tree(P, BH) ? tree_floats(P, BH, d_k, d_v, gate_per_head) : 0;
+    return chain_wants_tree(P, BH, d_k, d_v) ? tree_floats(P, BH, d_k, d_v, gate_per_head) : 0;
 }
 hipError_t launch_scan_chain(const zeco::ScanParams &sp, float *scratch, hipStream_t s) {
-    return chain_wants_tree(sp.P, sp.BH) ? launch_scan_tree(sp, scratch, s) : zeco::launch_scan(sp, s);
+    return chain_wants_tree(sp.P, sp.BH, sp.d_k, sp.d_v) ? launch_scan_tree(sp, scratch, s) : zeco::launch_scan(sp, s);
 }
 
 // Device address of zeco_static_scratch on the current GPU.  Every GPU has its own copy of the array at its

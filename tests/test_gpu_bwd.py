@@ -169,8 +169,8 @@ def test_backward_from_states_saved_by_the_forward(case):
 @pytest.mark.parametrize("H", [1, 2])
 def test_few_heads_long_sequence_scans_the_pieces_as_a_tree(H):
     """One or two heads and 32768 tokens per segment: the fused calls cut the sequence into 128 pieces and more
-    and scan them (from 512 pieces of one head on with the two-level scan: a serial chain that short on width is
-    latency-bound).  Forward by both schedules and backward against the oracle, with a state entering and a state gradient leaving."""
+    and scan them (from 512 pieces of one head of up to 8192 elements on with the two-level scan: a chain that short on width
+    is latency-bound).  Forward by both schedules and backward against the oracle, with a state entering and a state gradient leaving."""
     B, P, L, dk, dv = 1, 2, 32768, 64, 64
     print("few heads", H, flush=True)
     inp = synth.make_inputs(B, P * L, H, dk, dv, seed=500 + H, io="bf16", g="f32", device="cuda", gate_div=64.0)

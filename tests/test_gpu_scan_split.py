@@ -3,7 +3,8 @@ runs (32 segments), its rounds (256) and its rule, in both directions, for both 
 import pytest
 import torch
 
-from paper_2507_01004_amd import zeco
+from paper_2507_01004_amd import synth, zeco
+from tests.gpu_util import host, randn_seeded, rel_err_bh
 
 pytestmark = pytest.mark.gpu
 
@@ -59,3 +60,27 @@ def test_what_is_no_number_stays_behind_its_segment():
     bad[:, 0, 0, 3, 5] = False
     bad[:, 0, 0, 9, 9] = False
     assert not bad.any() and torch.isfinite(got[:291, 0, 0, 9, 9]).all() and not torch.isfinite(last[0, 0, 9, 9])
+
+
+@pytest.mark.parametrize("dk,dv", [(64, 64), (128, 64), (128, 128)])
+def test_one_head_in_512_pieces_either_side_of_the_trees_rule(dk, dv):
+    """The one-call forms in fp32 over one head of 131072 tokens: 512 pieces, scanned as a tree up to 8192 elements a state and as one chain
+    beyond; against the same head twice, which is never scanned as a tree.  (Sums in another order: 1e-5, dg, whose terms cancel, 1e-4.)"""
+    T = 131072
+    print("512 pieces", dk, dv, flush=True)
+    inp = synth.make_inputs(1, T, 1, dk, dv, seed=dk + dv, io="f32", g="f32", device="cuda", gate_div=64.0)
+    one = [inp[n] for n in "qkvg"] + [randn_seeded(tuple(inp["v"].shape), 81)]
+    two = [x.expand(1, T, 2, x.shape[-1]).contiguous() for x in one]
+    S0, dS_T = (0.3 * randn_seeded((1, 1, dk, dv), i) for i in (82, 83))
+    rest = zeco.fused_workspace_bytes(one[0], one[2], one[3], 1) - 4 * 512 * (2 * dk * dv + 4 * dk)   # states and decays of 512 pieces
+    tree = zeco.lib().zeco_state_scan_tree_workspace(512, 1, dk, dv, 0)
+    assert rest >= tree if dk * dv <= 8192 else 0 <= rest < tree
+    out = []
+    for x, s0, ds in ((one, S0, dS_T), (two, S0.repeat(1, 2, 1, 1), dS_T.repeat(1, 2, 1, 1))):
+        q, k, v, g, dO = x
+        o, S = zeco.gla_fused_fwd(q, k, v, g, 1, S0=s0)
+        out.append((o, S) + tuple(zeco.gla_fused_bwd(q, k, v, g, dO, 1, S0=s0, dS_T=ds)))
+    torch.cuda.synchronize()
+    for i, (x, y) in enumerate(zip(*out)):
+        y = y[:, :1] if x.shape[1] == 1 else y[:, :, :1]   # states, token rows
+        assert rel_err_bh(host(x), host(y), (0,)) <= (1e-4 if i == 5 else 1e-5), i
