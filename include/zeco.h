@@ -334,8 +334,9 @@ zeco_status zeco_gla_fused_fwd(const zeco_gla_desc *desc, const void *q, const v
 
 /* ---- Backward pass (App. A.4): gradients of  sum_t <o_t, dO_t> + <S_T, dS_T>  for the forward above.
  * q/k/v/dO and the gradients dq, dk, dv share one dtype, bf16 (bf16 MFMA operands, fp32 accumulation and
- * states: the throughput path) or fp32 (fp32 MFMA throughout, chunk length desc->C: the accuracy path, about
- * 4 times slower).  dO, dv use the layout of v;
+ * states: the throughput path) or fp32 (the accuracy path, 2 to 3 times slower, at C = 16 2 to 4: fp32 matrix instructions at C = 16; at C = 32 and
+ * 64 chunks of 32 tokens on the bf16 ones, every operand in three bf16 parts, and the fp32 ones from the first chunk of a segment on
+ * whose decay or values the parts cannot hold).  dO, dv use the layout of v;
  * dq, dk the layout of q; dg [B,T,H,d_k] fp32 contiguous; all state arrays fp32.  The state gradients
  * are true gradients (they include `scale`). --------------------------------------------------------- */
 

@@ -587,8 +587,9 @@ static long long pieces_for(const zeco_gla_desc *d, long long T, bool backward, 
         if (n > chunks) n = chunks;
         if (n < 2 || n < least || n == seen || n == best || n * BH > (1ll << 24)) return;   // (the descriptor's limit on workgroups)
         seen = n;
-        // (fp32 backward, C = 64: a second workgroup on a compute unit for pieces of 512 tokens, the distance of two checkpoints of dG,
-        // or more.  By time alone it would go on: 16 heads x 8192 tokens in 16 / 32 pieces, d = 64, 239 / 202 us, d = 128, 513 / 480)
+        // (fp32 backward, C = 64: a second workgroup on a compute unit only for pieces of 512 tokens or more.  Over 72 shapes of 2 .. 64
+        // heads the counts without this line take 0.91 of its time on geometric mean - 16 heads x 8192 tokens in 16 / 32 pieces, d = 64,
+        // 247 / 205 us, d = 128, 522 / 483 - but up to 1.07: 24 x 8192, 128 x 64, 550 / 588, 4 x 8192, d = 128, 171 / 179)
         if (backward && m.second > 1. && d->C == 64 && n * BH > kComputeUnits && chunks / n < 8) return;
         const bool even = T % (64 * n) == 0;
         const double longest = (double)(chunks / n + (even ? 0 : 1));
@@ -640,10 +641,12 @@ static int subsegments(const zeco_gla_desc *d) {
 
 // Pieces per segment of a building block (1: the segments are run whole), by an estimate in microseconds like the one above.
 // A whole segment costs whole + n chunks of (whole_chunk + what of the pass's traffic is not hidden), S pieces of it cut + the
-// same per chunk of the longest piece (the pass that makes the states included) + the scan.  Up to 128 workgroups the passes split
-// a stream over siblings, beyond that a chunk takes `alone` times as long.  Fitted to 360 measurements of each call (2 .. 128
-// streams of 512 .. 8192 tokens, 1 .. 128 pieces; 3 - 8 % off in the mean); the count picked takes 0.7 % more than the best one on
-// average, 19 % at worst.  64 streams x 8192 tokens, d = 128, whole -> in 4: states 171 -> 92, output pass 322 -> 226, state gradients 177 ->
+// same per chunk of the longest piece (the pass that makes the states included) + the scan.  Beyond 128 workgroups (256 for the
+// fp32 kernels at C = 32 and 64, two of which share a compute unit) a chunk's chain counts `alone` times: the bf16 passes stop splitting
+// a stream over siblings there.  The constants are a fit and stand together - of the kernels without siblings some have `alone` below
+// one, which takes back what `chunk` and the traffic term overstate - to 360 measurements of each call (2 .. 128 streams of 512 .. 8192
+// tokens, 1 .. 128 pieces; 3 - 8 % off in the mean); the count picked takes 0.7 % more than the best one on average, 19 % at worst.
+// More than 128 streams were not measured and are not cut.  64 streams x 8192 tokens, d = 128, whole -> in 4: states 171 -> 92, output pass 322 -> 226, state gradients 177 ->
 // 96, gradients 1193 -> 635 us; 16 x 2048 in 8: 38 -> 15, 73 -> 33, 38 -> 14, 255 -> 76; 128 x 8192 in 2: 194 -> 169, 371 whole, 197 -> 178,
 // 1342 -> 1231.
 struct BlockCost { double whole, cut, whole_chunk, chunk, hidden, step, states, alone; };

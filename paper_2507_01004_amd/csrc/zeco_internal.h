@@ -158,9 +158,9 @@ struct LdsLimit {
 };
 
 // Each returns hipSuccess or the launch error.  d_k, d_v in {64,128}.
-// fp32 kernel: chunk length C in {16, 32, 64} (p.n_chunks, p.pad count chunks of C tokens); mode 0 local pass,
-// 1 states only, 2 output pass from S_init, 3 backward state pass, 4 dV pass, 5 (as in the bf16 kernel below)
-// .. of f32_chunk tokens: the length the kernel of that mode works in
+// fp32 kernels: chunk length C in {16, 32, 64}; mode 0 local pass, 1 states only, 2 output pass from S_init, 3 backward state pass, 4 dV
+// pass, 5 (as in the bf16 kernel below).  p.n_chunks and p.pad count chunks of f32_chunk tokens, the length the kernel of that mode
+// works in.
 int f32_chunk(const ChunkParams &p, int C, int mode);
 hipError_t launch_chunk_f32(const ChunkParams &p, int d_k, int d_v, int C, int mode, hipStream_t s);
 // mode: 0 local pass (o, S_loc, G_cum, G_tot), 1 states only (S_loc, G_tot), 2 output pass from S_init (o),
