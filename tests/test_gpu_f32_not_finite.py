@@ -52,7 +52,7 @@ def test_a_value_of_v_stays_in_its_column(dims, bad, C):
 
 
 @pytest.mark.parametrize("dims", [(64, 64), (128, 128)], ids=lambda d: "%dx%d" % d)
-@pytest.mark.parametrize("bad", [INF, NAN])
+@pytest.mark.parametrize("bad", [INF, NAN, BIG])
 def test_a_value_of_the_incoming_state_stays_in_its_column(dims, bad):
     dk, dv = dims
     print("case", dims, bad, flush=True)
@@ -63,15 +63,14 @@ def test_a_value_of_the_incoming_state_stays_in_its_column(dims, bad):
     torch.cuda.synchronize()
     cols = [c for c in range(dv) if c != 9]
     assert torch.isfinite(o[..., cols]).all()
-    assert torch.isnan(o[..., 9]).all() if bad != bad else (o[..., 9] == INF).all()
+    assert torch.isnan(o[..., 9]).all() if bad != bad else not torch.isnan(o[..., 9]).any() and (o[..., 9] > 1e30).all()
 
 
 @pytest.mark.parametrize("C", [32, 64])
 @pytest.mark.parametrize("dims", [(64, 64), (128, 128), (64, 128), (128, 64)], ids=lambda d: "%dx%d" % d)
 @pytest.mark.parametrize("bad", [INF, NAN, BIG])
 def test_gradients_keep_to_their_columns_and_tokens(dims, bad, C):
-    """A value of dO reaches its column of dv and of the states' gradients, before its token (and inside its sixteen); a value of q its row of
-    dq only where the incoming gradient is read, so the other tokens' stay finite."""
+    """A value of dO reaches its column of dv and of the states' gradients, and no token behind its sixteen; dq of its own token only."""
     dk, dv = dims
     t0, j = 115, 11
     print("case", dims, bad, C, flush=True)
